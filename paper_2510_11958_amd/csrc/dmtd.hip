@@ -31,11 +31,34 @@ namespace {
 constexpr int kMaxTau = 64;          // steps per decode call (size of the emitted-token buffer)
 constexpr int kGemvRows = 4;         // activation rows per FMA weight-streaming pass
 constexpr int kMaxRows = 16;         // rows per sequence one pass through the layers may carry
-constexpr int kPassRows = 128;       // activation rows (all sequences together) a prefill or whole-sequence pass carries: one weight pass of the tiled kernel
-// Row capacity of the activation buffers, and positions per sequence of a prefill pass: passes of kPassRows rows in all,
-// at least kMaxRows per sequence (large batches: more passes of the tiled kernel per weight stream are not needed, B * 16 >= 128)
-inline int row_capacity(int max_batch) { return max_batch * kMaxRows > kPassRows ? max_batch * kMaxRows : kPassRows; }
-inline int pass_positions(int batch) { const int r = kPassRows / batch; return r > kMaxRows ? r : kMaxRows; }
+constexpr int kPassRows = 128;       // activation rows (all sequences together) a prefill or whole-sequence pass of an fp32 model carries
+// The same for a bf16 model.  Its wide GEMM (gemm_wide.hpp) is bound by the matrix cores, so a pass should fill the chip with
+// its tiles of 128 x 256 whatever the projection: 2048 rows give gate/up 1216 tiles and QKV 384 at 4B shapes for 256 CUs.
+// The activation buffers of such a pass take 0.2 GB at 4B shapes.
+constexpr int kWideRows = 2048;
+constexpr int kHeadRows = 512;       // rows of a whole-sequence pass whose logits are held at a time (0.3 GB at a 152k vocabulary)
+// Rows per sequence and in all that a decode step may carry: what the attention's partial results are laid out for.
+inline int step_row_capacity(int max_batch) { return max_batch * kMaxRows > kPassRows ? max_batch * kMaxRows : kPassRows; }
+inline int step_positions(int batch) { const int r = kPassRows / batch; return r > kMaxRows ? r : kMaxRows; }
+// Row capacity of the activation buffers: a decode step's rows, and a prefill pass's (never more than the longest batch has)
+inline int row_capacity(const dmtd_config& c) {
+  long cap = step_row_capacity(c.max_batch);
+  if (c.dtype == DMTD_DTYPE_BF16) {
+    const long all = (long)c.max_batch * c.max_seq_len;
+    cap = std::max(cap, std::min<long>(kWideRows, (all + 15) / 16 * 16));
+  }
+  return (int)cap;
+}
+inline int head_row_capacity(const dmtd_config& c) {
+  return c.dtype == DMTD_DTYPE_BF16 ? std::min(row_capacity(c), std::max(kHeadRows, step_row_capacity(c.max_batch))) : row_capacity(c);
+}
+// Positions per sequence of the passes that P positions take: as few passes as the buffers allow, of about equal length
+inline int pass_positions(const dmtd_config& c, int batch, int P) {
+  if (c.dtype != DMTD_DTYPE_BF16) return step_positions(batch);
+  const int most = std::max(kWideRows / batch, kMaxRows);
+  const int passes = (P + most - 1) / most;
+  return std::min(most, ((P + passes - 1) / passes + 15) / 16 * 16);
+}
 constexpr int kMaxPatterns = 64;     // distinct step patterns (which sequences start a cycle, with how many rows) a context keeps on the device
 constexpr size_t kPatternStride(size_t max_batch) { return (max_batch * 5 + 255) / 256 * 256; }   // int list [max_batch] + byte mask [max_batch]
 constexpr int kMfmaRows = 16;        // activation rows per pass of the one-tile-per-block MFMA kernel
@@ -218,12 +241,18 @@ size_t swizzled_layer_elems(const dmtd_config& c) {
   return swizzled_elems(nqkv, d) + swizzled_elems(d, qd) + 2 * swizzled_elems(ff, d) + swizzled_elems(d, ff);
 }
 
+// Floats the K-split partial sums of one launch may take (gemm_part)
+size_t gemm_part_floats(const dmtd_config& c) {
+  const size_t nqkv = (size_t)(c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
+  return (size_t)kGemmMaxSplit * kGemmRows * std::max({2 * (size_t)c.intermediate, nqkv, (size_t)c.hidden});
+}
+
 Ws layout(const dmtd_config& c) {
   Ws w{};
   const size_t e = c.dtype == DMTD_DTYPE_F32 ? 4 : 2;
   const size_t B = c.max_batch, S = c.max_seq_len, d = c.hidden, hd = c.head_dim;
   const size_t nqkv = (size_t)(c.n_q_heads + 2 * c.n_kv_heads) * hd, qd = (size_t)c.n_q_heads * hd;
-  const size_t rows = row_capacity(c.max_batch);
+  const size_t rows = row_capacity(c), step_rows = step_row_capacity(c.max_batch);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
   const size_t kv_one = B * c.n_kv_heads * S * hd * e;       // K (or V) of one layer
@@ -236,9 +265,10 @@ Ws layout(const dmtd_config& c) {
   w.attn = take(rows * qd * 4);                       // fp32 path: fp32 rows; packed path: bf16 rows
   w.mlp = take(rows * (size_t)c.intermediate * 4);    // likewise
   w.logits = take(B * (size_t)c.vocab * 4);
-  // partial results of the attention key ranges: laid out per sequence for kMaxRows rows in decode steps and for a pass's
-  // positions in prefill; sequences x rows per sequence never exceeds the row capacity
-  const size_t qv_rows = rows * (c.n_q_heads / c.n_kv_heads);
+  // partial results of the attention key ranges: laid out per sequence for kMaxRows rows in decode steps and for
+  // step_positions in prefill (a pass with more positions takes one key range per block); sequences x rows per sequence
+  // never exceeds a step's row capacity
+  const size_t qv_rows = step_rows * (c.n_q_heads / c.n_kv_heads);
   w.part_o = take(c.n_kv_heads * ATT_MAX_SPLITS * qv_rows * hd * 4);
   w.part_ml = take(c.n_kv_heads * ATT_MAX_SPLITS * qv_rows * 2 * 4);
   w.amax = take((size_t)AMAX_CELLS * B * 8);
@@ -252,8 +282,8 @@ Ws layout(const dmtd_config& c) {
   w.enc_tmp = take(rows * d * 4);
   w.rope_tab = take(S * (hd / 2) * 8);                 // (cos, sin) per position and frequency
   w.mask = take(S * 4);
-  w.logits_rows = take(rows * (size_t)c.vocab * 4);
-  w.amax_rows = take((size_t)AMAX_CELLS * rows * 8);
+  w.logits_rows = take(head_row_capacity(c) * (size_t)c.vocab * 4);
+  w.amax_rows = take((size_t)AMAX_CELLS * head_row_capacity(c) * 8);
   w.nll = take(B * S * 4);
   w.best = take(B * S * 4);
   w.loss = take(B * 4);
@@ -263,11 +293,7 @@ Ws layout(const dmtd_config& c) {
     w.xb_late = take(B * d * 2 * 2);
     w.ssp = take(parts * rows * 4);
     w.ssp_late = take(parts * rows * 4);
-    {
-      size_t widest = 2 * (size_t)c.intermediate > nqkv ? 2 * (size_t)c.intermediate : nqkv;
-      if (d > widest) widest = d;
-      w.gemm_part = take((size_t)kGemmMaxSplit * kGemmRows * widest * 4);
-    }
+    w.gemm_part = take(gemm_part_floats(c) * 4);
     w.wsw = take((swizzled_layer_elems(c) * c.n_layers + swizzled_elems(c.vocab, d)) * 2);
   }
   w.total = off;
@@ -362,7 +388,7 @@ hipError_t gemv_rows(dmtd_ctx* c, GemvArgs a, int rows) {
 bool attention_single_range(const dmtd_ctx* c, int r) {
   const dmtd_config& cf = c->cfg;
   const int gq = cf.n_q_heads / cf.n_kv_heads, rpb = 16 / gq, n_rg = (r + rpb - 1) / rpb;
-  return (long)cf.n_kv_heads * c->batch * n_rg >= c->num_cus;
+  return r > c->part_rows || (long)cf.n_kv_heads * c->batch * n_rg >= c->num_cus;     // more rows than the ranges' partials are laid out for: one range
 }
 
 // Whether `rows` packed activation rows of width K (both planes, plus n_parts partial sums of squares per row) stay in
@@ -373,8 +399,61 @@ bool mfma_rows_fit(const dmtd_ctx* c, int rows, int N, int K, int n_parts) {
   return lds_rows <= ((N + 15) / 16 <= c->num_cus ? (size_t)120 * 1024 : (size_t)DMTD_FIT_SMALL_KB * 1024);
 }
 
+// More than kGemmRows rows: the wide GEMM.  Tiles of GW_BM x GW_BN; K is split over blocks where that gives the chip's CUs a
+// fuller last round (and for the residual projections always goes through the finishing kernel, which owns their epilogue).
+template <int EPI, bool NORM>
+hipError_t launch_wide(dmtd_ctx* c, const MfmaArgs& a, int rows) {
+  const int KS = a.K / 64, ldp = (EPI == EPI_SWIGLU ? 2 : 1) * a.N;
+  const int nt = EPI == EPI_SWIGLU ? (a.N + 127) / 128 : (a.N + GW_BN - 1) / GW_BN;
+  const size_t part_rows = gemm_part_floats(c->cfg) / ldp;      // rows x splits the partial sums have room for
+  int pass = rows;
+  if (EPI == EPI_RESID && (size_t)pass > part_rows) pass = (int)(part_rows / GW_BM * GW_BM);
+  for (int m0 = 0; m0 < rows; m0 += pass) {
+    MfmaArgs g = a;
+    g.M = std::min(pass, rows - m0);
+    g.xb = a.xb + (size_t)m0 * a.ldxb;
+    g.xb_lo = a.xb_lo + (size_t)m0 * a.ldxb;
+    if (a.ssp) g.ssp = a.ssp + m0;
+    if (a.y) g.y = a.y + (size_t)m0 * a.ldy;
+    if (a.yb) { g.yb = a.yb + (size_t)m0 * a.ldyb; g.yb_lo = a.yb_lo + (size_t)m0 * a.ldyb; }
+    if (a.ssp_next) g.ssp_next = a.ssp_next + m0;
+    if (a.amax) g.amax = a.amax + m0;
+    const int mt = (g.M + GW_BM - 1) / GW_BM, tiles = mt * nt;
+    int ksplit = 1;
+    if constexpr (EPI != EPI_LOGITS) {
+      // time in k-steps: rounds of blocks over the CUs, plus what writing and reading the partial sums costs (about the time of
+      // one k-step per 128 KiB tile of them and CU)
+      double best = 1e30;
+      for (int ks = 1; ks <= kGemmMaxSplit && ks * 4 <= KS; ++ks) {
+        if ((size_t)ks * g.M > part_rows) break;
+        const int rounds = (tiles * ks + c->num_cus - 1) / c->num_cus;
+        const double parts = ks == 1 && EPI != EPI_RESID ? 0.0 : 6.0 * ks * tiles / c->num_cus + 8.0;
+        const double cost = (double)rounds * (2.0 * KS / ks + 6.0) + parts;
+        if (cost < best * 0.98) { best = cost; ksplit = ks; }
+      }
+    }
+    if (ksplit > 1 || EPI == EPI_RESID) {
+      if constexpr (EPI != EPI_LOGITS) {
+        g.ksplit = ksplit;
+        g.ldp = ldp;
+        g.part = c->gemm_part;
+        hipLaunchKernelGGL((gemm_wide_mfma_kernel<EPI, NORM, true>), dim3(tiles * ksplit), dim3(64 * GW_WAVES), 0, c->stream, g.W, g.W2, g.xb, g.xb_lo,
+                           g.M, g.N, g.K, g.ldxb, ksplit, mt, g);
+        hipLaunchKernelGGL((gemm_finish_kernel<EPI, NORM>), dim3((a.N / 4 + 255) / 256, g.M), dim3(256), 0, c->stream,
+                           (const float*)g.part, (const float*)g.y, (const bf16_t*)g.g_next, g.ksplit, g.M, g.N, g.ldp, g.ldy, g);
+      }
+    } else {
+      if constexpr (EPI != EPI_RESID)
+        hipLaunchKernelGGL((gemm_wide_mfma_kernel<EPI, NORM, false>), dim3(tiles), dim3(64 * GW_WAVES), 0, c->stream, g.W, g.W2, g.xb, g.xb_lo,
+                           g.M, g.N, g.K, g.ldxb, 1, mt, g);
+    }
+  }
+  return hipGetLastError();
+}
+
 template <int EPI, bool NORM, int PF = kMfmaPF, int ROLL_NW = 0>
 hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows) {
+  if (rows > kGemmRows) return launch_wide<EPI, NORM>(c, a, rows);
   const int KS = a.K / 64;
   constexpr int MATS = EPI == EPI_SWIGLU ? 2 : 1;
   const int nw_max = EPI == EPI_SWIGLU ? 5 : 8;
@@ -712,7 +791,7 @@ hipError_t run_layer(dmtd_ctx* c, int l, Rows& R, int r, int sel, int offset) {
   hipError_t e;
   if (c->packed) {
     const LayerSw& s = c->sw[l];
-    const size_t rows_cap = row_capacity(cf.max_batch);
+    const size_t rows_cap = row_capacity(cf);
     bf16_t* ab = (bf16_t*)(c->ws + c->o.attn);      // attention output, high parts; low parts behind them
     bf16_t* ab_lo = ab + rows_cap * qd;
     bf16_t* ub = (bf16_t*)(c->ws + c->o.mlp);       // SwiGLU output, likewise
@@ -810,7 +889,7 @@ hipError_t run_head(dmtd_ctx* c, const Rows& R, int full, int write_tokens, int 
 
 Rows front_rows(dmtd_ctx* c) {
   bf16_t* xb = (bf16_t*)(c->ws + c->o.xb);
-  return Rows{(float*)(c->ws + c->o.h), xb, xb + (size_t)row_capacity(c->cfg.max_batch) * c->cfg.hidden, (float*)(c->ws + c->o.ssp), 1};
+  return Rows{(float*)(c->ws + c->o.h), xb, xb + (size_t)row_capacity(c->cfg) * c->cfg.hidden, (float*)(c->ws + c->o.ssp), 1};
 }
 Rows late_rows(dmtd_ctx* c) {
   bf16_t* xb = (bf16_t*)(c->ws + c->o.xb_late);
@@ -1047,9 +1126,9 @@ hipError_t enqueue_prefill(dmtd_ctx* c, int P, int n_late, bool ragged) {
   hipError_t e;
   hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(64), 0, c->stream, dev_state(c), P - 1, P - 1, cf.max_batch);
   int r_last = 0, p_last = 0;
-  const int chunk = pass_positions(c->batch);
+  const int chunk = pass_positions(cf, c->batch, P);
   PartRowsGuard guard{c, c->part_rows};
-  c->part_rows = chunk;                 // the attention partials are laid out for a pass's rows per sequence
+  c->part_rows = step_positions(c->batch);   // the attention partials of a pass (see attention_single_range)
   for (int p0 = 0; p0 < P; p0 += chunk) {
     const int r = P - p0 < chunk ? P - p0 : chunk;
     choose_attention(c, p0 + r);
@@ -1081,10 +1160,10 @@ hipError_t enqueue_prefill(dmtd_ctx* c, int P, int n_late, bool ragged) {
 // encoding and thinking layers, Eq. 4 picks each position's input to the decoding layers by its mask bit, the
 // decoding layers and the LM head follow for every row, and a row kernel takes the Eq. 6 summands and the argmax.
 // Earlier chunks are seen through the KV caches, exactly as later decode steps would see them.
-hipError_t enqueue_masked_chunk(dmtd_ctx* c, int p0, int r, int n, int n_late) {
+hipError_t enqueue_masked_chunk(dmtd_ctx* c, Rows& R, int p0, int r, int n_late) {
   const dmtd_config& cf = c->cfg;
   const int F = cf.n_layers - n_late, E = c->sched.n_early, rows = c->batch * r;
-  Rows R = front_rows(c);
+  R = front_rows(c);
   float* enc = (float*)(c->ws + c->o.enc_tmp);
   hipError_t e;
   choose_attention(c, p0 + r);
@@ -1108,10 +1187,20 @@ hipError_t enqueue_masked_chunk(dmtd_ctx* c, int p0, int r, int n, int n_late) {
   if ((e = hipGetLastError()) != hipSuccess) return e;
   for (int l = F; l < cf.n_layers; ++l)
     if ((e = run_layer(c, l, R, r, POS_EXPLICIT, p0)) != hipSuccess) return e;
+  return hipSuccess;
+}
+
+// The LM head and the Eq. 6 summands of rows [m0, m0 + n_rows) of the chunk that enqueue_masked_chunk left in the row buffers
+hipError_t enqueue_masked_head(dmtd_ctx* c, const Rows& R, int m0, int n_rows, int p0, int r, int n) {
+  const dmtd_config& cf = c->cfg;
+  Rows H = R;
+  H.h += (size_t)m0 * cf.hidden;
+  if (c->packed) { H.xb += (size_t)m0 * cf.hidden; H.xb_lo += (size_t)m0 * cf.hidden; H.ssp += m0; }
   float* logits = (float*)(c->ws + c->o.logits_rows);
-  if ((e = head_logits(c, R, rows, logits, (unsigned long long*)(c->ws + c->o.amax_rows), row_capacity(cf.max_batch))) != hipSuccess) return e;
-  hipLaunchKernelGGL(nll_rows_kernel, dim3(rows), dim3(1024), 0, c->stream, (const float*)logits, cf.vocab, (const int*)dev_tokens(c), cf.max_seq_len,
-                     p0, r, n, (float*)(c->ws + c->o.nll), (int*)(c->ws + c->o.best));
+  const hipError_t e = head_logits(c, H, n_rows, logits, (unsigned long long*)(c->ws + c->o.amax_rows), head_row_capacity(cf));
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(nll_rows_kernel, dim3(n_rows), dim3(1024), 0, c->stream, (const float*)logits, cf.vocab, (const int*)dev_tokens(c), cf.max_seq_len,
+                     m0, p0, r, n, (float*)(c->ws + c->o.nll), (int*)(c->ws + c->o.best));
   return hipGetLastError();
 }
 
@@ -1145,7 +1234,7 @@ hipError_t time_one(dmtd_ctx* c, int kind, int l, int rows) {
     const int r = rows <= last + 1 ? rows : 1;
     // the cache append is switched off: the launch scores the rows' new keys from the scratch q/k/v, writes nothing
     choose_attention(c, last + 1);
-    if (c->packed) return launch_attention<bf16_t, bf16_t>(c, l, qkv, (bf16_t*)(c->ws + c->o.attn), (bf16_t*)(c->ws + c->o.attn) + (size_t)row_capacity(cf.max_batch) * cf.n_q_heads * cf.head_dim, (int)POS_EXPLICIT, last - r + 1, r, 0);
+    if (c->packed) return launch_attention<bf16_t, bf16_t>(c, l, qkv, (bf16_t*)(c->ws + c->o.attn), (bf16_t*)(c->ws + c->o.attn) + (size_t)row_capacity(cf) * cf.n_q_heads * cf.head_dim, (int)POS_EXPLICIT, last - r + 1, r, 0);
     return launch_attention<float, float>(c, l, qkv, (float*)(c->ws + c->o.attn), (float*)nullptr, (int)POS_EXPLICIT, last - r + 1, r, 0);
   }
   if (kind == DMTD_K_LMHEAD) {
@@ -1154,7 +1243,7 @@ hipError_t time_one(dmtd_ctx* c, int kind, int l, int rows) {
   }
   if (c->packed) {
     const LayerSw& s = c->sw[l];
-    const size_t rows_cap = row_capacity(cf.max_batch);
+    const size_t rows_cap = row_capacity(cf);
     bf16_t* ab = (bf16_t*)(c->ws + c->o.attn);
     bf16_t* ab_lo = ab + rows_cap * qd;
     bf16_t* ub = (bf16_t*)(c->ws + c->o.mlp);
@@ -1246,7 +1335,7 @@ int dmtd_create(const dmtd_config* cfg, const void* weights_dev, size_t weights_
   c->sched.n_layers = cfg->n_layers;
   c->sched.max_seq_len = cfg->max_seq_len;
   c->packed = cfg->dtype == DMTD_DTYPE_BF16;
-  c->ssp_ld = row_capacity(cfg->max_batch);
+  c->ssp_ld = row_capacity(*cfg);
   if (const char* ev = std::getenv("DMTD_TEST_FAIL_STEP")) c->test_fail_step = std::atoi(ev);
   c->plan_buf.reserve(kMaxTau + 1);
   c->sched.trace.reserve((size_t)12 * cfg->max_seq_len + 64);        // at most 3 records of 4 per step: later steps never reallocate
@@ -1824,7 +1913,7 @@ int dmtd_read_kv(dmtd_ctx* c, int32_t layer, int32_t b, int32_t n_pos, float* ou
 int dmtd_time_kernel(dmtd_ctx* c, int32_t kind, int32_t rows, int32_t reps, float* avg_us) {
   if (!c) return DMTD_EINVAL;
   // attention: rows per sequence (at most 16); projections: total activation rows (at most max_batch * 16, the row buffers' capacity)
-  const int rows_max = kind == DMTD_K_ATTN ? kMaxRows : row_capacity(c->cfg.max_batch);
+  const int rows_max = kind == DMTD_K_ATTN ? kMaxRows : step_row_capacity(c->cfg.max_batch);
   if (!avg_us || kind < 0 || kind > DMTD_K_READ_DOWN || rows < 1 || rows > rows_max || reps < 1) {
     c->err = "bad argument to dmtd_time_kernel"; return DMTD_EINVAL;
   }
@@ -1888,17 +1977,24 @@ int dmtd_masked_forward(dmtd_ctx* c, const int32_t* tokens, int32_t batch, int32
   hipError_t e = hipMemcpy2DAsync(c->ws + c->o.tokens, (size_t)cf.max_seq_len * 4, tokens, (size_t)n * 4, (size_t)n * 4, batch,
                                   hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(c->ws + c->o.mask, m32.data(), (size_t)n * 4, hipMemcpyHostToDevice, c->stream);
-  const int chunk = pass_positions(batch);
+  const int chunk = pass_positions(cf, batch, n);
   PartRowsGuard guard{c, c->part_rows};
-  c->part_rows = chunk;
+  c->part_rows = step_positions(batch);
   for (int p0 = 0; p0 < n && e == hipSuccess; p0 += chunk) {
     const int r = n - p0 < chunk ? n - p0 : chunk;
-    e = enqueue_masked_chunk(c, p0, r, n, n_late);
-    if (logits && e == hipSuccess) {
-      // the chunk's rows of sequence b follow each other: one copy per sequence, before the next chunk reuses the buffer
-      for (int b = 0; b < batch && e == hipSuccess; ++b)
-        e = hipMemcpyAsync(logits + ((size_t)b * n + p0) * cf.vocab, c->ws + c->o.logits_rows + (size_t)b * r * cf.vocab * 4,
-                           (size_t)r * cf.vocab * 4, hipMemcpyDeviceToHost, c->stream);
+    Rows R = front_rows(c);
+    e = enqueue_masked_chunk(c, R, p0, r, n_late);
+    const int rows = batch * r, head = head_row_capacity(cf);
+    for (int m0 = 0; m0 < rows && e == hipSuccess; m0 += head) {
+      const int m1 = std::min(rows, m0 + head);
+      e = enqueue_masked_head(c, R, m0, m1 - m0, p0, r, n);
+      if (!logits || e != hipSuccess) continue;
+      // the block's rows of sequence b follow each other: one copy per sequence, before the next block reuses the buffer
+      for (int b = m0 / r; b <= (m1 - 1) / r && e == hipSuccess; ++b) {
+        const int i0 = std::max(m0, b * r), i1 = std::min(m1, (b + 1) * r);
+        e = hipMemcpyAsync(logits + ((size_t)b * n + p0 + (i0 - b * r)) * cf.vocab, c->ws + c->o.logits_rows + (size_t)(i0 - m0) * cf.vocab * 4,
+                           (size_t)(i1 - i0) * cf.vocab * 4, hipMemcpyDeviceToHost, c->stream);
+      }
       if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     }
   }

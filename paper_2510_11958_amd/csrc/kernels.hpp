@@ -358,13 +358,13 @@ __global__ void __launch_bounds__(1024) sample_kernel(const float* __restrict__ 
 }
 
 // Summands of the next-token loss (Eq. 6) and the greedy choice for the rows of one chunk of a whole-sequence
-// forward: row b*r+i of the launch is position p0+i of sequence b; its target is the sequence's next token
+// forward: row b*r+i of the chunk is position p0+i of sequence b (the launch takes the chunk's rows from m0 on); its target is the sequence's next token
 // (none for the last position n-1: the summand is stored as 0).  nll = log(sum_v exp(z_v - max)) + max - z_target,
 // sums taken per thread, per wave and over the waves in a fixed order.  One block of 1024 threads per row.
 __global__ void __launch_bounds__(1024) nll_rows_kernel(const float* __restrict__ logits, int V, const int* __restrict__ tokens, int s_max,
-                                                        int p0, int r, int n, float* __restrict__ nll, int* __restrict__ best) {
-  const int row = blockIdx.x, b = row / r, pos = p0 + row % r;
-  const float* z = logits + (size_t)row * V;
+                                                        int m0, int p0, int r, int n, float* __restrict__ nll, int* __restrict__ best) {
+  const int row = m0 + blockIdx.x, b = row / r, pos = p0 + row % r;
+  const float* z = logits + (size_t)blockIdx.x * V;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   __shared__ unsigned long long key_w[16];
   __shared__ float sum_w[16];
@@ -424,5 +424,6 @@ __global__ void __launch_bounds__(256) mean_nll_kernel(const float* __restrict__
 #include "gemv.hpp"
 #include "gemv_mfma.hpp"
 #include "gemm_mfma.hpp"
+#include "gemm_wide.hpp"
 #include "attention.hpp"
 #include "attention_mfma.hpp"

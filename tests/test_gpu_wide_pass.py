@@ -1,0 +1,54 @@
+"""GPU parity of passes that carry many rows (more than 128 activation rows, more than 16 positions per sequence): the wide
+projection GEMM (tiles of 128 rows x 256 outputs, K optionally split over blocks) and the prefill attention kernel (128
+query vectors x 64 keys per tile), at the edges of their tiles, against the CPU oracle.
+
+Tolerance: that of the other bf16 parity tests (2e-2 of the largest logit: the bf16 KV cache's rounding through the layers);
+a wrong row, key or output of a tile is an error of order one.
+"""
+import numpy as np
+import pytest
+
+import dmtd_inputs as di
+import paper_2510_11958_amd as pkg
+from oracle import dmtd_oracle as O
+from parity_util import engine_config, norm_err, oracle_config
+
+pytestmark = pytest.mark.gpu
+
+TOL_BF16 = 2e-2
+
+S = di.ModelShape
+CASES = {
+    # name: (shape, batch, positions)
+    "rows_129_hd128_gq4": (S(2, 256, 8, 2, 128, 512, 1000), 1, 129),             # one row in the second row tile
+    "rows_3x43_hd64_gq1": (S(2, 192, 3, 3, 64, 320, 203), 3, 43),                # 129 rows; K = 192, outputs not multiples of 128 or 256
+    "rows_256_hd64_gq7": (S(2, 128, 7, 1, 64, 448, 515), 1, 256),                # 18 rows per attention block; full row tiles
+    "rows_2x257_hd128_gq2": (S(2, 320, 4, 2, 128, 960, 129), 2, 257),            # 514 rows: two blocks of logits; 64-key tiles + 1
+    "rows_17x17_hd64_gq16": (S(1, 128, 16, 1, 64, 64, 300), 17, 17),             # fewest positions of a wide pass, 8 rows per attention block
+    "rows_5x450_hd64_gq4": (S(1, 64, 4, 1, 64, 128, 97), 5, 450),                # 2250 rows: two passes, the second reads the first's keys
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_wide_pass_against_oracle(name):
+    sh, batch, n = CASES[name]
+    blob = di.make_weight_blob(sh, seed=31, std=0.04, gain_sigma=0.2)
+    toks = di.make_prompts(sh.vocab, batch, n, seed=5)
+    mask = O.inference_mask(n, n // 2, 3)
+    eng = pkg.Engine(engine_config(sh, n + 2, batch), blob)
+    got = eng.masked_forward(toks, mask, 1, want_logits=True)
+    ocfg = oracle_config(sh)
+    w = O.unpack_weights(blob, ocfg)
+    worst = 0.0
+    for b in range(batch):
+        ref = O.masked_forward(toks[b], mask, 1, w, ocfg)
+        worst = max(worst, max(norm_err(got["logits"][b, i], ref[i]) for i in range(n)))
+        err = np.abs(got["nll"][b, :n - 1] - O.next_token_nll(ref, toks[b])).max()
+        assert err < 2 * TOL_BF16 * np.abs(ref).max(), (b, err)
+    assert worst < TOL_BF16, worst
+    # prefill takes the same passes: its logits are the last position's, with every position full
+    eng.prefill(toks)
+    full = np.ones(n, np.uint8)
+    for b in range(batch):
+        assert norm_err(eng.logits()[b], O.masked_forward(toks[b], full, 1, w, ocfg)[-1]) < TOL_BF16
+    print(f"{name}: worst logit error {worst:.2e}")
