@@ -1,0 +1,244 @@
+// Attention for passes with many rows per sequence (prefill, whole-sequence scoring) over a bf16 KV cache on gfx950.
+// The rows' keys and values are in the cache already (kv_append_kernel); the output goes to the O projection as two
+// bf16 planes.
+//
+// A block takes 128 query vectors of one KV head and sequence (128 / GQ rows x the GQ query heads that share the head), its 4
+// waves 32 each, and walks the visible keys in tiles of 64: K and V pass through LDS once per block instead of once per
+// 16 query vectors.  Per tile and wave, with v_mfma_f32_32x32x16_bf16:
+//   scores   S^T[key, q] = sum_d K[key, d] Q[q, d]; K rows from LDS as the A operand, the queries (normalised, rotated, scaled
+//            by log2(e) / sqrt(HD), split into bf16 high and low parts, held in registers) as the B operand.  A lane ends up
+//            with 16 keys of ONE query per 32-key tile, so the softmax statistics need one exchange with lane ^ 32.
+//   output   O^T[d, q] += sum_key V^T[d, key] P^T[key, q]: a lane's own probabilities are the B operand as they stand (the
+//            contraction runs over the keys in the order the scores left them), V^T comes from LDS.  A probability goes in as
+//            three bf16 parts that add up to all 24 bits of it, so P.V keeps fp32 probabilities at three quarters of
+//            the bf16 rate per part instead of the fp32 matrix rate (1/16).
+// K goes from the cache straight into LDS (global_load ... lds; rows of HD with their 16-byte chunks permuted by the key
+// number), V through registers, transposed on the way (4 keys x HD/16 dims per thread, 8-byte pieces of 4 keys permuted by
+// the dim): fragment reads of both spread over all banks.  Two buffers of each; the next tile's loads fly during a tile.
+// What bounds it: the matrix cores (40 MFMAs of 32 cycles per 32 keys and wave at HD = 128) with the softmax and the
+// three-way split (about as many vector cycles) beside them in the other resident block's waves.
+// Against the decode kernel (attention_mfma.hpp, one pass over K and V per 16 query vectors, fp32 matrix instructions for
+// P.V), 32/8 heads of 128: a prompt of 8192 in passes of 2048 rows, 2 layers: the whole pass 18.0 -> 10.3 ms; 32 prompts of 2048 in
+// passes of 64 rows: 423 -> 99 us per launch; one prompt of 1003: 125 -> 54 us; 2048 rows against 2k-8k keys: 1330 -> 349 us (1.2 PFLOP/s).
+#pragma once
+#include "attention_mfma.hpp"
+#include "gemm_wide.hpp"
+
+namespace dmtd {
+
+constexpr int AP_QV = 128, AP_KT = 64;       // query vectors of a block, keys of a tile
+
+template <int HD>
+__global__ void __launch_bounds__(256, 2) attn_prefill_mfma_kernel(
+    const float* __restrict__ qkv, int ldq, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc, int nh, int nkv, int s_max,
+    int r_total, const DevState* st, int sel, int offset, const bf16_t* __restrict__ q_gain, const float2* __restrict__ rope_tab,
+    float eps, bf16_t* __restrict__ out, bf16_t* __restrict__ out_lo, int ldo) {
+  constexpr int T = HD / 16;           // MFMA steps over d for the scores
+  constexpr int DT = HD / 32;          // 32-dim tiles of the output
+  constexpr int DV = HD / 16;          // dims of V a thread carries
+  constexpr int CH = HD / 8;           // 16-byte chunks of a K row
+  constexpr int KI = AP_KT * CH / 256; // K pieces (16 bytes per lane) per wave and tile
+  typedef unsigned int vraw_t __attribute__((ext_vector_type(DV / 2)));
+  constexpr int TILE = AP_KT * HD;     // elements of a K or V tile
+  __shared__ __attribute__((aligned(1024))) bf16_t ring[4 * TILE];      // K, K, V^T, V^T
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = blockIdx.x, b = blockIdx.y, qt = gridDim.z - 1 - blockIdx.z;      // the tiles with the most keys start first
+  const int GQ = nh / nkv, rpb = AP_QV / GQ, row0 = qt * rpb;
+  const int rows = min(rpb, r_total - row0);
+  const int hi = lane >> 5, qv = 32 * w + (lane & 31);
+  const bool valid = qv < rows * GQ;
+  const int row = row0 + (valid ? qv / GQ : 0), head = g * GQ + (valid ? qv % GQ : 0);
+  const int pos0 = row_base(st, sel, offset, b) + row0;
+  const int key_end = pos0 + rows, my_pos = pos0 + (row - row0);
+  // a sequence's rows of one head are addressed with 32-bit element offsets (the launcher checks that they fit)
+  kc += ((size_t)b * nkv + g) * s_max * HD;
+  vc += ((size_t)b * nkv + g) * s_max * HD;
+
+  auto load_k = [&](int base, int buf) {
+#pragma unroll
+    for (int i = 0; i < KI; ++i) {
+      const int J = w * KI + i, k = J * (64 / CH) + lane / CH, c = (lane % CH) ^ (k & (CH - 1));
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(kc + (uint32_t)(min(base + k, key_end - 1) * HD + c * 8)),
+                                       (__attribute__((address_space(3))) void*)(ring + buf * TILE + J * 512), 16, 0, 0);
+    }
+  };
+  // this thread's 4 keys of a tile, its dims, and where its pieces go in a V^T row: 16 keys' groups of 4 in the order 0, 2, 1, 3, so
+  // that the two groups a lane of the PV product needs (kg, kg + 2) are one 16-byte slot; slots permuted by the dim
+  const int kgp = lane & 15, dg = w * 4 + (lane >> 4), vslot = 2 * (kgp >> 2) + (kgp & 1), vhalf = ((kgp >> 1) & 1) * 4;
+  vraw_t vr[4];
+  auto load_v = [&](int base) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) vr[m] = *(const vraw_t*)(vc + (uint32_t)(min(base + 4 * kgp + m, key_end - 1) * HD + dg * DV));
+  };
+  auto store_v = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < DV / 2; ++u) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int d = dg * DV + 2 * u + h;
+        const unsigned int s = h ? 0x07060302u : 0x05040100u;
+        *(uint2*)(ring + (2 + buf) * TILE + d * AP_KT + ((vslot ^ ((d >> 1) & 7)) * 8 + vhalf)) =
+            make_uint2(__builtin_amdgcn_perm(vr[1][u], vr[0][u], s), __builtin_amdgcn_perm(vr[3][u], vr[2][u], s));
+      }
+    }
+  };
+  load_k(0, 0);
+  load_v(0);
+
+  // the lane's query vector: dims 16 t + 8 hi + 0..7; its rotary partner dims (i, i + HD/2) are the lane's own
+  bf16x8_t qh[T], ql[T];
+  {
+    float x[T][8];
+    const float* src = qkv + (size_t)(b * r_total + row) * ldq + (size_t)head * HD + 8 * hi;
+    float ss = 0.f;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const f32x4 a = *(const f32x4*)(src + 16 * t), c = *(const f32x4*)(src + 16 * t + 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { x[t][e] = a[e]; x[t][4 + e] = c[e]; }
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ss += x[t][e] * x[t][e];
+    ss += __shfl_xor(ss, 32, 64);
+    const float rs = rsqrtf(ss / (float)HD + eps);
+    const float scale = rsqrtf((float)HD) * 1.4426950408889634f;
+    const float2* rp = rope_tab + (size_t)my_pos * (HD / 2) + 8 * hi;
+#pragma unroll
+    for (int t = 0; t < T / 2; ++t) {
+      float g0[8], g1[8];
+      Elem<bf16_t>::unpack(*(const u32x4*)(q_gain + 16 * t + 8 * hi), g0);
+      Elem<bf16_t>::unpack(*(const u32x4*)(q_gain + HD / 2 + 16 * t + 8 * hi), g1);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float2 cs = rp[16 * t + e];
+        const float a0 = x[t][e] * (rs * g0[e]), a1 = x[t + T / 2][e] * (rs * g1[e]);
+        x[t][e] = (a0 * cs.x - a1 * cs.y) * scale;
+        x[t + T / 2][e] = (a1 * cs.x + a0 * cs.y) * scale;
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      uint32_t h4[4], l4[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        h4[e] = pack_bf16x2(x[t][2 * e], x[t][2 * e + 1]);
+        l4[e] = pack_bf16x2(x[t][2 * e] - __uint_as_float(h4[e] << 16), x[t][2 * e + 1] - __uint_as_float(h4[e] & 0xFFFF0000u));
+      }
+      qh[t] = __builtin_bit_cast(bf16x8_t, u32x4{h4[0], h4[1], h4[2], h4[3]});
+      ql[t] = __builtin_bit_cast(bf16x8_t, u32x4{l4[0], l4[1], l4[2], l4[3]});
+    }
+  }
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x16 acc[DT];
+#pragma unroll
+  for (int t = 0; t < DT; ++t)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
+  store_v(0);
+  __builtin_amdgcn_s_waitcnt(7 << 4);      // vmcnt(0) lgkmcnt(0): this wave's share of K has landed too
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+
+  const int n_tiles = (key_end + AP_KT - 1) / AP_KT;
+  for (int it = 0; it < n_tiles; ++it) {
+    const int buf = it & 1, base = it * AP_KT;
+    const bool more = it + 1 < n_tiles;
+    if (more) { load_k(base + AP_KT, buf ^ 1); load_v(base + AP_KT); }
+    // scores (in units of log2) of keys base + 32 k + 8 (e / 4) + 4 hi + e % 4 for the lane's query
+    f32x16 s[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s[k][e] = 0.f;
+      const int key = 32 * k + (lane & 31);
+      const bf16_t* kp = ring + buf * TILE + key * HD;
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const bf16x8_t kf = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(kp + (((2 * t + hi) ^ (key & (CH - 1))) << 3)));
+        s[k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, ql[t], s[k], 0, 0, 0);
+        s[k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qh[t], s[k], 0, 0, 0);
+      }
+    }
+    if (base + AP_KT > pos0 + 1) {      // keys beyond some row's position in this tile
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (base + 32 * k + 8 * (e >> 2) + 4 * hi + (e & 3) > my_pos) s[k][e] = -INFINITY;
+    }
+    float mx = s[0][0];
+#pragma unroll
+    for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[0][e]);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[1][e]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float m_new = fmaxf(m_run, mx);       // the first tile holds key 0, which every row sees
+    if (__any(m_new > m_run)) {
+      const float f = __builtin_amdgcn_exp2f(m_run - m_new);
+      l_run *= f;
+#pragma unroll
+      for (int t = 0; t < DT; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[t][e] *= f;
+      m_run = m_new;
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        s[k][e] = __builtin_amdgcn_exp2f(s[k][e] - m_run);
+        l_run += s[k][e];
+      }
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        // the 8 probabilities of this contraction step as three bf16 parts (truncated leading 8 bits, the next 8, the rest: exact)
+        uint32_t p1[4], p2[4], p3[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float a = s[k][8 * c + 2 * e], d = s[k][8 * c + 2 * e + 1];
+          const float a1 = a - __uint_as_float(__float_as_uint(a) & 0xFFFF0000u), d1 = d - __uint_as_float(__float_as_uint(d) & 0xFFFF0000u);
+          const float a2 = a1 - __uint_as_float(__float_as_uint(a1) & 0xFFFF0000u), d2 = d1 - __uint_as_float(__float_as_uint(d1) & 0xFFFF0000u);
+          p1[e] = __builtin_amdgcn_perm(__float_as_uint(d), __float_as_uint(a), 0x07060302u);
+          p2[e] = __builtin_amdgcn_perm(__float_as_uint(d1), __float_as_uint(a1), 0x07060302u);
+          p3[e] = __builtin_amdgcn_perm(__float_as_uint(d2), __float_as_uint(a2), 0x07060302u);
+        }
+        const bf16x8_t f1 = __builtin_bit_cast(bf16x8_t, u32x4{p1[0], p1[1], p1[2], p1[3]});
+        const bf16x8_t f2 = __builtin_bit_cast(bf16x8_t, u32x4{p2[0], p2[1], p2[2], p2[3]});
+        const bf16x8_t f3 = __builtin_bit_cast(bf16x8_t, u32x4{p3[0], p3[1], p3[2], p3[3]});
+        const int slot = 4 * k + 2 * c + hi;
+#pragma unroll
+        for (int t = 0; t < DT; ++t) {
+          const int d = 32 * t + (lane & 31);
+          const bf16x8_t vf = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(ring + (2 + buf) * TILE + d * AP_KT + ((slot ^ ((d >> 1) & 7)) << 3)));
+          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, f3, acc[t], 0, 0, 0);
+          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, f2, acc[t], 0, 0, 0);
+          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, f1, acc[t], 0, 0, 0);
+        }
+      }
+    if (more) store_v(buf ^ 1);
+    __builtin_amdgcn_s_waitcnt(7 << 4);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  }
+  l_run += __shfl_xor(l_run, 32, 64);
+  if (!valid) return;
+  const float inv_l = 1.0f / l_run;
+  const size_t at = (size_t)(b * r_total + row) * ldo + (size_t)head * HD + 4 * hi;
+#pragma unroll
+  for (int t = 0; t < DT; ++t)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      bf16_t h4[4], l4[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) split_bf16(acc[t][4 * q + e] * inv_l, h4[e], l4[e]);
+      *(uint2*)(out + at + 32 * t + 8 * q) = make_uint2(h4[0] | ((uint32_t)h4[1] << 16), h4[2] | ((uint32_t)h4[3] << 16));
+      *(uint2*)(out_lo + at + 32 * t + 8 * q) = make_uint2(l4[0] | ((uint32_t)l4[1] << 16), l4[2] | ((uint32_t)l4[3] << 16));
+    }
+}
+
+}  // namespace dmtd

@@ -685,6 +685,20 @@ hipError_t launch_attention_mfma_t(dmtd_ctx* c, int l, const float* qkv, OT* att
   return hipGetLastError();
 }
 
+// Passes with more than kMaxRows rows per sequence, whose keys and values are in the cache (append = 2).
+template <int HD>
+hipError_t launch_attention_prefill(dmtd_ctx* c, int l, const float* qkv, bf16_t* attn, bf16_t* attn_lo, int sel, int offset, int r) {
+  const dmtd_config& cf = c->cfg;
+  const int nqkv = (cf.n_q_heads + 2 * cf.n_kv_heads) * HD, rpb = AP_QV / (cf.n_q_heads / cf.n_kv_heads);
+  const bf16_t* kc = (const bf16_t*)(c->ws + c->o.kv + (size_t)l * c->o.kv_layer_stride);
+  const bf16_t* vc = (const bf16_t*)(c->ws + c->o.kv + (size_t)l * c->o.kv_layer_stride + c->o.kv_v_off);
+  // KV heads fastest: with 8 of them a compute die's blocks share one head's keys and values in its L2
+  hipLaunchKernelGGL((attn_prefill_mfma_kernel<HD>), dim3(cf.n_kv_heads, c->batch, (r + rpb - 1) / rpb), dim3(256), 0, c->stream, qkv, nqkv, kc, vc,
+                     cf.n_q_heads, cf.n_kv_heads, cf.max_seq_len, r, (const DevState*)dev_state(c), sel, offset, (const bf16_t*)c->layers[l].q_norm,
+                     (const float2*)(c->ws + c->o.rope_tab), cf.rms_eps, attn, attn_lo, cf.n_q_heads * HD);
+  return hipGetLastError();
+}
+
 // Kernel choice.  bf16 caches: the matrix-core kernel (measured faster than the vector kernel even for
 // one row and 4 query heads per KV head: 11.7 vs 13.2 us at 1k context, 99 vs 119 us at 8 x 16k).
 // fp32 caches: the vector kernel; share_kv: all rows of a sequence go through one block so that K and V
@@ -695,6 +709,10 @@ hipError_t launch_attention(dmtd_ctx* c, int l, const float* qkv, OT* attn, OT* 
   const int gq = cf.n_q_heads / cf.n_kv_heads;
   if (r > kMaxRows && append != 2) return hipErrorInvalidValue;    // more rows than an attention block keeps in LDS: their keys must be in the cache
   if constexpr (std::is_same<CT, bf16_t>::value) {
+    if (append == 2 && (long)cf.max_seq_len * cf.head_dim < (1L << 31)) {      // the prefill kernel addresses a head's rows with 32 bits
+      if (cf.head_dim == 128) return launch_attention_prefill<128>(c, l, qkv, attn, attn_lo, sel, offset, r);
+      return launch_attention_prefill<64>(c, l, qkv, attn, attn_lo, sel, offset, r);
+    }
     if (cf.head_dim == 128) return launch_attention_mfma_t<OT, 128>(c, l, qkv, attn, attn_lo, sel, offset, r, append);
     return launch_attention_mfma_t<OT, 64>(c, l, qkv, attn, attn_lo, sel, offset, r, append);
   }

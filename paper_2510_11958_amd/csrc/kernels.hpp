@@ -427,3 +427,4 @@ __global__ void __launch_bounds__(256) mean_nll_kernel(const float* __restrict__
 #include "gemm_wide.hpp"
 #include "attention.hpp"
 #include "attention_mfma.hpp"
+#include "attention_prefill.hpp"
