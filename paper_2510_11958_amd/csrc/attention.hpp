@@ -348,7 +348,7 @@ template <int HD, typename OT>   // OT: float, or bf16_t (the packed input of th
 __global__ void __launch_bounds__(256) attn_merge_kernel(
     const float* __restrict__ part_o, const float* __restrict__ part_ml, OT* __restrict__ out, OT* __restrict__ out_lo, int ldo,
     int nh, int nkv, int kps, int n_splits, int qv_stride, const DevState* st, int sel, int offset, int r_total,
-    const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot (positions) */) {
+    const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot (positions) */, int blocked /* layout of a bf16 output (packed_at) */) {
   constexpr int T4 = HD / 4;              // threads per group: one per 4 consecutive d
   constexpr int NG = 256 / T4;            // groups (8 or 16); group sg takes ranges sg, sg + NG, ...
   constexpr int PRE = 4;                  // ranges per thread fetched before anything is waited for (4 * NG >= 32 ranges)
@@ -406,7 +406,7 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(
     f32x4 t = *(const f32x4*)&red[0][d];
 #pragma unroll
     for (int q = 1; q < NG; ++q) t += *(const f32x4*)&red[q][d];
-    const size_t at = (size_t)(b * r_total + i) * ldo + (size_t)head * HD + d;
+    const size_t at = packed_at(blocked, b * r_total + i, head * HD + d, ldo);     // 4 consecutive values stay together in both layouts
     const float inv_l = inv_l_s;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {

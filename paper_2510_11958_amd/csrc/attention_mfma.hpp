@@ -223,7 +223,7 @@ __global__ void __launch_bounds__(64 * NW) attn_split_mfma_kernel(
     const DevState* st, int sel, int offset, int n_splits, const void* __restrict__ q_gain,
     const void* __restrict__ k_gain, const float2* __restrict__ rope_tab,
     float* __restrict__ part_o, float* __restrict__ part_ml, float eps, int qv_stride, int do_append,
-    bf16_t* __restrict__ out, bf16_t* __restrict__ out_lo, int ldo /* FINAL only */, QkvSrc qs) {
+    bf16_t* __restrict__ out, bf16_t* __restrict__ out_lo, int ldo, int blocked /* FINAL only */, QkvSrc qs) {
   constexpr int QVT = 16;
   constexpr int NT = 64 * NW;
   constexpr int KSTEPS = HD / 32;      // MFMA steps over d for the scores
@@ -415,7 +415,7 @@ __global__ void __launch_bounds__(64 * NW) attn_split_mfma_kernel(
     }
     if (FINAL) {
       // row and head of query vector qv; every row sees at least its own key, so ll > 0
-      const size_t at = (size_t)(b * r_total + rg * rpb + qv / GQ) * ldo + (size_t)(g * GQ + qv % GQ) * HD + d;
+      const size_t at = packed_at(blocked, b * r_total + rg * rpb + qv / GQ, (g * GQ + qv % GQ) * HD + d, ldo);
       const float inv_l = 1.0f / ll;
       bf16_t hi[4], lo[4];
 #pragma unroll

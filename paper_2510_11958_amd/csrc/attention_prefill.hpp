@@ -32,7 +32,7 @@ template <int HD>
 __global__ void __launch_bounds__(256, 2) attn_prefill_mfma_kernel(
     const float* __restrict__ qkv, int ldq, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc, int nh, int nkv, int s_max,
     int r_total, const DevState* st, int sel, int offset, const bf16_t* __restrict__ q_gain, const float2* __restrict__ rope_tab,
-    float eps, bf16_t* __restrict__ out, bf16_t* __restrict__ out_lo, int ldo) {
+    float eps, bf16_t* __restrict__ out, bf16_t* __restrict__ out_lo, int ldo, int blocked) {
   constexpr int T = HD / 16;           // MFMA steps over d for the scores
   constexpr int DT = HD / 32;          // 32-dim tiles of the output
   constexpr int DV = HD / 16;          // dims of V a thread carries
@@ -55,10 +55,14 @@ __global__ void __launch_bounds__(256, 2) attn_prefill_mfma_kernel(
   kc += ((size_t)b * nkv + g) * s_max * HD;
   vc += ((size_t)b * nkv + g) * s_max * HD;
 
+  // The loads' addresses are worked out anew from the lane number in every tile: kept in registers through the loop they would
+  // push the kernel beyond the 256 that two blocks per CU allow.
   auto load_k = [&](int base, int buf) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
 #pragma unroll
     for (int i = 0; i < KI; ++i) {
-      const int J = w * KI + i, k = J * (64 / CH) + lane / CH, c = (lane % CH) ^ (k & (CH - 1));
+      const int J = w * KI + i, k = J * (64 / CH) + ln / CH, c = (ln % CH) ^ (k & (CH - 1));
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(kc + (uint32_t)(min(base + k, key_end - 1) * HD + c * 8)),
                                        (__attribute__((address_space(3))) void*)(ring + buf * TILE + J * 512), 16, 0, 0);
     }
@@ -68,8 +72,11 @@ __global__ void __launch_bounds__(256, 2) attn_prefill_mfma_kernel(
   const int kgp = lane & 15, dg = w * 4 + (lane >> 4), vslot = 2 * (kgp >> 2) + (kgp & 1), vhalf = ((kgp >> 1) & 1) * 4;
   vraw_t vr[4];
   auto load_v = [&](int base) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
 #pragma unroll
-    for (int m = 0; m < 4; ++m) vr[m] = *(const vraw_t*)(vc + (uint32_t)(min(base + 4 * kgp + m, key_end - 1) * HD + dg * DV));
+    for (int m = 0; m < 4; ++m)
+      vr[m] = *(const vraw_t*)(vc + (uint32_t)(min(base + 4 * (ln & 15) + m, key_end - 1) * HD + (w * 4 + (ln >> 4)) * DV));
   };
   auto store_v = [&](int buf) {
 #pragma unroll
@@ -193,7 +200,7 @@ __global__ void __launch_bounds__(256, 2) attn_prefill_mfma_kernel(
         l_run += s[k][e];
       }
 #pragma unroll
-    for (int k = 0; k < 2; ++k)
+    for (int k = 0; k < 2; ++k) {
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         // the 8 probabilities of this contraction step as three bf16 parts (truncated leading 8 bits, the next 8, the rest: exact)
@@ -220,15 +227,21 @@ __global__ void __launch_bounds__(256, 2) attn_prefill_mfma_kernel(
           acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, f1, acc[t], 0, 0, 0);
         }
       }
+    }
     if (more) store_v(buf ^ 1);
     __builtin_amdgcn_s_waitcnt(7 << 4);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   }
   l_run += __shfl_xor(l_run, 32, 64);
-  if (!valid) return;
+  // where the vector goes, likewise
+  int ln = lane;
+  asm volatile("" : "+v"(ln));
+  const int qo = 32 * w + (ln & 31), ro = qo / GQ;
+  if (qo >= rows * GQ) return;
   const float inv_l = 1.0f / l_run;
-  const size_t at = (size_t)(b * r_total + row) * ldo + (size_t)head * HD + 4 * hi;
+  const size_t at0 = packed_at(blocked, b * r_total + row0 + ro, (g * GQ + qo - ro * GQ) * HD + 4 * (ln >> 5), ldo);
+  const int t_step = blocked ? 512 : 32, q_step = blocked ? 128 : 8;        // 32 and 8 dims further
 #pragma unroll
   for (int t = 0; t < DT; ++t)
 #pragma unroll
@@ -236,8 +249,9 @@ __global__ void __launch_bounds__(256, 2) attn_prefill_mfma_kernel(
       bf16_t h4[4], l4[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) split_bf16(acc[t][4 * q + e] * inv_l, h4[e], l4[e]);
-      *(uint2*)(out + at + 32 * t + 8 * q) = make_uint2(h4[0] | ((uint32_t)h4[1] << 16), h4[2] | ((uint32_t)h4[3] << 16));
-      *(uint2*)(out_lo + at + 32 * t + 8 * q) = make_uint2(l4[0] | ((uint32_t)l4[1] << 16), l4[2] | ((uint32_t)l4[3] << 16));
+      const size_t at = at0 + t * t_step + q * q_step;
+      *(uint2*)(out + at) = make_uint2(h4[0] | ((uint32_t)h4[1] << 16), h4[2] | ((uint32_t)h4[3] << 16));
+      *(uint2*)(out_lo + at) = make_uint2(l4[0] | ((uint32_t)l4[1] << 16), l4[2] | ((uint32_t)l4[3] << 16));
     }
 }
 

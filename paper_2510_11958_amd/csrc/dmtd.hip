@@ -184,6 +184,8 @@ struct dmtd_ctx {
   bool sampling = false;      // tokens are drawn (dmtd_set_sampling) instead of taken greedily
   bool share_kv = false;      // attention launches: one pass over K/V for all rows of a sequence (long contexts)
   int att_bucket = 512;       // attention launches: context bucket (multiple of 512) the key ranges are laid out for
+  int late_batch = 0;         // a front pass over some sequences: sequences of the whole batch (0: all are in the pass)
+  int resid_parts = 0;        // partial sums of squares per row the last residual projection left for the next norm
   const int* fmap = nullptr;  // launches of a front pass over SOME sequences: launch sequence -> sequence slot (device); null = all, in order
   const unsigned char* full_mask = nullptr;   // the step's bookkeeping: which sequences close their refill gap (device); null = all or none
   // sequences at different points of their cycles (dmtd_decode_per_seq): per-sequence phase and front position (in the
@@ -309,6 +311,9 @@ Ws layout(const dmtd_config& c) {
     }                                                                                   \
   } while (0)
 
+// Whether the packed inputs of a pass with that many rows are in the wide GEMM's blocked layout (packed_at)
+int blocked_rows(const dmtd_ctx* c, int rows) { return c->packed && rows > kGemmRows; }
+
 DevState* dev_state(dmtd_ctx* c) { return (DevState*)(c->ws + c->o.state); }
 int* dev_tokens(dmtd_ctx* c) { return (int*)(c->ws + c->o.tokens); }
 const void* norm_gain_for_layer(const dmtd_ctx* c, int l) {   // gain of the norm that opens layer l (the final norm after the last)
@@ -399,61 +404,64 @@ bool mfma_rows_fit(const dmtd_ctx* c, int rows, int N, int K, int n_parts) {
   return lds_rows <= ((N + 15) / 16 <= c->num_cus ? (size_t)120 * 1024 : (size_t)DMTD_FIT_SMALL_KB * 1024);
 }
 
-// More than kGemmRows rows: the wide GEMM.  Tiles of GW_BM x GW_BN; K is split over blocks where that gives the chip's CUs a
-// fuller last round (and for the residual projections always goes through the finishing kernel, which owns their epilogue).
+// More than kGemmRows rows: the wide GEMM.  Two blocks share a CU, so a round is 2 * CUs blocks and takes 1.6 times as long as a
+// round with one block per CU (measured, 2048 x 2560 x 9728: 160 tiles 357 us, 320 half tiles 256, 480 thirds 192, 640
+// quarters 238).  Whole rounds compute a tile per block; the tiles left over are split along K so that their blocks fill
+// a round too, if that saves more than the raw sums and the finishing launch cost.  The residual projections go through
+// the finishing kernel whole (their few tiles are nearly always split, and it owns their epilogue).
 template <int EPI, bool NORM>
 hipError_t launch_wide(dmtd_ctx* c, const MfmaArgs& a, int rows) {
-  const int KS = a.K / 64, ldp = (EPI == EPI_SWIGLU ? 2 : 1) * a.N;
+  const int KS = a.K / 64;
   const int nt = EPI == EPI_SWIGLU ? (a.N + 127) / 128 : (a.N + GW_BN - 1) / GW_BN;
-  const size_t part_rows = gemm_part_floats(c->cfg) / ldp;      // rows x splits the partial sums have room for
+  const int part_tiles = (int)std::min<size_t>(gemm_part_floats(c->cfg) / GW_PART, 1 << 20);      // raw tiles the partial sums have room for (at least nt)
   int pass = rows;
-  if (EPI == EPI_RESID && (size_t)pass > part_rows) pass = (int)(part_rows / GW_BM * GW_BM);
+  if (EPI == EPI_RESID && (long)(pass + GW_BM - 1) / GW_BM * nt > part_tiles) pass = part_tiles / nt * GW_BM;
   for (int m0 = 0; m0 < rows; m0 += pass) {
     MfmaArgs g = a;
     g.M = std::min(pass, rows - m0);
-    g.xb = a.xb + (size_t)m0 * a.ldxb;
+    g.xb = a.xb + (size_t)m0 * a.ldxb;             // m0 is a multiple of 128: whole row groups of the blocked layout
     g.xb_lo = a.xb_lo + (size_t)m0 * a.ldxb;
     if (a.ssp) g.ssp = a.ssp + m0;
     if (a.y) g.y = a.y + (size_t)m0 * a.ldy;
     if (a.yb) { g.yb = a.yb + (size_t)m0 * a.ldyb; g.yb_lo = a.yb_lo + (size_t)m0 * a.ldyb; }
     if (a.ssp_next) g.ssp_next = a.ssp_next + m0;
     if (a.amax) g.amax = a.amax + m0;
-    const int mt = (g.M + GW_BM - 1) / GW_BM, tiles = mt * nt;
-    int ksplit = 1;
+    const int mt = (g.M + GW_BM - 1) / GW_BM, tiles = mt * nt, slots = 2 * c->num_cus;
+    int n_full = EPI == EPI_RESID ? 0 : tiles, ksplit = 1;
     if constexpr (EPI != EPI_LOGITS) {
-      // time in k-steps: rounds of blocks over the CUs, plus what writing and reading the partial sums costs (about the time of
-      // one k-step per 128 KiB tile of them and CU)
-      double best = 1e30;
-      for (int ks = 1; ks <= kGemmMaxSplit && ks * 4 <= KS; ++ks) {
-        if ((size_t)ks * g.M > part_rows) break;
-        const int rounds = (tiles * ks + c->num_cus - 1) / c->num_cus;
-        const double parts = ks == 1 && EPI != EPI_RESID ? 0.0 : 6.0 * ks * tiles / c->num_cus + 8.0;
-        const double cost = (double)rounds * (2.0 * KS / ks + 6.0) + parts;
-        if (cost < best * 0.98) { best = cost; ksplit = ks; }
+      const int whole = EPI == EPI_RESID ? 0 : tiles / slots * slots, left = tiles - whole;
+      // microseconds: a k-step of 32 takes 0.75 us in a round of one block per CU; a raw tile's 128 KiB are written and read
+      // by blocks all over the chip at about 2.5 TB/s; the finishing launch itself 5 us
+      auto round_us = [&](int blocks, int ks) {
+        const int rem = blocks % slots;
+        return (blocks / slots * 1.6 + (rem == 0 ? 0.0 : rem <= c->num_cus ? 1.0 : 1.6)) * (2.0 * KS / ks * 0.75 + 3.0);
+      };
+      auto parts_us = [&](int ks) { return left * ks * (GW_PART * 4) / 2.5e6 + 5.0; };
+      double best = EPI == EPI_RESID ? round_us(left, 1) + parts_us(1) : round_us(left, 1);
+      for (int ks = 2; ks <= kGemmMaxSplit && ks * 4 <= KS && left > 0 && (long)left * ks <= part_tiles; ++ks) {
+        const double us = round_us(left * ks, ks) + parts_us(ks);
+        if (us < best * 0.97) { best = us; ksplit = ks; n_full = whole; }
       }
     }
-    if (ksplit > 1 || EPI == EPI_RESID) {
-      if constexpr (EPI != EPI_LOGITS) {
-        g.ksplit = ksplit;
-        g.ldp = ldp;
-        g.part = c->gemm_part;
-        hipLaunchKernelGGL((gemm_wide_mfma_kernel<EPI, NORM, true>), dim3(tiles * ksplit), dim3(64 * GW_WAVES), 0, c->stream, g.W, g.W2, g.xb, g.xb_lo,
-                           g.M, g.N, g.K, g.ldxb, ksplit, mt, g);
-        hipLaunchKernelGGL((gemm_finish_kernel<EPI, NORM>), dim3((a.N / 4 + 255) / 256, g.M), dim3(256), 0, c->stream,
-                           (const float*)g.part, (const float*)g.y, (const bf16_t*)g.g_next, g.ksplit, g.M, g.N, g.ldp, g.ldy, g);
-      }
-    } else {
-      if constexpr (EPI != EPI_RESID)
-        hipLaunchKernelGGL((gemm_wide_mfma_kernel<EPI, NORM, false>), dim3(tiles), dim3(64 * GW_WAVES), 0, c->stream, g.W, g.W2, g.xb, g.xb_lo,
-                           g.M, g.N, g.K, g.ldxb, 1, mt, g);
+    const int n_tail = tiles - n_full;
+    g.part = c->gemm_part;
+    hipLaunchKernelGGL((gemm_wide_mfma_kernel<EPI, NORM>), dim3(n_full + n_tail * ksplit), dim3(64 * GW_WAVES), 0, c->stream, g.W, g.W2, g.xb, g.xb_lo,
+                       g.M, g.N, g.K, n_full, n_tail, ksplit, mt, nt, g);
+    if constexpr (EPI != EPI_LOGITS) {
+      if (n_tail > 0)
+        hipLaunchKernelGGL((gemm_wide_finish_kernel<EPI, NORM>), dim3(n_tail, GW_BM / 16), dim3(256), 0, c->stream, (const float*)g.part,
+                           g.M, g.N, n_full, n_tail, ksplit, mt, nt, g);
     }
   }
+  if (EPI == EPI_RESID) c->resid_parts = nt;
   return hipGetLastError();
 }
 
 template <int EPI, bool NORM, int PF = kMfmaPF, int ROLL_NW = 0>
 hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows) {
-  if (rows > kGemmRows) return launch_wide<EPI, NORM>(c, a, rows);
+  a.blocked = a.blocked || blocked_rows(c, rows);
+  if (a.blocked) return launch_wide<EPI, NORM>(c, a, rows);
+  if (EPI == EPI_RESID) c->resid_parts = (a.N + 15) / 16;      // one per 16 outputs; launches with a finishing kernel: see there
   const int KS = a.K / 64;
   constexpr int MATS = EPI == EPI_SWIGLU ? 2 : 1;
   const int nw_max = EPI == EPI_SWIGLU ? 5 : 8;
@@ -531,6 +539,7 @@ hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows) {
           } else {
             hipLaunchKernelGGL((gemm_finish_kernel<EPI, NORM>), dim3((a.N / 4 + 255) / 256, g.M), dim3(256), 0, c->stream,
                                (const float*)g.part, (const float*)g.y, (const bf16_t*)g.g_next, g.ksplit, g.M, g.N, g.ldp, g.ldy, g);
+            if (EPI == EPI_RESID) c->resid_parts = (a.N / 4 + 255) / 256;
           }
         }
       } else {
@@ -628,7 +637,7 @@ void launch_attention_t(dmtd_ctx* c, int l, const float* qkv, OT* attn, OT* attn
                      w.q_norm, w.k_norm, (const float2*)(c->ws + c->o.rope_tab), kc, vc, po, pml, cf.n_q_heads, cf.n_kv_heads,
                      cf.max_seq_len, cf.rms_eps, kps, ns, c->part_rows * gq, st, sel, offset, r, append, c->fmap);
   hipLaunchKernelGGL((attn_merge_kernel<HD, OT>), dim3(r, cf.n_q_heads, B), dim3(256), 0, c->stream, po, pml, attn, attn_lo, qd,
-                     cf.n_q_heads, cf.n_kv_heads, kps, ns, c->part_rows * gq, st, sel, offset, r, c->fmap);
+                     cf.n_q_heads, cf.n_kv_heads, kps, ns, c->part_rows * gq, st, sel, offset, r, c->fmap, blocked_rows(c, B * r));
 }
 
 // The matrix-core kernel (bf16 caches): one pass over K and V serves up to 16 query vectors per KV head.
@@ -667,7 +676,7 @@ hipError_t launch_attention_mfma_t(dmtd_ctx* c, int l, const float* qkv, OT* att
     hipLaunchKernelGGL(kern, dim3(n_rg, cf.n_kv_heads, B), dim3(64 * NW), lds, c->stream,
                        kc, vc, cf.n_q_heads, cf.n_kv_heads, cf.max_seq_len, kps, r, c->fmap, st, sel, offset, 1, w.q_norm,
                        w.k_norm, (const float2*)(c->ws + c->o.rope_tab), po, pml, cf.rms_eps, c->part_rows * gq, append,
-                       (bf16_t*)attn, (bf16_t*)attn_lo, qd, qs);
+                       (bf16_t*)attn, (bf16_t*)attn_lo, qd, blocked_rows(c, B * r), qs);
     return hipGetLastError();
   }
   constexpr int KPI = 64;
@@ -679,9 +688,9 @@ hipError_t launch_attention_mfma_t(dmtd_ctx* c, int l, const float* qkv, OT* att
   hipLaunchKernelGGL((attn_split_mfma_kernel<HD, 4, false>), dim3(ns * n_rg, cf.n_kv_heads, B), dim3(256), (size_t)4 * qv_max * HD * 4, c->stream,
                      kc, vc, cf.n_q_heads, cf.n_kv_heads, cf.max_seq_len, kps, r, c->fmap, st, sel, offset, ns, w.q_norm,
                      w.k_norm, (const float2*)(c->ws + c->o.rope_tab), po, pml, cf.rms_eps, c->part_rows * gq, append,
-                     (bf16_t*)nullptr, (bf16_t*)nullptr, 0, qs);
+                     (bf16_t*)nullptr, (bf16_t*)nullptr, 0, 0, qs);
   hipLaunchKernelGGL((attn_merge_kernel<HD, OT>), dim3(r, cf.n_q_heads, B), dim3(256), 0, c->stream, po, pml, attn, attn_lo, qd,
-                     cf.n_q_heads, cf.n_kv_heads, kps, ns, c->part_rows * gq, st, sel, offset, r, c->fmap);
+                     cf.n_q_heads, cf.n_kv_heads, kps, ns, c->part_rows * gq, st, sel, offset, r, c->fmap, blocked_rows(c, B * r));
   return hipGetLastError();
 }
 
@@ -695,7 +704,7 @@ hipError_t launch_attention_prefill(dmtd_ctx* c, int l, const float* qkv, bf16_t
   // KV heads fastest: with 8 of them a compute die's blocks share one head's keys and values in its L2
   hipLaunchKernelGGL((attn_prefill_mfma_kernel<HD>), dim3(cf.n_kv_heads, c->batch, (r + rpb - 1) / rpb), dim3(256), 0, c->stream, qkv, nqkv, kc, vc,
                      cf.n_q_heads, cf.n_kv_heads, cf.max_seq_len, r, (const DevState*)dev_state(c), sel, offset, (const bf16_t*)c->layers[l].q_norm,
-                     (const float2*)(c->ws + c->o.rope_tab), cf.rms_eps, attn, attn_lo, cf.n_q_heads * HD);
+                     (const float2*)(c->ws + c->o.rope_tab), cf.rms_eps, attn, attn_lo, cf.n_q_heads * HD, blocked_rows(c, c->batch * r));
   return hipGetLastError();
 }
 
@@ -739,7 +748,7 @@ hipError_t embed_rows(dmtd_ctx* c, Rows& R, int sel, int offset, int r, int next
   if (c->packed) {
     hipLaunchKernelGGL(embed_pack_kernel, dim3(rows), dim3(256), 0, c->stream, (const bf16_t*)c->embed, dev_tokens(c),
                        cf.max_seq_len, dev_state(c), sel, offset, r, cf.hidden, R.h, (const bf16_t*)norm_gain_for_layer(c, next_layer),
-                       R.xb, R.xb_lo, R.ssp, c->fmap);
+                       R.xb, R.xb_lo, R.ssp, c->fmap, blocked_rows(c, rows));
     R.n_parts = 1;
   } else {
     hipLaunchKernelGGL(embed_kernel<float>, dim3(rows), dim3(256), 0, c->stream, (const float*)c->embed, dev_tokens(c),
@@ -755,7 +764,7 @@ hipError_t add_embed_rows(dmtd_ctx* c, Rows& R, int sel, int offset, int r, int 
   if (c->packed) {
     hipLaunchKernelGGL(add_embed_pack_kernel, dim3(rows), dim3(256), 0, c->stream, R.h, (const bf16_t*)c->embed, dev_tokens(c),
                        cf.max_seq_len, dev_state(c), sel, offset, r, cf.hidden, (const bf16_t*)norm_gain_for_layer(c, next_layer),
-                       R.xb, R.xb_lo, R.ssp);
+                       R.xb, R.xb_lo, R.ssp, blocked_rows(c, rows));
     R.n_parts = 1;
   } else {
     hipLaunchKernelGGL(add_embed_rows_kernel<float>, dim3(rows), dim3(256), 0, c->stream, R.h, (const float*)c->embed,
@@ -770,9 +779,10 @@ hipError_t take_last_rows(dmtd_ctx* c, const Rows& src, Rows& dst, int r, int ad
                           const int* last_pos = nullptr) {
   const dmtd_config& cf = c->cfg;
   if (c->packed) {
+    const int late_blocked = blocked_rows(c, c->late_batch > 0 ? c->late_batch : c->batch);      // the late rows are one per sequence of the whole batch
     hipLaunchKernelGGL(take_last_pack_kernel, dim3(c->batch), dim3(256), 0, c->stream, src.h, dst.h, r, cf.hidden, add_embed,
                        (const bf16_t*)c->embed, dev_tokens(c), cf.max_seq_len, dev_state(c), sel, offset,
-                       (const bf16_t*)norm_gain_for_layer(c, next_layer), dst.xb, dst.xb_lo, dst.ssp, (const float*)nullptr, last_pos, c->fmap);
+                       (const bf16_t*)norm_gain_for_layer(c, next_layer), dst.xb, dst.xb_lo, dst.ssp, (const float*)nullptr, last_pos, c->fmap, late_blocked);
     dst.n_parts = 1;
   } else {
     hipLaunchKernelGGL(take_last_rows_kernel<float>, dim3(c->batch), dim3(256), 0, c->stream, src.h, dst.h, r, cf.hidden,
@@ -814,7 +824,6 @@ hipError_t run_layer(dmtd_ctx* c, int l, Rows& R, int r, int sel, int offset) {
     bf16_t* ab_lo = ab + rows_cap * qd;
     bf16_t* ub = (bf16_t*)(c->ws + c->o.mlp);       // SwiGLU output, likewise
     bf16_t* ub_lo = ub + rows_cap * ff;
-    const int tiles_d = (d + 15) / 16;
     MfmaArgs a{};
     // a2: RMSNorm + fused QKV projection
     a.W = s.qkv; a.xb = R.xb; a.xb_lo = R.xb_lo; a.ldxb = d; a.N = nqkv; a.K = d; a.ssp = R.ssp; a.n_parts = R.n_parts; a.ssp_ld = c->ssp_ld;
@@ -832,7 +841,7 @@ hipError_t run_layer(dmtd_ctx* c, int l, Rows& R, int r, int sel, int offset) {
     a.W = s.o; a.xb = ab; a.xb_lo = ab_lo; a.ldxb = qd; a.N = d; a.K = qd; a.y = R.h; a.ldy = d; a.yb = R.xb; a.yb_lo = R.xb_lo; a.ldyb = d;
     a.g_next = (const bf16_t*)w.mlp_norm; a.ssp_next = R.ssp; a.ssp_ld = c->ssp_ld;
     if ((e = launch_oproj(c, a, rows)) != hipSuccess) return e;
-    R.n_parts = tiles_d;
+    R.n_parts = c->resid_parts;
     // a6: RMSNorm + gate/up + SwiGLU
     a = MfmaArgs{};
     a.W = s.gate; a.W2 = s.up; a.xb = R.xb; a.xb_lo = R.xb_lo; a.ldxb = d; a.N = ff; a.K = d; a.ssp = R.ssp; a.n_parts = R.n_parts;
@@ -843,7 +852,7 @@ hipError_t run_layer(dmtd_ctx* c, int l, Rows& R, int r, int sel, int offset) {
     a.W = s.down; a.xb = ub; a.xb_lo = ub_lo; a.ldxb = ff; a.N = d; a.K = ff; a.y = R.h; a.ldy = d; a.yb = R.xb; a.yb_lo = R.xb_lo; a.ldyb = d;
     a.g_next = (const bf16_t*)norm_gain_for_layer(c, l + 1); a.ssp_next = R.ssp; a.ssp_ld = c->ssp_ld;
     if ((e = launch_down(c, a, rows)) != hipSuccess) return e;
-    R.n_parts = tiles_d;
+    R.n_parts = c->resid_parts;
     return hipSuccess;
   }
   float* attn = (float*)(c->ws + c->o.attn);
@@ -872,13 +881,14 @@ hipError_t run_layer(dmtd_ctx* c, int l, Rows& R, int r, int sel, int offset) {
 }
 
 // a9, first part: final RMSNorm + LM head (Eq. 5) of n_rows rows into logits [n_rows, vocab], selection keys into amax
-hipError_t head_logits(dmtd_ctx* c, const Rows& R, int n_rows, float* logits, unsigned long long* amax, int amax_ld) {
+hipError_t head_logits(dmtd_ctx* c, const Rows& R, int n_rows, float* logits, unsigned long long* amax, int amax_ld, int blocked = 0) {
   const dmtd_config& cf = c->cfg;
   if (c->packed) {
     MfmaArgs a{};
     a.W = c->lm_head_sw; a.xb = R.xb; a.xb_lo = R.xb_lo; a.ldxb = cf.hidden; a.N = cf.vocab; a.K = cf.hidden; a.ssp = R.ssp; a.n_parts = R.n_parts;
     a.ssp_ld = c->ssp_ld; a.eps = cf.rms_eps; a.y = logits; a.ldy = cf.vocab;
     a.amax = amax; a.amax_ld = amax_ld;
+    a.blocked = blocked;         // rows of a larger pass (else the row count decides)
     return launch_lmhead(c, a, n_rows);
   }
   GemvArgs a{};
@@ -923,10 +933,10 @@ hipError_t rows_op(dmtd_ctx* c, int mode, int n_rows, float* dst, const float* s
   const dmtd_config& cf = c->cfg;
   if (c->packed)
     hipLaunchKernelGGL(rows_op_kernel<true>, dim3(n_rows), dim3(256), 0, c->stream, mode, dst, src_a, src_b, cf.hidden, kMaxTau, r, c0, rc,
-                       dev_state(c), (const bf16_t*)norm_gain_for_layer(c, next_layer), xb, xb_lo, ssp);
+                       dev_state(c), (const bf16_t*)norm_gain_for_layer(c, next_layer), xb, xb_lo, ssp, blocked_rows(c, n_rows));
   else
     hipLaunchKernelGGL(rows_op_kernel<false>, dim3(n_rows), dim3(256), 0, c->stream, mode, dst, src_a, src_b, cf.hidden, kMaxTau, r, c0, rc,
-                       dev_state(c), (const bf16_t*)nullptr, (bf16_t*)nullptr, (bf16_t*)nullptr, (float*)nullptr);
+                       dev_state(c), (const bf16_t*)nullptr, (bf16_t*)nullptr, (bf16_t*)nullptr, (float*)nullptr, 0);
   return hipGetLastError();
 }
 
@@ -969,7 +979,8 @@ hipError_t enqueue_step(dmtd_ctx* c, bool full, int r, int n_late) {
           hipLaunchKernelGGL(take_last_pack_kernel, dim3(c->batch), dim3(256), 0, c->stream, front.h, late.h, rc, cf.hidden, 0,
                              (const bf16_t*)c->embed, dev_tokens(c), cf.max_seq_len, dev_state(c), (int)POS_NFRONT, c0 - rc,
                              (const bf16_t*)norm_gain_for_layer(c, F), late.xb, late.xb_lo, late.ssp,
-                             cf.full_pos_add_embed ? (const float*)late.h : (const float*)nullptr, (const int*)nullptr, (const int*)nullptr);
+                             cf.full_pos_add_embed ? (const float*)late.h : (const float*)nullptr, (const int*)nullptr, (const int*)nullptr,
+                             blocked_rows(c, c->batch));
         else
           hipLaunchKernelGGL(take_last_rows_kernel<float>, dim3(c->batch), dim3(256), 0, c->stream, front.h, late.h, rc, cf.hidden,
                              0, (const float*)c->embed, dev_tokens(c), cf.max_seq_len, dev_state(c), (int)POS_NFRONT, c0 - rc,
@@ -1020,11 +1031,13 @@ hipError_t enqueue_step_mixed(dmtd_ctx* c, const std::vector<std::pair<int, int>
   for (const auto& grp : groups) {
     const int r = grp.first, n = grp.second;
     c->batch = n;
+    c->late_batch = B;
     c->fmap = full_list + first;
     e = embed_rows(c, front, POS_NFRONT, 0, r, 0);
     for (int l = 0; l < F && e == hipSuccess; ++l) e = run_layer(c, l, front, r, POS_NFRONT, 0);
     if (e == hipSuccess) e = take_last_rows(c, front, late, r, cf.full_pos_add_embed ? 1 : 0, POS_NFRONT, 0, F);
     c->batch = B;
+    c->late_batch = 0;
     c->fmap = nullptr;
     if (e != hipSuccess) return e;
     first += n;
@@ -1195,12 +1208,12 @@ hipError_t enqueue_masked_chunk(dmtd_ctx* c, Rows& R, int p0, int r, int n_late)
   if (c->packed) {
     hipLaunchKernelGGL((mask_combine_kernel<bf16_t, true>), dim3(rows), dim3(256), 0, c->stream, R.h, E > 0 ? (const float*)enc : (const float*)nullptr,
                        (const bf16_t*)c->embed, dev_tokens(c), cf.max_seq_len, mask, p0, r, cf.hidden, cf.full_pos_add_embed,
-                       (const bf16_t*)norm_gain_for_layer(c, F), R.xb, R.xb_lo, R.ssp);
+                       (const bf16_t*)norm_gain_for_layer(c, F), R.xb, R.xb_lo, R.ssp, blocked_rows(c, rows));
     R.n_parts = 1;
   } else {
     hipLaunchKernelGGL((mask_combine_kernel<float, false>), dim3(rows), dim3(256), 0, c->stream, R.h, E > 0 ? (const float*)enc : (const float*)nullptr,
                        (const float*)c->embed, dev_tokens(c), cf.max_seq_len, mask, p0, r, cf.hidden, cf.full_pos_add_embed,
-                       (const bf16_t*)nullptr, (bf16_t*)nullptr, (bf16_t*)nullptr, (float*)nullptr);
+                       (const bf16_t*)nullptr, (bf16_t*)nullptr, (bf16_t*)nullptr, (float*)nullptr, 0);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   for (int l = F; l < cf.n_layers; ++l)
@@ -1209,13 +1222,13 @@ hipError_t enqueue_masked_chunk(dmtd_ctx* c, Rows& R, int p0, int r, int n_late)
 }
 
 // The LM head and the Eq. 6 summands of rows [m0, m0 + n_rows) of the chunk that enqueue_masked_chunk left in the row buffers
-hipError_t enqueue_masked_head(dmtd_ctx* c, const Rows& R, int m0, int n_rows, int p0, int r, int n) {
+hipError_t enqueue_masked_head(dmtd_ctx* c, const Rows& R, int m0 /* a multiple of 16 */, int n_rows, int p0, int r, int n) {
   const dmtd_config& cf = c->cfg;
   Rows H = R;
   H.h += (size_t)m0 * cf.hidden;
   if (c->packed) { H.xb += (size_t)m0 * cf.hidden; H.xb_lo += (size_t)m0 * cf.hidden; H.ssp += m0; }
   float* logits = (float*)(c->ws + c->o.logits_rows);
-  const hipError_t e = head_logits(c, H, n_rows, logits, (unsigned long long*)(c->ws + c->o.amax_rows), head_row_capacity(cf));
+  const hipError_t e = head_logits(c, H, n_rows, logits, (unsigned long long*)(c->ws + c->o.amax_rows), head_row_capacity(cf), blocked_rows(c, c->batch * r));
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(nll_rows_kernel, dim3(n_rows), dim3(1024), 0, c->stream, (const float*)logits, cf.vocab, (const int*)dev_tokens(c), cf.max_seq_len,
                      m0, p0, r, n, (float*)(c->ws + c->o.nll), (int*)(c->ws + c->o.best));

@@ -435,15 +435,17 @@ __global__ void __launch_bounds__(256) gemm_finish_kernel(const float* part_, co
       bf16_t hi[4], lo[4];
 #pragma unroll
       for (int jj = 0; jj < 4; ++jj) split_bf16(o[jj], hi[jj], lo[jj]);
-      *(uint2*)(a.yb + (size_t)m * a.ldyb + n0) = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
-      *(uint2*)(a.yb_lo + (size_t)m * a.ldyb + n0) = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
+      const size_t at = (size_t)m * a.ldyb + n0;
+      *(uint2*)(a.yb + at) = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
+      *(uint2*)(a.yb_lo + at) = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
     }
   }
   if (EPI == EPI_RESID) {
-    // sum of squares per tile of 16 outputs: the 4 neighbouring threads of a tile
-    hsq += __shfl_xor(hsq, 1, 64);
-    hsq += __shfl_xor(hsq, 2, 64);
-    if (act && (tid & 3) == 0) a.ssp_next[(size_t)(n0 >> 4) * a.ssp_ld + m] = hsq;
+    // one sum of squares per block (1024 outputs of a row): few parts for every reader of the next norm's scale to add up
+    hsq = wave_sum(hsq);
+    if ((tid & 63) == 0) red_s[tid >> 6] = hsq;
+    __syncthreads();
+    if (tid == 0) a.ssp_next[(size_t)blockIdx.x * a.ssp_ld + m] = red_s[0] + red_s[1] + red_s[2] + red_s[3];
   }
 }
 

@@ -6,7 +6,7 @@
 // v_mfma_f32_32x32x16_bf16, the activations as the A operand, so that a lane's results are 16 rows of one output and a
 // store instruction covers 32 neighbouring outputs).  K is walked in steps of 32: weights and both activation planes go
 // from memory straight into LDS (global_load ... lds), 32 pieces of 1 KiB per step, each piece holding 16 rows in the
-// order [16-byte chunk of k][row], which is the order the weights are stored in; a fragment read then takes 256 contiguous
+// order [16-byte chunk of k][row], which is the order the weights and the blocked activations (packed_at) are stored in; a fragment read then takes 256 contiguous
 // bytes per 16 lanes (no bank conflicts).  Two LDS buffers; the next step's loads fly while a step is computed.
 // What bounds it: getting the pieces out of L2 in time.  A step is 8 MFMAs of 32 cycles per wave; two blocks fit a CU
 // (64 KiB of LDS, 112 registers), so one block's waits are covered by the other's MFMAs.  Measured on a 2048 x 19456 x 2560
@@ -26,22 +26,33 @@ constexpr int GW_BM = 128, GW_BN = 256;      // activation rows, weight rows of 
 constexpr int GW_WAVES = 8;
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// Tile index of a block: die x = id % 8 owns tiles [x * q + min(x, rem), ...), q = total / 8.
-// Tiles are numbered by groups of 8 row tiles, within a group the row tiles fastest, then the splits of K, then the weight
-// tiles: what a die computes at a time is about square.
-__device__ __forceinline__ void gw_tile(int id, int total, int mt, int ksplit, int& mb, int& nb, int& ks) {
-  const int x = id & 7, j = id >> 3, q = total >> 3, rem = total & 7;
-  const int t = x * q + (x < rem ? x : rem) + j;
-  const int per_group = 8 * (total / mt), grp = t / per_group, in = t - grp * per_group, rows = min(8, mt - grp * 8);
-  mb = grp * 8 + in % rows;
-  const int rest = in / rows;
-  ks = rest % ksplit;
-  nb = rest / ksplit;
+constexpr int GW_PART = GW_BM * GW_BN;       // floats of a tile's raw sums
+
+// Which tile a block computes, and which part of K.  The launch has n_full blocks with a tile each and, behind them, ksplit blocks
+// for each of the other n_tail tiles.  Either segment goes round-robin over the dies: die x = id % 8 owns the contiguous run
+// [x * q + min(x, rem), ...) of it, q = size / 8.  Tiles are numbered by groups of 8 row tiles, within a group the row tiles
+// fastest: what a die computes at a time is about square.
+struct GwPlace { int t, mb, nb, ks; bool tail; };
+__device__ __forceinline__ GwPlace gw_place(int id, int blocks, int n_full, int n_tail, int mt, int nt) {
+  GwPlace p;
+  p.tail = id >= n_full;
+  if (p.tail) { id -= n_full; blocks -= n_full; } else blocks = n_full;
+  const int x = id & 7, q = blocks >> 3, rem = blocks & 7;
+  const int i = x * q + (x < rem ? x : rem) + (id >> 3);
+  p.ks = p.tail ? i / n_tail : 0;
+  p.t = p.tail ? n_full + i - p.ks * n_tail : i;
+  const int per_group = 8 * nt, grp = p.t / per_group, in = p.t - grp * per_group, rows = min(8, mt - grp * 8);
+  p.nb = in / rows;
+  p.mb = grp * 8 + in - p.nb * rows;
+  return p;
 }
 
-template <int EPI, bool NORM, bool SPLITK>
+template <int EPI, bool NORM>
 __global__ void __launch_bounds__(64 * GW_WAVES, 4) gemm_wide_mfma_kernel(const bf16_t* W_, const bf16_t* W2_, const bf16_t* xb_, const bf16_t* xb_lo_,
-                                                                int M_, int N_, int K_, int ldxb_, int ksplit_, int mt_, MfmaArgs a) {
+                                                                int M_, int N_, int K_, int n_full_, int n_tail_, int ksplit_, int mt_, int nt_, MfmaArgs a) {
+  // which operand gives the result's rows: with the weights there a lane holds 4 consecutive outputs of one activation row (8-byte
+  // pieces of the blocked layout, 512 contiguous bytes per two row groups and store), else 16 rows of one output (128 bytes of a row)
+  constexpr bool WA = EPI == EPI_SWIGLU;
   constexpr int STAGE = 32 * 512;                    // elements of a k-step's slice: 16 weight pieces, 8 high, 8 low activation pieces
   __shared__ __attribute__((aligned(1024))) bf16_t ring[2 * STAGE];
   __shared__ float rs_s[GW_BM];
@@ -49,16 +60,16 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 4) gemm_wide_mfma_kernel(const 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int M = M_, N = N_, K = K_, KS = K >> 6;
-  int mb, nb, ks;
-  gw_tile(blockIdx.x, gridDim.x, mt_, SPLITK ? ksplit_ : 1, mb, nb, ks);
+  const GwPlace pl = gw_place(blockIdx.x, gridDim.x, n_full_, n_tail_, mt_, nt_);
+  const int mb = pl.mb, nb = pl.nb;
   // k-steps of 32 of this block
-  const int s_lo = SPLITK ? 2 * (int)((long)ks * KS / ksplit_) : 0;
-  const int s_hi = SPLITK ? 2 * (int)((long)(ks + 1) * KS / ksplit_) : 2 * KS;
+  const int s_lo = pl.tail ? 2 * (int)((long)pl.ks * KS / ksplit_) : 0;
+  const int s_hi = pl.tail ? 2 * (int)((long)(pl.ks + 1) * KS / ksplit_) : 2 * KS;
   const int n_tiles = (N + 15) >> 4;
 
   // loads: wave w brings weight pieces 2w, 2w + 1 and activation pieces 2w, 2w + 1 of every step; the bases are uniform over
-  // the wave, a lane adds its 16 bytes.  Weight rows beyond N repeat the last tile, activation rows beyond M the last row
-  // (their results are never stored).
+  // the wave, a lane adds its 16 bytes.  Weight tiles beyond N and activation tiles beyond M repeat the last one, and the last
+  // activation tile's rows beyond M hold whatever the buffer held: each is an output row of its own that is never stored.
   const bf16_t* wsrc[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
@@ -67,13 +78,11 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 4) gemm_wide_mfma_kernel(const 
     if (gt >= n_tiles) gt = n_tiles - 1;
     wsrc[j] = ((EPI == EPI_SWIGLU && p >= 8) ? W2_ : W_) + ((size_t)gt * KS) * 1024 + (size_t)s_lo * 512;
   }
-  const bf16_t* xsrc = (w >= 4 ? xb_lo_ : xb_) + (size_t)mb * GW_BM * ldxb_ + (size_t)s_lo * 32;
-  int xoff[2];
+  const int m_tiles = (M + 15) >> 4;
+  const bf16_t* xsrc[2];
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int row = ((2 * w + j) & 7) * 16 + (lane & 15);
-    xoff[j] = min(row, M - 1 - mb * GW_BM) * ldxb_ + (lane >> 4) * 8;
-  }
+  for (int j = 0; j < 2; ++j)
+    xsrc[j] = (w >= 4 ? xb_lo_ : xb_) + (size_t)min(mb * 8 + ((2 * w + j) & 7), m_tiles - 1) * KS * 1024 + (size_t)s_lo * 512;
   auto issue = [&](int buf) {
     bf16_t* dst = ring + buf * STAGE;
 #pragma unroll
@@ -83,10 +92,11 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 4) gemm_wide_mfma_kernel(const 
       wsrc[j] += 512;
     }
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(xsrc + xoff[j]),
+    for (int j = 0; j < 2; ++j) {
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(xsrc[j] + lane * 8),
                                        (__attribute__((address_space(3))) void*)(dst + (16 + 2 * w + j) * 512), 16, 0, 0);
-    xsrc += 32;
+      xsrc[j] += 512;
+    }
   };
 
   const int wm = w & 1, wn = w >> 1;
@@ -102,6 +112,22 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 4) gemm_wide_mfma_kernel(const 
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
   issue(0);
+  if (NORM && !pl.tail) {
+    // the rows' 1/rms while the first step's pieces are on their way: four threads per row, eight parts each at a time
+    const int m = min(mb * GW_BM + (tid >> 2), M - 1);
+    float ss = 0.f;
+    for (int p0 = tid & 3; p0 < a.n_parts; p0 += 32) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = a.ssp[(size_t)min(p0 + 4 * u, a.n_parts - 1) * a.ssp_ld + m];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (p0 + 4 * u < a.n_parts) ss += v[u];
+    }
+    ss += __shfl_xor(ss, 1, 64);
+    ss += __shfl_xor(ss, 2, 64);
+    if ((tid & 3) == 0) rs_s[tid >> 2] = rsqrtf(ss / (float)K + a.eps);
+  }
   for (int s = s_lo; s < s_hi; ++s) {
     const int buf = (s - s_lo) & 1;
     // this step's pieces have landed (nothing newer is in flight), and every wave is done with the other buffer
@@ -123,62 +149,61 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 4) gemm_wide_mfma_kernel(const 
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl[i], wf[j], acc[i][j], 0, 0, 0);
+        for (int i = 0; i < 2; ++i) acc[i][j] = WA ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[j], xl[i], acc[i][j], 0, 0, 0)
+                                                   : __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl[i], wf[j], acc[i][j], 0, 0, 0);
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh[i], wf[j], acc[i][j], 0, 0, 0);
+        for (int i = 0; i < 2; ++i) acc[i][j] = WA ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[j], xh[i], acc[i][j], 0, 0, 0)
+                                                   : __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh[i], wf[j], acc[i][j], 0, 0, 0);
     }
   }
 
   // lane (column n = lane % 32 of a weight tile): element e of acc[i][j] is row 32 i + 8 (e / 4) + 4 (lane / 32) + e % 4 of the wave
   const int m_w = mb * GW_BM + wm * 64, m_l = 4 * (lane >> 5), col = lane & 31;
-  if (SPLITK) {
-    float* part = a.part + (size_t)ks * M * a.ldp;
+  if (EPI != EPI_LOGITS && pl.tail) {
+    // raw sums [128 rows][256 outputs] (SwiGLU: 128 gate, 128 up) of this part of K, for the finishing kernel
+    float* part = a.part + ((size_t)pl.ks * n_tail_ + (pl.t - n_full_)) * GW_PART + (size_t)(wm * 64) * GW_BN;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int n = EPI == EPI_SWIGLU ? nb * 128 + wn * 32 + col : nb * GW_BN + wtile(j) * 32 + col;
-      const int no = n + ((EPI == EPI_SWIGLU && j == 1) ? N : 0);
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int j = 0; j < 2; ++j) {
+        if (WA) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int m = m_w + 32 * i + 8 * (e >> 2) + m_l + (e & 3);
-          if (m < M && n < N) part[(size_t)m * a.ldp + no] = acc[i][j][e];
+          for (int q = 0; q < 4; ++q)
+            *(f32x4*)(part + (32 * i + col) * GW_BN + wtile(j) * 32 + 8 * q + m_l) = f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+        } else {
+#pragma unroll
+          for (int e = 0; e < 16; ++e) part[(32 * i + 8 * (e >> 2) + m_l + (e & 3)) * GW_BN + wtile(j) * 32 + col] = acc[i][j][e];
         }
-    }
+      }
     return;
-  }
-  if (NORM) {
-    // the rows' 1/rms: four threads per row sum interleaved partial sums of squares
-    const int m = mb * GW_BM + (tid >> 2);
-    float ss = 0.f;
-    for (int p = tid & 3; p < a.n_parts; p += 4) ss += a.ssp[(size_t)p * a.ssp_ld + min(m, M - 1)];
-    ss += __shfl_xor(ss, 1, 64);
-    ss += __shfl_xor(ss, 2, 64);
-    if ((tid & 3) == 0) rs_s[tid >> 2] = rsqrtf(ss / (float)K + a.eps);
   }
   if (EPI == EPI_LOGITS && tid < GW_BM) key_s[tid] = 0ull;
   __syncthreads();
   const int r_w = wm * 64 + m_l;
   if (EPI == EPI_SWIGLU) {
-    const int n = nb * 128 + wn * 32 + col;
+    // activation row 32 i + lane % 32 of the wave, outputs 8 q + 4 (lane / 32) + 0..3 of its 32
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i) {
+      const int m = m_w + 32 * i + col;
+      const float rs = rs_s[wm * 64 + 32 * i + col];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int ml = 32 * i + 8 * (e >> 2) + (e & 3);
-        const float rs = rs_s[r_w + ml];
-        const float gt = acc[i][0][e] * rs, up = acc[i][1][e] * rs;
-        bf16_t hi, lo;
-        split_bf16(gt / (1.0f + __expf(-gt)) * up, hi, lo);
-        // neighbouring lanes pair up: the even lane stores both high parts, the odd lane both low parts (4 bytes each)
-        const uint32_t mine = (uint32_t)hi | ((uint32_t)lo << 16);
-        const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mine, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
-        const uint32_t pair = (lane & 1) ? (other >> 16) | (mine & 0xFFFF0000u) : (mine & 0xFFFFu) | (other << 16);
-        const int m = m_w + m_l + ml;
-        if (m < M && n < N) *(uint32_t*)((lane & 1 ? a.yb_lo : a.yb) + (size_t)m * a.ldyb + (n & ~1)) = pair;
+      for (int q = 0; q < 4; ++q) {
+        const int n = nb * 128 + wn * 32 + 8 * q + m_l;
+        bf16_t hi[4], lo[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float gt = acc[i][0][4 * q + e] * rs, up = acc[i][1][4 * q + e] * rs;
+          split_bf16(gt / (1.0f + __expf(-gt)) * up, hi[e], lo[e]);
+        }
+        if (m < M && n < N) {
+          const size_t at = packed_at(1, m, n, a.ldyb);
+          *(uint2*)(a.yb + at) = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
+          *(uint2*)(a.yb_lo + at) = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
+        }
       }
+    }
     return;
   }
 #pragma unroll
@@ -202,6 +227,109 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 4) gemm_wide_mfma_kernel(const 
   if (EPI == EPI_LOGITS && a.amax) {
     __syncthreads();
     if (tid < GW_BM && mb * GW_BM + tid < M) atomicMax(a.amax + (size_t)(nb % AMAX_CELLS) * a.amax_ld + mb * GW_BM + tid, key_s[tid]);
+  }
+}
+
+// Second stage of the tiles whose K was split over blocks (and of every residual tile): epilogue(sum of the parts, in order).  A
+// block takes 16 rows of a tile, a wave 16 rows x 32 outputs at a time: lane (row = lane % 16, chunk = lane / 16) has 8
+// consecutive outputs, so a wave writes 1 KiB of contiguous blocked layout per plane.  (Row by row, 4 outputs per thread, the
+// blocked stores are 16-byte pieces: 38 us for 2048 x 2560 from 3 parts.)
+template <int EPI, bool NORM>
+__global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part_, int M_, int N_, int n_full_, int n_tail_, int ksplit_, int mt_, int nt_,
+                                                               MfmaArgs a) {
+  __shared__ float ss_s[4][16];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int M = M_, N = N_, t = n_full_ + blockIdx.x;
+  const int per_group = 8 * nt_, grp = t / per_group, in = t - grp * per_group, rows = min(8, mt_ - grp * 8);
+  const int nb = in / rows, mb = grp * 8 + in - nb * rows;
+  const int r = blockIdx.y * 16 + (lane & 15), m = mb * GW_BM + r, c8 = (lane >> 4) * 8;
+  if (mb * GW_BM + (int)blockIdx.y * 16 >= M) return;
+  const bool act = m < M;
+  const int mc = act ? m : M - 1;
+  constexpr int GROUPS = EPI == EPI_SWIGLU ? 1 : 2;      // groups of 32 outputs per wave
+  constexpr int PRE = 4;                                 // parts fetched at once
+  const size_t step = (size_t)n_tail_ * GW_PART;
+  float rs = 1.f;
+  if (NORM) {
+    float ss = 0.f;
+    for (int p = lane >> 4; p < a.n_parts; p += 4) ss += a.ssp[(size_t)p * a.ssp_ld + mc];
+    ss += __shfl_xor(ss, 16, 64);
+    ss += __shfl_xor(ss, 32, 64);
+    rs = rsqrtf(ss / (float)a.K + a.eps);
+  }
+  float hsq = 0.f;
+#pragma unroll
+  for (int gi = 0; gi < GROUPS; ++gi) {
+    const int lc = (w * GROUPS + gi) * 32 + c8;                              // output inside the tile
+    const int n = nb * (EPI == EPI_SWIGLU ? 128 : GW_BN) + lc;
+    if (n - c8 >= N) continue;                                               // N is a multiple of 64 here: whole groups
+    const float* p = part_ + (size_t)blockIdx.x * GW_PART + (size_t)r * GW_BN + lc;
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0, u0 = s0, u1 = s0;
+    f32x4 h0 = s0, h1 = s0;
+    u32x4 graw = {0, 0, 0, 0};
+    if (EPI == EPI_RESID) {
+      h0 = *(const f32x4*)(a.y + (size_t)mc * a.ldy + n);
+      h1 = *(const f32x4*)(a.y + (size_t)mc * a.ldy + n + 4);
+      graw = *(const u32x4*)(a.g_next + n);
+    }
+    for (int k0 = 0; k0 < ksplit_; k0 += PRE) {
+      f32x4 x0[PRE], x1[PRE], z0[PRE], z1[PRE];
+#pragma unroll
+      for (int k = 0; k < PRE; ++k) {
+        const float* q = p + (size_t)min(k0 + k, ksplit_ - 1) * step;
+        x0[k] = *(const f32x4*)q; x1[k] = *(const f32x4*)(q + 4);
+        if (EPI == EPI_SWIGLU) { z0[k] = *(const f32x4*)(q + 128); z1[k] = *(const f32x4*)(q + 132); }
+      }
+#pragma unroll
+      for (int k = 0; k < PRE; ++k)
+        if (k0 + k < ksplit_) {
+          s0 += x0[k]; s1 += x1[k];
+          if (EPI == EPI_SWIGLU) { u0 += z0[k]; u1 += z1[k]; }
+        }
+    }
+    float v[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+    if (EPI == EPI_STORE) {
+      if (act) {
+        *(f32x4*)(a.y + (size_t)m * a.ldy + n) = s0 * rs;
+        *(f32x4*)(a.y + (size_t)m * a.ldy + n + 4) = s1 * rs;
+      }
+      continue;
+    }
+    if (EPI == EPI_SWIGLU) {
+      const float up[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) { const float gt = v[e] * rs; v[e] = gt / (1.0f + __expf(-gt)) * (up[e] * rs); }
+    } else {
+      h0 += s0; h1 += s1;
+      if (act) {
+        *(f32x4*)(a.y + (size_t)m * a.ldy + n) = h0;
+        *(f32x4*)(a.y + (size_t)m * a.ldy + n + 4) = h1;
+      }
+      const float hn[8] = {h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w};
+      float gn[8];
+      Elem<bf16_t>::unpack(graw, gn);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) { hsq += hn[e] * hn[e]; v[e] = hn[e] * gn[e]; }
+    }
+    uint32_t hi[4], lo[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      hi[e] = pack_bf16x2(v[2 * e], v[2 * e + 1]);
+      lo[e] = pack_bf16x2(v[2 * e] - __uint_as_float(hi[e] << 16), v[2 * e + 1] - __uint_as_float(hi[e] & 0xFFFF0000u));
+    }
+    if (act) {
+      const size_t at = packed_at(1, m, n, a.ldyb);
+      *(u32x4*)(a.yb + at) = u32x4{hi[0], hi[1], hi[2], hi[3]};
+      *(u32x4*)(a.yb_lo + at) = u32x4{lo[0], lo[1], lo[2], lo[3]};
+    }
+  }
+  if (EPI == EPI_RESID) {
+    // one sum of squares per row and tile of 256 outputs
+    hsq += __shfl_xor(hsq, 16, 64);
+    hsq += __shfl_xor(hsq, 32, 64);
+    if (lane < 16) ss_s[w][lane] = hsq;
+    __syncthreads();
+    if (tid < 16 && act) a.ssp_next[(size_t)nb * a.ssp_ld + m] = ss_s[0][tid] + ss_s[1][tid] + ss_s[2][tid] + ss_s[3][tid];
   }
 }
 

@@ -84,6 +84,7 @@ struct MfmaArgs {
   float* ssp_next;       // RESID: partial sums of squares of the updated residual rows [tiles, ssp_ld]
   unsigned long long* amax;   // LOGITS: selection keys [AMAX_CELLS, amax_ld], already offset to this launch's rows
   int amax_ld;
+  int blocked;           // layout of xb and yb (packed_at): 0 row-major, 1 blocks of 16 x 32 (wide GEMM and its finishing launch only)
   float* part;           // tiled kernel with K split over blocks: partial sums [ksplit][M][ldp]
   int ksplit, ldp;
 };
@@ -338,17 +339,27 @@ __global__ void __launch_bounds__(64 * NWT) gemv_mfma_kernel(const bf16_t* W_, c
   }
 }
 
+// Packed projection inputs come in two layouts.  Up to 128 rows: row-major planes [rows, width].  More rows (the wide GEMM,
+// gemm_wide.hpp): blocks of 16 rows x 32 columns (1 KiB), blocks of a 16-row group following each other along the width, and
+// inside a block [8-column chunk][row][8 values] - the order its tiles are staged in, so a wave's load is 1 KiB of contiguous
+// memory.  Element offset of the 8-column chunk that holds (row, col), plus col % 8:
+__device__ __forceinline__ size_t packed_at(int blocked, int row, int col, int width) {
+  if (!blocked) return (size_t)row * width + col;
+  return ((size_t)(row >> 4) * (width >> 5) + (col >> 5)) * 512 + ((col >> 3) & 3) * 128 + (row & 15) * 8 + (col & 7);
+}
+
 // Row-wise helper for the packed path: from an fp32 row h write the packed input of a norm,
 // h * gain as high and low bf16 parts, and the row's sum of squares as a single partial (n_parts = 1).
 // Call with all threads of the block; contains a barrier.
-__device__ __forceinline__ void pack_row_for_norm(const float* __restrict__ h, const bf16_t* __restrict__ gain, int d,
+__device__ __forceinline__ void pack_row_for_norm(const float* __restrict__ h, const bf16_t* __restrict__ gain, int d, int blocked, int row,
                                                   bf16_t* __restrict__ xb, bf16_t* __restrict__ xb_lo, float* __restrict__ ssp_slot) {
   __shared__ float wsum[16];
   float ss = 0.f;
   for (int k = threadIdx.x; k < d; k += blockDim.x) {
     const float v = h[k];
     ss += v * v;
-    split_bf16(v * bf16_to_f32(gain[k]), xb[k], xb_lo[k]);
+    const size_t at = packed_at(blocked, row, k, d);
+    split_bf16(v * bf16_to_f32(gain[k]), xb[at], xb_lo[at]);
   }
   ss = wave_sum(ss);
   if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = ss;
@@ -366,7 +377,7 @@ __device__ __forceinline__ void pack_row_for_norm(const float* __restrict__ h, c
 __global__ void __launch_bounds__(256) embed_pack_kernel(
     const bf16_t* __restrict__ table, const int* __restrict__ tokens, int s_max, const DevState* st, int sel, int offset,
     int r, int d, float* __restrict__ h, const bf16_t* __restrict__ gain, bf16_t* __restrict__ xb, bf16_t* __restrict__ xb_lo,
-    float* __restrict__ ssp, const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot */) {
+    float* __restrict__ ssp, const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot */, int blocked) {
   // One pass, 8 elements (16 bytes of the table row) per thread and turn, up to NCH turns' loads in flight at once;
   // the row's values stay in registers between the fp32 store, the packed store and the sum of squares.
   constexpr int NCH = 4;
@@ -376,8 +387,6 @@ __global__ void __launch_bounds__(256) embed_pack_kernel(
   const int pos = row_base(st, sel, offset, b) + i;
   const bf16_t* src = table + (size_t)tokens[(size_t)b * s_max + pos] * d;
   float* dst = h + (size_t)row * d;
-  bf16_t* ob = xb + (size_t)row * d;
-  bf16_t* ob_lo = xb_lo + (size_t)row * d;
   const int n_ch = d >> 3;                       // d is a multiple of 64 on this path
   float ss = 0.f;
   for (int c0 = threadIdx.x; c0 < n_ch; c0 += NCH * 256) {
@@ -407,8 +416,9 @@ __global__ void __launch_bounds__(256) embed_pack_kernel(
         }
         *(f32x4*)(dst + (size_t)c * 8) = f32x4{v[0], v[1], v[2], v[3]};
         *(f32x4*)(dst + (size_t)c * 8 + 4) = f32x4{v[4], v[5], v[6], v[7]};
-        *(u32x4*)(ob + (size_t)c * 8) = u32x4{hi[0], hi[1], hi[2], hi[3]};
-        *(u32x4*)(ob_lo + (size_t)c * 8) = u32x4{lo[0], lo[1], lo[2], lo[3]};
+        const size_t at = packed_at(blocked, row, c * 8, d);
+        *(u32x4*)(xb + at) = u32x4{hi[0], hi[1], hi[2], hi[3]};
+        *(u32x4*)(xb_lo + at) = u32x4{lo[0], lo[1], lo[2], lo[3]};
       }
     }
   }
@@ -423,7 +433,7 @@ __global__ void __launch_bounds__(256) take_last_pack_kernel(
     const int* __restrict__ tokens, int s_max, const DevState* st, int sel, int offset, const bf16_t* __restrict__ gain,
     bf16_t* __restrict__ xb, bf16_t* __restrict__ xb_lo, float* __restrict__ ssp, const float* add_rows /* nullable; may be dst */,
     const int* __restrict__ last_pos /* nullable: sequence b's row is the one at explicit position last_pos[b], if in this launch */,
-    const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot */) {
+    const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot */, int blocked) {
   const int bl = blockIdx.x, b = fmap ? fmap[bl] : bl;         // source rows by launch sequence, everything else by slot
   const int i = last_pos ? last_pos[b] - offset : r - 1;
   if (i < 0 || i >= r) return;
@@ -433,18 +443,18 @@ __global__ void __launch_bounds__(256) take_last_pack_kernel(
   if (add_embed) e = table + (size_t)tokens[(size_t)b * s_max + row_base(st, sel, offset, b) + i] * d;
   const float* ar = add_rows ? add_rows + (size_t)b * d : nullptr;
   for (int k = threadIdx.x; k < d; k += blockDim.x) o[k] = s[k] + (add_embed ? bf16_to_f32(e[k]) : 0.0f) + (ar ? ar[k] : 0.0f);
-  pack_row_for_norm(o, gain, d, xb + (size_t)b * d, xb_lo + (size_t)b * d, ssp + b);
+  pack_row_for_norm(o, gain, d, blocked, b, xb, xb_lo, ssp + b);
 }
 
 __global__ void __launch_bounds__(256) add_embed_pack_kernel(
     float* __restrict__ h, const bf16_t* __restrict__ table, const int* __restrict__ tokens, int s_max, const DevState* st,
     int sel, int offset, int r, int d, const bf16_t* __restrict__ gain, bf16_t* __restrict__ xb, bf16_t* __restrict__ xb_lo,
-    float* __restrict__ ssp) {
+    float* __restrict__ ssp, int blocked) {
   const int row = blockIdx.x, b = row / r, i = row % r;
   const bf16_t* e = table + (size_t)tokens[(size_t)b * s_max + row_base(st, sel, offset, b) + i] * d;
   float* o = h + (size_t)row * d;
   for (int k = threadIdx.x; k < d; k += blockDim.x) o[k] += bf16_to_f32(e[k]);
-  pack_row_for_norm(o, gain, d, xb + (size_t)row * d, xb_lo + (size_t)row * d, ssp + row);
+  pack_row_for_norm(o, gain, d, blocked, row, xb, xb_lo, ssp + row);
 }
 
 // ---- ExDy variant (Sec. 2.1, last paragraph before Eq. 5): tokens inside a cycle pass the first
@@ -464,7 +474,7 @@ template <bool PACK>
 __global__ void __launch_bounds__(256) rows_op_kernel(int mode, float* __restrict__ dst, const float* src_a, const float* src_b,
                                                       int d, int store_rows /* slots per sequence */, int r, int c0, int rc,
                                                       const DevState* st, const bf16_t* __restrict__ gain,
-                                                      bf16_t* __restrict__ xb, bf16_t* __restrict__ xb_lo, float* __restrict__ ssp) {
+                                                      bf16_t* __restrict__ xb, bf16_t* __restrict__ xb_lo, float* __restrict__ ssp, int blocked) {
   const int row = blockIdx.x;
   const float* a = nullptr;
   const float* bsrc = nullptr;
@@ -486,7 +496,7 @@ __global__ void __launch_bounds__(256) rows_op_kernel(int mode, float* __restric
   for (int k = threadIdx.x; k < d; k += blockDim.x) o[k] = a[k] + (bsrc ? bsrc[k] : 0.f);
   if (PACK) {
     __syncthreads();
-    pack_row_for_norm(mode == ROWS_STASH ? a : o, gain, d, xb + (size_t)pack_row * d, xb_lo + (size_t)pack_row * d, ssp + pack_row);
+    pack_row_for_norm(mode == ROWS_STASH ? a : o, gain, d, blocked, pack_row, xb, xb_lo, ssp + pack_row);
   }
 }
 
@@ -498,7 +508,7 @@ template <typename WT, bool PACK>
 __global__ void __launch_bounds__(256) mask_combine_kernel(float* __restrict__ h, const float* __restrict__ enc, const WT* __restrict__ table,
                                                            const int* __restrict__ tokens, int s_max, const int* __restrict__ mask,
                                                            int p0, int r, int d, int literal, const bf16_t* __restrict__ gain,
-                                                           bf16_t* __restrict__ xb, bf16_t* __restrict__ xb_lo, float* __restrict__ ssp) {
+                                                           bf16_t* __restrict__ xb, bf16_t* __restrict__ xb_lo, float* __restrict__ ssp, int blocked) {
   const int row = blockIdx.x, b = row / r, pos = p0 + row % r;
   const bool full = mask[pos] != 0;
   float* o = h + (size_t)row * d;
@@ -512,7 +522,7 @@ __global__ void __launch_bounds__(256) mask_combine_kernel(float* __restrict__ h
   }
   if (PACK) {
     __syncthreads();
-    pack_row_for_norm(o, gain, d, xb + (size_t)row * d, xb_lo + (size_t)row * d, ssp + row);
+    pack_row_for_norm(o, gain, d, blocked, row, xb, xb_lo, ssp + row);
   }
 }
 
