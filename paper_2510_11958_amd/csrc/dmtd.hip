@@ -52,12 +52,11 @@ inline int row_capacity(const dmtd_config& c) {
 inline int head_row_capacity(const dmtd_config& c) {
   return c.dtype == DMTD_DTYPE_BF16 ? std::min(row_capacity(c), std::max(kHeadRows, step_row_capacity(c.max_batch))) : row_capacity(c);
 }
-// Positions per sequence of the passes that P positions take: as few passes as the buffers allow, of about equal length
-inline int pass_positions(const dmtd_config& c, int batch, int P) {
-  if (c.dtype != DMTD_DTYPE_BF16) return step_positions(batch);
-  const int most = std::max(kWideRows / batch, kMaxRows);
-  const int passes = (P + most - 1) / most;
-  return std::min(most, ((P + passes - 1) / passes + 15) / 16 * 16);
+// Positions per sequence of a prefill or whole-sequence pass.  Full passes and a short last one rather than equal ones: a full
+// pass is 8 row tiles of the wide GEMM, and equal passes would pad each to whole tiles (3 x 701 positions at 4B shapes: 2046 + 57
+// rows against 1056 + 1047, which are 5 tiles each).
+inline int pass_positions(const dmtd_config& c, int batch) {
+  return c.dtype == DMTD_DTYPE_BF16 ? std::max(kWideRows / batch, kMaxRows) : step_positions(batch);
 }
 constexpr int kMaxPatterns = 64;     // distinct step patterns (which sequences start a cycle, with how many rows) a context keeps on the device
 constexpr size_t kPatternStride(size_t max_batch) { return (max_batch * 5 + 255) / 256 * 256; }   // int list [max_batch] + byte mask [max_batch]
@@ -404,11 +403,10 @@ bool mfma_rows_fit(const dmtd_ctx* c, int rows, int N, int K, int n_parts) {
   return lds_rows <= ((N + 15) / 16 <= c->num_cus ? (size_t)120 * 1024 : (size_t)DMTD_FIT_SMALL_KB * 1024);
 }
 
-// More than kGemmRows rows: the wide GEMM.  Two blocks share a CU, so a round is 2 * CUs blocks and takes 1.6 times as long as a
-// round with one block per CU (measured, 2048 x 2560 x 9728: 160 tiles 357 us, 320 half tiles 256, 480 thirds 192, 640
-// quarters 238).  Whole rounds compute a tile per block; the tiles left over are split along K so that their blocks fill
-// a round too, if that saves more than the raw sums and the finishing launch cost.  The residual projections go through
-// the finishing kernel whole (their few tiles are nearly always split, and it owns their epilogue).
+// More than kGemmRows rows: the wide GEMM, one block per CU.  Whole rounds of the CUs compute a tile per block; the tiles left
+// over are split along K so that their blocks fill a round too, if that saves more than their raw sums and the finishing launch
+// cost.  The residual projections go through the finishing kernel whole (their few tiles are nearly always split, and it
+// owns their epilogue).
 template <int EPI, bool NORM>
 hipError_t launch_wide(dmtd_ctx* c, const MfmaArgs& a, int rows) {
   const int KS = a.K / 64;
@@ -419,33 +417,37 @@ hipError_t launch_wide(dmtd_ctx* c, const MfmaArgs& a, int rows) {
   for (int m0 = 0; m0 < rows; m0 += pass) {
     MfmaArgs g = a;
     g.M = std::min(pass, rows - m0);
-    g.xb = a.xb + (size_t)m0 * a.ldxb;             // m0 is a multiple of 128: whole row groups of the blocked layout
+    g.xb = a.xb + (size_t)m0 * a.ldxb;             // m0 is a multiple of 256: whole row groups of the blocked layout
     g.xb_lo = a.xb_lo + (size_t)m0 * a.ldxb;
     if (a.ssp) g.ssp = a.ssp + m0;
     if (a.y) g.y = a.y + (size_t)m0 * a.ldy;
     if (a.yb) { g.yb = a.yb + (size_t)m0 * a.ldyb; g.yb_lo = a.yb_lo + (size_t)m0 * a.ldyb; }
     if (a.ssp_next) g.ssp_next = a.ssp_next + m0;
     if (a.amax) g.amax = a.amax + m0;
-    const int mt = (g.M + GW_BM - 1) / GW_BM, tiles = mt * nt, slots = 2 * c->num_cus;
+    const int mt = (g.M + GW_BM - 1) / GW_BM, tiles = mt * nt, slots = c->num_cus;
     int n_full = EPI == EPI_RESID ? 0 : tiles, ksplit = 1;
     if constexpr (EPI != EPI_LOGITS) {
       const int whole = EPI == EPI_RESID ? 0 : tiles / slots * slots, left = tiles - whole;
-      // microseconds: a k-step of 32 takes 0.75 us in a round of one block per CU; a raw tile's 128 KiB are written and read
-      // by blocks all over the chip at about 2.5 TB/s; the finishing launch itself 5 us
-      auto round_us = [&](int blocks, int ks) {
-        const int rem = blocks % slots;
-        return (blocks / slots * 1.6 + (rem == 0 ? 0.0 : rem <= c->num_cus ? 1.0 : 1.6)) * (2.0 * KS / ks * 0.75 + 3.0);
-      };
+      // microseconds: a k-step of 32 takes 1.25 us (measured, cold weights), a block's start and end about 4; a raw tile's 256 KiB
+      // are written and read by blocks all over the chip at about 2.5 TB/s in all; the finishing launch itself 5 us
+      auto round_us = [&](int ks) { return (left * ks + slots - 1) / slots * (2.0 * KS / ks * 1.25 + 4.0); };
       auto parts_us = [&](int ks) { return left * ks * (GW_PART * 4) / 2.5e6 + 5.0; };
-      double best = EPI == EPI_RESID ? round_us(left, 1) + parts_us(1) : round_us(left, 1);
-      for (int ks = 2; ks <= kGemmMaxSplit && ks * 4 <= KS && left > 0 && (long)left * ks <= part_tiles; ++ks) {
-        const double us = round_us(left * ks, ks) + parts_us(ks);
+      double best = EPI == EPI_RESID ? round_us(1) + parts_us(1) : round_us(1);
+      for (int ks = 2; ks <= kGemmMaxSplit && ks * 4 <= KS && left > 0 && (long)left * ks <= part_tiles; ++ks) {      // at least 8 steps per part
+        const double us = round_us(ks) + parts_us(ks);
         if (us < best * 0.97) { best = us; ksplit = ks; n_full = whole; }
       }
     }
     const int n_tail = tiles - n_full;
     g.part = c->gemm_part;
-    hipLaunchKernelGGL((gemm_wide_mfma_kernel<EPI, NORM>), dim3(n_full + n_tail * ksplit), dim3(64 * GW_WAVES), 0, c->stream, g.W, g.W2, g.xb, g.xb_lo,
+    auto kern = gemm_wide_mfma_kernel<EPI, NORM>;
+    static bool big_lds = false;
+    if (!big_lds) {
+      hipError_t ae = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)GW_LDS);
+      if (ae != hipSuccess) return ae;
+      big_lds = true;
+    }
+    hipLaunchKernelGGL(kern, dim3(n_full + n_tail * ksplit), dim3(64 * GW_WAVES), GW_LDS, c->stream, g.W, g.W2, g.xb, g.xb_lo,
                        g.M, g.N, g.K, n_full, n_tail, ksplit, mt, nt, g);
     if constexpr (EPI != EPI_LOGITS) {
       if (n_tail > 0)
@@ -1157,7 +1159,7 @@ hipError_t enqueue_prefill(dmtd_ctx* c, int P, int n_late, bool ragged) {
   hipError_t e;
   hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(64), 0, c->stream, dev_state(c), P - 1, P - 1, cf.max_batch);
   int r_last = 0, p_last = 0;
-  const int chunk = pass_positions(cf, c->batch, P);
+  const int chunk = pass_positions(cf, c->batch);
   PartRowsGuard guard{c, c->part_rows};
   c->part_rows = step_positions(c->batch);   // the attention partials of a pass (see attention_single_range)
   for (int p0 = 0; p0 < P; p0 += chunk) {
@@ -2008,7 +2010,7 @@ int dmtd_masked_forward(dmtd_ctx* c, const int32_t* tokens, int32_t batch, int32
   hipError_t e = hipMemcpy2DAsync(c->ws + c->o.tokens, (size_t)cf.max_seq_len * 4, tokens, (size_t)n * 4, (size_t)n * 4, batch,
                                   hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(c->ws + c->o.mask, m32.data(), (size_t)n * 4, hipMemcpyHostToDevice, c->stream);
-  const int chunk = pass_positions(cf, batch, n);
+  const int chunk = pass_positions(cf, batch);
   PartRowsGuard guard{c, c->part_rows};
   c->part_rows = step_positions(batch);
   for (int p0 = 0; p0 < n && e == hipSuccess; p0 += chunk) {

@@ -1,29 +1,34 @@
 // Projection GEMM for many activation rows of a bf16 model on gfx950 (prefill, whole-sequence scoring, batches whose
 // steps carry more than 128 rows): y[m, n] = sum_k W[n, k] * x[m, k] with x in two bf16 planes (see gemv_mfma.hpp).
 //
-// With hundreds of rows the projection is a matrix-core problem, not a weight stream.  A block computes a tile of 128
-// rows x 256 weight rows (SwiGLU: 128 gate and the same 128 up rows) with 8 waves of 64 x 64 (2 x 2 tiles of
-// v_mfma_f32_32x32x16_bf16, the activations as the A operand, so that a lane's results are 16 rows of one output and a
-// store instruction covers 32 neighbouring outputs).  K is walked in steps of 32: weights and both activation planes go
-// from memory straight into LDS (global_load ... lds), 32 pieces of 1 KiB per step, each piece holding 16 rows in the
-// order [16-byte chunk of k][row], which is the order the weights and the blocked activations (packed_at) are stored in; a fragment read then takes 256 contiguous
-// bytes per 16 lanes (no bank conflicts).  Two LDS buffers; the next step's loads fly while a step is computed.
-// What bounds it: getting the pieces out of L2 in time.  A step is 8 MFMAs of 32 cycles per wave; two blocks fit a CU
-// (64 KiB of LDS, 112 registers), so one block's waits are covered by the other's MFMAs.  Measured on a 2048 x 19456 x 2560
-// product without epilogue (TFLOP/s counting both planes): 8 waves, 2 buffers, 2 blocks per CU 1108; 4 waves of 64 x 128 with 2
-// blocks per CU 900, with 4 buffers and one block 888; 256 x 256 tiles with 3 buffers 984; fragments of the next half step read
-// ahead of a step's MFMAs 954 to 1018 (the earlier wait costs more than the read-ahead gains).
+// With hundreds of rows the projection is a matrix-core problem, not a weight stream.  A block computes a tile of 256
+// rows x 256 weight rows (SwiGLU: 128 gate and the same 128 up rows) with 8 waves of 64 x 128 (2 x 4 tiles of
+// v_mfma_f32_32x32x16_bf16).  K is walked in steps of 32: weights and both activation planes go from memory straight into
+// LDS (global_load ... lds), 48 pieces of 1 KiB per step, each piece holding 16 rows in the order [16-byte chunk of k][row],
+// which is the order the weights and the blocked activations (packed_at) are stored in; a fragment read then takes 256
+// contiguous bytes per 16 lanes (no bank conflicts).  A ring of three LDS buffers (144 KiB, one block per CU): a step is
+// waited for by the exact count of its loads while the next one's are in flight, and requests the one after that behind
+// its first fragment reads.
+// What bounds it: per step and CU 2048 cycles of MFMAs per SIMD against 1400 cycles of LDS traffic (128 KiB of fragments, 48 KiB
+// of arriving pieces) that overlap only in part.  Measured without epilogue, 2048 rows, cold weights (us, both planes), this
+// tile / 128 x 256 with 8 waves of 64 x 64 and two blocks per CU: 192 tiles of 6144 x 2560 118 / 127, 608 tiles of
+// 19456 x 2560 370 / 348 where the last of three rounds is 38 % full (hence the split of the last round's tiles, see the
+// launcher); other shapes and orders at 19456 x 2560: 4 waves of 128 x 128 472, waves of 128 x 64 384, fragments read half a
+// step ahead (which needs the next step landed half a step earlier) 384, raised wave priority around the MFMAs 435.
 // Blocks go round-robin over the 8 compute dies; a die takes a contiguous run of tiles with the row tiles fastest, so a
 // weight byte enters one die's L2 only and its row tiles share it there.
 // Against passes of 128 rows through gemm_mfma.hpp (4B shapes, 2048 rows, us with the finishing launch, before / now):
-// gate/up 660 / 454, QKV 390 / 166, down + O 763 / 345.
+// gate/up 660 / 357, QKV 390 / 125, down + O 763 / 297.
 #pragma once
 #include "gemm_mfma.hpp"
 
 namespace dmtd {
 
-constexpr int GW_BM = 128, GW_BN = 256;      // activation rows, weight rows of a block's tile
+constexpr int GW_BM = 256, GW_BN = 256;      // activation rows, weight rows of a block's tile
 constexpr int GW_WAVES = 8;
+constexpr int GW_BUF = 3;                    // LDS buffers
+constexpr int GW_STAGE = 48 * 512;           // elements of a k-step's slice: 16 weight pieces, 16 high and 16 low activation pieces
+constexpr size_t GW_LDS = (size_t)GW_BUF * GW_STAGE * 2;
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int GW_PART = GW_BM * GW_BN;       // floats of a tile's raw sums
@@ -48,13 +53,13 @@ __device__ __forceinline__ GwPlace gw_place(int id, int blocks, int n_full, int 
 }
 
 template <int EPI, bool NORM>
-__global__ void __launch_bounds__(64 * GW_WAVES, 4) gemm_wide_mfma_kernel(const bf16_t* W_, const bf16_t* W2_, const bf16_t* xb_, const bf16_t* xb_lo_,
+__global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const bf16_t* W_, const bf16_t* W2_, const bf16_t* xb_, const bf16_t* xb_lo_,
                                                                 int M_, int N_, int K_, int n_full_, int n_tail_, int ksplit_, int mt_, int nt_, MfmaArgs a) {
   // which operand gives the result's rows: with the weights there a lane holds 4 consecutive outputs of one activation row (8-byte
   // pieces of the blocked layout, 512 contiguous bytes per two row groups and store), else 16 rows of one output (128 bytes of a row)
   constexpr bool WA = EPI == EPI_SWIGLU;
-  constexpr int STAGE = 32 * 512;                    // elements of a k-step's slice: 16 weight pieces, 8 high, 8 low activation pieces
-  __shared__ __attribute__((aligned(1024))) bf16_t ring[2 * STAGE];
+  extern __shared__ float4 gemm_dyn_smem[];
+  bf16_t* ring = (bf16_t*)gemm_dyn_smem;
   __shared__ float rs_s[GW_BM];
   __shared__ unsigned long long key_s[EPI == EPI_LOGITS ? GW_BM : 1];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -67,9 +72,10 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 4) gemm_wide_mfma_kernel(const 
   const int s_hi = pl.tail ? 2 * (int)((long)(pl.ks + 1) * KS / ksplit_) : 2 * KS;
   const int n_tiles = (N + 15) >> 4;
 
-  // loads: wave w brings weight pieces 2w, 2w + 1 and activation pieces 2w, 2w + 1 of every step; the bases are uniform over
-  // the wave, a lane adds its 16 bytes.  Weight tiles beyond N and activation tiles beyond M repeat the last one, and the last
-  // activation tile's rows beyond M hold whatever the buffer held: each is an output row of its own that is never stored.
+  // loads: wave w brings weight pieces 2w, 2w + 1 and activation pieces 4w .. 4w + 3 (waves 0-3 the high plane) of every step;
+  // the bases are uniform over the wave, a lane adds its 16 bytes.  Weight tiles beyond N and activation tiles beyond M repeat
+  // the last one, and the last activation tile's rows beyond M hold whatever the buffer held: each is an output row of its
+  // own that is never stored.
   const bf16_t* wsrc[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
@@ -79,12 +85,12 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 4) gemm_wide_mfma_kernel(const 
     wsrc[j] = ((EPI == EPI_SWIGLU && p >= 8) ? W2_ : W_) + ((size_t)gt * KS) * 1024 + (size_t)s_lo * 512;
   }
   const int m_tiles = (M + 15) >> 4;
-  const bf16_t* xsrc[2];
+  const bf16_t* xsrc[4];
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
-    xsrc[j] = (w >= 4 ? xb_lo_ : xb_) + (size_t)min(mb * 8 + ((2 * w + j) & 7), m_tiles - 1) * KS * 1024 + (size_t)s_lo * 512;
+  for (int j = 0; j < 4; ++j)
+    xsrc[j] = (w >= 4 ? xb_lo_ : xb_) + (size_t)min(mb * 16 + ((4 * w + j) & 15), m_tiles - 1) * KS * 1024 + (size_t)s_lo * 512;
   auto issue = [&](int buf) {
-    bf16_t* dst = ring + buf * STAGE;
+    bf16_t* dst = ring + buf * GW_STAGE;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(wsrc[j] + lane * 8),
@@ -92,82 +98,96 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 4) gemm_wide_mfma_kernel(const 
       wsrc[j] += 512;
     }
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < 4; ++j) {
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(xsrc[j] + lane * 8),
-                                       (__attribute__((address_space(3))) void*)(dst + (16 + 2 * w + j) * 512), 16, 0, 0);
+                                       (__attribute__((address_space(3))) void*)(dst + (16 + 4 * w + j) * 512), 16, 0, 0);
       xsrc[j] += 512;
     }
   };
+  constexpr int LPS = 6;                 // loads a wave issues per step
 
-  const int wm = w & 1, wn = w >> 1;
-  // 32-row weight tiles of this wave (SwiGLU: a gate tile and the up tile of the same outputs)
-  auto wtile = [&](int j) { return EPI == EPI_SWIGLU ? 4 * j + wn : 2 * wn + j; };
+  const int wm = w & 3, wn = w >> 2;
+  // 32-row weight tiles of this wave (SwiGLU: two gate tiles and the up tiles of the same outputs)
+  auto wtile = [&](int j) { return EPI == EPI_SWIGLU ? (j >> 1) * 4 + 2 * wn + (j & 1) : 4 * wn + j; };
   const int frag = ((lane >> 4) & 1) * 512 + (lane >> 5) * 128 + (lane & 15) * 8;   // this lane's 16 bytes of a 32-row tile, k chunk 0
-  f32x16 acc[2][2];
+  f32x16 acc[2][4];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
   issue(0);
+  issue(1);                              // K is a multiple of 64, a part of it at least 8 steps: there is a second one
   if (NORM && !pl.tail) {
-    // the rows' 1/rms while the first step's pieces are on their way: four threads per row, eight parts each at a time
-    const int m = min(mb * GW_BM + (tid >> 2), M - 1);
+    // the rows' 1/rms while the first steps' pieces are on their way: two threads per row, eight parts each at a time
+    const int m = min(mb * GW_BM + (tid >> 1), M - 1);
     float ss = 0.f;
-    for (int p0 = tid & 3; p0 < a.n_parts; p0 += 32) {
+    for (int p0 = tid & 1; p0 < a.n_parts; p0 += 16) {
       float v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = a.ssp[(size_t)min(p0 + 4 * u, a.n_parts - 1) * a.ssp_ld + m];
+      for (int u = 0; u < 8; ++u) v[u] = a.ssp[(size_t)min(p0 + 2 * u, a.n_parts - 1) * a.ssp_ld + m];
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        if (p0 + 4 * u < a.n_parts) ss += v[u];
+        if (p0 + 2 * u < a.n_parts) ss += v[u];
     }
     ss += __shfl_xor(ss, 1, 64);
-    ss += __shfl_xor(ss, 2, 64);
-    if ((tid & 3) == 0) rs_s[tid >> 2] = rsqrtf(ss / (float)K + a.eps);
+    if ((tid & 1) == 0) rs_s[tid >> 1] = rsqrtf(ss / (float)K + a.eps);
   }
+  struct Frag { bf16x8_t xl[2], xh[2], wf[4]; };
+  auto read = [&](Frag& f, const bf16_t* base, int c) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) f.xl[i] = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(base + (32 + (2 * wm + i) * 2) * 512 + c * 256));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f.wf[j] = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(base + wtile(j) * 1024 + c * 256));
+#pragma unroll
+    for (int i = 0; i < 2; ++i) f.xh[i] = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(base + (16 + (2 * wm + i) * 2) * 512 + c * 256));
+  };
+  auto mul = [&](const Frag& f) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p)            // low parts first
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const bf16x8_t x = p ? f.xh[i] : f.xl[i];
+          acc[i][j] = WA ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.wf[j], x, acc[i][j], 0, 0, 0)
+                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, f.wf[j], acc[i][j], 0, 0, 0);
+        }
+  };
+  int buf = 0, nxt = GW_BUF - 1;
   for (int s = s_lo; s < s_hi; ++s) {
-    const int buf = (s - s_lo) & 1;
-    // this step's pieces have landed (nothing newer is in flight), and every wave is done with the other buffer
-    __builtin_amdgcn_s_waitcnt(7 << 4);      // vmcnt(0) lgkmcnt(0), expcnt untouched
+    // this step's pieces have landed once all loads but the next step's have returned (they return in order); behind the
+    // barrier every wave's have, and every wave is done with the buffer that is filled next
+    if (s + 1 < s_hi) __builtin_amdgcn_s_waitcnt(LPS | (7 << 4));      // vmcnt(LPS) lgkmcnt(0), expcnt untouched
+    else __builtin_amdgcn_s_waitcnt(7 << 4);
     __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    if (s + 1 < s_hi) issue(buf ^ 1);
-    const bf16_t* base = ring + buf * STAGE + frag;
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      bf16x8_t xh[2], xl[2], wf[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        xl[i] = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(base + (24 + (2 * wm + i) * 2) * 512 + c * 256));
-        xh[i] = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(base + (16 + (2 * wm + i) * 2) * 512 + c * 256));
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) wf[j] = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(base + wtile(j) * 1024 + c * 256));
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int i = 0; i < 2; ++i) acc[i][j] = WA ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[j], xl[i], acc[i][j], 0, 0, 0)
-                                                   : __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl[i], wf[j], acc[i][j], 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int i = 0; i < 2; ++i) acc[i][j] = WA ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[j], xh[i], acc[i][j], 0, 0, 0)
-                                                   : __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh[i], wf[j], acc[i][j], 0, 0, 0);
-    }
+    asm volatile("" ::: "memory");         // no LDS read of the slice moves above the barrier
+    const bf16_t* base = ring + buf * GW_STAGE + frag;
+    Frag f0, f1;
+    read(f0, base, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (s + 2 < s_hi) issue(nxt);
+    read(f1, base, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    buf = buf + 1 == GW_BUF ? 0 : buf + 1;
+    nxt = nxt + 1 == GW_BUF ? 0 : nxt + 1;
+    mul(f0);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(f1);
+    __builtin_amdgcn_sched_barrier(0);
   }
 
   // lane (column n = lane % 32 of a weight tile): element e of acc[i][j] is row 32 i + 8 (e / 4) + 4 (lane / 32) + e % 4 of the wave
   const int m_w = mb * GW_BM + wm * 64, m_l = 4 * (lane >> 5), col = lane & 31;
   if (EPI != EPI_LOGITS && pl.tail) {
-    // raw sums [128 rows][256 outputs] (SwiGLU: 128 gate, 128 up) of this part of K, for the finishing kernel
+    // raw sums [256 rows][256 outputs] (SwiGLU: 128 gate, 128 up) of this part of K, for the finishing kernel
     float* part = a.part + ((size_t)pl.ks * n_tail_ + (pl.t - n_full_)) * GW_PART + (size_t)(wm * 64) * GW_BN;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < 4; ++j) {
         if (WA) {
 #pragma unroll
           for (int q = 0; q < 4; ++q)
@@ -183,18 +203,18 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 4) gemm_wide_mfma_kernel(const 
   __syncthreads();
   const int r_w = wm * 64 + m_l;
   if (EPI == EPI_SWIGLU) {
-    // activation row 32 i + lane % 32 of the wave, outputs 8 q + 4 (lane / 32) + 0..3 of its 32
+    // activation row 32 i + lane % 32 of the wave, outputs 32 j + 8 q + 4 (lane / 32) + 0..3 of its 64
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int m = m_w + 32 * i + col;
       const float rs = rs_s[wm * 64 + 32 * i + col];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int n = nb * 128 + wn * 32 + 8 * q + m_l;
+      for (int jq = 0; jq < 8; ++jq) {
+        const int j = jq >> 2, q = jq & 3, n = nb * 128 + wn * 64 + 32 * j + 8 * q + m_l;
         bf16_t hi[4], lo[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float gt = acc[i][0][4 * q + e] * rs, up = acc[i][1][4 * q + e] * rs;
+          const float gt = acc[i][j][4 * q + e] * rs, up = acc[i][j + 2][4 * q + e] * rs;
           split_bf16(gt / (1.0f + __expf(-gt)) * up, hi[e], lo[e]);
         }
         if (m < M && n < N) {
@@ -214,7 +234,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 4) gemm_wide_mfma_kernel(const 
       const float rs = NORM ? rs_s[r_w + ml] : 1.f;
       unsigned long long best = 0ull;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < 4; ++j) {
         const int n = nb * GW_BN + wtile(j) * 32 + col;
         const float v = acc[i][j][e] * rs;
         if (m < M && n < N) {
