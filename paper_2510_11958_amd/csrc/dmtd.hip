@@ -142,6 +142,7 @@ struct Ws {   // device workspace carve-up (byte offsets)
   size_t xb, xb_late, ssp, ssp_late, wsw;      // packed path only
   size_t gemm_part;                            // K-split partial sums of the tiled kernel
   size_t patterns;
+  size_t sample_count, sample_list, sample_best;   // sampled steps: per sequence the list of entries that may stay in, and the slices' best draws
   size_t pend_enc, enc_tmp;                    // ExDy: stored encoding outputs of pending tokens; of a prefill chunk
   size_t mask, logits_rows, amax_rows, nll, best, loss;   // whole-sequence masked forward: mask, a chunk's logits and keys, per-position results
   size_t total;
@@ -278,6 +279,9 @@ Ws layout(const dmtd_config& c) {
   w.forced = take((size_t)kMaxTau * B * 4);
   w.state = take(kStateDeltaOff + 12 * B);            // counters, sampling parameters, per-sequence (delta, front position) pairs, last prompt positions
   w.patterns = take((size_t)kMaxPatterns * kPatternStride(B));   // sequence lists and masks of steps whose sequences are at different points of their cycles
+  w.sample_count = take(B * 4);
+  w.sample_list = take(B * SAMPLE_CAP * sizeof(SampleCand));
+  w.sample_best = take(B * ((c.vocab + SAMPLE_SLICE - 1) / SAMPLE_SLICE) * 8);
   w.inv_freq = take((hd / 2) * 8);
   w.pend_enc = take(B * kMaxTau * d * 4);
   w.enc_tmp = take(rows * d * 4);
@@ -314,6 +318,7 @@ Ws layout(const dmtd_config& c) {
 int blocked_rows(const dmtd_ctx* c, int rows) { return c->packed && rows > kGemmRows; }
 
 DevState* dev_state(dmtd_ctx* c) { return (DevState*)(c->ws + c->o.state); }
+int* sample_count(dmtd_ctx* c) { return (int*)(c->ws + c->o.sample_count); }
 int* dev_tokens(dmtd_ctx* c) { return (int*)(c->ws + c->o.tokens); }
 const void* norm_gain_for_layer(const dmtd_ctx* c, int l) {   // gain of the norm that opens layer l (the final norm after the last)
   return l < c->cfg.n_layers ? c->layers[l].attn_norm : c->final_norm;
@@ -908,8 +913,14 @@ hipError_t run_head(dmtd_ctx* c, const Rows& R, int full, int write_tokens, int 
   hipError_t e = head_logits(c, R, n_rows, (float*)(c->ws + c->o.logits), amax, cf.max_batch);
   if (e != hipSuccess) return e;
   if (c->sampling && write_tokens) {
-    hipLaunchKernelGGL(sample_kernel, dim3(n_rows), dim3(1024), 0, c->stream, (const float*)(c->ws + c->o.logits), cf.vocab,
-                       (const SampleCfg*)(c->ws + c->o.state + kStateSampleOff), (const DevState*)dev_state(c), amax, AMAX_CELLS, cf.max_batch);
+    const float* z = (const float*)(c->ws + c->o.logits);
+    const SampleCfg* sc = (const SampleCfg*)(c->ws + c->o.state + kStateSampleOff);
+    const int slices = (cf.vocab + SAMPLE_SLICE - 1) / SAMPLE_SLICE;
+    const SampleScratch ss{sample_count(c), (SampleCand*)(c->ws + c->o.sample_list), (unsigned long long*)(c->ws + c->o.sample_best), slices};
+    hipLaunchKernelGGL(sample_scan_kernel, dim3(slices, n_rows), dim3(256), 0, c->stream, z, cf.vocab, sc, (const DevState*)dev_state(c),
+                       (const unsigned long long*)amax, AMAX_CELLS, cf.max_batch, ss);
+    hipLaunchKernelGGL(sample_pick_kernel, dim3(n_rows), dim3(1024), 0, c->stream, z, cf.vocab, sc, (const DevState*)dev_state(c), amax, AMAX_CELLS,
+                       cf.max_batch, ss);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   hipLaunchKernelGGL(finish_step_kernel, dim3(1), dim3(n_rows >= 16 ? 1024 : 64 * n_rows), 0, c->stream, dev_state(c), amax, AMAX_CELLS, cf.max_batch,
@@ -1157,7 +1168,7 @@ hipError_t enqueue_prefill(dmtd_ctx* c, int P, int n_late, bool ragged) {
   Rows front = front_rows(c), late = late_rows(c);
   const int add_at = cf.full_pos_add_embed ? cf.n_layers - n_late : -1;
   hipError_t e;
-  hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(64), 0, c->stream, dev_state(c), P - 1, P - 1, cf.max_batch);
+  hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(64), 0, c->stream, dev_state(c), P - 1, P - 1, cf.max_batch, sample_count(c));
   int r_last = 0, p_last = 0;
   const int chunk = pass_positions(cf, c->batch);
   PartRowsGuard guard{c, c->part_rows};
@@ -1565,7 +1576,7 @@ static int decode_steps(dmtd_ctx* c, int32_t tau, int32_t n_late, int32_t n_step
       HIP_TRY(c, hipMemcpyAsync(fdev, fhost.data(), (size_t)B * nf * 4, hipMemcpyHostToDevice, c->stream));
     }
     hipLaunchKernelGGL(begin_call_kernel, dim3(1), dim3(256), 0, c->stream, (DevState*)(c->ws + c->o.state),
-                       (int*)(c->ws + c->o.tokens), cf.max_seq_len, fdev, nf, nf, cf.vocab, B);
+                       (int*)(c->ws + c->o.tokens), cf.max_seq_len, fdev, nf, nf, cf.vocab, B, sample_count(c));
     HIP_TRY(c, hipGetLastError());
     int rc = DMTD_OK;
     if (c->test_fail_step >= 0) {
@@ -1583,7 +1594,7 @@ static int decode_steps(dmtd_ctx* c, int32_t tau, int32_t n_late, int32_t n_step
         // device state may be ahead of the host's; resynchronise it to the host's unchanged view
         (void)hipStreamSynchronize(c->stream);
         hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(64), 0, c->stream, (DevState*)(c->ws + c->o.state),
-                           c->sched.n_tok, c->sched.n_front, cf.max_batch);
+                           c->sched.n_tok, c->sched.n_front, cf.max_batch, sample_count(c));
         (void)hipStreamSynchronize(c->stream);
         return rc;
       }
@@ -1676,7 +1687,7 @@ int dmtd_decode_cycle_noalloc(dmtd_ctx* c, int32_t tau, int32_t n_late, int32_t 
     // caller may capture this call into a graph)
     hipLaunchKernelGGL(zero_u64_kernel, dim3(4), dim3(256), 0, c->stream, c->amax, AMAX_CELLS * cf.max_batch);
     hipLaunchKernelGGL(begin_call_kernel, dim3(1), dim3(256), 0, c->stream, (DevState*)(c->ws + c->o.state),
-                       (int*)(c->ws + c->o.tokens), cf.max_seq_len, forced_dev, nf, n_forced, cf.vocab, B);
+                       (int*)(c->ws + c->o.tokens), cf.max_seq_len, forced_dev, nf, n_forced, cf.vocab, B, sample_count(c));
     hipError_t e = hipGetLastError();
     for (int i = 0; i < n && e == hipSuccess; ++i) {
       choose_attention(c, steps[i].pos + 1);
@@ -1747,7 +1758,7 @@ int dmtd_decode_per_seq(dmtd_ctx* c, const int32_t* tau, int32_t n_late, int32_t
       HIP_TRY(c, hipMemcpyAsync(fdev, fhost.data(), (size_t)B * nf * 4, hipMemcpyHostToDevice, c->stream));
     }
     hipLaunchKernelGGL(begin_call_kernel, dim3(1), dim3(256), 0, c->stream, (DevState*)(c->ws + c->o.state),
-                       (int*)(c->ws + c->o.tokens), cf.max_seq_len, fdev, nf, nf, cf.vocab, B);
+                       (int*)(c->ws + c->o.tokens), cf.max_seq_len, fdev, nf, nf, cf.vocab, B, sample_count(c));
     HIP_TRY(c, hipGetLastError());
     std::vector<std::vector<char>> uploads;           // host images of new patterns: alive until the call's synchronisation
     int rc = DMTD_OK;
@@ -1819,7 +1830,7 @@ int dmtd_decode_per_seq(dmtd_ctx* c, const int32_t* tau, int32_t n_late, int32_t
     if (rc != DMTD_OK) {
       // back to the host's unchanged view: counters, and every sequence's front position
       (void)hipStreamSynchronize(c->stream);
-      hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(64), 0, c->stream, (DevState*)(c->ws + c->o.state), c->sched.n_tok, c->sched.n_front, cf.max_batch);
+      hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(64), 0, c->stream, (DevState*)(c->ws + c->o.state), c->sched.n_tok, c->sched.n_front, cf.max_batch, sample_count(c));
       if (c->diverged) {
         int* tmp = (int*)(c->ws + c->o.forced);
         (void)hipMemcpyAsync(tmp, c->seq_front.data(), (size_t)B * 4, hipMemcpyHostToDevice, c->stream);
@@ -2044,7 +2055,7 @@ int dmtd_masked_forward(dmtd_ctx* c, const int32_t* tokens, int32_t batch, int32
                                                     hipMemcpyDeviceToHost, c->stream);
   // the caches served as scratch: back to the empty state on the device as on the host
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(64), 0, c->stream, dev_state(c), 0, 0, cf.max_batch);
+    hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(64), 0, c->stream, dev_state(c), 0, 0, cf.max_batch, sample_count(c));
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -2084,7 +2095,7 @@ int dmtd_reset(dmtd_ctx* c) {
   if (!c) return DMTD_EINVAL;
   if (!c->cfg.dry_run) {
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(64), 0, c->stream, (DevState*)(c->ws + c->o.state), 0, 0, c->cfg.max_batch);
+    hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(64), 0, c->stream, (DevState*)(c->ws + c->o.state), 0, 0, c->cfg.max_batch, sample_count(c));
     HIP_TRY(c, hipGetLastError());
     HIP_TRY(c, hipMemsetAsync(c->ws + c->o.state + kStateDeltaOff, 0, 12 * (size_t)c->cfg.max_batch, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));

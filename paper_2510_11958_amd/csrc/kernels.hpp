@@ -113,8 +113,10 @@ __device__ __forceinline__ float wave_max(float v) {
 // caller-forced input tokens into the token history at the positions they will occupy.
 // forced: [batch, f_stride], the first n_forced entries of a row are used; ids are clamped into the vocabulary (the host
 // has checked them where it can see them; a caller's DEVICE buffer it cannot).
-__global__ void begin_call_kernel(DevState* st, int* tokens, int s_max, const int* forced, int n_forced, int f_stride, int vocab, int batch) {
+__global__ void begin_call_kernel(DevState* st, int* tokens, int s_max, const int* forced, int n_forced, int f_stride, int vocab, int batch,
+                                  int* __restrict__ sample_count /* lists of sampled steps: empty */) {
   const int base = st->n_tok;
+  for (int b = threadIdx.x; b < batch; b += blockDim.x) sample_count[b] = 0;
   for (int i = threadIdx.x; i < batch * n_forced; i += blockDim.x) {
     const int b = i / n_forced, j = i % n_forced;
     const int pos = base + seq_info(st)[b].delta + j;
@@ -156,7 +158,8 @@ __global__ void zero_u64_kernel(unsigned long long* p, int n) {
 }
 
 // Counters to (n_tok, n_front), every sequence's own front position to n_front + its delta (one phase for all).
-__global__ void set_state_kernel(DevState* st, int n_tok, int n_front, int max_batch) {
+__global__ void set_state_kernel(DevState* st, int n_tok, int n_front, int max_batch, int* __restrict__ sample_count) {
+  for (int b = threadIdx.x; b < max_batch; b += blockDim.x) sample_count[b] = 0;
   for (int b = threadIdx.x; b < max_batch; b += blockDim.x) seq_info(st)[b].front = n_front + seq_info(st)[b].delta;
   if (threadIdx.x == 0) { st->n_tok = n_tok; st->n_front = n_front; st->forced_until = 0; st->step_idx = 0; }
 }
@@ -283,22 +286,124 @@ __device__ __forceinline__ uint32_t ordered_u32(float v) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// One block of 1024 threads per sequence, after the LM head: the row at position st->n_tok draws its token from
-// softmax(z / temperature) over the top_k largest logits (logits equal to the k-th largest all stay in).  The
-// k-th largest logit comes from a 4-pass radix select over the ordered bit patterns (integer counts: exact and
-// order independent); the draw is the argmax of z_v / temperature - log(-log(u_v)), u_v the midpoint of one of
-// 2^23 cells of (0, 1) picked by the generator's top 23 bits.  The result replaces the greedy selection keys.
-__global__ void __launch_bounds__(1024) sample_kernel(const float* __restrict__ logits, int V, const SampleCfg* __restrict__ cfg,
-                                                      const DevState* st, unsigned long long* amax, int n_cells, int amax_ld) {
+// Perturbed logit of vocabulary entry v for the row keyed by `base`: z / temperature - log(-log(u)), u the midpoint of one of 2^23
+// cells of (0, 1) picked by the generator's top 23 bits, as a selection key.
+__device__ __forceinline__ unsigned long long draw_key(unsigned long long base, float z, float inv_temp, int v) {
+  const unsigned long long r = splitmix_mix(base + (unsigned long long)(v + 1) * 0x9E3779B97F4A7C15ull);
+  const float u = ((float)(r >> 41) + 0.5f) * (1.0f / 8388608.0f);
+  return argmax_key(z * inv_temp - logf(-logf(u)), v);
+}
+__device__ __forceinline__ unsigned long long draw_base(const SampleCfg* cfg, const DevState* st, int b) {
+  const unsigned long long seed = ((unsigned long long)cfg->seed_hi << 32) | cfg->seed_lo;
+  const unsigned long long stream = ((unsigned long long)(unsigned int)b << 32) | (unsigned int)(st->n_tok + seq_info(st)[b].delta);
+  return splitmix_mix(splitmix_mix(seed + 0x9E3779B97F4A7C15ull) ^ (stream * 0xD6E8FEB86659FD93ull));
+}
+__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long key) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long other = __shfl_xor(key, o, 64);
+    if (other > key) key = other;
+  }
+  return key;
+}
+
+// Token selection by sampling, after the LM head: the row at position st->n_tok of sequence b draws its token from
+// softmax(z / temperature) over the top_k largest logits (logits equal to the k-th largest all stay in); the draw is the
+// argmax of the perturbed logits and replaces the greedy selection keys.  Two launches, since a sequence's 152k logits are far
+// too many for one block (one block per sequence, four radix passes over them: 177 us at batch 8, now 12 + 5):
+//  sample_scan_kernel, a block per 2048 logits:  no restriction: the slice's best perturbed logit.  top_k <= 64: the greedy
+//    selection keys' 64 cells hold the largest logits of 64 disjoint parts of the vocabulary, so the k-th largest of them is at
+//    most the k-th largest logit; the entries that reach it (about 100 of 152k for k = 50) go to the sequence's list.
+//  sample_pick_kernel, a block per sequence:  an entry of the list stays in if fewer than k are larger, the draw is over
+//    those.  A list that overflows (thousands of equal logits) and 64 < top_k < V: radix select over all logits.
+constexpr int SAMPLE_SLICE = 2048, SAMPLE_CAP = 4096;
+struct SampleCand { uint32_t ordered; float z; int v; };
+struct SampleScratch {               // per sequence b: count[b], list[b][SAMPLE_CAP], best[b][slices]
+  int* count; SampleCand* list; unsigned long long* best; int slices;
+};
+
+__global__ void __launch_bounds__(256) sample_scan_kernel(const float* __restrict__ logits, int V, const SampleCfg* __restrict__ cfg,
+                                                          const DevState* st, const unsigned long long* __restrict__ amax, int n_cells, int amax_ld,
+                                                          SampleScratch sc) {
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, v0 = blockIdx.x * SAMPLE_SLICE;
+  const float* z = logits + (size_t)b * V;
+  constexpr int PT = SAMPLE_SLICE / 256;
+  float zv[PT];
+#pragma unroll
+  for (int i = 0; i < PT; ++i) zv[i] = z[min(v0 + tid + 256 * i, V - 1)];
+  const int top_k = cfg->top_k;
+  if (top_k <= 0 || top_k >= V) {
+    __shared__ unsigned long long key_w[4];
+    const unsigned long long base = draw_base(cfg, st, b);
+    const float inv_temp = cfg->inv_temp;
+    unsigned long long key = 0ull;
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+      const int v = v0 + tid + 256 * i;
+      const unsigned long long k = draw_key(base, zv[i], inv_temp, v);
+      if (v < V && k > key) key = k;
+    }
+    key = wave_max_key(key);
+    if (lane == 0) key_w[tid >> 6] = key;
+    __syncthreads();
+    if (tid == 0) {
+      for (int w = 1; w < 4; ++w) if (key_w[w] > key) key = key_w[w];
+      sc.best[(size_t)b * sc.slices + blockIdx.x] = key;
+    }
+    return;
+  }
+  if (top_k > n_cells || n_cells > 64) return;         // radix select in the second launch
+  // the k-th largest of the cells (their ordered logits), bit by bit from the top: every wave for itself
+  const uint32_t cell = lane < n_cells ? (uint32_t)(amax[(size_t)lane * amax_ld + b] >> 32) : 0u;
+  uint32_t bound = 0u;
+#pragma unroll
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t t = bound | (1u << bit);
+    if (__popcll(__ballot(cell >= t)) >= top_k) bound = t;
+  }
+#pragma unroll
+  for (int i = 0; i < PT; ++i) {
+    const int v = v0 + tid + 256 * i;
+    const uint32_t o = ordered_u32(zv[i]);
+    if (v < V && o >= bound) {
+      const int at = atomicAdd(sc.count + b, 1);
+      if (at < SAMPLE_CAP) sc.list[(size_t)b * SAMPLE_CAP + at] = SampleCand{o, zv[i], v};
+    }
+  }
+}
+
+__global__ void __launch_bounds__(1024) sample_pick_kernel(const float* __restrict__ logits, int V, const SampleCfg* __restrict__ cfg,
+                                                           const DevState* st, unsigned long long* amax, int n_cells, int amax_ld, SampleScratch sc) {
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float* z = logits + (size_t)b * V;
   __shared__ unsigned int hist[256];
   __shared__ unsigned int sel_prefix, sel_remaining;
   __shared__ unsigned long long key_w[16];
-  const int top_k = cfg->top_k;
+  __shared__ uint32_t ord_s[SAMPLE_CAP];
+  const int top_k = cfg->top_k, n = sc.count[b];
   const float inv_temp = cfg->inv_temp;
-  uint32_t thr = 0u;                    // entries whose ordered pattern is >= thr stay in
-  if (top_k > 0 && top_k < V) {
+  const unsigned long long base = draw_base(cfg, st, b);
+  unsigned long long key = 0ull;
+  if (top_k <= 0 || top_k >= V) {
+    for (int s = tid; s < sc.slices; s += 1024) {
+      const unsigned long long k = sc.best[(size_t)b * sc.slices + s];
+      if (k > key) key = k;
+    }
+  } else if (top_k <= n_cells && n_cells <= 64 && n <= SAMPLE_CAP) {
+    const SampleCand* list = sc.list + (size_t)b * SAMPLE_CAP;
+    for (int i = tid; i < n; i += 1024) ord_s[i] = list[i].ordered;
+    __syncthreads();
+    for (int i = tid; i < n; i += 1024) {
+      const SampleCand c = list[i];
+      int larger = 0;
+      for (int j = 0; j < n; ++j) larger += ord_s[j] > c.ordered ? 1 : 0;
+      if (larger < top_k) {
+        const unsigned long long k = draw_key(base, c.z, inv_temp, c.v);
+        if (k > key) key = k;
+      }
+    }
+  } else {
+    // k-th largest logit by a 4-pass radix select over the ordered bit patterns (integer counts: exact and order independent)
     uint32_t prefix = 0u;
     unsigned int remaining = (unsigned int)top_k;
     for (int pass = 0; pass < 4; ++pass) {
@@ -325,26 +430,15 @@ __global__ void __launch_bounds__(1024) sample_kernel(const float* __restrict__ 
       prefix = sel_prefix;
       remaining = sel_remaining;
     }
-    thr = prefix;
-  }
-  const unsigned long long seed = ((unsigned long long)cfg->seed_hi << 32) | cfg->seed_lo;
-  const unsigned long long stream = ((unsigned long long)(unsigned int)b << 32) | (unsigned int)(st->n_tok + seq_info(st)[b].delta);
-  const unsigned long long base = splitmix_mix(splitmix_mix(seed + 0x9E3779B97F4A7C15ull) ^ (stream * 0xD6E8FEB86659FD93ull));
-  unsigned long long key = 0ull;
-  for (int v = tid; v < V; v += 1024) {
-    const float zv = z[v];
-    if (ordered_u32(zv) >= thr) {
-      const unsigned long long r = splitmix_mix(base + (unsigned long long)(v + 1) * 0x9E3779B97F4A7C15ull);
-      const float u = ((float)(r >> 41) + 0.5f) * (1.0f / 8388608.0f);
-      const unsigned long long k = argmax_key(zv * inv_temp - logf(-logf(u)), v);
-      if (k > key) key = k;
+    for (int v = tid; v < V; v += 1024) {
+      const float zv = z[v];
+      if (ordered_u32(zv) >= prefix) {
+        const unsigned long long k = draw_key(base, zv, inv_temp, v);
+        if (k > key) key = k;
+      }
     }
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned long long other = __shfl_xor(key, o, 64);
-    if (other > key) key = other;
-  }
+  key = wave_max_key(key);
   if (lane == 0) key_w[wave] = key;
   __syncthreads();
   if (tid < n_cells) {
@@ -355,6 +449,7 @@ __global__ void __launch_bounds__(1024) sample_kernel(const float* __restrict__ 
     }
     amax[(size_t)tid * amax_ld + b] = k;     // cell 0: the draw; the other cells (greedy partial keys): cleared
   }
+  if (tid == 0) sc.count[b] = 0;             // for the next step (every call clears the counts at its start as well)
 }
 
 // Summands of the next-token loss (Eq. 6) and the greedy choice for the rows of one chunk of a whole-sequence
