@@ -327,16 +327,16 @@ const void* norm_gain_for_layer(const dmtd_ctx* c, int l) {   // gain of the nor
 // ------------------------------------------------------- fp32 path: FMA weight streaming
 
 template <typename WT, int M, int EPI, bool NORM>
-hipError_t launch_gemv(dmtd_ctx* c, GemvArgs a) {
+hipError_t launch_gemv(dmtd_ctx* c, GemvArgs a, int groups) {
   // narrow outputs with long rows: the waves of a block split K
   if constexpr ((EPI == EPI_RESID || EPI == EPI_STORE) && !NORM) {
     if (a.K >= 1024 && a.N <= 8192) {
       if (a.K <= 4 * 2 * 512) {
-        hipLaunchKernelGGL((gemv_ksplit_kernel<WT, M, EPI, 2, 4, 1>), dim3((a.N + 3) / 4), dim3(256), 0, c->stream, a);
+        hipLaunchKernelGGL((gemv_ksplit_kernel<WT, M, EPI, 2, 4, 1>), dim3((a.N + 3) / 4, groups), dim3(256), 0, c->stream, a);
         return hipGetLastError();
       }
       if (a.K <= 4 * 5 * 512) {
-        hipLaunchKernelGGL((gemv_ksplit_kernel<WT, M, EPI, 5, 4, 1>), dim3((a.N + 3) / 4), dim3(256), 0, c->stream, a);
+        hipLaunchKernelGGL((gemv_ksplit_kernel<WT, M, EPI, 5, 4, 1>), dim3((a.N + 3) / 4, groups), dim3(256), 0, c->stream, a);
         return hipGetLastError();
       }
     }
@@ -362,27 +362,31 @@ hipError_t launch_gemv(dmtd_ctx* c, GemvArgs a) {
   int blocks = (tasks + 3) / 4;                      // one task per wave ...
   const int cap = c->num_cus * occ_cache;            // ... unless that exceeds what is resident at once
   if (blocks > cap) blocks = cap;
-  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, c->stream, a);
+  hipLaunchKernelGGL(kern, dim3(blocks, groups), dim3(256), lds, c->stream, a);
   return hipGetLastError();
 }
 
 template <typename WT, int EPI, bool NORM>
 hipError_t gemv_rows(dmtd_ctx* c, GemvArgs a, int rows) {
-  // rows are processed in groups of up to kGemvRows; each group streams the matrix once
-  for (int m0 = 0; m0 < rows; m0 += kGemvRows) {
-    const int m = rows - m0 < kGemvRows ? rows - m0 : kGemvRows;
+  // Groups of kGemvRows rows, all full groups in one launch (a group per grid row), the rest in another.  One launch per group
+  // had the groups wait for each other on a model whose weights sit in cache: the tiny model's 32-row
+  // prompt took 1.0 of a request's 2.6 ms.
+  for (int m0 = 0; m0 < rows;) {
+    const int groups = (rows - m0) / kGemvRows;
+    const int m = groups > 0 ? kGemvRows : rows - m0;
     GemvArgs g = a;
     g.x = a.x + (size_t)m0 * a.ldx;
     g.y = a.y + (size_t)m0 * a.ldy;
     if (a.amax) g.amax = a.amax + m0;
     hipError_t e;
     switch (m) {
-      case 1: e = launch_gemv<WT, 1, EPI, NORM>(c, g); break;
-      case 2: e = launch_gemv<WT, 2, EPI, NORM>(c, g); break;
-      case 3: e = launch_gemv<WT, 3, EPI, NORM>(c, g); break;
-      default: e = launch_gemv<WT, 4, EPI, NORM>(c, g); break;
+      case 1: e = launch_gemv<WT, 1, EPI, NORM>(c, g, 1); break;
+      case 2: e = launch_gemv<WT, 2, EPI, NORM>(c, g, 1); break;
+      case 3: e = launch_gemv<WT, 3, EPI, NORM>(c, g, 1); break;
+      default: e = launch_gemv<WT, 4, EPI, NORM>(c, g, groups); break;
     }
     if (e != hipSuccess) return e;
+    m0 += groups > 0 ? groups * kGemvRows : m;
   }
   return hipSuccess;
 }

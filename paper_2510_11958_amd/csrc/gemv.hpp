@@ -61,6 +61,10 @@ template <typename WT, int M, int EPI, bool NORM, int GEMV_ITS>   // GEMV_ITS: k
 __global__ void __launch_bounds__(256) gemv_rows_kernel(GemvArgs a) {
   extern __shared__ float4 smem4[];
   float* xs = (float*)smem4;                       // [M][K]
+  // blockIdx.y: group of M activation rows (the groups of one launch share the weights in cache)
+  a.x += (size_t)blockIdx.y * M * a.ldx;
+  a.y += (size_t)blockIdx.y * M * a.ldy;
+  if (EPI == EPI_LOGITS) a.amax += blockIdx.y * M;
   __shared__ float red[4][M];
   __shared__ float rs_s[M];
   __shared__ unsigned long long best_s[M];
@@ -195,6 +199,8 @@ __global__ void __launch_bounds__(256) gemv_rows_kernel(GemvArgs a) {
 // w, w+NW, w+2NW, ... (ITS of them at most, so K <= NW * ITS * 512).
 template <typename WT, int M, int EPI, int ITS, int NW, int RG>
 __global__ void __launch_bounds__(64 * NW) gemv_ksplit_kernel(GemvArgs a) {
+  a.x += (size_t)blockIdx.y * M * a.ldx;           // group of M activation rows
+  a.y += (size_t)blockIdx.y * M * a.ldy;
   typedef typename Elem<WT>::Raw Raw;
   constexpr int MP = PadRows<M>::MP, V = 4 * MP;
   constexpr int LOGV = V == 4 ? 2 : V == 8 ? 3 : 4;
