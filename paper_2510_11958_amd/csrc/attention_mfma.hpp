@@ -15,11 +15,13 @@
 //            scores of keys 4 kq .. 4 kq + 3 for query q;
 //   softmax  running maximum and sum per query in those lanes (maximum across the 4 kq lanes by
 //            two shuffles);
-//   output   O[q, d] += sum_key P[q, key] V[key, d]     v_mfma_f32_16x16x4_f32 (contraction over 4 keys,
-//            one fp32 value per lane and operand, so no operand has to be transposed): for m = 0..3 the A
-//            operand is the lane's own p of key 4 kq + m, the B operand the lane's own V[4 kq + m][8 sl + e]
-//            (sl = lane % 16; the lane loaded those 8 consecutive d with one 16-byte load), one MFMA
-//            per e; accumulator e of lane (sl, kq) holds O[4 kq + j][8 sl + e], j = 0..3.
+//   output   O[q, d] += sum_key P[q, key] V[key, d]     v_mfma_f32_16x16x16_bf16 (a lane's operand: 4 consecutive
+//            keys of one row or column, so nothing has to be transposed between lanes): the A operand is the
+//            lane's own p of keys 4 kq .. 4 kq + 3, the B operand the lane's own V[4 kq ..][8 sl + e] (sl = lane % 16;
+//            the lane loaded those 8 consecutive d of each key with one 16-byte load), for each e; accumulator e of lane
+//            (sl, kq) holds O[4 kq + j][8 sl + e], j = 0..3.  A probability goes in as three bf16 parts that add up to
+//            all 24 bits of it (V is bf16), 24 MFMAs of 16 cycles per 16 keys; the fp32 matrix instruction
+//            (16x16x4, a quarter of the keys in twice the time) took 1024 cycles for the same sums.
 // Nothing moves between lanes except the maxima and the per-query rescale factors.
 #pragma once
 #include "attention.hpp"
@@ -40,6 +42,7 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v;
 }
 
+typedef short bf16x4s_t __attribute__((ext_vector_type(4)));      // operand of the 16x16x16 bf16 matrix instruction
 constexpr int ATT_QPAD = 8;     // bf16 elements of padding per LDS query row
 
 // A vector of the prologue is handled by the 16 lanes of a DPP row; lane l holds the rotary pairs
@@ -310,16 +313,11 @@ __global__ void __launch_bounds__(64 * NW) attn_split_mfma_kernel(
   for (int it0 = key_begin; it0 < key_end; it0 += 16 * NW) {
     const int base = it0 + 16 * wave;                           // this wave's 16 keys
     u32x4 ka[KSTEPS];
-    float vf[4][DPL];
+    vraw_t va[4];
 #pragma unroll
     for (int t = 0; t < KSTEPS; ++t) ka[t] = kr[t];
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
-#pragma unroll
-      for (int e = 0; e < DPL / 2; ++e) {
-        vf[m][2 * e] = __uint_as_float(vr[m][e] << 16);
-        vf[m][2 * e + 1] = __uint_as_float(vr[m][e] & 0xFFFF0000u);
-      }
+    for (int m = 0; m < 4; ++m) va[m] = vr[m];
     if (it0 + 16 * NW < key_end) load_kv(base + 16 * NW, key_end);   // the next iteration's keys fly during this one
     if (holds_new) {
       // new positions: key and value come from LDS (the cache slot is written by this launch, maybe not yet)
@@ -336,7 +334,7 @@ __global__ void __launch_bounds__(64 * NW) attn_split_mfma_kernel(
         const int iv = base + 4 * kq + m - pos_first;
         if (iv >= 0 && iv < n_new) {
 #pragma unroll
-          for (int e = 0; e < DPL; ++e) vf[m][e] = vnew_s[iv][DPL * sl + e];
+          for (int e = 0; e < DPL / 2; ++e) va[m][e] = pack_bf16x2(vnew_s[iv][DPL * sl + 2 * e], vnew_s[iv][DPL * sl + 2 * e + 1]);   // exact: rounded already
         }
       }
     }
@@ -377,10 +375,26 @@ __global__ void __launch_bounds__(64 * NW) attn_split_mfma_kernel(
     for (int j = 0; j < 4; ++j) rj[j] = __shfl(resc, 4 * kq + j, 64);
 #pragma unroll
     for (int e = 0; e < DPL; ++e) { acc[e].x *= rj[0]; acc[e].y *= rj[1]; acc[e].z *= rj[2]; acc[e].w *= rj[3]; }
+    // the lane's 4 probabilities in three bf16 parts (leading 8 bits truncated, the next 8, the rest: exact)
+    uint2 pp[3];
+    {
+      float q[4] = {p[0], p[1], p[2], p[3]};
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
+      for (int s3 = 0; s3 < 3; ++s3) {
+        pp[s3].x = __builtin_amdgcn_perm(__float_as_uint(q[1]), __float_as_uint(q[0]), 0x07060302u);
+        pp[s3].y = __builtin_amdgcn_perm(__float_as_uint(q[3]), __float_as_uint(q[2]), 0x07060302u);
 #pragma unroll
-      for (int e = 0; e < DPL; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[m], vf[m][e], acc[e], 0, 0, 0);
+        for (int j = 0; j < 4; ++j) q[j] -= __uint_as_float(__float_as_uint(q[j]) & 0xFFFF0000u);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < DPL; ++e) {
+      const unsigned int sel = (e & 1) ? 0x07060302u : 0x05040100u;
+      const uint2 v4 = make_uint2(__builtin_amdgcn_perm(va[1][e >> 1], va[0][e >> 1], sel), __builtin_amdgcn_perm(va[3][e >> 1], va[2][e >> 1], sel));
+#pragma unroll
+      for (int s3 = 2; s3 >= 0; --s3)
+        acc[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4s_t, pp[s3]), __builtin_bit_cast(bf16x4s_t, v4), acc[e], 0, 0, 0);
+    }
   }
   // per-wave totals: l summed over the 4 kq lanes of a query
   l_run += __shfl_xor(l_run, 16, 64);

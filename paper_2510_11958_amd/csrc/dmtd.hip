@@ -183,7 +183,7 @@ struct dmtd_ctx {
   std::map<std::vector<int>, hipGraphExec_t> group_graphs;            // several steps in one graph (dmtd_decode)
   bool sampling = false;      // tokens are drawn (dmtd_set_sampling) instead of taken greedily
   bool share_kv = false;      // attention launches: one pass over K/V for all rows of a sequence (long contexts)
-  int att_bucket = 512;       // attention launches: context bucket (multiple of 512) the key ranges are laid out for
+  int att_bucket = 512;       // attention launches: context bucket (256 or a multiple of 512) the key ranges are laid out for
   int late_batch = 0;         // a front pass over some sequences: sequences of the whole batch (0: all are in the pass)
   int resid_parts = 0;        // partial sums of squares per row the last residual projection left for the next norm
   const int* fmap = nullptr;  // launches of a front pass over SOME sequences: launch sequence -> sequence slot (device); null = all, in order
@@ -401,7 +401,13 @@ hipError_t gemv_rows(dmtd_ctx* c, GemvArgs a, int rows) {
 bool attention_single_range(const dmtd_ctx* c, int r) {
   const dmtd_config& cf = c->cfg;
   const int gq = cf.n_q_heads / cf.n_kv_heads, rpb = 16 / gq, n_rg = (r + rpb - 1) / rpb;
-  return r > c->part_rows || (long)cf.n_kv_heads * c->batch * n_rg >= c->num_cus;     // more rows than the ranges' partials are laid out for: one range
+  const long blocks = (long)cf.n_kv_heads * c->batch * n_rg;
+  if (r > c->part_rows || blocks >= c->num_cus) return true;         // more rows than the ranges' partials are laid out for: one range
+  // Fewer blocks than CUs, short contexts: a block walks 128 keys in about 1.4 us (2.3 us with 8 blocks on the chip), the merge
+  // launch and, with K-split QKV sums, their finishing launch cost 4-9 us.  us per step of 8 layers, one range / ranges + merge:
+  // 64 blocks (batch 8), 2560 wide: 100 keys 485 / 523, 400 keys 519 / 526, 900 keys 592 / 580; 1024 wide: 250 / 272, 288 / 276,
+  // 355 / 324; 128 blocks: 400 keys 572 / 626 and 346 / 381, 900 keys 639 / 653 and 421 / 408; 8 blocks: 400 keys 483 / 434.
+  return c->att_bucket <= 4 * blocks;
 }
 
 // Whether `rows` packed activation rows of width K (both planes, plus n_parts partial sums of squares per row) stay in
@@ -1074,7 +1080,7 @@ bool kv_is_large(const dmtd_ctx* c, int ctx) {
 }
 
 void choose_attention(dmtd_ctx* c, int ctx) {
-  c->att_bucket = (ctx + 511) / 512 * 512;
+  c->att_bucket = ctx <= 256 ? 256 : (ctx + 511) / 512 * 512;      // 256: contexts short enough for one range per block at small batches
   c->share_kv = kv_is_large(c, ctx);
 }
 
