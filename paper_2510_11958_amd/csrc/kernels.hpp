@@ -464,16 +464,34 @@ __global__ void __launch_bounds__(1024) nll_rows_kernel(const float* __restrict_
   __shared__ unsigned long long key_w[16];
   __shared__ float sum_w[16];
   __shared__ float top_s;
-  unsigned long long key = 0ull;
-  for (int v = tid; v < V; v += 1024) {
-    const unsigned long long k = argmax_key(z[v], v);
-    if (k > key) key = k;
-  }
+  // One pass: eight loads in flight per thread; the best entry by its ordered bit pattern (a thread's entries come in rising
+  // order, so the first of equal ones stays), the sum of exponentials against a running maximum.  (Two passes with one load in
+  // flight: 180 us for 512 rows of 152k, now 68.)
+  uint32_t bo = 0u;
+  int bi = 0;
+  float mx = -INFINITY, s = 0.f;
+  for (int v0 = tid; v0 < V; v0 += 8 * 1024) {
+    float zv[8];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned long long other = __shfl_xor(key, o, 64);
-    if (other > key) key = other;
+    for (int u = 0; u < 8; ++u) zv[u] = z[min(v0 + 1024 * u, V - 1)];
+    float m8 = mx;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int v = v0 + 1024 * u;
+      if (v >= V) zv[u] = -INFINITY;
+      const uint32_t b32 = __float_as_uint(zv[u]), o = (b32 & 0x80000000u) ? ~b32 : (b32 | 0x80000000u);
+      if (v < V && o > bo) { bo = o; bi = v; }
+      m8 = fmaxf(m8, zv[u]);
+    }
+    if (m8 != -INFINITY) {
+      s *= __expf(mx - m8);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += __expf(zv[u] - m8);
+      mx = m8;
+    }
   }
+  unsigned long long key = ((unsigned long long)bo << 32) | (uint32_t)(0x7FFFFFFF - bi);
+  key = wave_max_key(key);
   if (lane == 0) key_w[wave] = key;
   __syncthreads();
   if (tid == 0) {
@@ -485,8 +503,7 @@ __global__ void __launch_bounds__(1024) nll_rows_kernel(const float* __restrict_
   }
   __syncthreads();
   const float top = top_s;
-  float s = 0.f;
-  for (int v = tid; v < V; v += 1024) s += __expf(z[v] - top);
+  s = mx == -INFINITY ? 0.f : s * __expf(mx - top);      // to the row's maximum
   s = wave_sum(s);
   if (lane == 0) sum_w[wave] = s;
   __syncthreads();
