@@ -72,6 +72,9 @@ constexpr int kGemmMaxSplit = DMTD_GEMM_MAXSPLIT;   // K splits of the tiled ker
 #define DMTD_GEMM_ROWS 128
 #endif
 constexpr int kGemmRows = DMTD_GEMM_ROWS;   // activation rows per pass of the LDS-tiled MFMA kernel (launches with more than 16 rows)
+// Up to this many rows go through the LDS-tiled kernel in passes, more through the wide GEMM (all four projections of a layer at
+// 4B shapes, us: 160 rows 172 / 190, 192 rows 191 / 190, 256 rows 220 / 190 with tiles of 256 rows)
+constexpr int kTiledRows = 192;
 constexpr int kMfmaPF = 10;          // k-steps (64 elements) a wave of the MFMA kernel holds in registers
 // Waves that split K for one matrix (NW) and k-steps a wave keeps in flight as a rolling window (PF), per projection;
 // NW = 0: the one-round rule of launch_mfma with kMfmaPF.  Defaults from sweeps at 4B shapes on MI355X, us per launch
@@ -263,16 +266,22 @@ Ws layout(const dmtd_config& c) {
   w.kv = take(w.kv_layer_stride * c.n_layers);
   w.h = take(rows * d * 4);
   w.h_late = take(B * d * 4);
+  // A whole-sequence pass keeps its logits where the layers' scratch is: nothing of that is alive between the last layer
+  // of a chunk and the first of the next
+  const size_t scratch = off;
   w.qkv = take(rows * nqkv * 4);
   w.attn = take(rows * qd * 4);                       // fp32 path: fp32 rows; packed path: bf16 rows
   w.mlp = take(rows * (size_t)c.intermediate * 4);    // likewise
-  w.logits = take(B * (size_t)c.vocab * 4);
   // partial results of the attention key ranges: laid out per sequence for kMaxRows rows in decode steps and for
   // step_positions in prefill (a pass with more positions takes one key range per block); sequences x rows per sequence
   // never exceeds a step's row capacity
   const size_t qv_rows = step_rows * (c.n_q_heads / c.n_kv_heads);
   w.part_o = take(c.n_kv_heads * ATT_MAX_SPLITS * qv_rows * hd * 4);
   w.part_ml = take(c.n_kv_heads * ATT_MAX_SPLITS * qv_rows * 2 * 4);
+  if (c.dtype == DMTD_DTYPE_BF16) w.gemm_part = take(gemm_part_floats(c) * 4);
+  w.logits_rows = scratch;
+  off = std::max(off, align_up(scratch + head_row_capacity(c) * (size_t)c.vocab * 4, 256));
+  w.logits = take(B * (size_t)c.vocab * 4);
   w.amax = take((size_t)AMAX_CELLS * B * 8);
   w.tokens = take(B * S * 4);
   w.emitted = take((size_t)kMaxTau * B * 4);
@@ -287,7 +296,6 @@ Ws layout(const dmtd_config& c) {
   w.enc_tmp = take(rows * d * 4);
   w.rope_tab = take(S * (hd / 2) * 8);                 // (cos, sin) per position and frequency
   w.mask = take(S * 4);
-  w.logits_rows = take(head_row_capacity(c) * (size_t)c.vocab * 4);
   w.amax_rows = take((size_t)AMAX_CELLS * head_row_capacity(c) * 8);
   w.nll = take(B * S * 4);
   w.best = take(B * S * 4);
@@ -298,7 +306,6 @@ Ws layout(const dmtd_config& c) {
     w.xb_late = take(B * d * 2 * 2);
     w.ssp = take(parts * rows * 4);
     w.ssp_late = take(parts * rows * 4);
-    w.gemm_part = take(gemm_part_floats(c) * 4);
     w.wsw = take((swizzled_layer_elems(c) * c.n_layers + swizzled_elems(c.vocab, d)) * 2);
   }
   w.total = off;
@@ -315,7 +322,7 @@ Ws layout(const dmtd_config& c) {
   } while (0)
 
 // Whether the packed inputs of a pass with that many rows are in the wide GEMM's blocked layout (packed_at)
-int blocked_rows(const dmtd_ctx* c, int rows) { return c->packed && rows > kGemmRows; }
+int blocked_rows(const dmtd_ctx* c, int rows) { return c->packed && rows > kTiledRows; }
 
 DevState* dev_state(dmtd_ctx* c) { return (DevState*)(c->ws + c->o.state); }
 int* sample_count(dmtd_ctx* c) { return (int*)(c->ws + c->o.sample_count); }
@@ -418,17 +425,59 @@ bool mfma_rows_fit(const dmtd_ctx* c, int rows, int N, int K, int n_parts) {
   return lds_rows <= ((N + 15) / 16 <= c->num_cus ? (size_t)120 * 1024 : (size_t)DMTD_FIT_SMALL_KB * 1024);
 }
 
-// More than kGemmRows rows: the wide GEMM, one block per CU.  Whole rounds of the CUs compute a tile per block; the tiles left
+// More than kTiledRows rows: the wide GEMM, one block per CU.  Whole rounds of the CUs compute a tile per block; the tiles left
 // over are split along K so that their blocks fill a round too, if that saves more than their raw sums and the finishing launch
 // cost.  The residual projections go through the finishing kernel whole (their few tiles are nearly always split, and it
 // owns their epilogue).
+struct WidePlan { double us; int n_full, ksplit; };
+template <int EPI, int BM>
+WidePlan plan_wide(const dmtd_ctx* c, int rows, int nt, int KS) {
+  const int tiles = (rows + BM - 1) / BM * nt, slots = c->num_cus;
+  // a k-step of 32 takes 1.25 us with 256 rows and 0.8 with 128 (measured, cold weights), a block's start and end about 4;
+  // a raw tile's bytes are written and read by blocks all over the chip at about 3.5 TB/s in all; the finishing launch itself 5 us
+  const double step_us = BM == 256 ? 1.25 : 0.8;
+  const int part_tiles = (int)std::min<size_t>(gemm_part_floats(c->cfg) / GwTile<BM>::PART, 1 << 20);
+  const int whole = EPI == EPI_RESID ? 0 : tiles / slots * slots, left = tiles - whole;
+  auto round_us = [&](int ks) { return (left * ks + slots - 1) / slots * (2.0 * KS / ks * step_us + 4.0); };
+  auto parts_us = [&](int ks) { return left * ks * (GwTile<BM>::PART * 4) / 3.5e6 + 5.0; };
+  WidePlan p{round_us(1) + (EPI == EPI_RESID ? parts_us(1) : 0.0), EPI == EPI_RESID ? 0 : tiles, 1};
+  if (EPI == EPI_RESID && left > part_tiles) p.us = 1e30;            // the raw sums do not fit
+  if (EPI != EPI_LOGITS)
+    for (int ks = 2; ks <= kGemmMaxSplit && ks * 4 <= KS && left > 0 && (long)left * ks <= part_tiles; ++ks) {      // at least 8 steps per part
+      const double us = round_us(ks) + parts_us(ks);
+      if (us < p.us * 0.97) p = WidePlan{us, whole, ks};
+    }
+  p.us += whole / slots * (2.0 * KS * step_us + 4.0);
+  return p;
+}
+
+template <int EPI, bool NORM, int BM>
+hipError_t launch_wide_tiles(dmtd_ctx* c, const MfmaArgs& g, int nt, const WidePlan& p) {
+  const int mt = (g.M + BM - 1) / BM, n_tail = mt * nt - p.n_full;
+  auto kern = gemm_wide_mfma_kernel<EPI, NORM, BM>;
+  static bool big_lds = false;
+  if (!big_lds) {
+    hipError_t ae = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)GwTile<BM>::LDS);
+    if (ae != hipSuccess) return ae;
+    big_lds = true;
+  }
+  hipLaunchKernelGGL(kern, dim3(p.n_full + n_tail * p.ksplit), dim3(64 * GW_WAVES), GwTile<BM>::LDS, c->stream, g.W, g.W2, g.xb, g.xb_lo,
+                     g.M, g.N, g.K, p.n_full, n_tail, p.ksplit, mt, nt, g);
+  if constexpr (EPI != EPI_LOGITS) {
+    if (n_tail > 0)
+      hipLaunchKernelGGL((gemm_wide_finish_kernel<EPI, NORM, BM>), dim3(n_tail, BM / 16), dim3(256), 0, c->stream, (const float*)g.part,
+                         g.M, g.N, p.n_full, n_tail, p.ksplit, mt, nt, g);
+  }
+  return hipGetLastError();
+}
+
 template <int EPI, bool NORM>
 hipError_t launch_wide(dmtd_ctx* c, const MfmaArgs& a, int rows) {
   const int KS = a.K / 64;
   const int nt = EPI == EPI_SWIGLU ? (a.N + 127) / 128 : (a.N + GW_BN - 1) / GW_BN;
-  const int part_tiles = (int)std::min<size_t>(gemm_part_floats(c->cfg) / GW_PART, 1 << 20);      // raw tiles the partial sums have room for (at least nt)
+  const int part_tiles = (int)std::min<size_t>(gemm_part_floats(c->cfg) / GwTile<256>::PART, 1 << 20);      // at least nt
   int pass = rows;
-  if (EPI == EPI_RESID && (long)(pass + GW_BM - 1) / GW_BM * nt > part_tiles) pass = part_tiles / nt * GW_BM;
+  if (EPI == EPI_RESID && (long)(pass + 255) / 256 * nt > part_tiles) pass = part_tiles / nt * 256;
   for (int m0 = 0; m0 < rows; m0 += pass) {
     MfmaArgs g = a;
     g.M = std::min(pass, rows - m0);
@@ -439,39 +488,13 @@ hipError_t launch_wide(dmtd_ctx* c, const MfmaArgs& a, int rows) {
     if (a.yb) { g.yb = a.yb + (size_t)m0 * a.ldyb; g.yb_lo = a.yb_lo + (size_t)m0 * a.ldyb; }
     if (a.ssp_next) g.ssp_next = a.ssp_next + m0;
     if (a.amax) g.amax = a.amax + m0;
-    const int mt = (g.M + GW_BM - 1) / GW_BM, tiles = mt * nt, slots = c->num_cus;
-    int n_full = EPI == EPI_RESID ? 0 : tiles, ksplit = 1;
-    if constexpr (EPI != EPI_LOGITS) {
-      const int whole = EPI == EPI_RESID ? 0 : tiles / slots * slots, left = tiles - whole;
-      // microseconds: a k-step of 32 takes 1.25 us (measured, cold weights), a block's start and end about 4; a raw tile's 256 KiB
-      // are written and read by blocks all over the chip at about 2.5 TB/s in all; the finishing launch itself 5 us
-      auto round_us = [&](int ks) { return (left * ks + slots - 1) / slots * (2.0 * KS / ks * 1.25 + 4.0); };
-      auto parts_us = [&](int ks) { return left * ks * (GW_PART * 4) / 2.5e6 + 5.0; };
-      double best = EPI == EPI_RESID ? round_us(1) + parts_us(1) : round_us(1);
-      for (int ks = 2; ks <= kGemmMaxSplit && ks * 4 <= KS && left > 0 && (long)left * ks <= part_tiles; ++ks) {      // at least 8 steps per part
-        const double us = round_us(ks) + parts_us(ks);
-        if (us < best * 0.97) { best = us; ksplit = ks; n_full = whole; }
-      }
-    }
-    const int n_tail = tiles - n_full;
     g.part = c->gemm_part;
-    auto kern = gemm_wide_mfma_kernel<EPI, NORM>;
-    static bool big_lds = false;
-    if (!big_lds) {
-      hipError_t ae = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)GW_LDS);
-      if (ae != hipSuccess) return ae;
-      big_lds = true;
-    }
-    hipLaunchKernelGGL(kern, dim3(n_full + n_tail * ksplit), dim3(64 * GW_WAVES), GW_LDS, c->stream, g.W, g.W2, g.xb, g.xb_lo,
-                       g.M, g.N, g.K, n_full, n_tail, ksplit, mt, nt, g);
-    if constexpr (EPI != EPI_LOGITS) {
-      if (n_tail > 0)
-        hipLaunchKernelGGL((gemm_wide_finish_kernel<EPI, NORM>), dim3(n_tail, GW_BM / 16), dim3(256), 0, c->stream, (const float*)g.part,
-                           g.M, g.N, n_full, n_tail, ksplit, mt, nt, g);
-    }
+    const WidePlan p256 = plan_wide<EPI, 256>(c, g.M, nt, KS), p128 = plan_wide<EPI, 128>(c, g.M, nt, KS);
+    const hipError_t e = p128.us < p256.us ? launch_wide_tiles<EPI, NORM, 128>(c, g, nt, p128) : launch_wide_tiles<EPI, NORM, 256>(c, g, nt, p256);
+    if (e != hipSuccess) return e;
   }
   if (EPI == EPI_RESID) c->resid_parts = nt;
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 template <int EPI, bool NORM, int PF = kMfmaPF, int ROLL_NW = 0>

@@ -17,6 +17,7 @@
 // step ahead (which needs the next step landed half a step earlier) 384, raised wave priority around the MFMAs 435.
 // Blocks go round-robin over the 8 compute dies; a die takes a contiguous run of tiles with the row tiles fastest, so a
 // weight byte enters one die's L2 only and its row tiles share it there.
+// Tiles of 128 rows (waves of 64 x 64, a ring of four buffers, 0.8 instead of 1.25 us per step) where they pad a launch's rows less.
 // Against passes of 128 rows through gemm_mfma.hpp (4B shapes, 2048 rows, us with the finishing launch, before / now):
 // gate/up 660 / 357, QKV 390 / 125, down + O 763 / 297.
 #pragma once
@@ -24,14 +25,17 @@
 
 namespace dmtd {
 
-constexpr int GW_BM = 256, GW_BN = 256;      // activation rows, weight rows of a block's tile
+constexpr int GW_BN = 256;                   // weight rows of a block's tile (SwiGLU: 128 gate and 128 up rows)
 constexpr int GW_WAVES = 8;
-constexpr int GW_BUF = 3;                    // LDS buffers
-constexpr int GW_STAGE = 48 * 512;           // elements of a k-step's slice: 16 weight pieces, 16 high and 16 low activation pieces
-constexpr size_t GW_LDS = (size_t)GW_BUF * GW_STAGE * 2;
+// The tile's shape by its activation rows BM: waves along the rows and the weight rows (64 rows each), 32-wide weight tiles per
+// wave, LDS buffers, 1 KiB pieces of a step (16 of weights, BM / 16 per activation plane), loads a wave issues per step.
+template <int BM> struct GwTile {
+  static constexpr int WM = BM / 64, WN = GW_WAVES / WM, NJ = GW_BN / 32 / WN, BUF = BM == 256 ? 3 : 4;
+  static constexpr int XT = BM / 16, PIECES = 16 + 2 * XT, STAGE = PIECES * 512, LPS = PIECES / GW_WAVES;
+  static constexpr size_t LDS = (size_t)BUF * STAGE * 2;
+  static constexpr int PART = BM * GW_BN;    // floats of a tile's raw sums
+};
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-constexpr int GW_PART = GW_BM * GW_BN;       // floats of a tile's raw sums
 
 // Which tile a block computes, and which part of K.  The launch has n_full blocks with a tile each and, behind them, ksplit blocks
 // for each of the other n_tail tiles.  Either segment goes round-robin over the dies: die x = id % 8 owns the contiguous run
@@ -52,16 +56,18 @@ __device__ __forceinline__ GwPlace gw_place(int id, int blocks, int n_full, int 
   return p;
 }
 
-template <int EPI, bool NORM>
+template <int EPI, bool NORM, int BM>
 __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const bf16_t* W_, const bf16_t* W2_, const bf16_t* xb_, const bf16_t* xb_lo_,
                                                                 int M_, int N_, int K_, int n_full_, int n_tail_, int ksplit_, int mt_, int nt_, MfmaArgs a) {
   // which operand gives the result's rows: with the weights there a lane holds 4 consecutive outputs of one activation row (8-byte
   // pieces of the blocked layout, 512 contiguous bytes per two row groups and store), else 16 rows of one output (128 bytes of a row)
   constexpr bool WA = EPI == EPI_SWIGLU;
+  typedef GwTile<BM> T;
+  constexpr int NJ = T::NJ;
   extern __shared__ float4 gemm_dyn_smem[];
   bf16_t* ring = (bf16_t*)gemm_dyn_smem;
-  __shared__ float rs_s[GW_BM];
-  __shared__ unsigned long long key_s[EPI == EPI_LOGITS ? GW_BM : 1];
+  __shared__ float rs_s[BM];
+  __shared__ unsigned long long key_s[EPI == EPI_LOGITS ? BM : 1];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int M = M_, N = N_, K = K_, KS = K >> 6;
@@ -72,7 +78,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
   const int s_hi = pl.tail ? 2 * (int)((long)(pl.ks + 1) * KS / ksplit_) : 2 * KS;
   const int n_tiles = (N + 15) >> 4;
 
-  // loads: wave w brings weight pieces 2w, 2w + 1 and activation pieces 4w .. 4w + 3 (waves 0-3 the high plane) of every step;
+  // loads: wave w brings weight pieces 2w, 2w + 1 and XP activation pieces from XP w on (waves 0-3 the high plane) of every step;
   // the bases are uniform over the wave, a lane adds its 16 bytes.  Weight tiles beyond N and activation tiles beyond M repeat
   // the last one, and the last activation tile's rows beyond M hold whatever the buffer held: each is an output row of its
   // own that is never stored.
@@ -85,12 +91,13 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
     wsrc[j] = ((EPI == EPI_SWIGLU && p >= 8) ? W2_ : W_) + ((size_t)gt * KS) * 1024 + (size_t)s_lo * 512;
   }
   const int m_tiles = (M + 15) >> 4;
-  const bf16_t* xsrc[4];
+  constexpr int XP = T::LPS - 2;
+  const bf16_t* xsrc[XP];
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-    xsrc[j] = (w >= 4 ? xb_lo_ : xb_) + (size_t)min(mb * 16 + ((4 * w + j) & 15), m_tiles - 1) * KS * 1024 + (size_t)s_lo * 512;
+  for (int j = 0; j < XP; ++j)
+    xsrc[j] = (w >= 4 ? xb_lo_ : xb_) + (size_t)min(mb * T::XT + (XP * w + j) % T::XT, m_tiles - 1) * KS * 1024 + (size_t)s_lo * 512;
   auto issue = [&](int buf) {
-    bf16_t* dst = ring + buf * GW_STAGE;
+    bf16_t* dst = ring + buf * T::STAGE;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(wsrc[j] + lane * 8),
@@ -98,49 +105,51 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
       wsrc[j] += 512;
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < XP; ++j) {
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(xsrc[j] + lane * 8),
-                                       (__attribute__((address_space(3))) void*)(dst + (16 + 4 * w + j) * 512), 16, 0, 0);
+                                       (__attribute__((address_space(3))) void*)(dst + (16 + XP * w + j) * 512), 16, 0, 0);
       xsrc[j] += 512;
     }
   };
-  constexpr int LPS = 6;                 // loads a wave issues per step
-
-  const int wm = w & 3, wn = w >> 2;
-  // 32-row weight tiles of this wave (SwiGLU: two gate tiles and the up tiles of the same outputs)
-  auto wtile = [&](int j) { return EPI == EPI_SWIGLU ? (j >> 1) * 4 + 2 * wn + (j & 1) : 4 * wn + j; };
+  const int wm = w % T::WM, wn = w / T::WM;
+  // 32-row weight tiles of this wave (SwiGLU: NJ / 2 gate tiles and the up tiles of the same outputs)
+  constexpr int HJ = NJ / 2;
+  auto wtile = [&](int j) { return EPI == EPI_SWIGLU ? (j / HJ) * 4 + HJ * wn + j % HJ : NJ * wn + j; };
   const int frag = ((lane >> 4) & 1) * 512 + (lane >> 5) * 128 + (lane & 15) * 8;   // this lane's 16 bytes of a 32-row tile, k chunk 0
-  f32x16 acc[2][4];
+  f32x16 acc[2][NJ];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  issue(0);
-  issue(1);                              // K is a multiple of 64, a part of it at least 8 steps: there is a second one
+#pragma unroll
+  for (int s = 0; s < T::BUF - 1; ++s)
+    if (s_lo + s < s_hi) issue(s);
   if (NORM && !pl.tail) {
-    // the rows' 1/rms while the first steps' pieces are on their way: two threads per row, eight parts each at a time
-    const int m = min(mb * GW_BM + (tid >> 1), M - 1);
+    // the rows' 1/rms while the first steps' pieces are on their way: two or four threads per row, eight parts each at a time
+    constexpr int TR = 64 * GW_WAVES / BM;
+    const int m = min(mb * BM + tid / TR, M - 1);
     float ss = 0.f;
-    for (int p0 = tid & 1; p0 < a.n_parts; p0 += 16) {
+    for (int p0 = tid % TR; p0 < a.n_parts; p0 += 8 * TR) {
       float v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = a.ssp[(size_t)min(p0 + 2 * u, a.n_parts - 1) * a.ssp_ld + m];
+      for (int u = 0; u < 8; ++u) v[u] = a.ssp[(size_t)min(p0 + TR * u, a.n_parts - 1) * a.ssp_ld + m];
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        if (p0 + 2 * u < a.n_parts) ss += v[u];
+        if (p0 + TR * u < a.n_parts) ss += v[u];
     }
     ss += __shfl_xor(ss, 1, 64);
-    if ((tid & 1) == 0) rs_s[tid >> 1] = rsqrtf(ss / (float)K + a.eps);
+    if (TR == 4) ss += __shfl_xor(ss, 2, 64);
+    if (tid % TR == 0) rs_s[tid / TR] = rsqrtf(ss / (float)K + a.eps);
   }
-  struct Frag { bf16x8_t xl[2], xh[2], wf[4]; };
+  struct Frag { bf16x8_t xl[2], xh[2], wf[NJ]; };
   auto read = [&](Frag& f, const bf16_t* base, int c) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) f.xl[i] = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(base + (32 + (2 * wm + i) * 2) * 512 + c * 256));
+    for (int i = 0; i < 2; ++i) f.xl[i] = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(base + (16 + T::XT + (2 * wm + i) * 2) * 512 + c * 256));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) f.wf[j] = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(base + wtile(j) * 1024 + c * 256));
+    for (int j = 0; j < NJ; ++j) f.wf[j] = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(base + wtile(j) * 1024 + c * 256));
 #pragma unroll
     for (int i = 0; i < 2; ++i) f.xh[i] = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(base + (16 + (2 * wm + i) * 2) * 512 + c * 256));
   };
@@ -148,7 +157,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
 #pragma unroll
     for (int p = 0; p < 2; ++p)            // low parts first
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
           const bf16x8_t x = p ? f.xh[i] : f.xl[i];
@@ -156,23 +165,25 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
                          : __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, f.wf[j], acc[i][j], 0, 0, 0);
         }
   };
-  int buf = 0, nxt = GW_BUF - 1;
+  int buf = 0, nxt = T::BUF - 1;
   for (int s = s_lo; s < s_hi; ++s) {
-    // this step's pieces have landed once all loads but the next step's have returned (they return in order); behind the
-    // barrier every wave's have, and every wave is done with the buffer that is filled next
-    if (s + 1 < s_hi) __builtin_amdgcn_s_waitcnt(LPS | (7 << 4));      // vmcnt(LPS) lgkmcnt(0), expcnt untouched
+    // this step's pieces have landed once all loads but those of the newer steps (BUF - 2 of them, fewer at the end) have
+    // returned (they return in order); behind the barrier every wave's have, and every wave is done with the buffer that is
+    // filled next.  vmcnt(newer steps x LPS) lgkmcnt(0), expcnt untouched
+    if (T::BUF == 4 && s + 2 < s_hi) __builtin_amdgcn_s_waitcnt(2 * T::LPS | (7 << 4));
+    else if (s + 1 < s_hi) __builtin_amdgcn_s_waitcnt(T::LPS | (7 << 4));
     else __builtin_amdgcn_s_waitcnt(7 << 4);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");         // no LDS read of the slice moves above the barrier
-    const bf16_t* base = ring + buf * GW_STAGE + frag;
+    const bf16_t* base = ring + buf * T::STAGE + frag;
     Frag f0, f1;
     read(f0, base, 0);
     __builtin_amdgcn_sched_barrier(0);
-    if (s + 2 < s_hi) issue(nxt);
+    if (s + T::BUF - 1 < s_hi) issue(nxt);
     read(f1, base, 1);
     __builtin_amdgcn_sched_barrier(0);
-    buf = buf + 1 == GW_BUF ? 0 : buf + 1;
-    nxt = nxt + 1 == GW_BUF ? 0 : nxt + 1;
+    buf = buf + 1 == T::BUF ? 0 : buf + 1;
+    nxt = nxt + 1 == T::BUF ? 0 : nxt + 1;
     mul(f0);
     __builtin_amdgcn_sched_barrier(0);
     mul(f1);
@@ -180,14 +191,14 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
   }
 
   // lane (column n = lane % 32 of a weight tile): element e of acc[i][j] is row 32 i + 8 (e / 4) + 4 (lane / 32) + e % 4 of the wave
-  const int m_w = mb * GW_BM + wm * 64, m_l = 4 * (lane >> 5), col = lane & 31;
+  const int m_w = mb * BM + wm * 64, m_l = 4 * (lane >> 5), col = lane & 31;
   if (EPI != EPI_LOGITS && pl.tail) {
-    // raw sums [256 rows][256 outputs] (SwiGLU: 128 gate, 128 up) of this part of K, for the finishing kernel
-    float* part = a.part + ((size_t)pl.ks * n_tail_ + (pl.t - n_full_)) * GW_PART + (size_t)(wm * 64) * GW_BN;
+    // raw sums [BM rows][256 outputs] (SwiGLU: 128 gate, 128 up) of this part of K, for the finishing kernel
+    float* part = a.part + ((size_t)pl.ks * n_tail_ + (pl.t - n_full_)) * T::PART + (size_t)(wm * 64) * GW_BN;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < NJ; ++j) {
         if (WA) {
 #pragma unroll
           for (int q = 0; q < 4; ++q)
@@ -199,22 +210,22 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
       }
     return;
   }
-  if (EPI == EPI_LOGITS && tid < GW_BM) key_s[tid] = 0ull;
+  if (EPI == EPI_LOGITS && tid < BM) key_s[tid] = 0ull;
   __syncthreads();
   const int r_w = wm * 64 + m_l;
   if (EPI == EPI_SWIGLU) {
-    // activation row 32 i + lane % 32 of the wave, outputs 32 j + 8 q + 4 (lane / 32) + 0..3 of its 64
+    // activation row 32 i + lane % 32 of the wave, outputs 32 j + 8 q + 4 (lane / 32) + 0..3 of its 32 HJ
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int m = m_w + 32 * i + col;
       const float rs = rs_s[wm * 64 + 32 * i + col];
 #pragma unroll
-      for (int jq = 0; jq < 8; ++jq) {
-        const int j = jq >> 2, q = jq & 3, n = nb * 128 + wn * 64 + 32 * j + 8 * q + m_l;
+      for (int jq = 0; jq < 4 * HJ; ++jq) {
+        const int j = jq >> 2, q = jq & 3, n = nb * 128 + wn * 32 * HJ + 32 * j + 8 * q + m_l;
         bf16_t hi[4], lo[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float gt = acc[i][j][4 * q + e] * rs, up = acc[i][j + 2][4 * q + e] * rs;
+          const float gt = acc[i][j][4 * q + e] * rs, up = acc[i][j + HJ][4 * q + e] * rs;
           split_bf16(gt / (1.0f + __expf(-gt)) * up, hi[e], lo[e]);
         }
         if (m < M && n < N) {
@@ -234,7 +245,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
       const float rs = NORM ? rs_s[r_w + ml] : 1.f;
       unsigned long long best = 0ull;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < NJ; ++j) {
         const int n = nb * GW_BN + wtile(j) * 32 + col;
         const float v = acc[i][j][e] * rs;
         if (m < M && n < N) {
@@ -246,7 +257,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
     }
   if (EPI == EPI_LOGITS && a.amax) {
     __syncthreads();
-    if (tid < GW_BM && mb * GW_BM + tid < M) atomicMax(a.amax + (size_t)(nb % AMAX_CELLS) * a.amax_ld + mb * GW_BM + tid, key_s[tid]);
+    if (tid < BM && mb * BM + tid < M) atomicMax(a.amax + (size_t)(nb % AMAX_CELLS) * a.amax_ld + mb * BM + tid, key_s[tid]);
   }
 }
 
@@ -254,7 +265,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
 // block takes 16 rows of a tile, a wave 16 rows x 32 outputs at a time: lane (row = lane % 16, chunk = lane / 16) has 8
 // consecutive outputs, so a wave writes 1 KiB of contiguous blocked layout per plane.  (Row by row, 4 outputs per thread, the
 // blocked stores are 16-byte pieces: 38 us for 2048 x 2560 from 3 parts.)
-template <int EPI, bool NORM>
+template <int EPI, bool NORM, int BM>
 __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part_, int M_, int N_, int n_full_, int n_tail_, int ksplit_, int mt_, int nt_,
                                                                MfmaArgs a) {
   __shared__ float ss_s[4][16];
@@ -262,13 +273,14 @@ __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part
   const int M = M_, N = N_, t = n_full_ + blockIdx.x;
   const int per_group = 8 * nt_, grp = t / per_group, in = t - grp * per_group, rows = min(8, mt_ - grp * 8);
   const int nb = in / rows, mb = grp * 8 + in - nb * rows;
-  const int r = blockIdx.y * 16 + (lane & 15), m = mb * GW_BM + r, c8 = (lane >> 4) * 8;
-  if (mb * GW_BM + (int)blockIdx.y * 16 >= M) return;
+  const int r = blockIdx.y * 16 + (lane & 15), m = mb * BM + r, c8 = (lane >> 4) * 8;
+  constexpr int PART = GwTile<BM>::PART;
+  if (mb * BM + (int)blockIdx.y * 16 >= M) return;
   const bool act = m < M;
   const int mc = act ? m : M - 1;
   constexpr int GROUPS = EPI == EPI_SWIGLU ? 1 : 2;      // groups of 32 outputs per wave
   constexpr int PRE = 4;                                 // parts fetched at once
-  const size_t step = (size_t)n_tail_ * GW_PART;
+  const size_t step = (size_t)n_tail_ * PART;
   float rs = 1.f;
   if (NORM) {
     float ss = 0.f;
@@ -283,7 +295,7 @@ __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part
     const int lc = (w * GROUPS + gi) * 32 + c8;                              // output inside the tile
     const int n = nb * (EPI == EPI_SWIGLU ? 128 : GW_BN) + lc;
     if (n - c8 >= N) continue;                                               // N is a multiple of 64 here: whole groups
-    const float* p = part_ + (size_t)blockIdx.x * GW_PART + (size_t)r * GW_BN + lc;
+    const float* p = part_ + (size_t)blockIdx.x * PART + (size_t)r * GW_BN + lc;
     f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0, u0 = s0, u1 = s0;
     f32x4 h0 = s0, h1 = s0;
     u32x4 graw = {0, 0, 0, 0};

@@ -1,5 +1,5 @@
-"""GPU parity of passes that carry many rows (more than 128 activation rows, more than 16 positions per sequence): the wide
-projection GEMM (tiles of 128 rows x 256 outputs, K optionally split over blocks) and the prefill attention kernel (128
+"""GPU parity of passes that carry many rows (more than 192 activation rows, more than 16 positions per sequence): the wide
+projection GEMM (tiles of 128 or 256 rows x 256 outputs, K optionally split over blocks) and the prefill attention kernel (128
 query vectors x 64 keys per tile), at the edges of their tiles, against the CPU oracle.
 
 Tolerance: that of the other bf16 parity tests (2e-2 of the largest logit: the bf16 KV cache's rounding through the layers);
@@ -20,8 +20,10 @@ TOL_BF16 = 2e-2
 S = di.ModelShape
 CASES = {
     # name: (shape, batch, positions)
-    "rows_129_hd128_gq4": (S(2, 256, 8, 2, 128, 512, 1000), 1, 129),             # one row in the second row tile
-    "rows_3x43_hd64_gq1": (S(2, 192, 3, 3, 64, 320, 203), 3, 43),                # 129 rows; K = 192, outputs not multiples of 128 or 256
+    "rows_129_hd128_gq4": (S(2, 256, 8, 2, 128, 512, 1000), 1, 129),             # the LDS-tiled kernel's two passes below the wide GEMM's least rows
+    "rows_193_hd128_gq4": (S(2, 256, 8, 2, 128, 512, 1000), 1, 193),             # the wide GEMM's least rows; one row in a group of 16
+    "rows_385_hd128_gq2": (S(2, 1024, 8, 4, 128, 1600, 2000), 1, 385),           # one row in the fourth tile of 128; K split over blocks
+    "rows_3x83_hd64_gq1": (S(2, 192, 3, 3, 64, 320, 203), 3, 83),                # K = 192, outputs not multiples of 128 or 256
     "rows_256_hd64_gq7": (S(2, 128, 7, 1, 64, 448, 515), 1, 256),                # 18 rows per attention block; full row tiles
     "rows_2x257_hd128_gq2": (S(2, 320, 4, 2, 128, 960, 129), 2, 257),            # 514 rows: two blocks of logits; 64-key tiles + 1
     "rows_17x17_hd64_gq16": (S(1, 128, 16, 1, 64, 64, 300), 17, 17),             # fewest positions of a wide pass, 8 rows per attention block
