@@ -216,7 +216,8 @@ __global__ void __launch_bounds__(256) attn_split_kernel(
     int kps /* keys per range, a multiple of the block iteration */, int n_splits, int qv_stride,
     const DevState* st, int sel, int offset, int r_total,
     int do_append /* 1: the launch appends its rows' keys and values; 0: it scores them from its inputs and leaves the cache untouched (measurement); 2: they are in the cache already */,
-    const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot (cache rows, positions) */) {
+    const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot (cache rows, positions) */,
+    float* __restrict__ out, int ldo /* nullable: one range, no merge launch follows */) {
   typedef typename Elem<CT>::Raw Raw;
   constexpr int LPK = HD / 8;          // lanes per key (16 or 8)
   constexpr int GPW = 64 / LPK;        // lane groups per wave (4 or 8)
@@ -333,6 +334,10 @@ __global__ void __launch_bounds__(256) attn_split_kernel(
       const float f = (wm[w][qv] == -INFINITY) ? 0.f : __expf(wm[w][qv] - mm);
       o += f * wacc[w][qv][d];
       ll += f * wl[w][qv];
+    }
+    if (out) {       // the launch's only range: the block's result is the attention output (what the merge of one range gives)
+      out[(size_t)(b * r_total + rg * rpb + qv / GQ) * ldo + (size_t)(g * GQ + qv % GQ) * HD + d] = o * (1.0f / ll);
+      continue;
     }
     my_o[qv * HD + d] = o;
     if (d == 0) { my_ml[qv * 2] = mm; my_ml[qv * 2 + 1] = ll; }

@@ -513,7 +513,13 @@ hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows) {
   // The one-tile-per-block kernel keeps all rows (both planes) in LDS: comfortably (two blocks per CU) in general,
   // up to most of a CU's LDS when the launch has no more blocks than the chip has CUs anyway.  Rows that do not
   // fit, and more than 16 rows (batched steps), go through the LDS-tiled kernel in passes of up to kGemmRows rows.
-  const bool fits = a.ldxb == a.K && mfma_rows_fit(c, rows, a.N, a.K, NORM ? a.n_parts : 0);
+  // Two more that the tiled kernel takes, unsplit, although the rows would fit: an LM head with tile streams in abundance (4B
+  // shape, in the step, 1 / 5 rows: 127 / 150 us here, 121 there; 1024 wide, 12 rows: 123 / 57), and gate/up with many tiles
+  // from 50 KiB of rows on (2560 wide, 5 rows: 20.5 / 19.4; 896 wide, 304 tiles, 8 rows: 6.7 / 8.5, hence the tile count).
+  const int out_tiles = (a.N + 15) / 16;
+  const bool prefers_tiled = EPI == EPI_LOGITS ? out_tiles >= 16 * c->num_cus
+                                               : (EPI == EPI_SWIGLU && out_tiles >= 2 * c->num_cus && (size_t)rows * 4 * a.K >= (size_t)50 * 1024);
+  const bool fits = a.ldxb == a.K && !prefers_tiled && mfma_rows_fit(c, rows, a.N, a.K, NORM ? a.n_parts : 0);
   // one launch of the tiled kernel; with 64 and more rows its ring of activation slices is dynamic LDS beyond the default limit
 #define DMTD_LAUNCH_GEMM(CG_, SPLIT_, GRID_)                                                                                   \
   do {                                                                                                                         \
@@ -669,13 +675,17 @@ void launch_attention_t(dmtd_ctx* c, int l, const float* qkv, OT* attn, OT* attn
   if (want_splits > ATT_MAX_SPLITS) want_splits = ATT_MAX_SPLITS;
   if (want_splits < 1) want_splits = 1;
   int kps = ((bucket + want_splits - 1) / want_splits + KPI - 1) / KPI * KPI;
+  // short contexts: one range of at most two block iterations instead of the merge launch (4.4 us; an iteration takes about 2)
+  const bool one = std::is_same<OT, float>::value && bucket <= 2 * KPI;
+  if (one) kps = bucket;
   const int ns = (bucket + kps - 1) / kps;
   float* po = c->part_o;
   float* pml = c->part_ml;
   const DevState* st = dev_state(c);
   hipLaunchKernelGGL((attn_split_kernel<CT, HD, QVT>), dim3(ns * n_rg, cf.n_kv_heads, B), dim3(256), 0, c->stream, qkv, nqkv,
                      w.q_norm, w.k_norm, (const float2*)(c->ws + c->o.rope_tab), kc, vc, po, pml, cf.n_q_heads, cf.n_kv_heads,
-                     cf.max_seq_len, cf.rms_eps, kps, ns, c->part_rows * gq, st, sel, offset, r, append, c->fmap);
+                     cf.max_seq_len, cf.rms_eps, kps, ns, c->part_rows * gq, st, sel, offset, r, append, c->fmap, one ? (float*)attn : (float*)nullptr, qd);
+  if (one) return;
   hipLaunchKernelGGL((attn_merge_kernel<HD, OT>), dim3(r, cf.n_q_heads, B), dim3(256), 0, c->stream, po, pml, attn, attn_lo, qd,
                      cf.n_q_heads, cf.n_kv_heads, kps, ns, c->part_rows * gq, st, sel, offset, r, c->fmap, blocked_rows(c, B * r));
 }
