@@ -752,10 +752,22 @@ hipError_t launch_attention_prefill(dmtd_ctx* c, int l, const float* qkv, bf16_t
   const bf16_t* kc = (const bf16_t*)(c->ws + c->o.kv + (size_t)l * c->o.kv_layer_stride);
   const bf16_t* vc = (const bf16_t*)(c->ws + c->o.kv + (size_t)l * c->o.kv_layer_stride + c->o.kv_v_off);
   // KV heads fastest: with 8 of them a compute die's blocks share one head's keys and values in its L2
-  hipLaunchKernelGGL((attn_prefill_mfma_kernel<HD>), dim3(cf.n_kv_heads, c->batch, (r + rpb - 1) / rpb), dim3(256), 0, c->stream, qkv, nqkv, kc, vc,
-                     cf.n_q_heads, cf.n_kv_heads, cf.max_seq_len, r, (const DevState*)dev_state(c), sel, offset, (const bf16_t*)c->layers[l].q_norm,
-                     (const float2*)(c->ws + c->o.rope_tab), cf.rms_eps, attn, attn_lo, cf.n_q_heads * HD, blocked_rows(c, c->batch * r));
-  return hipGetLastError();
+  const dim3 grid(cf.n_kv_heads, c->batch, (r + rpb - 1) / rpb);
+  auto launch = [&](auto kg_c) -> hipError_t {
+    constexpr int KG = decltype(kg_c)::value;
+    auto kern = attn_prefill_mfma_kernel<HD, KG>;
+    static bool big_lds = false;
+    if (!big_lds) {
+      hipError_t ae = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)attn_prefill_lds(HD, KG));
+      if (ae != hipSuccess) return ae;
+      big_lds = true;
+    }
+    hipLaunchKernelGGL(kern, grid, dim3(256 * KG), attn_prefill_lds(HD, KG), c->stream, qkv, nqkv, kc, vc,
+                       cf.n_q_heads, cf.n_kv_heads, cf.max_seq_len, r, (const DevState*)dev_state(c), sel, offset, (const bf16_t*)c->layers[l].q_norm,
+                       (const float2*)(c->ws + c->o.rope_tab), cf.rms_eps, attn, attn_lo, cf.n_q_heads * HD, blocked_rows(c, c->batch * r));
+    return hipGetLastError();
+  };
+  return (long)grid.x * grid.y * grid.z <= c->num_cus ? launch(std::integral_constant<int, 2>()) : launch(std::integral_constant<int, 1>());
 }
 
 // Kernel choice.  bf16 caches: the matrix-core kernel (measured faster than the vector kernel even for
