@@ -68,6 +68,9 @@ constexpr int gemm_waves(int cg, int epi) { return (cg >= 2 && epi != EPI_RESID 
 // QKV 18.3 / 19.8, O 13.4 / 14.0 - so only the 128-row kernels take the direct path (3 k-steps in flight instead of 2).
 constexpr bool gemm_uses_dma(int cg) { return cg >= 8; }
 constexpr int gemm_pf(int cg) { return cg >= 8 ? 3 : (cg >= 4 ? (DMTD_GEMM_PF < 2 ? DMTD_GEMM_PF : 2) : DMTD_GEMM_PF); }
+// The LM head runs unsplit over thousands of blocks: with 17 to 32 rows two k-steps in flight leave a block 108 registers and two
+// blocks fit a CU (three: 154, one block; 594 blocks are then 2.3 rounds of 256 CUs): 32 rows 156 -> 149 us at 4B shapes.
+constexpr int gemm_pf(int cg, int epi) { return epi == EPI_LOGITS && cg == 2 ? 2 : gemm_pf(cg); }
 // dynamic LDS of a launch (bytes): the ring of activation slices
 constexpr size_t gemm_dyn_lds(int cg) { return gemm_uses_dma(cg) ? (size_t)(gemm_pf(cg) + 1) * 2 * cg * 16 * 64 * 2 : 0; }
 
@@ -82,7 +85,7 @@ __global__ void __launch_bounds__(64 * gemm_waves(CG, EPI)) gemm_mfma_kernel(
   // k-steps in flight: 3; 2 with 64 and more rows, where the accumulators leave fewer registers (measured at 4B shapes, 64 rows:
   // gate/up 37.4 against 38.8 us, QKV 19.9 against 21.9)
   constexpr bool DMA = gemm_uses_dma(CG);
-  constexpr int PF = gemm_pf(CG);
+  constexpr int PF = gemm_pf(CG, EPI);
   constexpr int LDB = 72;                // LDS row (register-staged slices): 64 values + 8 of padding
   constexpr int NT = 64 * GEMM_WAVES;
   constexpr int PIECES = 2 * BM * 8;     // 16-byte pieces of one k-step's activation slice (2 planes)
