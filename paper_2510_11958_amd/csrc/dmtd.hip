@@ -49,6 +49,8 @@ inline int row_capacity(const dmtd_config& c) {
   }
   return (int)cap;
 }
+// Packed rows of the late layers, one per sequence: whole groups of 16, which is how the wide GEMM's layout stores them
+inline size_t late_row_capacity(const dmtd_config& c) { return ((size_t)c.max_batch + 15) / 16 * 16; }
 inline int head_row_capacity(const dmtd_config& c) {
   return c.dtype == DMTD_DTYPE_BF16 ? std::min(row_capacity(c), std::max(kHeadRows, step_row_capacity(c.max_batch))) : row_capacity(c);
 }
@@ -303,7 +305,7 @@ Ws layout(const dmtd_config& c) {
   if (c.dtype == DMTD_DTYPE_BF16) {
     const size_t parts = (d + 15) / 16;
     w.xb = take(rows * d * 2 * 2);                     // high and low planes
-    w.xb_late = take(B * d * 2 * 2);
+    w.xb_late = take(late_row_capacity(c) * d * 2 * 2);
     w.ssp = take(parts * rows * 4);
     w.ssp_late = take(parts * rows * 4);
     w.wsw = take((swizzled_layer_elems(c) * c.n_layers + swizzled_elems(c.vocab, d)) * 2);
@@ -656,7 +658,7 @@ hipError_t launch_gateup(dmtd_ctx* c, MfmaArgs a, int rows) {
 // ------------------------------------------------------------------------- attention
 
 // a3 + a4: QK-RMSNorm, RoPE, KV append and split-K attention in one launch over static key ranges, then the merge.
-// The ranges follow from the context bucket (c->att_bucket, a multiple of 512 that covers the context), so a
+// The ranges follow from the context bucket (c->att_bucket, 256 or a multiple of 512 that covers the context), so a
 // captured step stays valid until the sequence grows into the next bucket.
 template <typename CT, typename OT, int HD, int QVT>
 void launch_attention_t(dmtd_ctx* c, int l, const float* qkv, OT* attn, OT* attn_lo, int sel, int offset, int r, int append) {
@@ -989,7 +991,7 @@ Rows front_rows(dmtd_ctx* c) {
 }
 Rows late_rows(dmtd_ctx* c) {
   bf16_t* xb = (bf16_t*)(c->ws + c->o.xb_late);
-  return Rows{(float*)(c->ws + c->o.h_late), xb, xb + (size_t)c->cfg.max_batch * c->cfg.hidden, (float*)(c->ws + c->o.ssp_late), 1};
+  return Rows{(float*)(c->ws + c->o.h_late), xb, xb + late_row_capacity(c->cfg) * c->cfg.hidden, (float*)(c->ws + c->o.ssp_late), 1};
 }
 
 // One decode step (Sec. 2.2).  Full: embed the pending rows and the newest row, run the front
@@ -1161,7 +1163,7 @@ int run_step(dmtd_ctx* c, const Step& s, int n_late) {
 // Several consecutive steps of one call as ONE graph (dmtd_decode): the steps of a cycle - a full step and the late-only
 // steps behind it - or, at tau = 1, up to kStepsPerGraph full steps.  Between two graph launches the GPU idles for ~8 us
 // (end of one graph to the first kernel of the next), three times per C3 cycle with a graph per step.  The steps of a
-// group share their attention launch shape (512-token context bucket, KV sharing), otherwise the group ends early.
+// group share their attention launch shape (context bucket, KV sharing), otherwise the group ends early.
 constexpr int kStepsPerGraph = 4;
 int run_steps_grouped(dmtd_ctx* c, const std::vector<Step>& steps, int tau, int n_late) {
   const int n = (int)steps.size();

@@ -1,0 +1,70 @@
+"""GPU parity of decoding at the row counts and contexts where a step's launches change their route: more than 192 rows in one
+step (the wide GEMM and its activation layout under decode steps), one attention range against ranges with a merge around 256
+keys, the fp32 kernels' groups of rows and their single attention range.  Teacher-forced against one oracle run per sequence.
+
+Tolerances: those of the other parity tests (fp32 1e-4 of the largest logit, bf16 2e-2: the KV cache's rounding through the layers).
+"""
+import numpy as np
+import pytest
+
+import dmtd_inputs as di
+import paper_2510_11958_amd as pkg
+from oracle import dmtd_oracle as O
+from parity_util import Pair, engine_config, oracle_config
+
+pytestmark = pytest.mark.gpu
+
+S = di.ModelShape
+TOL = {"fp32": 1e-4, "bf16": 2e-2}
+CASES = {
+    # name: (shape, batch, prompt, tau, n_late, n_early, literal, steps)
+    "rows_up_to_300": (S(3, 128, 4, 2, 64, 256, 500), 100, 5, 3, 1, 0, False, 7),
+    "rows_up_to_300_early": (S(4, 128, 4, 1, 64, 192, 300), 100, 4, 3, 2, 1, True, 7),
+    "rows_193_per_step": (S(2, 64, 2, 1, 64, 128, 200), 193, 3, 1, 1, 0, False, 3),
+    "rows_20_to_60": (S(3, 256, 4, 2, 128, 512, 1000), 20, 9, 3, 2, 0, False, 7),
+    "one_range_to_256_keys": (S(2, 256, 16, 8, 64, 320, 300), 8, 250, 2, 1, 0, False, 12),      # 64 attention blocks: ranges from 257 keys on
+    "one_range_to_512_keys": (S(2, 128, 16, 16, 64, 192, 300), 8, 508, 2, 1, 0, False, 8),      # 128 blocks
+    "fp32_one_range_hd64": (S(2, 128, 4, 2, 64, 192, 130, dtype="fp32"), 2, 252, 3, 1, 0, False, 9),
+    "fp32_rows_5_10": (S(3, 96, 2, 2, 64, 160, 130, dtype="fp32"), 5, 6, 2, 1, 0, False, 6),
+    "fp32_rows_3_9_hd128": (S(2, 128, 2, 1, 128, 160, 130, dtype="fp32"), 3, 6, 3, 1, 0, False, 7),
+}
+
+
+def forced_string(sh, batch, prompts, total):
+    cont = di.make_continuation(sh.vocab, batch, total, seed=1001)
+    return [np.concatenate([prompts[b], cont[b]])[:total] for b in range(batch)]
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_steps_against_oracles(name):
+    sh, batch, n, tau, n_late, n_early, literal, steps = CASES[name]
+    blob = di.make_weight_blob(sh, seed=3)
+    prompts = di.make_prompts(sh.vocab, batch, n, seed=5)
+    toks = forced_string(sh, batch, prompts, n + steps + 2)
+    p = Pair(sh, blob, n + steps + 2, batch=batch, literal=literal, n_early=n_early)
+    p.prefill(prompts, n_late if literal else 0)
+    for _ in range(steps):
+        p.step_forced(tau, n_late, toks)
+    assert p.worst < TOL[sh.dtype], p.worst
+    assert p.token_checks > 0
+    print(f"{name}: worst {p.worst:.2e}, tokens checked {p.token_checks}")
+
+
+def test_many_rows_with_cycle_lengths_per_sequence():
+    """A batch of 100 in cycles of 1 to 4: the steps' front passes carry the rows of the sequences that start a cycle."""
+    from test_gpu_per_seq import run_calls
+    sh, batch, n, n_late = S(3, 128, 4, 2, 64, 256, 500), 100, 6, 1
+    blob = di.make_weight_blob(sh, seed=3)
+    prompts = di.make_prompts(sh.vocab, batch, n, seed=5)
+    toks = forced_string(sh, batch, prompts, n + 16)
+    eng = pkg.Engine(engine_config(sh, n + 16, batch), blob)
+    ocfg = oracle_config(sh)
+    w = O.unpack_weights(blob, ocfg, np.float64)
+    orcs = [O.DmtdOracle(ocfg, w, n + 16, np.float64) for _ in range(batch)]
+    eng.prefill(prompts)
+    for b, o in enumerate(orcs):
+        o.prefill(prompts[b])
+    taus = [(4, 3, 4, 1, 4)[b % 5] for b in range(batch)]
+    worst, checked = run_calls(eng, orcs, toks, [(taus, 5), (taus, 4)], n_late, TOL["bf16"])
+    assert checked > 0
+    print(f"per sequence, batch 100: worst {worst:.2e}, tokens checked {checked}")
