@@ -782,7 +782,13 @@ hipError_t launch_attention(dmtd_ctx* c, int l, const float* qkv, OT* attn, OT* 
   const int gq = cf.n_q_heads / cf.n_kv_heads;
   if (r > kMaxRows && append != 2) return hipErrorInvalidValue;    // more rows than an attention block keeps in LDS: their keys must be in the cache
   if constexpr (std::is_same<CT, bf16_t>::value) {
-    if (append == 2 && (long)cf.max_seq_len * cf.head_dim < (1L << 31)) {      // the prefill kernel addresses a head's rows with 32 bits
+    // Blocks of 16 query vectors put at most two on a CU: the decode kernel (its 8 waves share a tile's keys, where the prefill
+    // kernel's few blocks of 128 vectors walk the key tiles one after the other).  Layers of 4B shapes, whole pass, us, prefill
+    // kernel / decode kernel: 64 positions 476 / 443, 128: 632 / 584, 256: 869 / 852, 400: 1189 / 1215, 8 x 24: 994 / 990, 8 x 64:
+    // 1224 / 1270, 32 x 64: 3493 / 3725; the last 32 and 128 positions behind 8192: the prompt 18367 / 17398 and 18652 / 17965.
+    const long blocks = (long)cf.n_kv_heads * c->batch * ((r + 16 / gq - 1) / (16 / gq));
+    // the prefill kernel addresses a head's rows with 32 bits
+    if (append == 2 && blocks > 2 * c->num_cus && (long)cf.max_seq_len * cf.head_dim < (1L << 31)) {
       if (cf.head_dim == 128) return launch_attention_prefill<128>(c, l, qkv, attn, attn_lo, sel, offset, r);
       return launch_attention_prefill<64>(c, l, qkv, attn, attn_lo, sel, offset, r);
     }

@@ -28,6 +28,13 @@ CASES = {
     "rows_2x257_hd128_gq2": (S(2, 320, 4, 2, 128, 960, 129), 2, 257),            # 514 rows: two blocks of logits; 64-key tiles + 1
     "rows_17x17_hd64_gq16": (S(1, 128, 16, 1, 64, 64, 300), 17, 17),             # fewest positions of a wide pass, 8 rows per attention block
     "rows_5x450_hd64_gq4": (S(1, 64, 4, 1, 64, 128, 97), 5, 450),                # 2250 rows: two passes, the second reads the first's keys
+    # more than 512 blocks of 16 query vectors, from which on the prefill attention kernel takes a pass
+    "vectors_8224_hd128_gq4": (S(2, 256, 32, 8, 128, 512, 1000), 1, 257),        # 513 blocks of 16; one row in the ninth tile of 32
+    "vectors_8106_hd64_gq7": (S(2, 128, 21, 3, 64, 448, 515), 2, 193),           # 18 rows per block, 13 rows in the last
+    "vectors_9600_hd64_gq1": (S(2, 192, 16, 16, 64, 320, 203), 3, 200),          # 128 rows per block
+    "vectors_8224_hd128_gq2": (S(2, 320, 16, 8, 128, 960, 129), 2, 257),         # one row in the fifth tile of 64
+    "vectors_19200_hd64_gq8": (S(1, 128, 8, 1, 64, 128, 97), 48, 50),            # 192 blocks of 128, two groups of waves
+    "vectors_38400_hd64_gq8": (S(1, 128, 16, 2, 64, 128, 97), 48, 50),           # 384 blocks of 128, more than a block per CU: one group of waves
 }
 
 
