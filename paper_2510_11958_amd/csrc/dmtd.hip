@@ -77,6 +77,12 @@ constexpr int kGemmRows = DMTD_GEMM_ROWS;   // activation rows per pass of the L
 // Up to this many rows go through the LDS-tiled kernel in passes, more through the wide GEMM (all four projections of a layer at
 // 4B shapes, us: 160 rows 172 / 190, 192 rows 191 / 190, 256 rows 220 / 190 with tiles of 256 rows)
 constexpr int kTiledRows = 192;
+// Key ranges an O projection's blocks merge by themselves (two kernels: up to 4 and up to 8), and the bytes of partial results
+// every block may read for that.  us per step with the merge launch / merged here: 64 KiB 331.6 / 319.9 (2560 wide, 6
+// layers, 4 ranges), 350.7 / 333.4 (1024 wide, 12 layers, 2 rows); 128 KiB 330.8 / 326.1 (8 ranges), 354.5 / 346.1; 256 KiB
+// 337.3 / 346.4 and 374.4 / 392.3: a block's prologue then takes longer than the launch.
+constexpr int kMergeFew = 4, kMergeRanges = 8;
+constexpr size_t kMergeBytes = 128 * 1024;
 constexpr int kMfmaPF = 10;          // k-steps (64 elements) a wave of the MFMA kernel holds in registers
 // Waves that split K for one matrix (NW) and k-steps a wave keeps in flight as a rolling window (PF), per projection;
 // NW = 0: the one-round rule of launch_mfma with kMfmaPF.  Defaults from sweeps at 4B shapes on MI355X, us per launch
@@ -201,6 +207,8 @@ struct dmtd_ctx {
   std::map<std::vector<int>, hipGraphExec_t> mixed_graphs;
   bool fold_qkv = false;      // run_layer: a K-split QKV launch may leave its finishing step to the attention launch that follows
   QkvSrc qkv_pending{};       // ... and says so here (part != nullptr) until that launch picks it up
+  bool fold_merge = false;    // run_layer: an attention launch over key ranges may leave their merge to the O projection that follows
+  MergeSrc merge_pending{};   // ... and says so here (po != nullptr) until that launch picks it up
   // Scratch of the step kernels (partial results that live for one launch pair): the attention ranges' partial outputs
   // and softmax statistics, the LM head's selection-key cells, the K-split partial sums of the tiled kernel.  They sit
   // in the caller's workspace, except inside dmtd_decode_cycle_noalloc, which points them at the library's own array.
@@ -610,9 +618,9 @@ hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows) {
     if (a.ssp_next) g.ssp_next = a.ssp_next + m0;
     if (a.amax) g.amax = a.amax + m0;
     const size_t lds = (size_t)2 * g.M * a.K * 2 + (NORM ? (size_t)g.M * a.n_parts * 4 : 0);   // the rows, both planes; partial sums of squares
-#define DMTD_LAUNCH_MFMA(NWT_)                                                                                            \
+#define DMTD_LAUNCH_MFMA_MR(NWT_, MR_)                                                                                            \
     do {                                                                                                                  \
-      auto kern = gemv_mfma_kernel<EPI, NORM, PF, NWT_, (ROLL_NW > 0)>;                                             \
+      auto kern = gemv_mfma_kernel<EPI, NORM, PF, NWT_, (ROLL_NW > 0), MR_>;                                             \
       static bool big_lds = false;                                                                                        \
       if (lds > 48 * 1024 && !big_lds) {                                                                                  \
         hipError_t ae = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 120 * 1024);   \
@@ -621,6 +629,11 @@ hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows) {
       }                                                                                                                   \
       hipLaunchKernelGGL(kern, grid, dim3(64 * NWT_), lds, c->stream, g.W, g.W2, g.xb, g.xb_lo, (const float*)g.ssp, g.M, g.N, g.K, g.n_parts, g.ssp_ld, g); \
     } while (0)
+#define DMTD_LAUNCH_MFMA(NWT_) DMTD_LAUNCH_MFMA_MR(NWT_, 0)
+    if constexpr (EPI == EPI_RESID && ROLL_NW == DMTD_O_NW) {
+      if (g.mg.po && g.mg.ns <= kMergeFew) { DMTD_LAUNCH_MFMA_MR(ROLL_NW, kMergeFew); continue; }
+      if (g.mg.po) { DMTD_LAUNCH_MFMA_MR(ROLL_NW, kMergeRanges); continue; }
+    }
     if constexpr (ROLL_NW > 0) DMTD_LAUNCH_MFMA(ROLL_NW * MATS);
     else if (nw == 2) DMTD_LAUNCH_MFMA(2 * MATS);
     else if (nw == 4) DMTD_LAUNCH_MFMA(4 * MATS);
@@ -630,6 +643,7 @@ hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows) {
       if constexpr (EPI != EPI_SWIGLU) DMTD_LAUNCH_MFMA(8);
     }
 #undef DMTD_LAUNCH_MFMA
+#undef DMTD_LAUNCH_MFMA_MR
   }
   return hipGetLastError();
 }
@@ -647,6 +661,8 @@ hipError_t launch_down(dmtd_ctx* c, MfmaArgs a, int rows) {
   else return launch_mfma<EPI_RESID, false>(c, a, rows);
 }
 hipError_t launch_oproj(dmtd_ctx* c, MfmaArgs a, int rows) {
+  a.mg = c->merge_pending;
+  c->merge_pending = MergeSrc{};
   if constexpr (DMTD_O_NW > 0) return launch_mfma<EPI_RESID, false, DMTD_O_PF, DMTD_O_NW>(c, a, rows);
   else return launch_mfma<EPI_RESID, false>(c, a, rows);
 }
@@ -695,8 +711,8 @@ void launch_attention_t(dmtd_ctx* c, int l, const float* qkv, OT* attn, OT* attn
 // The matrix-core kernel (bf16 caches): one pass over K and V serves up to 16 query vectors per KV head.
 // Two launch shapes.  (1) ONE key range per (row group, KV head, sequence), 8 waves per block, the output written
 // by the kernel itself (no partials, no merge launch): for batches whose (KV head, sequence) pairs fill the chip
-// without splitting.  (2) Key ranges over 4-wave blocks plus the merge: everything else (a single block per KV head
-// would be bound by its matrix-core work: about 1300 cycles per 16 keys and wave).
+// without splitting.  (2) Key ranges over 4-wave blocks plus the merge, by a launch of its own or, where
+// the partial results are few, by the O projection's blocks (kMergeBytes): everything else.
 template <typename OT, int HD>
 hipError_t launch_attention_mfma_t(dmtd_ctx* c, int l, const float* qkv, OT* attn, OT* attn_lo, int sel, int offset, int r, int append) {
   const dmtd_config& cf = c->cfg;
@@ -741,6 +757,11 @@ hipError_t launch_attention_mfma_t(dmtd_ctx* c, int l, const float* qkv, OT* att
                      kc, vc, cf.n_q_heads, cf.n_kv_heads, cf.max_seq_len, kps, r, c->fmap, st, sel, offset, ns, w.q_norm,
                      w.k_norm, (const float2*)(c->ws + c->o.rope_tab), po, pml, cf.rms_eps, c->part_rows * gq, append,
                      (bf16_t*)nullptr, (bf16_t*)nullptr, 0, 0, qs);
+  // Few partial results: the O projection's blocks merge them on the way in (it has to be the one-tile-per-block kernel)
+  if (DMTD_O_NW > 0 && c->fold_merge && ns <= kMergeRanges && (size_t)B * r * qd * ns * 4 <= kMergeBytes && mfma_rows_fit(c, B * r, cf.hidden, qd, 0)) {
+    c->merge_pending = MergeSrc{po, pml, st, c->fmap, kps, ns, c->part_rows * gq, ATT_MAX_SPLITS, cf.n_kv_heads, gq, HD, sel, offset, r};
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL((attn_merge_kernel<HD, OT>), dim3(r, cf.n_q_heads, B), dim3(256), 0, c->stream, po, pml, attn, attn_lo, qd,
                      cf.n_q_heads, cf.n_kv_heads, kps, ns, c->part_rows * gq, st, sel, offset, r, c->fmap, blocked_rows(c, B * r));
   return hipGetLastError();
@@ -905,7 +926,10 @@ hipError_t run_layer(dmtd_ctx* c, int l, Rows& R, int r, int sel, int offset) {
     if (e != hipSuccess) { c->qkv_pending = QkvSrc{}; return e; }
     // a3 + a4: QK-RMSNorm + RoPE + KV append + split-K attention, then the merge (output packed for the O projection)
     if (wide && (e = launch_kv_append<bf16_t>(c, l, qkv, sel, offset, r)) != hipSuccess) return e;
-    if ((e = launch_attention<bf16_t, bf16_t>(c, l, qkv, ab, ab_lo, sel, offset, r, wide ? 2 : 1)) != hipSuccess) return e;
+    c->fold_merge = true;
+    e = launch_attention<bf16_t, bf16_t>(c, l, qkv, ab, ab_lo, sel, offset, r, wide ? 2 : 1);
+    c->fold_merge = false;
+    if (e != hipSuccess) { c->merge_pending = MergeSrc{}; return e; }
     // a5: O projection + residual; emits the MLP norm's input
     a = MfmaArgs{};
     a.W = s.o; a.xb = ab; a.xb_lo = ab_lo; a.ldxb = qd; a.N = d; a.K = qd; a.y = R.h; a.ldy = d; a.yb = R.xb; a.yb_lo = R.xb_lo; a.ldyb = d;

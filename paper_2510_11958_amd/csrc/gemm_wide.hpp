@@ -1,5 +1,5 @@
 // Projection GEMM for many activation rows of a bf16 model on gfx950 (prefill, whole-sequence scoring, batches whose
-// steps carry more than 128 rows): y[m, n] = sum_k W[n, k] * x[m, k] with x in two bf16 planes (see gemv_mfma.hpp).
+// steps carry more than 192 rows): y[m, n] = sum_k W[n, k] * x[m, k] with x in two bf16 planes (see gemv_mfma.hpp).
 //
 // With hundreds of rows the projection is a matrix-core problem, not a weight stream.  A block computes a tile of 256
 // rows x 256 weight rows (SwiGLU: 128 gate and the same 128 up rows) with 8 waves of 64 x 128 (2 x 4 tiles of

@@ -66,6 +66,50 @@ __global__ void swizzle_weights_kernel(const bf16_t* __restrict__ W, bf16_t* __r
   }
 }
 
+// Partial results of the key ranges of an attention launch (attn_split_mfma_kernel): what the merge kernel reads
+struct MergeSrc {
+  const float* po;       // [sequence][KV head][ATT_MAX_SPLITS][qv_stride][hd], unnormalised
+  const float* pml;      // likewise, (max, sum) pairs
+  const DevState* st;
+  const int* fmap;       // nullable: launch sequence -> sequence slot
+  int kps, ns, qv_stride, range_stride /* ranges a KV head's slots are laid out for */, nkv, gq, hd, sel, offset, r;
+};
+
+// 8 values of one head of one row, merged over at most MR ranges; load() issues every load, value() waits for them.
+template <int MR>
+struct MergedChunk {
+  f32x4 o[MR][2];
+  float2 ml[MR];
+  int n_act;
+  __device__ __forceinline__ void load(const MergeSrc& q, int m, int k) {
+    const int head = k / q.hd, b = m / q.r, i = m % q.r;
+    const size_t at = ((size_t)b * q.nkv + head / q.gq) * q.range_stride * q.qv_stride + (size_t)i * q.gq + head % q.gq;
+    const float* p = q.po + at * q.hd + k % q.hd;
+    const float* pm = q.pml + at * 2;
+#pragma unroll
+    for (int s = 0; s < MR; ++s) {
+      const size_t ss = (size_t)(s < q.ns ? s : 0) * q.qv_stride;          // a range beyond ns gets factor 0 below
+      ml[s] = *(const float2*)(pm + ss * 2);
+      o[s][0] = *(const f32x4*)(p + ss * q.hd);
+      o[s][1] = *(const f32x4*)(p + ss * q.hd + 4);
+    }
+    n_act = min(q.ns, (row_base(q.st, q.sel, q.offset, q.fmap ? q.fmap[b] : b) + i) / q.kps + 1);    // later ranges hold stale partials
+  }
+  __device__ __forceinline__ void value(f32x4& v0, f32x4& v1) const {
+    float mm = -INFINITY, ll = 0.f;
+    f32x4 a = {0.f, 0.f, 0.f, 0.f}, c = a;
+#pragma unroll
+    for (int s = 0; s < MR; ++s) mm = s < n_act ? fmaxf(mm, ml[s].x) : mm;
+#pragma unroll
+    for (int s = 0; s < MR; ++s) {
+      const float f = s < n_act && ml[s].x != -INFINITY ? __expf(ml[s].x - mm) : 0.f;
+      if (f != 0.f) { a += f * o[s][0]; c += f * o[s][1]; ll += f * ml[s].y; }
+    }
+    const float inv = 1.0f / ll;
+    v0 = a * inv; v1 = c * inv;
+  }
+};
+
 struct MfmaArgs {
   const bf16_t* W;       // swizzled [N, K]; SwiGLU: the gate matrix
   const bf16_t* W2;      // SwiGLU: the up matrix
@@ -87,6 +131,7 @@ struct MfmaArgs {
   int blocked;           // layout of xb and yb (packed_at): 0 row-major, 1 blocks of 16 x 32 (wide GEMM and its finishing launch only)
   float* part;           // tiled kernel with K split over blocks: partial sums [ksplit][M][ldp]
   int ksplit, ldp;
+  MergeSrc mg;           // MR > 0: the input rows are still the attention's partial results
 };
 
 // The block first copies the M packed activation rows (both planes) into LDS (dynamic shared
@@ -95,7 +140,10 @@ struct MfmaArgs {
 // that do not fit there to the LDS-tiled kernel (gemm_mfma.hpp).
 // The arguments every wave needs before it can issue its first loads are passed as scalars ahead of the struct: the
 // leading scalar arguments of a kernel arrive in registers at wave launch, the struct through a load.
-template <int EPI, bool NORM, int PF, int NWT, bool ROLL = false>   // NWT: waves per block (all matrices)
+// MR > 0 (O projection): the block merges the attention's key ranges (at most MR of them) itself instead of copying finished rows.
+// Every block reads all partial results (from its L2) while its first weights are on their way, which pays while they are few: one row
+// of 32 heads of 128 in 4 ranges, 64 KiB, costs a block about 2 us, the merge launch it replaces about 4.
+template <int EPI, bool NORM, int PF, int NWT, bool ROLL = false, int MR = 0>   // NWT: waves per block (all matrices)
 __global__ void __launch_bounds__(64 * NWT) gemv_mfma_kernel(const bf16_t* W_, const bf16_t* W2_,
                                                              const bf16_t* xb_, const bf16_t* xb_lo_, const float* ssp_,
                                                              int M_, int N_, int K_, int n_parts_, int ssp_ld_, MfmaArgs a) {
@@ -141,10 +189,17 @@ __global__ void __launch_bounds__(64 * NWT) gemv_mfma_kernel(const bf16_t* W_, c
     return (const u32x4*)(c >= n_chunks ? xb_lo_ + (size_t)(c - n_chunks) * 8 : xb_ + (size_t)c * 8);
   };
   auto chunk_dst = [&](int c) { return (u32x4*)(xs + (size_t)c * 8); };
+  MergedChunk<MR ? MR : 1> mch;
+  const int cpr = K >> 3;                           // chunks per row
+  if constexpr (MR > 0) {
+    const int c = tid < n_chunks ? tid : n_chunks - 1;
+    mch.load(a.mg, c / cpr, c % cpr * 8);
+  } else {
 #pragma unroll
-  for (int j = 0; j < NBST; ++j) {
-    const int c = tid + j * NT;
-    bst[j] = *chunk_src(c < 2 * n_chunks ? c : 2 * n_chunks - 1);
+    for (int j = 0; j < NBST; ++j) {
+      const int c = tid + j * NT;
+      bst[j] = *chunk_src(c < 2 * n_chunks ? c : 2 * n_chunks - 1);
+    }
   }
   // NORM: the producer's partial sums of squares, M * n_parts floats: thread (part p = tid / 16 + j * NT / 16, row m = tid % 16)
   constexpr int NSS = 8;
@@ -194,12 +249,26 @@ __global__ void __launch_bounds__(64 * NWT) gemv_mfma_kernel(const bf16_t* W_, c
       for (int p = ss_p0 + NSS * (NT / 16); p < n_parts_; p += NT / 16) ss_items[p * M + ss_m] = ssp_[(size_t)p * ssp_ld_ + ss_m];
     }
   }
+  if constexpr (MR > 0) {
+    auto put = [&](int c) {
+      f32x4 v[2];
+      mch.value(v[0], v[1]);
 #pragma unroll
-  for (int j = 0; j < NBST; ++j) {
-    const int c = tid + j * NT;
-    if (c < 2 * n_chunks) *chunk_dst(c) = bst[j];
+      for (int e = 0; e < 8; ++e) split_bf16(v[e >> 2][e & 3], xs[(size_t)c * 8 + e], xs[((size_t)n_chunks + c) * 8 + e]);
+    };
+    if (tid < n_chunks) put(tid);
+    for (int c = tid + NT; c < n_chunks; c += NT) {
+      mch.load(a.mg, c / cpr, c % cpr * 8);
+      put(c);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < NBST; ++j) {
+      const int c = tid + j * NT;
+      if (c < 2 * n_chunks) *chunk_dst(c) = bst[j];
+    }
+    for (int c = tid + NBST * NT; c < 2 * n_chunks; c += NT) *chunk_dst(c) = *chunk_src(c);   // beyond what the early loads covered
   }
-  for (int c = tid + NBST * NT; c < 2 * n_chunks; c += NT) *chunk_dst(c) = *chunk_src(c);   // beyond what the early loads covered
   __syncthreads();
   if (NORM) {
     // the rows' 1/rms while the weights are still on their way: per column, 16 threads sum interleaved parts, then
@@ -339,7 +408,7 @@ __global__ void __launch_bounds__(64 * NWT) gemv_mfma_kernel(const bf16_t* W_, c
   }
 }
 
-// Packed projection inputs come in two layouts.  Up to 128 rows: row-major planes [rows, width].  More rows (the wide GEMM,
+// Packed projection inputs come in two layouts.  Up to 192 rows: row-major planes [rows, width].  More rows (the wide GEMM,
 // gemm_wide.hpp): blocks of 16 rows x 32 columns (1 KiB), blocks of a 16-row group following each other along the width, and
 // inside a block [8-column chunk][row][8 values] - the order its tiles are staged in, so a wave's load is 1 KiB of contiguous
 // memory.  Element offset of the 8-column chunk that holds (row, col), plus col % 8:

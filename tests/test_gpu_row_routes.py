@@ -24,6 +24,11 @@ CASES = {
     "rows_20_to_60": (S(3, 256, 4, 2, 128, 512, 1000), 20, 9, 3, 2, 0, False, 7),
     "one_range_to_256_keys": (S(2, 256, 16, 8, 64, 320, 300), 8, 250, 2, 1, 0, False, 12),      # 64 attention blocks: ranges from 257 keys on
     "one_range_to_512_keys": (S(2, 128, 16, 16, 64, 192, 300), 8, 508, 2, 1, 0, False, 8),      # 128 blocks
+    # the attention's ranges merged by the O projection's blocks (up to 4 or 8 ranges, 128 KiB of partial results) or by a launch
+    "merge_4_hd128_gq4": (S(3, 256, 32, 8, 128, 320, 300), 1, 60, 2, 1, 0, False, 8),           # 1 row: 64 KiB, 2 rows: 128 KiB; ranges beyond the context
+    "merge_4_to_8_hd128": (S(2, 128, 16, 8, 128, 192, 300), 1, 250, 3, 1, 0, False, 12),        # 4, then 8 ranges; 1 to 3 rows
+    "merge_8_hd64_gq7": (S(3, 192, 14, 2, 64, 320, 300), 3, 300, 2, 1, 1, False, 6),            # 3 sequences, 3 and 6 rows
+    "merge_limit_hd64_gq1": (S(2, 128, 16, 16, 64, 192, 300), 3, 510, 2, 1, 0, False, 6),       # 96 KiB with 8 ranges, then 24 ranges
     "fp32_one_range_hd64": (S(2, 128, 4, 2, 64, 192, 130, dtype="fp32"), 2, 252, 3, 1, 0, False, 9),
     "fp32_rows_5_10": (S(3, 96, 2, 2, 64, 160, 130, dtype="fp32"), 5, 6, 2, 1, 0, False, 6),
     "fp32_rows_3_9_hd128": (S(2, 128, 2, 1, 128, 160, 130, dtype="fp32"), 3, 6, 3, 1, 0, False, 7),
