@@ -989,7 +989,7 @@ hipError_t head_logits(dmtd_ctx* c, const Rows& R, int n_rows, float* logits, un
   a.eps = cf.rms_eps;
   a.W = c->lm_head; a.gain = c->final_norm; a.x = R.h; a.ldx = cf.hidden;
   a.y = logits; a.ldy = cf.vocab; a.N = cf.vocab; a.K = cf.hidden;
-  a.amax = amax;
+  a.amax = amax; a.amax_ld = amax_ld;
   return gemv_rows<float, EPI_LOGITS, true>(c, a, n_rows);
 }
 

@@ -28,7 +28,8 @@ struct GemvArgs {
   float* y;             // [M, ldy]
   int ldx, ldy, N, K;
   float eps;
-  unsigned long long* amax;   // LOGITS: one selection key per sequence of this launch (already offset)
+  unsigned long long* amax;   // LOGITS: selection keys [AMAX_CELLS, amax_ld], already offset to this launch's rows
+  int amax_ld;
 };
 
 // Sum V (a power of two <= 64) per-lane values over the 64 lanes with V - 1 + (6 - log2 V)
@@ -191,7 +192,7 @@ __global__ void __launch_bounds__(256) gemv_rows_kernel(GemvArgs a) {
   if (EPI == EPI_LOGITS) {
     if (owner && best != 0ull) atomicMax(&best_s[my_m], best);
     __syncthreads();
-    if (tid < M && best_s[tid] != 0ull) atomicMax(a.amax + tid, best_s[tid]);
+    if (tid < M && best_s[tid] != 0ull) atomicMax(a.amax + (size_t)(blockIdx.x % AMAX_CELLS) * a.amax_ld + tid, best_s[tid]);
   }
 }
 

@@ -45,7 +45,6 @@ __device__ __forceinline__ void split_bf16(float v, bf16_t& hi, bf16_t& lo) {
 }
 
 constexpr int MFMA_MAX_WAVES = 16;   // waves that split K for one tile
-constexpr int AMAX_CELLS = 64;       // selection keys are spread over this many cells per sequence
 
 // Elements of the swizzled image of an [N, K] matrix (rows padded to a multiple of 16).
 __host__ __device__ inline size_t swizzled_elems(size_t N, size_t K) { return (N + 15) / 16 * 16 * K; }

@@ -168,6 +168,8 @@ __global__ void set_fronts_kernel(DevState* st, const int* __restrict__ fronts, 
   for (int b = threadIdx.x; b < batch; b += blockDim.x) seq_info(st)[b].front = fronts[b] + seq_info(st)[b].delta;
 }
 
+constexpr int AMAX_CELLS = 64;       // the LM head's blocks spread a sequence's selection keys over this many cells
+
 // Greedy selection keys: a logit and its vocabulary index packed into one 64-bit integer whose
 // unsigned order is (larger logit first, then lower index), so an integer max over any
 // partition of the vocabulary, in any order, gives the argmax with ties to the lowest index.
@@ -311,12 +313,18 @@ __device__ __forceinline__ unsigned long long wave_max_key(unsigned long long ke
 // softmax(z / temperature) over the top_k largest logits (logits equal to the k-th largest all stay in); the draw is the
 // argmax of the perturbed logits and replaces the greedy selection keys.  Two launches, since a sequence's 152k logits are far
 // too many for one block (one block per sequence, four radix passes over them: 177 us at batch 8, now 12 + 5):
-//  sample_scan_kernel, a block per 2048 logits:  no restriction: the slice's best perturbed logit.  top_k <= 64: the greedy
-//    selection keys' 64 cells hold the largest logits of 64 disjoint parts of the vocabulary, so the k-th largest of them is at
-//    most the k-th largest logit; the entries that reach it (about 100 of 152k for k = 50) go to the sequence's list.
-//  sample_pick_kernel, a block per sequence:  an entry of the list stays in if fewer than k are larger, the draw is over
-//    those.  A list that overflows (thousands of equal logits) and 64 < top_k < V: radix select over all logits.
-constexpr int SAMPLE_SLICE = 2048, SAMPLE_CAP = 4096;
+//  sample_scan_kernel, a block per 2048 logits:  no restriction: the slice's best perturbed logit.  top_k <= 64: every filled cell
+//    of the greedy selection keys holds the largest logit of a part of the vocabulary of its own (a part per LM head block,
+//    block number modulo 64), so with k cells filled the k-th largest of them is at most the k-th largest logit; the entries
+//    that reach it (about 100 of 152k for k = 50) go to the sequence's list.  An LM head of few blocks (a block of the tiled
+//    kernels takes 128 or 256 entries) fills fewer cells and gives no bound: then the list is the whole of a vocabulary of up to
+//    SAMPLE_RANKED entries, and stays empty for a larger one.
+//  sample_pick_kernel, a block per sequence:  the draw is over the entries of the list with fewer than k larger ones.  Up to
+//    SAMPLE_RANKED entries are ranked one against all, more of them (flat logits) go through a radix select.  An
+//    empty list, one that overflows (thousands of equal logits) and 64 < top_k < V: radix select over all logits.
+//    us per step of a one-layer model, all V listed and ranked / radix select over the logits: V = 1000 80 / 94 (batch 32) and
+//    60 / 66 (one sequence), V = 2000 142 / 95, V = 4000 379 / 98.
+constexpr int SAMPLE_SLICE = 2048, SAMPLE_CAP = 4096, SAMPLE_RANKED = 1024;
 struct SampleCand { uint32_t ordered; float z; int v; };
 struct SampleScratch {               // per sequence b: count[b], list[b][SAMPLE_CAP], best[b][slices]
   int* count; SampleCand* list; unsigned long long* best; int slices;
@@ -352,9 +360,10 @@ __global__ void __launch_bounds__(256) sample_scan_kernel(const float* __restric
     }
     return;
   }
-  if (top_k > n_cells || n_cells > 64) return;         // radix select in the second launch
-  // the k-th largest of the cells (their ordered logits), bit by bit from the top: every wave for itself
+  if (top_k > n_cells || n_cells > 64) return;         // empty list: radix select in the second launch
+  // the k-th largest of the cells (their ordered logits; 0: not filled), bit by bit from the top: every wave for itself
   const uint32_t cell = lane < n_cells ? (uint32_t)(amax[(size_t)lane * amax_ld + b] >> 32) : 0u;
+  if (V > SAMPLE_RANKED && __popcll(__ballot(cell != 0u)) < top_k) return;
   uint32_t bound = 0u;
 #pragma unroll
   for (int bit = 31; bit >= 0; --bit) {
@@ -379,7 +388,7 @@ __global__ void __launch_bounds__(1024) sample_pick_kernel(const float* __restri
   __shared__ unsigned int hist[256];
   __shared__ unsigned int sel_prefix, sel_remaining;
   __shared__ unsigned long long key_w[16];
-  __shared__ uint32_t ord_s[SAMPLE_CAP];
+  __shared__ uint32_t ord_s[SAMPLE_RANKED];
   const int top_k = cfg->top_k, n = sc.count[b];
   const float inv_temp = cfg->inv_temp;
   const unsigned long long base = draw_base(cfg, st, b);
@@ -389,7 +398,7 @@ __global__ void __launch_bounds__(1024) sample_pick_kernel(const float* __restri
       const unsigned long long k = sc.best[(size_t)b * sc.slices + s];
       if (k > key) key = k;
     }
-  } else if (top_k <= n_cells && n_cells <= 64 && n <= SAMPLE_CAP) {
+  } else if (n >= top_k && n <= SAMPLE_RANKED) {      // a list that holds the k largest has at least k entries
     const SampleCand* list = sc.list + (size_t)b * SAMPLE_CAP;
     for (int i = tid; i < n; i += 1024) ord_s[i] = list[i].ordered;
     __syncthreads();
@@ -403,40 +412,47 @@ __global__ void __launch_bounds__(1024) sample_pick_kernel(const float* __restri
       }
     }
   } else {
-    // k-th largest logit by a 4-pass radix select over the ordered bit patterns (integer counts: exact and order independent)
-    uint32_t prefix = 0u;
-    unsigned int remaining = (unsigned int)top_k;
-    for (int pass = 0; pass < 4; ++pass) {
-      const int shift = 24 - 8 * pass;
-      const uint32_t himask = pass == 0 ? 0u : (0xFFFFFFFFu << (shift + 8));
-      if (tid < 256) hist[tid] = 0u;
-      __syncthreads();
-      for (int v = tid; v < V; v += 1024) {
-        const uint32_t o = ordered_u32(z[v]);
-        if ((o & himask) == prefix) atomicAdd(&hist[(o >> shift) & 255u], 1u);
-      }
-      __syncthreads();
-      if (tid == 0) {
-        unsigned int above = 0u;
-        int bin = 255;
-        for (; bin > 0; --bin) {
-          if (above + hist[bin] >= remaining) break;
-          above += hist[bin];
+    // k-th largest logit by a 4-pass radix select over the ordered bit patterns (integer counts: exact and order independent),
+    // of the list's entries or of all logits.  A loop each: with the source chosen per entry the loads of the logits no longer
+    // overlapped (152k entries 208 -> 230 us per step).
+    auto select = [&](int entries, auto entry) {
+      uint32_t prefix = 0u;
+      unsigned int remaining = (unsigned int)top_k;
+      for (int pass = 0; pass < 4; ++pass) {
+        const int shift = 24 - 8 * pass;
+        const uint32_t himask = pass == 0 ? 0u : (0xFFFFFFFFu << (shift + 8));
+        if (tid < 256) hist[tid] = 0u;
+        __syncthreads();
+        for (int i = tid; i < entries; i += 1024) {
+          const uint32_t o = ordered_u32(entry(i).z);
+          if ((o & himask) == prefix) atomicAdd(&hist[(o >> shift) & 255u], 1u);
         }
-        sel_prefix = prefix | ((uint32_t)bin << shift);
-        sel_remaining = remaining - above;
+        __syncthreads();
+        if (tid == 0) {
+          unsigned int above = 0u;
+          int bin = 255;
+          for (; bin > 0; --bin) {
+            if (above + hist[bin] >= remaining) break;
+            above += hist[bin];
+          }
+          sel_prefix = prefix | ((uint32_t)bin << shift);
+          sel_remaining = remaining - above;
+        }
+        __syncthreads();
+        prefix = sel_prefix;
+        remaining = sel_remaining;
       }
-      __syncthreads();
-      prefix = sel_prefix;
-      remaining = sel_remaining;
-    }
-    for (int v = tid; v < V; v += 1024) {
-      const float zv = z[v];
-      if (ordered_u32(zv) >= prefix) {
-        const unsigned long long k = draw_key(base, zv, inv_temp, v);
-        if (k > key) key = k;
+      for (int i = tid; i < entries; i += 1024) {
+        const SampleCand c = entry(i);
+        if (ordered_u32(c.z) >= prefix) {
+          const unsigned long long k = draw_key(base, c.z, inv_temp, c.v);
+          if (k > key) key = k;
+        }
       }
-    }
+    };
+    const SampleCand* list = sc.list + (size_t)b * SAMPLE_CAP;
+    if (n >= top_k && n <= SAMPLE_CAP) select(n, [&](int i) { return list[i]; });
+    else select(V, [&](int i) { return SampleCand{0u, z[i], i}; });
   }
   key = wave_max_key(key);
   if (lane == 0) key_w[wave] = key;
