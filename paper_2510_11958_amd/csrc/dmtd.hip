@@ -508,7 +508,7 @@ hipError_t launch_wide(dmtd_ctx* c, const MfmaArgs& a, int rows) {
 }
 
 template <int EPI, bool NORM, int PF = kMfmaPF, int ROLL_NW = 0>
-hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows) {
+hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows, const MergeSrc& merge = MergeSrc{} /* po: the rows are still the attention's partial results */) {
   a.blocked = a.blocked || blocked_rows(c, rows);
   if (a.blocked) return launch_wide<EPI, NORM>(c, a, rows);
   if (EPI == EPI_RESID) c->resid_parts = (a.N + 15) / 16;      // one per 16 outputs; launches with a finishing kernel: see there
@@ -618,7 +618,7 @@ hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows) {
     if (a.ssp_next) g.ssp_next = a.ssp_next + m0;
     if (a.amax) g.amax = a.amax + m0;
     const size_t lds = (size_t)2 * g.M * a.K * 2 + (NORM ? (size_t)g.M * a.n_parts * 4 : 0);   // the rows, both planes; partial sums of squares
-#define DMTD_LAUNCH_MFMA_MR(NWT_, MR_)                                                                                            \
+#define DMTD_LAUNCH_MFMA_MR(NWT_, MR_, MG_)                                                                               \
     do {                                                                                                                  \
       auto kern = gemv_mfma_kernel<EPI, NORM, PF, NWT_, (ROLL_NW > 0), MR_>;                                             \
       static bool big_lds = false;                                                                                        \
@@ -627,12 +627,12 @@ hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows) {
         if (ae != hipSuccess) return ae;                                                                                  \
         big_lds = true;                                                                                                   \
       }                                                                                                                   \
-      hipLaunchKernelGGL(kern, grid, dim3(64 * NWT_), lds, c->stream, g.W, g.W2, g.xb, g.xb_lo, (const float*)g.ssp, g.M, g.N, g.K, g.n_parts, g.ssp_ld, g); \
+      hipLaunchKernelGGL(kern, grid, dim3(64 * NWT_), lds, c->stream, g.W, g.W2, g.xb, g.xb_lo, (const float*)g.ssp, g.M, g.N, g.K, g.n_parts, g.ssp_ld, g, MG_); \
     } while (0)
-#define DMTD_LAUNCH_MFMA(NWT_) DMTD_LAUNCH_MFMA_MR(NWT_, 0)
+#define DMTD_LAUNCH_MFMA(NWT_) DMTD_LAUNCH_MFMA_MR(NWT_, 0, MergeArg<0>{})
     if constexpr (EPI == EPI_RESID && ROLL_NW == DMTD_O_NW) {
-      if (g.mg.po && g.mg.ns <= kMergeFew) { DMTD_LAUNCH_MFMA_MR(ROLL_NW, kMergeFew); continue; }
-      if (g.mg.po) { DMTD_LAUNCH_MFMA_MR(ROLL_NW, kMergeRanges); continue; }
+      if (merge.po && merge.ns <= kMergeFew) { DMTD_LAUNCH_MFMA_MR(ROLL_NW, kMergeFew, MergeArg<kMergeFew>{merge}); continue; }
+      if (merge.po) { DMTD_LAUNCH_MFMA_MR(ROLL_NW, kMergeRanges, MergeArg<kMergeRanges>{merge}); continue; }
     }
     if constexpr (ROLL_NW > 0) DMTD_LAUNCH_MFMA(ROLL_NW * MATS);
     else if (nw == 2) DMTD_LAUNCH_MFMA(2 * MATS);
@@ -661,9 +661,9 @@ hipError_t launch_down(dmtd_ctx* c, MfmaArgs a, int rows) {
   else return launch_mfma<EPI_RESID, false>(c, a, rows);
 }
 hipError_t launch_oproj(dmtd_ctx* c, MfmaArgs a, int rows) {
-  a.mg = c->merge_pending;
+  const MergeSrc merge = c->merge_pending;
   c->merge_pending = MergeSrc{};
-  if constexpr (DMTD_O_NW > 0) return launch_mfma<EPI_RESID, false, DMTD_O_PF, DMTD_O_NW>(c, a, rows);
+  if constexpr (DMTD_O_NW > 0) return launch_mfma<EPI_RESID, false, DMTD_O_PF, DMTD_O_NW>(c, a, rows, merge);
   else return launch_mfma<EPI_RESID, false>(c, a, rows);
 }
 hipError_t launch_gateup(dmtd_ctx* c, MfmaArgs a, int rows) {

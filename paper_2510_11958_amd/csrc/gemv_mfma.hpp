@@ -74,6 +74,10 @@ struct MergeSrc {
   int kps, ns, qv_stride, range_stride /* ranges a KV head's slots are laid out for */, nkv, gq, hd, sel, offset, r;
 };
 
+// The kernels that merge take the source behind their other arguments; the others' arguments do not grow by it
+template <int MR> struct MergeArg { MergeSrc src; };
+template <> struct MergeArg<0> {};
+
 // 8 values of one head of one row, merged over at most MR ranges; load() issues every load, value() waits for them.
 template <int MR>
 struct MergedChunk {
@@ -130,8 +134,10 @@ struct MfmaArgs {
   int blocked;           // layout of xb and yb (packed_at): 0 row-major, 1 blocks of 16 x 32 (wide GEMM and its finishing launch only)
   float* part;           // tiled kernel with K split over blocks: partial sums [ksplit][M][ldp]
   int ksplit, ldp;
-  MergeSrc mg;           // MR > 0: the input rows are still the attention's partial results
 };
+// Every projection launch carries these.  With the 80 bytes of a MergeSrc among them, launches outside a graph took longer at small
+// shapes (us, 1536 wide: QKV 4.9 / 4.2, O 4.9 / 4.2, down with 5 rows 10.6 / 9.9).
+static_assert(sizeof(MfmaArgs) <= 160, "arguments of one kernel variant go into an argument of its own (MergeArg)");
 
 // The block first copies the M packed activation rows (both planes) into LDS (dynamic shared
 // memory, 2 * M * K * 2 bytes, plus M * n_parts * 4 for the partial sums of squares if NORM) and the
@@ -145,7 +151,7 @@ struct MfmaArgs {
 template <int EPI, bool NORM, int PF, int NWT, bool ROLL = false, int MR = 0>   // NWT: waves per block (all matrices)
 __global__ void __launch_bounds__(64 * NWT) gemv_mfma_kernel(const bf16_t* W_, const bf16_t* W2_,
                                                              const bf16_t* xb_, const bf16_t* xb_lo_, const float* ssp_,
-                                                             int M_, int N_, int K_, int n_parts_, int ssp_ld_, MfmaArgs a) {
+                                                             int M_, int N_, int K_, int n_parts_, int ssp_ld_, MfmaArgs a, MergeArg<MR> mg) {
   extern __shared__ float4 dyn_smem[];
   bf16_t* xs = (bf16_t*)dyn_smem;                        // [2 planes][M][K], then (NORM) M * n_parts floats
   constexpr int MATS = (EPI == EPI_SWIGLU) ? 2 : 1;
@@ -192,7 +198,7 @@ __global__ void __launch_bounds__(64 * NWT) gemv_mfma_kernel(const bf16_t* W_, c
   const int cpr = K >> 3;                           // chunks per row
   if constexpr (MR > 0) {
     const int c = tid < n_chunks ? tid : n_chunks - 1;
-    mch.load(a.mg, c / cpr, c % cpr * 8);
+    mch.load(mg.src, c / cpr, c % cpr * 8);
   } else {
 #pragma unroll
     for (int j = 0; j < NBST; ++j) {
@@ -257,7 +263,7 @@ __global__ void __launch_bounds__(64 * NWT) gemv_mfma_kernel(const bf16_t* W_, c
     };
     if (tid < n_chunks) put(tid);
     for (int c = tid + NT; c < n_chunks; c += NT) {
-      mch.load(a.mg, c / cpr, c % cpr * 8);
+      mch.load(mg.src, c / cpr, c % cpr * 8);
       put(c);
     }
   } else {
