@@ -526,8 +526,15 @@ hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows, const MergeSrc& merge 
   // Two more that the tiled kernel takes, unsplit, although the rows would fit: an LM head with tile streams in abundance (4B
   // shape, in the step, 1 / 5 rows: 127 / 150 us here, 121 there; 1024 wide, 12 rows: 123 / 57), and gate/up with many tiles
   // from 50 KiB of rows on (2560 wide, 5 rows: 20.5 / 19.4; 896 wide, 304 tiles, 8 rows: 6.7 / 8.5, hence the tile count).
+  // An LM head with up to 4 rows stays here where the tiled kernel's blocks leave a fifth of their rounds of the chip empty and the
+  // rows are long enough for this kernel's waves (us per step of one layer, 3 rows, here / there: 2048 wide, 70000 entries, 71 %
+  // 93 / 100, 100352, 77 % 113 / 124, 80000, 81 % 99 / 102, 92000, 94 % 107 / 109, 128256, 98 % 131 / 132; 2560 wide 120 / 125,
+  // 143 / 149, 127 / 127, 137 / 133, 165 / 161; 896 wide, 70000: 59 / 57).
   const int out_tiles = (a.N + 15) / 16;
-  const bool prefers_tiled = EPI == EPI_LOGITS ? out_tiles >= 16 * c->num_cus
+  const int lm_blocks = (out_tiles + 2 * gemm_waves(1, EPI_LOGITS) - 1) / (2 * gemm_waves(1, EPI_LOGITS));
+  const int lm_slots = (lm_blocks + c->num_cus - 1) / c->num_cus * c->num_cus;
+  const bool lm_stays = rows <= 4 && a.K >= 1024 && lm_blocks * 5L < lm_slots * 4L;
+  const bool prefers_tiled = EPI == EPI_LOGITS ? out_tiles >= 16 * c->num_cus && !lm_stays
                                                : (EPI == EPI_SWIGLU && out_tiles >= 2 * c->num_cus && (size_t)rows * 4 * a.K >= (size_t)50 * 1024);
   const bool fits = a.ldxb == a.K && !prefers_tiled && mfma_rows_fit(c, rows, a.N, a.K, NORM ? a.n_parts : 0);
   // one launch of the tiled kernel; with 64 and more rows its ring of activation slices is dynamic LDS beyond the default limit

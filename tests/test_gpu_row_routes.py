@@ -29,6 +29,10 @@ CASES = {
     "merge_4_to_8_hd128": (S(2, 128, 16, 8, 128, 192, 300), 1, 250, 3, 1, 0, False, 12),        # 4, then 8 ranges; 1 to 3 rows
     "merge_8_hd64_gq7": (S(3, 192, 14, 2, 64, 320, 300), 3, 300, 2, 1, 1, False, 6),            # 3 sequences, 3 and 6 rows
     "merge_limit_hd64_gq1": (S(2, 128, 16, 16, 64, 192, 300), 3, 510, 2, 1, 0, False, 6),       # 96 KiB with 8 ranges, then 24 ranges
+    # LM heads of 65536 entries and more: up to 4 rows through the one-tile kernel where the tiled kernel's last round is nearly empty
+    "lm_head_65600_4_rows": (S(1, 1024, 8, 4, 128, 1024, 65600), 4, 3, 2, 1, 0, False, 3),      # 513 blocks of 128 entries
+    "lm_head_65600_5_rows": (S(1, 1024, 8, 4, 128, 1024, 65600), 5, 3, 2, 1, 0, False, 2),
+    "lm_head_81920_4_rows": (S(1, 1024, 8, 4, 128, 1024, 81920), 4, 3, 2, 1, 0, False, 2),      # 640 blocks: the tiled kernel
     "fp32_one_range_hd64": (S(2, 128, 4, 2, 64, 192, 130, dtype="fp32"), 2, 252, 3, 1, 0, False, 9),
     "fp32_rows_5_10": (S(3, 96, 2, 2, 64, 160, 130, dtype="fp32"), 5, 6, 2, 1, 0, False, 6),
     "fp32_rows_3_9_hd128": (S(2, 128, 2, 1, 128, 160, 130, dtype="fp32"), 3, 6, 3, 1, 0, False, 7),
@@ -73,3 +77,15 @@ def test_many_rows_with_cycle_lengths_per_sequence():
     worst, checked = run_calls(eng, orcs, toks, [(taus, 5), (taus, 4)], n_late, TOL["bf16"])
     assert checked > 0
     print(f"per sequence, batch 100: worst {worst:.2e}, tokens checked {checked}")
+
+
+def test_lm_head_time_has_no_step_where_its_route_changes():
+    """5 more tiles of 16 entries than 65520 may go through another kernel, but not at another price: 53.6 us against 47.2 with the
+    tiled kernel's 513th block in a round of its own.  The margin covers the bytes (0.1 %) and the spread of the best of 8."""
+    us = {}
+    for vocab in (65520, 65600):
+        sh = S(1, 2048, 16, 8, 128, 2048, vocab)
+        eng = pkg.Engine(engine_config(sh, 16, 3), di.make_weight_blob(sh, seed=3))
+        eng.prefill(di.make_prompts(vocab, 3, 4, seed=5))
+        us[vocab] = min(eng.time_kernel("lmhead", 3, reps=20) for _ in range(8))
+    assert us[65600] < 1.07 * us[65520], us
