@@ -237,6 +237,13 @@ int dmtd_read_kv(dmtd_ctx* ctx, int32_t layer, int32_t b, int32_t n_pos, float* 
 #define DMTD_K_READ_DOWN   9
 int dmtd_time_kernel(dmtd_ctx* ctx, int32_t kind, int32_t rows, int32_t reps, float* avg_us);
 
+/* How a projection (one of the five kinds DMTD_K_QKV .. DMTD_K_LMHEAD) of a pass with `rows` activation rows, more than 192, is
+ * laid out on a chip of num_cus compute units: plan[0] rows per launch, plan[1] rows of a tile (128 or 256; a tile has 256
+ * outputs, gate/up 128), plan[2] tiles a block computes whole, plan[3] tiles that pass through a second launch, plan[4] parts K
+ * of these is split into.  Needs no GPU and changes nothing: with it a test can state which layouts its sizes reach.
+ * Errors: DMTD_EINVAL (also an fp32 model, and rows <= 192). */
+int dmtd_wide_plan(const dmtd_config* cfg, int32_t kind, int32_t rows, int32_t num_cus, int32_t plan[5]);
+
 /* ExDy variant (Sec. 2.1, the paragraph before Eq. 5; layer allocations of Sec. 3.3): the in-cycle tokens
  * reuse the first n_early (encoding) layers as well as the last n_late (decoding) layers, i.e. h_masked is built
  * from h_enc instead of h_emb.  A late-only step then runs layers [0, n_early) and [L - n_late, L) on its token

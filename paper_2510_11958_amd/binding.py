@@ -80,6 +80,8 @@ def load_library():
     lib.dmtd_read_kv.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, P(C.c_float), C.c_size_t]
     lib.dmtd_time_kernel.restype = C.c_int
     lib.dmtd_time_kernel.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, P(C.c_float)]
+    lib.dmtd_wide_plan.restype = C.c_int
+    lib.dmtd_wide_plan.argtypes = [P(_Config), C.c_int32, C.c_int32, C.c_int32, P(C.c_int32)]
     lib.dmtd_set_n_early.restype = C.c_int
     lib.dmtd_set_n_early.argtypes = [C.c_void_p, C.c_int32]
     lib.dmtd_set_sampling.restype = C.c_int

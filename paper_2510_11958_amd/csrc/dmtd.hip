@@ -441,12 +441,12 @@ bool mfma_rows_fit(const dmtd_ctx* c, int rows, int N, int K, int n_parts) {
 // owns their epilogue).
 struct WidePlan { double us; int n_full, ksplit; };
 template <int EPI, int BM>
-WidePlan plan_wide(const dmtd_ctx* c, int rows, int nt, int KS) {
-  const int tiles = (rows + BM - 1) / BM * nt, slots = c->num_cus;
+WidePlan plan_wide(const dmtd_config& cf, int num_cus, int rows, int nt, int KS) {
+  const int tiles = (rows + BM - 1) / BM * nt, slots = num_cus;
   // a k-step of 32 takes 1.25 us with 256 rows and 0.8 with 128 (measured, cold weights), a block's start and end about 4;
   // a raw tile's bytes are written and read by blocks all over the chip at about 3.5 TB/s in all; the finishing launch itself 5 us
   const double step_us = BM == 256 ? 1.25 : 0.8;
-  const int part_tiles = (int)std::min<size_t>(gemm_part_floats(c->cfg) / GwTile<BM>::PART, 1 << 20);
+  const int part_tiles = (int)std::min<size_t>(gemm_part_floats(cf) / GwTile<BM>::PART, 1 << 20);
   const int whole = EPI == EPI_RESID ? 0 : tiles / slots * slots, left = tiles - whole;
   auto round_us = [&](int ks) { return (left * ks + slots - 1) / slots * (2.0 * KS / ks * step_us + 4.0); };
   auto parts_us = [&](int ks) { return left * ks * (GwTile<BM>::PART * 4) / 3.5e6 + 5.0; };
@@ -481,16 +481,29 @@ hipError_t launch_wide_tiles(dmtd_ctx* c, const MfmaArgs& g, int nt, const WideP
   return hipGetLastError();
 }
 
+// How a launch of `rows` rows of an [N, K] projection is laid out: rows of a launch, and the tile height with its plan
+struct WideChoice { int nt, pass, bm; WidePlan p; };
+template <int EPI>
+WideChoice choose_wide(const dmtd_config& cf, int num_cus, int rows, int N, int K) {
+  WideChoice w{};
+  w.nt = EPI == EPI_SWIGLU ? (N + 127) / 128 : (N + GW_BN - 1) / GW_BN;
+  const int part_tiles = (int)std::min<size_t>(gemm_part_floats(cf) / GwTile<256>::PART, 1 << 20);      // at least nt
+  w.pass = rows;
+  if (EPI == EPI_RESID && (long)(rows + 255) / 256 * w.nt > part_tiles) w.pass = part_tiles / w.nt * 256;
+  const WidePlan p256 = plan_wide<EPI, 256>(cf, num_cus, w.pass, w.nt, K / 64), p128 = plan_wide<EPI, 128>(cf, num_cus, w.pass, w.nt, K / 64);
+  w.bm = p128.us < p256.us ? 128 : 256;
+  w.p = w.bm == 128 ? p128 : p256;
+  return w;
+}
+
 template <int EPI, bool NORM>
 hipError_t launch_wide(dmtd_ctx* c, const MfmaArgs& a, int rows) {
-  const int KS = a.K / 64;
-  const int nt = EPI == EPI_SWIGLU ? (a.N + 127) / 128 : (a.N + GW_BN - 1) / GW_BN;
-  const int part_tiles = (int)std::min<size_t>(gemm_part_floats(c->cfg) / GwTile<256>::PART, 1 << 20);      // at least nt
-  int pass = rows;
-  if (EPI == EPI_RESID && (long)(pass + 255) / 256 * nt > part_tiles) pass = part_tiles / nt * 256;
+  WideChoice w = choose_wide<EPI>(c->cfg, c->num_cus, rows, a.N, a.K);
+  const int pass = w.pass;
   for (int m0 = 0; m0 < rows; m0 += pass) {
     MfmaArgs g = a;
     g.M = std::min(pass, rows - m0);
+    if (g.M < pass) w = choose_wide<EPI>(c->cfg, c->num_cus, g.M, a.N, a.K);
     g.xb = a.xb + (size_t)m0 * a.ldxb;             // m0 is a multiple of 256: whole row groups of the blocked layout
     g.xb_lo = a.xb_lo + (size_t)m0 * a.ldxb;
     if (a.ssp) g.ssp = a.ssp + m0;
@@ -499,11 +512,10 @@ hipError_t launch_wide(dmtd_ctx* c, const MfmaArgs& a, int rows) {
     if (a.ssp_next) g.ssp_next = a.ssp_next + m0;
     if (a.amax) g.amax = a.amax + m0;
     g.part = c->gemm_part;
-    const WidePlan p256 = plan_wide<EPI, 256>(c, g.M, nt, KS), p128 = plan_wide<EPI, 128>(c, g.M, nt, KS);
-    const hipError_t e = p128.us < p256.us ? launch_wide_tiles<EPI, NORM, 128>(c, g, nt, p128) : launch_wide_tiles<EPI, NORM, 256>(c, g, nt, p256);
+    const hipError_t e = w.bm == 128 ? launch_wide_tiles<EPI, NORM, 128>(c, g, w.nt, w.p) : launch_wide_tiles<EPI, NORM, 256>(c, g, w.nt, w.p);
     if (e != hipSuccess) return e;
   }
-  if (EPI == EPI_RESID) c->resid_parts = nt;
+  if (EPI == EPI_RESID) c->resid_parts = w.nt;
   return hipSuccess;
 }
 
@@ -2089,6 +2101,27 @@ int dmtd_time_kernel(dmtd_ctx* c, int32_t kind, int32_t rows, int32_t reps, floa
   (void)hipEventDestroy(e1);
   if (e != hipSuccess) { c->err = std::string("dmtd_time_kernel: ") + hipGetErrorString(e); return DMTD_EHIP; }
   *avg_us = ms * 1000.0f / (float)launches;
+  return DMTD_OK;
+}
+
+int dmtd_wide_plan(const dmtd_config* cfg, int32_t kind, int32_t rows, int32_t num_cus, int32_t plan[5]) {
+  std::string why;
+  if (!plan || !valid_config(cfg, why) || cfg->dtype != DMTD_DTYPE_BF16 || rows <= kTiledRows || num_cus < 1) return DMTD_EINVAL;
+  const int d = cfg->hidden, qd = cfg->n_q_heads * cfg->head_dim, nqkv = qd + 2 * cfg->n_kv_heads * cfg->head_dim, ff = cfg->intermediate;
+  WideChoice w{};
+  switch (kind) {
+    case DMTD_K_QKV:    w = choose_wide<EPI_STORE>(*cfg, num_cus, rows, nqkv, d); break;
+    case DMTD_K_OPROJ:  w = choose_wide<EPI_RESID>(*cfg, num_cus, rows, d, qd); break;
+    case DMTD_K_GATEUP: w = choose_wide<EPI_SWIGLU>(*cfg, num_cus, rows, ff, d); break;
+    case DMTD_K_DOWN:   w = choose_wide<EPI_RESID>(*cfg, num_cus, rows, d, ff); break;
+    case DMTD_K_LMHEAD: w = choose_wide<EPI_LOGITS>(*cfg, num_cus, rows, cfg->vocab, d); break;
+    default: return DMTD_EINVAL;
+  }
+  plan[0] = w.pass;
+  plan[1] = w.bm;
+  plan[2] = w.p.n_full;
+  plan[3] = (w.pass + w.bm - 1) / w.bm * w.nt - w.p.n_full;
+  plan[4] = w.p.ksplit;
   return DMTD_OK;
 }
 

@@ -5,6 +5,8 @@ query vectors x 64 keys per tile), at the edges of their tiles, against the CPU 
 Tolerance: that of the other bf16 parity tests (2e-2 of the largest logit: the bf16 KV cache's rounding through the layers);
 a wrong row, key or output of a tile is an error of order one.
 """
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -12,8 +14,6 @@ import dmtd_inputs as di
 import paper_2510_11958_amd as pkg
 from oracle import dmtd_oracle as O
 from parity_util import engine_config, norm_err, oracle_config
-
-pytestmark = pytest.mark.gpu
 
 TOL_BF16 = 2e-2
 
@@ -34,10 +34,48 @@ CASES = {
     "vectors_9600_hd64_gq1": (S(2, 192, 16, 16, 64, 320, 203), 3, 200),          # 128 rows per block
     "vectors_8224_hd128_gq2": (S(2, 320, 16, 8, 128, 960, 129), 2, 257),         # one row in the fifth tile of 64
     "vectors_19200_hd64_gq8": (S(1, 128, 8, 1, 64, 128, 97), 48, 50),            # 192 blocks of 128, two groups of waves
+    # the layouts that the plan of a projection reaches at these sizes: LAYOUTS below
+    "tiles_256_whole_and_tail": (S(2, 896, 14, 2, 64, 8896, 17000), 8, 256),
+    "tiles_256_qkv_ragged": (S(1, 512, 66, 22, 64, 704, 300), 4, 505),            # 2020 rows: the last row tile has 228, nqkv is 27.5 tiles
+    "tiles_256_qkv_tail_ragged": (S(1, 1024, 93, 31, 64, 704, 300), 4, 449),      # the last row tile has 4 rows, nqkv is 38.75 tiles
+    "resid_in_two_launches": (S(2, 1024, 4, 2, 64, 128, 300), 5, 400),
     "vectors_38400_hd64_gq8": (S(1, 128, 16, 2, 64, 128, 97), 48, 50),           # 384 blocks of 128, more than a block per CU: one group of waves
 }
 
 
+# What the cases above are there for, on 256 compute units: (rows per launch, rows of a tile, whole tiles, tiles of the second launch,
+# parts of K).  The kinds a case does not name run tiles of 128 rows without a whole round before a tail.
+KINDS = {"qkv": 0, "oproj": 1, "gateup": 2, "down": 3, "lmhead": 4}
+LAYOUTS = {
+    "tiles_256_whole_and_tail": {"gateup": (2048, 256, 512, 48, 3), "down": (2048, 256, 0, 32, 8), "lmhead": (512, 256, 134, 0, 1)},
+    "tiles_256_qkv_ragged": {"qkv": (2020, 256, 224, 0, 1)},
+    "tiles_256_qkv_tail_ragged": {"qkv": (1796, 256, 256, 56, 3)},
+    "resid_in_two_launches": {"oproj": (1536, 128, 0, 48, 1), "down": (1536, 128, 0, 48, 1)},
+}
+
+
+@pytest.mark.parametrize("name", list(LAYOUTS))
+def test_cases_reach_the_layouts_they_are_there_for(name):
+    """Runs without a GPU: the cases that cover the tiles of 256 rows, split tails and launches in parts really reach them."""
+    sh, batch, n = CASES[name]
+    cfg = engine_config(sh, n + 2, batch).to_c()
+    for kind, want in LAYOUTS[name].items():
+        plan = (C.c_int32 * 5)()
+        rows = batch * n if kind != "lmhead" else min(batch * n, 512)      # a scoring pass holds the logits of 512 rows at a time
+        assert pkg.load_library().dmtd_wide_plan(C.byref(cfg), KINDS[kind], rows, 256, plan) == pkg.DMTD_OK
+        assert tuple(plan) == want, kind
+
+
+def test_wide_plan_refuses_what_the_wide_kernel_does_not_take():
+    lib, plan = pkg.load_library(), (C.c_int32 * 5)()
+    bf16, fp32 = (engine_config(S(2, 256, 8, 2, 128, 512, 1000, dtype=t), 64, 8).to_c() for t in ("bf16", "fp32"))
+    assert lib.dmtd_wide_plan(C.byref(bf16), 0, 193, 256, plan) == pkg.DMTD_OK
+    for cfg, kind, rows, cus, out in ((bf16, 0, 192, 256, plan), (bf16, 5, 193, 256, plan), (bf16, -1, 193, 256, plan), (bf16, 0, 193, 0, plan),
+                                      (bf16, 0, 193, 256, None), (fp32, 0, 193, 256, plan)):
+        assert lib.dmtd_wide_plan(C.byref(cfg), kind, rows, cus, out) == pkg.DMTD_EINVAL
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("name", list(CASES))
 def test_wide_pass_against_oracle(name):
     sh, batch, n = CASES[name]
