@@ -21,6 +21,8 @@ CASES = {
     "rows_up_to_300": (S(3, 128, 4, 2, 64, 256, 500), 100, 5, 3, 1, 0, False, 7),
     "rows_up_to_300_early": (S(4, 128, 4, 1, 64, 192, 300), 100, 4, 3, 2, 1, True, 7),
     "rows_193_per_step": (S(2, 64, 2, 1, 64, 128, 200), 193, 3, 1, 1, 0, False, 3),
+    "rows_193_early": (S(3, 64, 2, 1, 64, 128, 200), 193, 3, 3, 1, 1, False, 5),                # stored and gathered rows of the early layers in the wide layout
+    "rows_193_early_literal": (S(3, 64, 2, 1, 64, 128, 200), 193, 3, 2, 1, 1, True, 3),
     "rows_20_to_60": (S(3, 256, 4, 2, 128, 512, 1000), 20, 9, 3, 2, 0, False, 7),
     "one_range_to_256_keys": (S(2, 256, 16, 8, 64, 320, 300), 8, 250, 2, 1, 0, False, 12),      # 64 attention blocks: ranges from 257 keys on
     "one_range_to_512_keys": (S(2, 128, 16, 16, 64, 192, 300), 8, 508, 2, 1, 0, False, 8),      # 128 blocks
@@ -77,6 +79,27 @@ def test_many_rows_with_cycle_lengths_per_sequence():
     worst, checked = run_calls(eng, orcs, toks, [(taus, 5), (taus, 4)], n_late, TOL["bf16"])
     assert checked > 0
     print(f"per sequence, batch 100: worst {worst:.2e}, tokens checked {checked}")
+
+
+def test_front_groups_on_both_sides_of_the_wide_layout_with_late_rows_in_it():
+    """A batch of 200: the late rows are in the wide GEMM's layout, while a step's front passes carry 342 rows (171 sequences in cycles
+    of 2), in that layout too, and 116 (29 sequences in cycles of 4), row by row."""
+    from test_gpu_per_seq import run_calls
+    sh, batch, n, n_late = S(2, 64, 2, 1, 64, 128, 200), 200, 4, 1
+    blob = di.make_weight_blob(sh, seed=3)
+    prompts = di.make_prompts(sh.vocab, batch, n, seed=5)
+    toks = forced_string(sh, batch, prompts, n + 16)
+    eng = pkg.Engine(engine_config(sh, n + 16, batch), blob)
+    ocfg = oracle_config(sh)
+    w = O.unpack_weights(blob, ocfg, np.float64)
+    orcs = [O.DmtdOracle(ocfg, w, n + 16, np.float64) for _ in range(batch)]
+    eng.prefill(prompts)
+    for b, o in enumerate(orcs):
+        o.prefill(prompts[b])
+    taus = [4 if b % 7 == 3 else 2 for b in range(batch)]
+    worst, checked = run_calls(eng, orcs, toks, [(taus, 4), (taus, 4), ([2] * batch, 3)], n_late, TOL["bf16"])
+    assert checked > 0
+    print(f"per sequence, batch 200: worst {worst:.2e}, tokens checked {checked}")
 
 
 def test_lm_head_time_has_no_step_where_its_route_changes():
