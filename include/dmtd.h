@@ -83,8 +83,10 @@ typedef struct dmtd_config {
 size_t dmtd_workspace_bytes(const dmtd_config* cfg);
 
 /* Create a context.  weights_dev: DEVICE weight blob of weights_bytes bytes (layout
- * above), 16-byte aligned.  workspace_dev: DEVICE, 256-byte aligned, at least
- * dmtd_workspace_bytes(cfg).  With cfg->dry_run both may be NULL.  On success *out
+ * above), 16-byte aligned.  workspace_dev: DEVICE, 256-byte aligned,
+ * dmtd_workspace_bytes(cfg) bytes; a bf16 model also takes a smaller one, as long as passes of
+ * 128 activation rows fit, and its prefill and whole-sequence passes are then shorter (half,
+ * a quarter, ... of 2048 rows) and slower.  With cfg->dry_run both may be NULL.  On success *out
  * receives the context.  Errors: DMTD_EINVAL (shape, size or alignment), DMTD_ECAPACITY
  * (workspace too small), DMTD_EHIP. */
 int dmtd_create(const dmtd_config* cfg, const void* weights_dev, size_t weights_bytes,

@@ -37,29 +37,35 @@ constexpr int kPassRows = 128;       // activation rows (all sequences together)
 // The activation buffers of such a pass take 0.2 GB at 4B shapes.
 constexpr int kWideRows = 2048;
 constexpr int kHeadRows = 512;       // rows of a whole-sequence pass whose logits are held at a time (0.3 GB at a 152k vocabulary)
+// Up to this many rows go through the LDS-tiled kernel in passes, more through the wide GEMM (all four projections of a layer at
+// 4B shapes, us: 160 rows 172 / 190, 192 rows 191 / 190, 256 rows 220 / 190 with tiles of 256 rows)
+constexpr int kTiledRows = 192;
 // Rows per sequence and in all that a decode step may carry: what the attention's partial results are laid out for.
 inline int step_row_capacity(int max_batch) { return max_batch * kMaxRows > kPassRows ? max_batch * kMaxRows : kPassRows; }
 inline int step_positions(int batch) { const int r = kPassRows / batch; return r > kMaxRows ? r : kMaxRows; }
-// Row capacity of the activation buffers: a decode step's rows, and a prefill pass's (never more than the longest batch has)
-inline int row_capacity(const dmtd_config& c) {
+// Row capacity of the activation buffers: a decode step's rows, and a prefill pass's (never more than the longest batch has).
+// wide: rows of a bf16 model's pass (kWideRows, fewer where the caller's workspace does not hold that many: dmtd_create)
+inline int row_capacity(const dmtd_config& c, int wide) {
   long cap = step_row_capacity(c.max_batch);
   if (c.dtype == DMTD_DTYPE_BF16) {
     const long all = (long)c.max_batch * c.max_seq_len;
-    cap = std::max(cap, std::min<long>(kWideRows, (all + 15) / 16 * 16));
+    cap = std::max(cap, std::min<long>(wide, (all + 15) / 16 * 16));
   }
   return (int)cap;
 }
-// Packed rows of the late layers, one per sequence: whole groups of 16, which is how the wide GEMM's layout stores them
-inline size_t late_row_capacity(const dmtd_config& c) { return ((size_t)c.max_batch + 15) / 16 * 16; }
-inline int head_row_capacity(const dmtd_config& c) {
-  return c.dtype == DMTD_DTYPE_BF16 ? std::min(row_capacity(c), std::max(kHeadRows, step_row_capacity(c.max_batch))) : row_capacity(c);
+// Packed rows of the late layers, one per sequence: whole groups of 16 where they may be in the wide GEMM's layout, which stores them so
+inline size_t late_row_capacity(const dmtd_config& c) { return c.max_batch > kTiledRows ? ((size_t)c.max_batch + 15) / 16 * 16 : (size_t)c.max_batch; }
+inline int head_row_capacity(const dmtd_config& c, int wide) {
+  return c.dtype == DMTD_DTYPE_BF16 ? std::min(row_capacity(c, wide), std::max(kHeadRows, step_row_capacity(c.max_batch))) : row_capacity(c, wide);
 }
 // Positions per sequence of a prefill or whole-sequence pass.  Full passes and a short last one rather than equal ones: a full
 // pass is 8 row tiles of the wide GEMM, and equal passes would pad each to whole tiles (3 x 701 positions at 4B shapes: 2046 + 57
 // rows against 1056 + 1047, which are 5 tiles each).
-inline int pass_positions(const dmtd_config& c, int batch) {
-  return c.dtype == DMTD_DTYPE_BF16 ? std::max(kWideRows / batch, kMaxRows) : step_positions(batch);
+inline int pass_positions(const dmtd_config& c, int wide, int batch) {
+  return c.dtype == DMTD_DTYPE_BF16 ? std::max(wide / batch, kMaxRows) : step_positions(batch);
 }
+// Entries of a sequence's list of a sampled step
+inline int sample_cap(const dmtd_config& c) { return std::min(SAMPLE_CAP, c.vocab); }
 constexpr int kMaxPatterns = 64;     // distinct step patterns (which sequences start a cycle, with how many rows) a context keeps on the device
 constexpr size_t kPatternStride(size_t max_batch) { return (max_batch * 5 + 255) / 256 * 256; }   // int list [max_batch] + byte mask [max_batch]
 constexpr int kMfmaRows = 16;        // activation rows per pass of the one-tile-per-block MFMA kernel
@@ -74,9 +80,6 @@ constexpr int kGemmMaxSplit = DMTD_GEMM_MAXSPLIT;   // K splits of the tiled ker
 #define DMTD_GEMM_ROWS 128
 #endif
 constexpr int kGemmRows = DMTD_GEMM_ROWS;   // activation rows per pass of the LDS-tiled MFMA kernel (launches with more than 16 rows)
-// Up to this many rows go through the LDS-tiled kernel in passes, more through the wide GEMM (all four projections of a layer at
-// 4B shapes, us: 160 rows 172 / 190, 192 rows 191 / 190, 256 rows 220 / 190 with tiles of 256 rows)
-constexpr int kTiledRows = 192;
 // Key ranges an O projection's blocks merge by themselves (two kernels: up to 4 and up to 8), and the bytes of partial results
 // every block may read for that.  us per step with the merge launch / merged here: 64 KiB 331.6 / 319.9 (2560 wide, 6
 // layers, 4 ranges), 350.7 / 333.4 (1024 wide, 12 layers, 2 rows); 128 KiB 330.8 / 326.1 (8 ranges), 354.5 / 346.1; 256 KiB
@@ -180,6 +183,7 @@ struct dmtd_ctx {
   bool packed = false;        // bf16 model: MFMA path
   int num_cus = 256;
   int batch = 0;              // batch of the current sequence set (after prefill)
+  int wide_rows = kWideRows;  // activation rows of a bf16 model's prefill or whole-sequence pass
   int ssp_ld = 0;             // row capacity of the sum-of-squares buffers
   const char* wbase = nullptr;
   char* ws = nullptr;
@@ -262,12 +266,12 @@ size_t gemm_part_floats(const dmtd_config& c) {
   return (size_t)kGemmMaxSplit * kGemmRows * std::max({2 * (size_t)c.intermediate, nqkv, (size_t)c.hidden});
 }
 
-Ws layout(const dmtd_config& c) {
+Ws layout(const dmtd_config& c, int wide = kWideRows) {
   Ws w{};
   const size_t e = c.dtype == DMTD_DTYPE_F32 ? 4 : 2;
   const size_t B = c.max_batch, S = c.max_seq_len, d = c.hidden, hd = c.head_dim;
   const size_t nqkv = (size_t)(c.n_q_heads + 2 * c.n_kv_heads) * hd, qd = (size_t)c.n_q_heads * hd;
-  const size_t rows = row_capacity(c), step_rows = step_row_capacity(c.max_batch);
+  const size_t rows = row_capacity(c, wide), step_rows = step_row_capacity(c.max_batch);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
   const size_t kv_one = B * c.n_kv_heads * S * hd * e;       // K (or V) of one layer
@@ -290,7 +294,7 @@ Ws layout(const dmtd_config& c) {
   w.part_ml = take(c.n_kv_heads * ATT_MAX_SPLITS * qv_rows * 2 * 4);
   if (c.dtype == DMTD_DTYPE_BF16) w.gemm_part = take(gemm_part_floats(c) * 4);
   w.logits_rows = scratch;
-  off = std::max(off, align_up(scratch + head_row_capacity(c) * (size_t)c.vocab * 4, 256));
+  off = std::max(off, align_up(scratch + head_row_capacity(c, wide) * (size_t)c.vocab * 4, 256));
   w.logits = take(B * (size_t)c.vocab * 4);
   w.amax = take((size_t)AMAX_CELLS * B * 8);
   w.tokens = take(B * S * 4);
@@ -299,14 +303,14 @@ Ws layout(const dmtd_config& c) {
   w.state = take(kStateDeltaOff + 12 * B);            // counters, sampling parameters, per-sequence (delta, front position) pairs, last prompt positions
   w.patterns = take((size_t)kMaxPatterns * kPatternStride(B));   // sequence lists and masks of steps whose sequences are at different points of their cycles
   w.sample_count = take(B * 4);
-  w.sample_list = take(B * SAMPLE_CAP * sizeof(SampleCand));
+  w.sample_list = take(B * sample_cap(c) * sizeof(SampleCand));
   w.sample_best = take(B * ((c.vocab + SAMPLE_SLICE - 1) / SAMPLE_SLICE) * 8);
   w.inv_freq = take((hd / 2) * 8);
   w.pend_enc = take(B * kMaxTau * d * 4);
   w.enc_tmp = take(rows * d * 4);
   w.rope_tab = take(S * (hd / 2) * 8);                 // (cos, sin) per position and frequency
   w.mask = take(S * 4);
-  w.amax_rows = take((size_t)AMAX_CELLS * head_row_capacity(c) * 8);
+  w.amax_rows = take((size_t)AMAX_CELLS * head_row_capacity(c, wide) * 8);
   w.nll = take(B * S * 4);
   w.best = take(B * S * 4);
   w.loss = take(B * 4);
@@ -929,7 +933,7 @@ hipError_t run_layer(dmtd_ctx* c, int l, Rows& R, int r, int sel, int offset) {
   hipError_t e;
   if (c->packed) {
     const LayerSw& s = c->sw[l];
-    const size_t rows_cap = row_capacity(cf);
+    const size_t rows_cap = row_capacity(cf, c->wide_rows);
     bf16_t* ab = (bf16_t*)(c->ws + c->o.attn);      // attention output, high parts; low parts behind them
     bf16_t* ab_lo = ab + rows_cap * qd;
     bf16_t* ub = (bf16_t*)(c->ws + c->o.mlp);       // SwiGLU output, likewise
@@ -1022,7 +1026,7 @@ hipError_t run_head(dmtd_ctx* c, const Rows& R, int full, int write_tokens, int 
     const float* z = (const float*)(c->ws + c->o.logits);
     const SampleCfg* sc = (const SampleCfg*)(c->ws + c->o.state + kStateSampleOff);
     const int slices = (cf.vocab + SAMPLE_SLICE - 1) / SAMPLE_SLICE;
-    const SampleScratch ss{sample_count(c), (SampleCand*)(c->ws + c->o.sample_list), (unsigned long long*)(c->ws + c->o.sample_best), slices};
+    const SampleScratch ss{sample_count(c), (SampleCand*)(c->ws + c->o.sample_list), (unsigned long long*)(c->ws + c->o.sample_best), slices, sample_cap(cf)};
     hipLaunchKernelGGL(sample_scan_kernel, dim3(slices, n_rows), dim3(256), 0, c->stream, z, cf.vocab, sc, (const DevState*)dev_state(c),
                        (const unsigned long long*)amax, AMAX_CELLS, cf.max_batch, ss);
     hipLaunchKernelGGL(sample_pick_kernel, dim3(n_rows), dim3(1024), 0, c->stream, z, cf.vocab, sc, (const DevState*)dev_state(c), amax, AMAX_CELLS,
@@ -1036,7 +1040,7 @@ hipError_t run_head(dmtd_ctx* c, const Rows& R, int full, int write_tokens, int 
 
 Rows front_rows(dmtd_ctx* c) {
   bf16_t* xb = (bf16_t*)(c->ws + c->o.xb);
-  return Rows{(float*)(c->ws + c->o.h), xb, xb + (size_t)row_capacity(c->cfg) * c->cfg.hidden, (float*)(c->ws + c->o.ssp), 1};
+  return Rows{(float*)(c->ws + c->o.h), xb, xb + (size_t)row_capacity(c->cfg, c->wide_rows) * c->cfg.hidden, (float*)(c->ws + c->o.ssp), 1};
 }
 Rows late_rows(dmtd_ctx* c) {
   bf16_t* xb = (bf16_t*)(c->ws + c->o.xb_late);
@@ -1276,7 +1280,7 @@ hipError_t enqueue_prefill(dmtd_ctx* c, int P, int n_late, bool ragged) {
   hipError_t e;
   hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(64), 0, c->stream, dev_state(c), P - 1, P - 1, cf.max_batch, sample_count(c));
   int r_last = 0, p_last = 0;
-  const int chunk = pass_positions(cf, c->batch);
+  const int chunk = pass_positions(cf, c->wide_rows, c->batch);
   PartRowsGuard guard{c, c->part_rows};
   c->part_rows = step_positions(c->batch);   // the attention partials of a pass (see attention_single_range)
   for (int p0 = 0; p0 < P; p0 += chunk) {
@@ -1347,7 +1351,7 @@ hipError_t enqueue_masked_head(dmtd_ctx* c, const Rows& R, int m0 /* a multiple 
   H.h += (size_t)m0 * cf.hidden;
   if (c->packed) { H.xb += (size_t)m0 * cf.hidden; H.xb_lo += (size_t)m0 * cf.hidden; H.ssp += m0; }
   float* logits = (float*)(c->ws + c->o.logits_rows);
-  const hipError_t e = head_logits(c, H, n_rows, logits, (unsigned long long*)(c->ws + c->o.amax_rows), head_row_capacity(cf), blocked_rows(c, c->batch * r));
+  const hipError_t e = head_logits(c, H, n_rows, logits, (unsigned long long*)(c->ws + c->o.amax_rows), head_row_capacity(cf, c->wide_rows), blocked_rows(c, c->batch * r));
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(nll_rows_kernel, dim3(n_rows), dim3(1024), 0, c->stream, (const float*)logits, cf.vocab, (const int*)dev_tokens(c), cf.max_seq_len,
                      m0, p0, r, n, (float*)(c->ws + c->o.nll), (int*)(c->ws + c->o.best));
@@ -1384,7 +1388,7 @@ hipError_t time_one(dmtd_ctx* c, int kind, int l, int rows) {
     const int r = rows <= last + 1 ? rows : 1;
     // the cache append is switched off: the launch scores the rows' new keys from the scratch q/k/v, writes nothing
     choose_attention(c, last + 1);
-    if (c->packed) return launch_attention<bf16_t, bf16_t>(c, l, qkv, (bf16_t*)(c->ws + c->o.attn), (bf16_t*)(c->ws + c->o.attn) + (size_t)row_capacity(cf) * cf.n_q_heads * cf.head_dim, (int)POS_EXPLICIT, last - r + 1, r, 0);
+    if (c->packed) return launch_attention<bf16_t, bf16_t>(c, l, qkv, (bf16_t*)(c->ws + c->o.attn), (bf16_t*)(c->ws + c->o.attn) + (size_t)row_capacity(cf, c->wide_rows) * cf.n_q_heads * cf.head_dim, (int)POS_EXPLICIT, last - r + 1, r, 0);
     return launch_attention<float, float>(c, l, qkv, (float*)(c->ws + c->o.attn), (float*)nullptr, (int)POS_EXPLICIT, last - r + 1, r, 0);
   }
   if (kind == DMTD_K_LMHEAD) {
@@ -1393,7 +1397,7 @@ hipError_t time_one(dmtd_ctx* c, int kind, int l, int rows) {
   }
   if (c->packed) {
     const LayerSw& s = c->sw[l];
-    const size_t rows_cap = row_capacity(cf);
+    const size_t rows_cap = row_capacity(cf, c->wide_rows);
     bf16_t* ab = (bf16_t*)(c->ws + c->o.attn);
     bf16_t* ab_lo = ab + rows_cap * qd;
     bf16_t* ub = (bf16_t*)(c->ws + c->o.mlp);
@@ -1466,7 +1470,8 @@ int dmtd_create(const dmtd_config* cfg, const void* weights_dev, size_t weights_
   *out = nullptr;
   if (!valid_config(cfg, why)) { g_create_error = why; return DMTD_EINVAL; }
   const size_t elem = cfg->dtype == DMTD_DTYPE_F32 ? 4 : 2;
-  const Ws lay = layout(*cfg);
+  int wide = kWideRows;
+  Ws lay = layout(*cfg);
   if (!cfg->dry_run) {
     if (!weights_dev || !workspace_dev) { g_create_error = "null device pointer"; return DMTD_EINVAL; }
     if (((uintptr_t)weights_dev & 15) || ((uintptr_t)workspace_dev & 255)) {
@@ -1475,6 +1480,8 @@ int dmtd_create(const dmtd_config* cfg, const void* weights_dev, size_t weights_
     if (weights_bytes != weight_elems(*cfg) * elem) {
       g_create_error = "weight blob size does not match the configuration"; return DMTD_EINVAL;
     }
+    // a workspace with no room for full passes gets shorter ones, down to kPassRows rows
+    while (workspace_bytes < lay.total && wide > kPassRows) lay = layout(*cfg, wide /= 2);
     if (workspace_bytes < lay.total) { g_create_error = "workspace too small"; return DMTD_ECAPACITY; }
   }
   dmtd_ctx* c = new dmtd_ctx();
@@ -1485,7 +1492,8 @@ int dmtd_create(const dmtd_config* cfg, const void* weights_dev, size_t weights_
   c->sched.n_layers = cfg->n_layers;
   c->sched.max_seq_len = cfg->max_seq_len;
   c->packed = cfg->dtype == DMTD_DTYPE_BF16;
-  c->ssp_ld = row_capacity(*cfg);
+  c->wide_rows = wide;
+  c->ssp_ld = row_capacity(*cfg, wide);
   if (const char* ev = std::getenv("DMTD_TEST_FAIL_STEP")) c->test_fail_step = std::atoi(ev);
   c->plan_buf.reserve(kMaxTau + 1);
   c->sched.trace.reserve((size_t)12 * cfg->max_seq_len + 64);        // at most 3 records of 4 per step: later steps never reallocate
@@ -2148,14 +2156,14 @@ int dmtd_masked_forward(dmtd_ctx* c, const int32_t* tokens, int32_t batch, int32
   hipError_t e = hipMemcpy2DAsync(c->ws + c->o.tokens, (size_t)cf.max_seq_len * 4, tokens, (size_t)n * 4, (size_t)n * 4, batch,
                                   hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(c->ws + c->o.mask, m32.data(), (size_t)n * 4, hipMemcpyHostToDevice, c->stream);
-  const int chunk = pass_positions(cf, batch);
+  const int chunk = pass_positions(cf, c->wide_rows, batch);
   PartRowsGuard guard{c, c->part_rows};
   c->part_rows = step_positions(batch);
   for (int p0 = 0; p0 < n && e == hipSuccess; p0 += chunk) {
     const int r = n - p0 < chunk ? n - p0 : chunk;
     Rows R = front_rows(c);
     e = enqueue_masked_chunk(c, R, p0, r, n_late);
-    const int rows = batch * r, head = head_row_capacity(cf);
+    const int rows = batch * r, head = head_row_capacity(cf, c->wide_rows);
     for (int m0 = 0; m0 < rows && e == hipSuccess; m0 += head) {
       const int m1 = std::min(rows, m0 + head);
       e = enqueue_masked_head(c, R, m0, m1 - m0, p0, r, n);

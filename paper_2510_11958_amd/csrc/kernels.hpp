@@ -326,8 +326,8 @@ __device__ __forceinline__ unsigned long long wave_max_key(unsigned long long ke
 //    60 / 66 (one sequence), V = 2000 142 / 95, V = 4000 379 / 98.
 constexpr int SAMPLE_SLICE = 2048, SAMPLE_CAP = 4096, SAMPLE_RANKED = 1024;
 struct SampleCand { uint32_t ordered; float z; int v; };
-struct SampleScratch {               // per sequence b: count[b], list[b][SAMPLE_CAP], best[b][slices]
-  int* count; SampleCand* list; unsigned long long* best; int slices;
+struct SampleScratch {               // per sequence b: count[b], list[b][cap], best[b][slices]; cap: the smaller of SAMPLE_CAP and V
+  int* count; SampleCand* list; unsigned long long* best; int slices, cap;
 };
 
 __global__ void __launch_bounds__(256) sample_scan_kernel(const float* __restrict__ logits, int V, const SampleCfg* __restrict__ cfg,
@@ -376,7 +376,7 @@ __global__ void __launch_bounds__(256) sample_scan_kernel(const float* __restric
     const uint32_t o = ordered_u32(zv[i]);
     if (v < V && o >= bound) {
       const int at = atomicAdd(sc.count + b, 1);
-      if (at < SAMPLE_CAP) sc.list[(size_t)b * SAMPLE_CAP + at] = SampleCand{o, zv[i], v};
+      if (at < sc.cap) sc.list[(size_t)b * sc.cap + at] = SampleCand{o, zv[i], v};
     }
   }
 }
@@ -399,7 +399,7 @@ __global__ void __launch_bounds__(1024) sample_pick_kernel(const float* __restri
       if (k > key) key = k;
     }
   } else if (n >= top_k && n <= SAMPLE_RANKED) {      // a list that holds the k largest has at least k entries
-    const SampleCand* list = sc.list + (size_t)b * SAMPLE_CAP;
+    const SampleCand* list = sc.list + (size_t)b * sc.cap;
     for (int i = tid; i < n; i += 1024) ord_s[i] = list[i].ordered;
     __syncthreads();
     for (int i = tid; i < n; i += 1024) {
@@ -450,8 +450,8 @@ __global__ void __launch_bounds__(1024) sample_pick_kernel(const float* __restri
         }
       }
     };
-    const SampleCand* list = sc.list + (size_t)b * SAMPLE_CAP;
-    if (n >= top_k && n <= SAMPLE_CAP) select(n, [&](int i) { return list[i]; });
+    const SampleCand* list = sc.list + (size_t)b * sc.cap;
+    if (n >= top_k && n <= sc.cap) select(n, [&](int i) { return list[i]; });
     else select(V, [&](int i) { return SampleCand{0u, z[i], i}; });
   }
   key = wave_max_key(key);
