@@ -222,6 +222,9 @@ int dmtd_read_kv(dmtd_ctx* ctx, int32_t layer, int32_t b, int32_t n_pos, float* 
  * context's stream between two HIP events, and return the average duration of one launch
  * in microseconds.  Activations are whatever the workspace holds; caches, token history and
  * scheduler state are not modified (the residual stream scratch is).  kind: DMTD_K_*.
+ * A kernel runs as in a decode step with that many rows at the current context: where the O projection merges the
+ * attention's key ranges, its time holds the merge and the attention's does not.  QKV and the LM head read one partial sum
+ * of squares per row, as behind the embedding (behind a layer's down projection there are up to hidden / 16).
  * Needs a prefilled context (attention reads the current context length).
  * Errors: DMTD_EINVAL (kind, rows outside [1, 16] for attention (rows per sequence) or [1, 16 * max_batch] for the projections (total rows), reps < 1), DMTD_ESTATE, DMTD_EHIP. */
 #define DMTD_K_QKV     0   /* RMSNorm + fused QKV projection (Sec. 3.1 model; hot-path step a2) */

@@ -731,6 +731,30 @@ void launch_attention_t(dmtd_ctx* c, int l, const float* qkv, OT* attn, OT* attn
                      cf.n_q_heads, cf.n_kv_heads, kps, ns, c->part_rows * gq, st, sel, offset, r, c->fmap, blocked_rows(c, B * r));
 }
 
+// Key ranges of a launch with r rows per sequence that is not in one range: keys per range (whole iterations of 64 keys) and ranges
+struct AttRanges { int kps, ns; };
+AttRanges attention_ranges(const dmtd_ctx* c, int r) {
+  const dmtd_config& cf = c->cfg;
+  const int gq = cf.n_q_heads / cf.n_kv_heads, rpb = 16 / gq, n_rg = (r + rpb - 1) / rpb;
+  const long per_split_blocks = (long)cf.n_kv_heads * c->batch * n_rg;
+  int want_splits = (int)((4L * c->num_cus + per_split_blocks - 1) / per_split_blocks);
+  if (want_splits > ATT_MAX_SPLITS) want_splits = ATT_MAX_SPLITS;
+  if (want_splits < 1) want_splits = 1;
+  AttRanges a;
+  a.kps = ((c->att_bucket + want_splits - 1) / want_splits + 63) / 64 * 64;
+  a.ns = (c->att_bucket + a.kps - 1) / a.kps;
+  return a;
+}
+// Few partial results: the O projection's blocks merge them on the way in (it has to be the one-tile-per-block kernel)
+bool oproj_merges(const dmtd_ctx* c, int r, const AttRanges& ar) {
+  const int qd = c->cfg.n_q_heads * c->cfg.head_dim, rows = c->batch * r;
+  return DMTD_O_NW > 0 && ar.ns <= kMergeRanges && (size_t)rows * qd * ar.ns * 4 <= kMergeBytes && mfma_rows_fit(c, rows, c->cfg.hidden, qd, 0);
+}
+MergeSrc merge_source(dmtd_ctx* c, int r, const AttRanges& ar, int sel, int offset) {
+  const int gq = c->cfg.n_q_heads / c->cfg.n_kv_heads;
+  return MergeSrc{c->part_o, c->part_ml, dev_state(c), c->fmap, ar.kps, ar.ns, c->part_rows * gq, ATT_MAX_SPLITS, c->cfg.n_kv_heads, gq, c->cfg.head_dim, sel, offset, r};
+}
+
 // The matrix-core kernel (bf16 caches): one pass over K and V serves up to 16 query vectors per KV head.
 // Two launch shapes.  (1) ONE key range per (row group, KV head, sequence), 8 waves per block, the output written
 // by the kernel itself (no partials, no merge launch): for batches whose (KV head, sequence) pairs fill the chip
@@ -745,8 +769,6 @@ hipError_t launch_attention_mfma_t(dmtd_ctx* c, int l, const float* qkv, OT* att
   bf16_t* kc = (bf16_t*)(c->ws + c->o.kv + (size_t)l * c->o.kv_layer_stride);
   bf16_t* vc = (bf16_t*)(c->ws + c->o.kv + (size_t)l * c->o.kv_layer_stride + c->o.kv_v_off);
   const LayerW& w = c->layers[l];
-  const int bucket = c->att_bucket;
-  long per_split_blocks = (long)cf.n_kv_heads * B * n_rg;
   float* po = c->part_o;
   float* pml = c->part_ml;
   const DevState* st = dev_state(c);
@@ -755,7 +777,7 @@ hipError_t launch_attention_mfma_t(dmtd_ctx* c, int l, const float* qkv, OT* att
   qs.qkv = qkv; qs.ldq = nqkv;
   if (attention_single_range(c, r)) {
     constexpr int NW = 8;
-    const int kps = (bucket + 16 * NW - 1) / (16 * NW) * (16 * NW);
+    const int kps = (c->att_bucket + 16 * NW - 1) / (16 * NW) * (16 * NW);
     const size_t lds = (size_t)NW * qv_max * HD * 4;
     auto kern = attn_split_mfma_kernel<HD, NW, true>;
     static bool big_lds = false;
@@ -770,19 +792,14 @@ hipError_t launch_attention_mfma_t(dmtd_ctx* c, int l, const float* qkv, OT* att
                        (bf16_t*)attn, (bf16_t*)attn_lo, qd, blocked_rows(c, B * r), qs);
     return hipGetLastError();
   }
-  constexpr int KPI = 64;
-  int want_splits = (int)((4L * c->num_cus + per_split_blocks - 1) / per_split_blocks);
-  if (want_splits > ATT_MAX_SPLITS) want_splits = ATT_MAX_SPLITS;
-  if (want_splits < 1) want_splits = 1;
-  int kps = ((bucket + want_splits - 1) / want_splits + KPI - 1) / KPI * KPI;
-  const int ns = (bucket + kps - 1) / kps;
+  const AttRanges ar = attention_ranges(c, r);
+  const int kps = ar.kps, ns = ar.ns;
   hipLaunchKernelGGL((attn_split_mfma_kernel<HD, 4, false>), dim3(ns * n_rg, cf.n_kv_heads, B), dim3(256), (size_t)4 * qv_max * HD * 4, c->stream,
                      kc, vc, cf.n_q_heads, cf.n_kv_heads, cf.max_seq_len, kps, r, c->fmap, st, sel, offset, ns, w.q_norm,
                      w.k_norm, (const float2*)(c->ws + c->o.rope_tab), po, pml, cf.rms_eps, c->part_rows * gq, append,
                      (bf16_t*)nullptr, (bf16_t*)nullptr, 0, 0, qs);
-  // Few partial results: the O projection's blocks merge them on the way in (it has to be the one-tile-per-block kernel)
-  if (DMTD_O_NW > 0 && c->fold_merge && ns <= kMergeRanges && (size_t)B * r * qd * ns * 4 <= kMergeBytes && mfma_rows_fit(c, B * r, cf.hidden, qd, 0)) {
-    c->merge_pending = MergeSrc{po, pml, st, c->fmap, kps, ns, c->part_rows * gq, ATT_MAX_SPLITS, cf.n_kv_heads, gq, HD, sel, offset, r};
+  if (c->fold_merge && oproj_merges(c, r, ar)) {
+    c->merge_pending = merge_source(c, r, ar, sel, offset);
     return hipGetLastError();
   }
   hipLaunchKernelGGL((attn_merge_kernel<HD, OT>), dim3(r, cf.n_q_heads, B), dim3(256), 0, c->stream, po, pml, attn, attn_lo, qd,
@@ -1388,7 +1405,13 @@ hipError_t time_one(dmtd_ctx* c, int kind, int l, int rows) {
     const int r = rows <= last + 1 ? rows : 1;
     // the cache append is switched off: the launch scores the rows' new keys from the scratch q/k/v, writes nothing
     choose_attention(c, last + 1);
-    if (c->packed) return launch_attention<bf16_t, bf16_t>(c, l, qkv, (bf16_t*)(c->ws + c->o.attn), (bf16_t*)(c->ws + c->o.attn) + (size_t)row_capacity(cf, c->wide_rows) * cf.n_q_heads * cf.head_dim, (int)POS_EXPLICIT, last - r + 1, r, 0);
+    if (c->packed) {
+      c->fold_merge = true;      // as in a step: no merge launch where the O projection merges
+      const hipError_t e = launch_attention<bf16_t, bf16_t>(c, l, qkv, (bf16_t*)(c->ws + c->o.attn), (bf16_t*)(c->ws + c->o.attn) + (size_t)row_capacity(cf, c->wide_rows) * cf.n_q_heads * cf.head_dim, (int)POS_EXPLICIT, last - r + 1, r, 0);
+      c->fold_merge = false;
+      c->merge_pending = MergeSrc{};
+      return e;
+    }
     return launch_attention<float, float>(c, l, qkv, (float*)(c->ws + c->o.attn), (float*)nullptr, (int)POS_EXPLICIT, last - r + 1, r, 0);
   }
   if (kind == DMTD_K_LMHEAD) {
@@ -1411,9 +1434,14 @@ hipError_t time_one(dmtd_ctx* c, int kind, int l, int rows) {
       case DMTD_K_OPROJ:
         a.W = s.o; a.xb = ab; a.xb_lo = ab_lo; a.ldxb = qd; a.N = d; a.K = qd; a.y = R.h; a.ldy = d; a.yb = R.xb; a.yb_lo = R.xb_lo; a.ldyb = d;
         a.g_next = (const bf16_t*)w.mlp_norm; a.ssp_next = R.ssp;
+        if (const int r = rows / c->batch, last = c->sched.n_tok - 1; r * c->batch == rows && r <= kMaxRows && r <= last + 1) {
+          choose_attention(c, last + 1);
+          if (const AttRanges ar = attention_ranges(c, r); !attention_single_range(c, r) && oproj_merges(c, r, ar))
+            c->merge_pending = merge_source(c, r, ar, (int)POS_EXPLICIT, last - r + 1);
+        }
         return launch_oproj(c, a, rows);
       case DMTD_K_GATEUP:
-        a.W = s.gate; a.W2 = s.up; a.xb = R.xb; a.xb_lo = R.xb_lo; a.ldxb = d; a.N = ff; a.K = d; a.ssp = R.ssp; a.n_parts = (d + 15) / 16;
+        a.W = s.gate; a.W2 = s.up; a.xb = R.xb; a.xb_lo = R.xb_lo; a.ldxb = d; a.N = ff; a.K = d; a.ssp = R.ssp; a.n_parts = c->resid_parts;
         a.yb = ub; a.yb_lo = ub_lo; a.ldyb = ff;
         return launch_gateup(c, a, rows);
       default:
@@ -2070,7 +2098,7 @@ int dmtd_read_kv(dmtd_ctx* c, int32_t layer, int32_t b, int32_t n_pos, float* ou
 
 int dmtd_time_kernel(dmtd_ctx* c, int32_t kind, int32_t rows, int32_t reps, float* avg_us) {
   if (!c) return DMTD_EINVAL;
-  // attention: rows per sequence (at most 16); projections: total activation rows (at most max_batch * 16, the row buffers' capacity)
+  // attention: rows per sequence (at most 16); projections: total activation rows, at most what a decode step may carry
   const int rows_max = kind == DMTD_K_ATTN ? kMaxRows : step_row_capacity(c->cfg.max_batch);
   if (!avg_us || kind < 0 || kind > DMTD_K_READ_DOWN || rows < 1 || rows > rows_max || reps < 1) {
     c->err = "bad argument to dmtd_time_kernel"; return DMTD_EINVAL;
@@ -2085,6 +2113,11 @@ int dmtd_time_kernel(dmtd_ctx* c, int32_t kind, int32_t rows, int32_t reps, floa
   const int saved_batch = c->batch;
   long launches = 0;
   hipError_t e = hipSuccess;
+  // what a step launches before the kernel leaves something that kernel reads: the attention's partial results, and the partial sums
+  // of squares of the O projection (their number depends on its route)
+  if (c->packed && (kind == DMTD_K_OPROJ || kind == DMTD_K_GATEUP) && rows % c->batch == 0 && rows / c->batch <= kMaxRows)
+    e = time_one(c, DMTD_K_ATTN, 0, rows / c->batch);
+  if (c->packed && kind == DMTD_K_GATEUP && e == hipSuccess) e = time_one(c, DMTD_K_OPROJ, 0, rows);
   for (int pass = 0; pass < 2 && e == hipSuccess; ++pass) {   // pass 0 warms up (one repetition)
     const int n = pass == 0 ? 1 : reps;
     if (pass == 1) e = hipEventRecord(e0, c->stream);
