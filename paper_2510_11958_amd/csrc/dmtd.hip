@@ -320,6 +320,10 @@ Ws layout(const dmtd_config& c, int wide = kWideRows) {
     w.xb_late = take(late_row_capacity(c) * d * 2 * 2);
     w.ssp = take(parts * rows * 4);
     w.ssp_late = take(parts * rows * 4);
+    // The weight image starts 1 KiB off a multiple of 2 (of the workspace, which torch puts on far larger ones).  Gate/up, us, by the
+    // start modulo 2 KiB, 0 / 256 / 512 / 1024 / 1536: 2560 wide, 1 row 17.97 / 17.78 / 17.72 / 17.65 / 17.88, 3 rows 18.74 /
+    // 18.48 / 18.45 / 18.30 / 18.59; the other projections and widths differ by less than their spread.
+    off = (off + 1024 + 2047) / 2048 * 2048 - 1024;
     w.wsw = take((swizzled_layer_elems(c) * c.n_layers + swizzled_elems(c.vocab, d)) * 2);
   }
   w.total = off;

@@ -346,3 +346,20 @@ def test_per_sequence_cycle_lengths_schedule_like_one_oracle_per_sequence():
     with pytest.raises(pkg.DmtdError) as e:
         eng.decode_per_seq([20, 2, 2], n_late, 1)
     assert e.value.code == pkg.DMTD_ECAPACITY
+
+
+def test_weight_image_starts_1_kib_off_a_multiple_of_2():
+    """Where the repacked weights start decides 2 % of gate/up's time; what else the workspace holds must not move them onto the slow
+    places.  The image is the workspace's last part, and a multiple of 2 KiB long."""
+    lib = pkg.load_library()
+
+    def image(n, k):
+        return (n + 15) // 16 * 16 * k * 2
+
+    for L, d, h, k, hd, ff, vocab, batch, seq in ((36, 2560, 32, 8, 128, 9728, 151936, 1, 1600), (4, 2560, 32, 8, 128, 9728, 151936, 16, 600),
+                                                  (28, 1024, 16, 8, 128, 3072, 151936, 1, 512), (2, 64, 2, 1, 64, 128, 201, 200, 20),
+                                                  (3, 896, 14, 2, 64, 4864, 1000, 3, 77), (2, 1536, 12, 2, 128, 8960, 30000, 8, 16384)):
+        cfg = pkg.ModelConfig(L, d, h, k, hd, ff, vocab, max_batch=batch, max_seq_len=seq)
+        layer = image((h + 2 * k) * hd, d) + image(d, h * hd) + 2 * image(ff, d) + image(d, ff)
+        start = lib.dmtd_workspace_bytes(C.byref(cfg.to_c())) - (layer * L + image(vocab, d))
+        assert start % 2048 == 1024, (cfg, start % 2048)
