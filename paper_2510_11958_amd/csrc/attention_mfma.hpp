@@ -21,7 +21,9 @@
 //            the lane loaded those 8 consecutive d of each key with one 16-byte load), for each e; accumulator e of lane
 //            (sl, kq) holds O[4 kq + j][8 sl + e], j = 0..3.  A probability goes in as three bf16 parts that add up to
 //            all 24 bits of it (V is bf16), 24 MFMAs of 16 cycles per 16 keys; the fp32 matrix instruction
-//            (16x16x4, a quarter of the keys in twice the time) took 1024 cycles for the same sums.
+//            (16x16x4, a quarter of the keys in twice the time) took 1024 cycles for the same sums.  An infinite value of V
+//            gives NaN here (0 * inf in the lower parts) where the fp32 instruction gave infinity; the two bf16 planes of the
+//            output, whose low part is then inf - inf, made NaN of it for the O projection all the same.
 // Nothing moves between lanes except the maxima and the per-query rescale factors.
 #pragma once
 #include "attention.hpp"

@@ -20,9 +20,11 @@
 // the dim): fragment reads of both spread over all banks.  Two buffers of each; the next tile's loads fly during a tile.
 // What bounds it: the matrix cores (40 MFMAs of 32 cycles per 32 keys and wave at HD = 128) with the softmax and the
 // three-way split (about as many vector cycles) beside them in the other resident block's waves.
-// Against the decode kernel (attention_mfma.hpp, one pass over K and V per 16 query vectors, fp32 matrix instructions for
-// P.V), 32/8 heads of 128: a prompt of 8192 in passes of 2048 rows, 2 layers: the whole pass 18.0 -> 10.3 ms; 32 prompts of 2048 in
-// passes of 64 rows: 423 -> 99 us per launch; one prompt of 1003: 125 -> 54 us; 2048 rows against 2k-8k keys: 1330 -> 349 us (1.2 PFLOP/s).
+// Against the decode kernel (attention_mfma.hpp, one pass over K and V per 16 query vectors, the same products) on the same passes,
+// 32/8 heads of 128, us per launch: one prompt of 1003 111 -> 52; 2048 rows against 2k to 8k keys 1044 -> 322 (the prompt of
+// 8192, 2 layers: 14.5 -> 8.8 ms); 32 prompts of 2048 in passes of 64 rows 386 -> 90; one prompt of 400 33 -> 28.
+// A value that is not finite (an overflowed cache entry) makes NaN of every row of its block that sees its tile, also of the up to
+// 128 / GQ - 1 rows before its own position, whose probability for it is 0; in the decode kernel it is the up to 16 / GQ - 1 before it.
 #pragma once
 #include "attention_mfma.hpp"
 #include "gemm_wide.hpp"

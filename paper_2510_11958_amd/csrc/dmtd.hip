@@ -33,8 +33,9 @@ constexpr int kGemvRows = 4;         // activation rows per FMA weight-streaming
 constexpr int kMaxRows = 16;         // rows per sequence one pass through the layers may carry
 constexpr int kPassRows = 128;       // activation rows (all sequences together) a prefill or whole-sequence pass of an fp32 model carries
 // The same for a bf16 model.  Its wide GEMM (gemm_wide.hpp) is bound by the matrix cores, so a pass should fill the chip with
-// its tiles of 128 x 256 whatever the projection: 2048 rows give gate/up 1216 tiles and QKV 384 at 4B shapes for 256 CUs.
-// The activation buffers of such a pass take 0.2 GB at 4B shapes.
+// its tiles whatever the projection: 2048 rows give gate/up 608 tiles of 256 x 256 at 4B shapes, QKV 192 and O and down 80 (their K is
+// split over the 256 CUs).  The activation buffers of such a pass and 512 rows of logits make a 4B context of one sequence 137 MB
+// larger than passes of 128 rows did; with less workspace the passes are shorter.
 constexpr int kWideRows = 2048;
 constexpr int kHeadRows = 512;       // rows of a whole-sequence pass whose logits are held at a time (0.3 GB at a 152k vocabulary)
 // Up to this many rows go through the LDS-tiled kernel in passes, more through the wide GEMM (all four projections of a layer at
@@ -158,7 +159,9 @@ struct Ws {   // device workspace carve-up (byte offsets)
   size_t patterns;
   size_t sample_count, sample_list, sample_best;   // sampled steps: per sequence the list of entries that may stay in, and the slices' best draws
   size_t pend_enc, enc_tmp;                    // ExDy: stored encoding outputs of pending tokens; of a prefill chunk
-  size_t mask, logits_rows, amax_rows, nll, best, loss;   // whole-sequence masked forward: mask, a chunk's logits and keys, per-position results
+  // whole-sequence masked forward: mask, a chunk's logits, the LM head's selection keys for them (written by its kernels, read by
+  // nobody: nll_rows_kernel finds the best entry of a row itself), per-position results
+  size_t mask, logits_rows, amax_rows, nll, best, loss;
   size_t total;
 };
 
@@ -811,7 +814,8 @@ hipError_t launch_attention_mfma_t(dmtd_ctx* c, int l, const float* qkv, OT* att
   return hipGetLastError();
 }
 
-// Passes with more than kMaxRows rows per sequence, whose keys and values are in the cache (append = 2).
+// Passes whose keys and values are in the cache already (append = 2: more than kMaxRows rows per sequence), with so many rows
+// that launch_attention sends them here.
 template <int HD>
 hipError_t launch_attention_prefill(dmtd_ctx* c, int l, const float* qkv, bf16_t* attn, bf16_t* attn_lo, int sel, int offset, int r) {
   const dmtd_config& cf = c->cfg;

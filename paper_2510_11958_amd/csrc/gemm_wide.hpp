@@ -9,8 +9,8 @@
 // contiguous bytes per 16 lanes (no bank conflicts).  A ring of three LDS buffers (144 KiB, one block per CU): a step is
 // waited for by the exact count of its loads while the next one's are in flight, and requests the one after that behind
 // its first fragment reads.
-// What bounds it: per step and CU 2048 cycles of MFMAs per SIMD against 1400 cycles of LDS traffic (128 KiB of fragments, 48 KiB
-// of arriving pieces) that overlap only in part.  Measured without epilogue, 2048 rows, cold weights (us, both planes), this
+// What bounds it: per step and CU 2048 cycles of MFMAs per SIMD (32 of 32 cycles for each of its two waves) against 1400 cycles of LDS
+// traffic (128 KiB of fragments and 48 KiB of arriving pieces at 128 bytes a cycle) that overlap only in part.  Measured without epilogue, 2048 rows, cold weights (us, both planes), this
 // tile / 128 x 256 with 8 waves of 64 x 64 and two blocks per CU: 192 tiles of 6144 x 2560 118 / 127, 608 tiles of
 // 19456 x 2560 370 / 348 where the last of three rounds is 38 % full (hence the split of the last round's tiles, see the
 // launcher); other shapes and orders at 19456 x 2560: 4 waves of 128 x 128 472, waves of 128 x 64 384, fragments read half a
@@ -20,6 +20,10 @@
 // Tiles of 128 rows (waves of 64 x 64, a ring of four buffers, 0.8 instead of 1.25 us per step) where they pad a launch's rows less.
 // Against passes of 128 rows through gemm_mfma.hpp (4B shapes, 2048 rows, us with the finishing launch, before / now):
 // gate/up 660 / 357, QKV 390 / 125, down + O 763 / 297.
+// A tile that takes its whole K in one block sums it in one fp32 chain, a rounding per 8 products: 4.4e-7 of the result's norm at K = 2560
+// in two planes, where five parts summed apart (what gemm_mfma.hpp does with 128 rows) leave 2.0e-7.  3.2e-4 instead of 2.3e-4 of
+// the cached values then round the other way in bf16.  Each step summed by itself and added to the chain makes it 1.5e-7, and
+// costs 3 to 8 % of a pass at 1024 wide and 11 to 26 % at 2560 (128 additions a step beside 32 MFMAs, and registers): not taken.
 #pragma once
 #include "gemm_mfma.hpp"
 
