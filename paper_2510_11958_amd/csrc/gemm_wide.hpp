@@ -20,10 +20,12 @@
 // Tiles of 128 rows (waves of 64 x 64, a ring of four buffers, 0.8 instead of 1.25 us per step) where they pad a launch's rows less.
 // Against passes of 128 rows through gemm_mfma.hpp (4B shapes, 2048 rows, us with the finishing launch, before / now):
 // gate/up 660 / 357, QKV 390 / 125, down + O 763 / 297.
-// A tile that takes its whole K in one block sums it in one fp32 chain, a rounding per 8 products: 4.4e-7 of the result's norm at K = 2560
-// in two planes, where five parts summed apart (what gemm_mfma.hpp does with 128 rows) leave 2.0e-7.  3.2e-4 instead of 2.3e-4 of
-// the cached values then round the other way in bf16.  Each step summed by itself and added to the chain makes it 1.5e-7, and
-// costs 3 to 8 % of a pass at 1024 wide and 11 to 26 % at 2560 (128 additions a step beside 32 MFMAs, and registers): not taken.
+// Sums: a tile that takes its whole K in one block sums it in one fp32 chain, a rounding per 8 products, 4.4e-7 of the result's norm at
+// K = 2560 in two planes; five parts summed apart (gemm_mfma.hpp with 128 rows) leave 2.0e-7.  In the QKV projection, whose K
+// and V are then rounded to bf16, that decides roundings (STEP_SUMS below): each k-step of 32 is summed by itself and added to the
+// chain, 1.5e-7.  Logits of a prompt of 1003, 2560 wide, against 64 bits with the cache's rounding taken along, 1 / 2 layers:
+// chain 8.5e-5 / 1.15e-4, steps 5.2e-5 / 7.5e-5, 128-row parts 5.2e-5 / 7.5e-5.  It costs 128 additions a step beside 32 MFMAs:
+// 1 to 2 % of a pass; in all projections 9 to 10 % at 2560 wide, for no smaller an error.
 #pragma once
 #include "gemm_mfma.hpp"
 
@@ -148,14 +150,21 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
     if (TR == 4) ss += __shfl_xor(ss, 2, 64);
     if (tid % TR == 0) rs_s[tid / TR] = rsqrtf(ss / (float)K + a.eps);
   }
+  // Results that are rounded to 16 bits afterwards (QKV: the cache): a k-step's products are summed by themselves and added to the
+  // chain once, not in its roundings of 8 products at a time
+  constexpr bool STEP_SUMS = EPI == EPI_STORE;
+  auto chunk = [](const bf16_t* q) { return __builtin_bit_cast(bf16x8_t, *(const u32x4*)q); };
+  auto mma = [](bf16x8_t wv, bf16x8_t xv, const f32x16& c) {
+    return WA ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, xv, c, 0, 0, 0) : __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv, wv, c, 0, 0, 0);
+  };
   struct Frag { bf16x8_t xl[2], xh[2], wf[NJ]; };
   auto read = [&](Frag& f, const bf16_t* base, int c) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) f.xl[i] = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(base + (16 + T::XT + (2 * wm + i) * 2) * 512 + c * 256));
+    for (int i = 0; i < 2; ++i) f.xl[i] = chunk(base + (16 + T::XT + (2 * wm + i) * 2) * 512 + c * 256);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) f.wf[j] = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(base + wtile(j) * 1024 + c * 256));
+    for (int j = 0; j < NJ; ++j) f.wf[j] = chunk(base + wtile(j) * 1024 + c * 256);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) f.xh[i] = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(base + (16 + (2 * wm + i) * 2) * 512 + c * 256));
+    for (int i = 0; i < 2; ++i) f.xh[i] = chunk(base + (16 + (2 * wm + i) * 2) * 512 + c * 256);
   };
   auto mul = [&](const Frag& f) {
 #pragma unroll
@@ -163,11 +172,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          const bf16x8_t x = p ? f.xh[i] : f.xl[i];
-          acc[i][j] = WA ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.wf[j], x, acc[i][j], 0, 0, 0)
-                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, f.wf[j], acc[i][j], 0, 0, 0);
-        }
+        for (int i = 0; i < 2; ++i) acc[i][j] = mma(f.wf[j], p ? f.xh[i] : f.xl[i], acc[i][j]);
   };
   int buf = 0, nxt = T::BUF - 1;
   for (int s = s_lo; s < s_hi; ++s) {
@@ -180,18 +185,56 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");         // no LDS read of the slice moves above the barrier
     const bf16_t* base = ring + buf * T::STAGE + frag;
-    Frag f0, f1;
-    read(f0, base, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    if (s + T::BUF - 1 < s_hi) issue(nxt);
-    read(f1, base, 1);
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (STEP_SUMS) {
+      bf16x8_t xf[2][2][2];                // [low, high part][half of the step][row tile]
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int i = 0; i < 2; ++i) xf[p][c][i] = chunk(base + (16 + (1 - p) * T::XT + (2 * wm + i) * 2) * 512 + c * 256);
+      bf16x8_t w0 = chunk(base + wtile(0) * 1024), w1 = chunk(base + wtile(0) * 1024 + 256);
+      __builtin_amdgcn_sched_barrier(0);
+      if (s + T::BUF - 1 < s_hi) issue(nxt);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {       // the next tile's weights are read while this one's products run
+        const bf16_t* wn = base + wtile(j + 1 < NJ ? j + 1 : j) * 1024;
+        const bf16x8_t n0 = chunk(wn), n1 = chunk(wn + 256);
+        f32x16 t[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          f32x16 z;
+#pragma unroll
+          for (int e = 0; e < 16; ++e) z[e] = 0.f;
+          t[i] = mma(w0, xf[0][0][i], z);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) t[i] = mma(w1, xf[0][1][i], t[i]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) t[i] = mma(w0, xf[1][0][i], t[i]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) t[i] = mma(w1, xf[1][1][i], t[i]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) acc[i][j][e] += t[i][e];
+        w0 = n0; w1 = n1;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
+      Frag f0, f1;
+      read(f0, base, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (s + T::BUF - 1 < s_hi) issue(nxt);
+      read(f1, base, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(f0);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(f1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     buf = buf + 1 == T::BUF ? 0 : buf + 1;
     nxt = nxt + 1 == T::BUF ? 0 : nxt + 1;
-    mul(f0);
-    __builtin_amdgcn_sched_barrier(0);
-    mul(f1);
-    __builtin_amdgcn_sched_barrier(0);
   }
 
   // lane (column n = lane % 32 of a weight tile): element e of acc[i][j] is row 32 i + 8 (e / 4) + 4 (lane / 32) + e % 4 of the wave
