@@ -23,8 +23,9 @@
 // Against the decode kernel (attention_mfma.hpp, one pass over K and V per 16 query vectors, the same products) on the same passes,
 // 32/8 heads of 128, us per launch: one prompt of 1003 111 -> 52; 2048 rows against 2k to 8k keys 1044 -> 322 (the prompt of
 // 8192, 2 layers: 14.5 -> 8.8 ms); 32 prompts of 2048 in passes of 64 rows 386 -> 90; one prompt of 400 33 -> 28.
-// A value that is not finite (an overflowed cache entry) makes NaN of every row of its block that sees its tile, also of the up to
-// 128 / GQ - 1 rows before its own position, whose probability for it is 0; in the decode kernel it is the up to 16 / GQ - 1 before it.
+// The product runs over a whole tile with probability 0 for the keys a row does not see, and 0 * inf is NaN: in the tiles on the
+// diagonal values that are not finite go into LDS as 0, and the rows at or behind the first of them come out as NaN, which their
+// own products would give; the rows before it are as if it were not there.
 #pragma once
 #include "attention_mfma.hpp"
 #include "gemm_wide.hpp"
@@ -48,6 +49,7 @@ __global__ void __launch_bounds__(256 * KG, 2) attn_prefill_mfma_kernel(
   typedef unsigned int vraw_t __attribute__((ext_vector_type(DV / 2)));
   constexpr int TILE = AP_KT * HD;     // elements of a K or V tile
   extern __shared__ float4 attn_dyn_smem[];
+  __shared__ int poison_s;             // first key of the tiles on the diagonal with a value that is not finite
   const int tid = threadIdx.x, lane = tid & 63;
   const int w8 = __builtin_amdgcn_readfirstlane(tid >> 6), w = w8 & 3, kg = KG == 2 ? w8 >> 2 : 0;      // wave of its group; group (tiles of that parity)
   bf16_t* ring = (bf16_t*)attn_dyn_smem + kg * 4 * TILE;                // the group's buffers: K, K, V^T, V^T
@@ -86,7 +88,34 @@ __global__ void __launch_bounds__(256 * KG, 2) attn_prefill_mfma_kernel(
     for (int m = 0; m < 4; ++m)
       vr[m] = *(const vraw_t*)(vc + (uint32_t)(min(base + 4 * (ln & 15) + m, key_end - 1) * HD + (w * 4 + (ln >> 4)) * DV));
   };
-  auto store_v = [&](int buf) {
+  auto drop_bad = [&](int base) {       // seldom: values that are not finite become 0, their first key is noted
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+#pragma unroll 1
+    for (int m = 0; m < 4; ++m) {
+      bool bad = false;
+#pragma unroll
+      for (int mm = 0; mm < 4; ++mm)
+        if (mm == m)
+#pragma unroll
+          for (int u = 0; u < DV / 2; ++u) {
+            const bool b0 = (vr[mm][u] & 0x7F80u) == 0x7F80u, b1 = (vr[mm][u] & 0x7F800000u) == 0x7F800000u;
+            vr[mm][u] = (b0 ? 0u : vr[mm][u] & 0xFFFFu) | (b1 ? 0u : vr[mm][u] & 0xFFFF0000u);
+            bad |= b0 || b1;
+          }
+      if (bad) atomicMin(&poison_s, min(base + 4 * (ln & 15) + m, key_end - 1));
+    }
+  };
+  auto store_v = [&](int base, int buf) {
+    if (base + AP_KT > pos0 + 1) {      // a tile with keys that some row does not see (uniform over the group)
+      // the largest exponent field among the thread's values (2 in a register); 255: one of them is not finite
+      unsigned int top = 0u;
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int u = 0; u < DV / 2; ++u) top = max(top, max(vr[m][u] & 0x7F80u, (vr[m][u] >> 16) & 0x7F80u));
+      if (__any(top == 0x7F80u)) drop_bad(base);
+    }
 #pragma unroll
     for (int u = 0; u < DV / 2; ++u) {
 #pragma unroll
@@ -100,6 +129,7 @@ __global__ void __launch_bounds__(256 * KG, 2) attn_prefill_mfma_kernel(
   };
   const int n_tiles = (key_end + AP_KT - 1) / AP_KT;
   if (kg < n_tiles) { load_k(kg * AP_KT, 0); load_v(kg * AP_KT); }
+  if (tid == 0) poison_s = 0x7FFFFFFF;
 
   // the lane's query vector: dims 16 t + 8 hi + 0..7; its rotary partner dims (i, i + HD/2) are the lane's own
   bf16x8_t qh[T], ql[T];
@@ -152,7 +182,10 @@ __global__ void __launch_bounds__(256 * KG, 2) attn_prefill_mfma_kernel(
   for (int t = 0; t < DT; ++t)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
-  if (kg < n_tiles) store_v(0);
+  __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0): poison_s is set before a wave adds to it; the loads stay in flight
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  if (kg < n_tiles) store_v(kg * AP_KT, 0);
   __builtin_amdgcn_s_waitcnt(7 << 4);      // vmcnt(0) lgkmcnt(0): this wave's share of K has landed too
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
@@ -238,7 +271,7 @@ __global__ void __launch_bounds__(256 * KG, 2) attn_prefill_mfma_kernel(
       }
     }
     }
-    if (more) store_v(buf ^ 1);
+    if (more) store_v(base + KG * AP_KT, buf ^ 1);
     __builtin_amdgcn_s_waitcnt(7 << 4);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -272,7 +305,7 @@ __global__ void __launch_bounds__(256 * KG, 2) attn_prefill_mfma_kernel(
   asm volatile("" : "+v"(ln));
   const int qo = 32 * w + (ln & 31), ro = qo / GQ;
   if (qo >= rows * GQ) return;
-  const float inv_l = 1.0f / l_run;
+  const float inv_l = my_pos >= poison_s ? __uint_as_float(0x7FC00000u) : 1.0f / l_run;
   const size_t at0 = packed_at(blocked, b * r_total + row0 + ro, (g * GQ + qo - ro * GQ) * HD + 4 * (ln >> 5), ldo);
   const int t_step = blocked ? 512 : 32, q_step = blocked ? 128 : 8;        // 32 and 8 dims further
 #pragma unroll

@@ -121,3 +121,28 @@ def test_few_cached_values_round_the_other_way():
         share = float((got[which] != want).mean())
         print(("keys", "values")[which], f"{share:.2e}")
         assert share < 2.6e-4, (which, share)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,at", [("vectors_8224_hd128_gq4", 40), ("vectors_8224_hd128_gq4", 95), ("vectors_9600_hd64_gq1", 100),
+                                     ("vectors_19200_hd64_gq8", 13), ("vectors_38400_hd64_gq8", 41), ("vectors_8106_hd64_gq7", 192)])
+def test_a_value_that_is_not_finite_stays_behind_its_position(name, at):
+    """Passes through the prefill attention, one token's embedding NaN (the LM head is a table of its own): its row and the later ones,
+    which see it, are NaN, the rows before it are bit for bit those of the same sequence with another token there."""
+    sh, batch, n = CASES[name]
+    sh = S(sh.n_layers, sh.hidden, sh.n_q_heads, sh.n_kv_heads, sh.head_dim, sh.intermediate, sh.vocab, tied_embeddings=False)
+    blob = di.make_weight_blob(sh, seed=31, std=0.04, gain_sigma=0.2)
+    bad, good = 7, 8
+    blob[bad * sh.hidden:(bad + 1) * sh.hidden] = 0x7FC0
+    toks = di.make_prompts(sh.vocab, batch, n, seed=5)
+    toks[toks == bad] = good
+    eng = pkg.Engine(engine_config(sh, n + 2, batch), blob)
+    mask = np.ones(n, np.uint8)
+    clean = eng.masked_forward(toks, mask, 1, want_logits=True)["logits"]
+    assert np.isfinite(clean).all()
+    broken = toks.copy()
+    broken[-1, at] = bad
+    got = eng.masked_forward(broken, mask, 1, want_logits=True)["logits"]
+    assert np.array_equal(got[:-1], clean[:-1])
+    assert np.array_equal(got[-1, :at], clean[-1, :at])
+    assert np.isnan(got[-1, at:]).all()
