@@ -23,9 +23,9 @@
 // Against the decode kernel (attention_mfma.hpp, one pass over K and V per 16 query vectors, the same products) on the same passes,
 // 32/8 heads of 128, us per launch: one prompt of 1003 111 -> 52; 2048 rows against 2k to 8k keys 1044 -> 322 (the prompt of
 // 8192, 2 layers: 14.5 -> 8.8 ms); 32 prompts of 2048 in passes of 64 rows 386 -> 90; one prompt of 400 33 -> 28.
-// The product runs over a whole tile with probability 0 for the keys a row does not see, and 0 * inf is NaN: in the tiles on the
-// diagonal values that are not finite go into LDS as 0, and the rows at or behind the first of them come out as NaN, which their
-// own products would give; the rows before it are as if it were not there.
+// The product runs over a whole tile with probability 0 for the keys a row does not see, and 0 * inf is NaN.  So a block looks at the
+// values of its own rows' positions first; if one is not finite, it and its like behind it go into LDS as 0, and the rows at or
+// behind the first of them come out as NaN, which their own products would give; the rows before it are as if it were not there.
 #pragma once
 #include "attention_mfma.hpp"
 #include "gemm_wide.hpp"
@@ -37,7 +37,7 @@ constexpr size_t attn_prefill_lds(int hd, int kg) { return (size_t)kg * 4 * 64 *
 constexpr int AP_QV = 128, AP_KT = 64;       // query vectors of a block, keys of a tile
 
 template <int HD, int KG>
-__global__ void __launch_bounds__(256 * KG, 2) attn_prefill_mfma_kernel(
+__global__ void __launch_bounds__(256 * KG, HD == 64 && KG == 1 ? 3 : 2) attn_prefill_mfma_kernel(
     const float* __restrict__ qkv, int ldq, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc, int nh, int nkv, int s_max,
     int r_total, const DevState* st, int sel, int offset, const bf16_t* __restrict__ q_gain, const float2* __restrict__ rope_tab,
     float eps, bf16_t* __restrict__ out, bf16_t* __restrict__ out_lo, int ldo, int blocked) {
@@ -49,7 +49,7 @@ __global__ void __launch_bounds__(256 * KG, 2) attn_prefill_mfma_kernel(
   typedef unsigned int vraw_t __attribute__((ext_vector_type(DV / 2)));
   constexpr int TILE = AP_KT * HD;     // elements of a K or V tile
   extern __shared__ float4 attn_dyn_smem[];
-  __shared__ int poison_s;             // first key of the tiles on the diagonal with a value that is not finite
+  __shared__ int poison_s;             // first of the block's own positions, but its first, with a value that is not finite
   const int tid = threadIdx.x, lane = tid & 63;
   const int w8 = __builtin_amdgcn_readfirstlane(tid >> 6), w = w8 & 3, kg = KG == 2 ? w8 >> 2 : 0;      // wave of its group; group (tiles of that parity)
   bf16_t* ring = (bf16_t*)attn_dyn_smem + kg * 4 * TILE;                // the group's buffers: K, K, V^T, V^T
@@ -88,34 +88,16 @@ __global__ void __launch_bounds__(256 * KG, 2) attn_prefill_mfma_kernel(
     for (int m = 0; m < 4; ++m)
       vr[m] = *(const vraw_t*)(vc + (uint32_t)(min(base + 4 * (ln & 15) + m, key_end - 1) * HD + (w * 4 + (ln >> 4)) * DV));
   };
-  auto drop_bad = [&](int base) {       // seldom: values that are not finite become 0, their first key is noted
-    int ln = lane;
-    asm volatile("" : "+v"(ln));
-#pragma unroll 1
-    for (int m = 0; m < 4; ++m) {
-      bool bad = false;
+  auto drop_bad = [&](int base) {       // values from poison_s on that are not finite become 0
 #pragma unroll
-      for (int mm = 0; mm < 4; ++mm)
-        if (mm == m)
+    for (int m = 0; m < 4; ++m)
+      if (min(base + 4 * kgp + m, key_end - 1) >= poison_s) {
 #pragma unroll
-          for (int u = 0; u < DV / 2; ++u) {
-            const bool b0 = (vr[mm][u] & 0x7F80u) == 0x7F80u, b1 = (vr[mm][u] & 0x7F800000u) == 0x7F800000u;
-            vr[mm][u] = (b0 ? 0u : vr[mm][u] & 0xFFFFu) | (b1 ? 0u : vr[mm][u] & 0xFFFF0000u);
-            bad |= b0 || b1;
-          }
-      if (bad) atomicMin(&poison_s, min(base + 4 * (ln & 15) + m, key_end - 1));
-    }
+        for (int u = 0; u < DV / 2; ++u)
+          vr[m][u] = ((vr[m][u] & 0x7F80u) == 0x7F80u ? 0u : vr[m][u] & 0xFFFFu) | ((vr[m][u] & 0x7F800000u) == 0x7F800000u ? 0u : vr[m][u] & 0xFFFF0000u);
+      }
   };
-  auto store_v = [&](int base, int buf) {
-    if (base + AP_KT > pos0 + 1) {      // a tile with keys that some row does not see (uniform over the group)
-      // the largest exponent field among the thread's values (2 in a register); 255: one of them is not finite
-      unsigned int top = 0u;
-#pragma unroll
-      for (int m = 0; m < 4; ++m)
-#pragma unroll
-        for (int u = 0; u < DV / 2; ++u) top = max(top, max(vr[m][u] & 0x7F80u, (vr[m][u] >> 16) & 0x7F80u));
-      if (__any(top == 0x7F80u)) drop_bad(base);
-    }
+  auto store_v = [&](int buf) {
 #pragma unroll
     for (int u = 0; u < DV / 2; ++u) {
 #pragma unroll
@@ -130,6 +112,20 @@ __global__ void __launch_bounds__(256 * KG, 2) attn_prefill_mfma_kernel(
   const int n_tiles = (key_end + AP_KT - 1) / AP_KT;
   if (kg < n_tiles) { load_k(kg * AP_KT, 0); load_v(kg * AP_KT); }
   if (tid == 0) poison_s = 0x7FFFFFFF;
+  // values of the keys that some row does not see, 16 bytes each: is one of them not finite?
+  constexpr int NT = 256 * KG, SC = 2;
+  const int n_scan = (rows - 1) * CH;
+  auto scan_key = [&](int c) { return min(pos0 + 1 + c / CH, key_end - 1); };
+  auto scan_load = [&](int c) { return *(const u32x4*)(vc + (uint32_t)(scan_key(c) * HD + c % CH * 8)); };
+  auto scan_check = [&](const u32x4& v, int c) {
+    bool bad = false;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) bad |= (v[u] & 0x7F80u) == 0x7F80u || (v[u] & 0x7F800000u) == 0x7F800000u;
+    if (bad) atomicMin(&poison_s, scan_key(c));
+  };
+  u32x4 sc[SC];
+#pragma unroll
+  for (int j = 0; j < SC; ++j) sc[j] = scan_load(tid + j * NT);
 
   // the lane's query vector: dims 16 t + 8 hi + 0..7; its rotary partner dims (i, i + HD/2) are the lane's own
   bf16x8_t qh[T], ql[T];
@@ -185,11 +181,16 @@ __global__ void __launch_bounds__(256 * KG, 2) attn_prefill_mfma_kernel(
   __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0): poison_s is set before a wave adds to it; the loads stay in flight
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  if (kg < n_tiles) store_v(kg * AP_KT, 0);
+#pragma unroll
+  for (int j = 0; j < SC; ++j) scan_check(sc[j], tid + j * NT);
+  for (int c = tid + SC * NT; c < n_scan; c += NT) scan_check(scan_load(c), c);
+  if (kg < n_tiles) store_v(0);
   __builtin_amdgcn_s_waitcnt(7 << 4);      // vmcnt(0) lgkmcnt(0): this wave's share of K has landed too
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 
+  auto walk = [&](auto drop_c) {
+  constexpr bool DROP = decltype(drop_c)::value;
   for (int it = 0; KG * it < n_tiles; ++it) {
     const int buf = it & 1, base = (KG * it + kg) * AP_KT;
     const bool more = KG * (it + 1) + kg < n_tiles;
@@ -271,10 +272,23 @@ __global__ void __launch_bounds__(256 * KG, 2) attn_prefill_mfma_kernel(
       }
     }
     }
-    if (more) store_v(base + KG * AP_KT, buf ^ 1);
+    if (more) {
+      if (DROP) drop_bad(base + KG * AP_KT);
+      store_v(buf ^ 1);
+    }
     __builtin_amdgcn_s_waitcnt(7 << 4);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+  }
+  };
+  if (__builtin_amdgcn_readfirstlane(poison_s) == 0x7FFFFFFF) {
+    walk(std::integral_constant<bool, false>());
+  } else {                            // seldom; the first tile's values once more
+    if (kg < n_tiles) { load_v(kg * AP_KT); drop_bad(kg * AP_KT); store_v(0); }
+    __builtin_amdgcn_s_waitcnt(7 << 4);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    walk(std::integral_constant<bool, true>());
   }
   l_run += __shfl_xor(l_run, 32, 64);
   if constexpr (KG == 2) {

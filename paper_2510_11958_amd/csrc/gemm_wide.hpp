@@ -10,7 +10,7 @@
 // waited for by the exact count of its loads while the next one's are in flight, and requests the one after that behind
 // its first fragment reads.
 // What bounds it: per step and CU 2048 cycles of MFMAs per SIMD (32 of 32 cycles for each of its two waves) against 1400 cycles of LDS
-// traffic (128 KiB of fragments and 48 KiB of arriving pieces at 128 bytes a cycle) that overlap only in part.  Measured without epilogue, 2048 rows, cold weights (us, both planes), this
+// traffic (128 KiB of fragments and 48 KiB of arriving pieces at 128 bytes a cycle) that overlap only in part.  Measured without epilogue, 2048 rows, cold weights, one chain of sums (us, both planes), this
 // tile / 128 x 256 with 8 waves of 64 x 64 and two blocks per CU: 192 tiles of 6144 x 2560 118 / 127, 608 tiles of
 // 19456 x 2560 370 / 348 where the last of three rounds is 38 % full (hence the split of the last round's tiles, see the
 // launcher); other shapes and orders at 19456 x 2560: 4 waves of 128 x 128 472, waves of 128 x 64 384, fragments read half a
@@ -19,13 +19,13 @@
 // weight byte enters one die's L2 only and its row tiles share it there.
 // Tiles of 128 rows (waves of 64 x 64, a ring of four buffers, 0.8 instead of 1.25 us per step) where they pad a launch's rows less.
 // Against passes of 128 rows through gemm_mfma.hpp (4B shapes, 2048 rows, us with the finishing launch, before / now):
-// gate/up 660 / 357, QKV 390 / 125, down + O 763 / 297.
+// gate/up 660 / 357, QKV 390 / 144, down + O 763 / 297.
 // Sums: a tile that takes its whole K in one block sums it in one fp32 chain, a rounding per 8 products, 4.4e-7 of the result's norm at
 // K = 2560 in two planes; five parts summed apart (gemm_mfma.hpp with 128 rows) leave 2.0e-7.  In the QKV projection, whose K
 // and V are then rounded to bf16, that decides roundings (STEP_SUMS below): each k-step of 32 is summed by itself and added to the
 // chain, 1.5e-7.  Logits of a prompt of 1003, 2560 wide, against 64 bits with the cache's rounding taken along, 1 / 2 layers:
 // chain 8.5e-5 / 1.15e-4, steps 5.2e-5 / 7.5e-5, 128-row parts 5.2e-5 / 7.5e-5.  It costs 128 additions a step beside 32 MFMAs:
-// 1 to 2 % of a pass; in all projections 9 to 10 % at 2560 wide, for no smaller an error.
+// QKV 125 -> 144 us with 2048 rows, 1 to 2 % of a pass; in all projections 9 to 10 % at 2560 wide, for no smaller an error.
 #pragma once
 #include "gemm_mfma.hpp"
 
