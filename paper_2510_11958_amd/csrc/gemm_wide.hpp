@@ -10,11 +10,12 @@
 // waited for by the exact count of its loads while the next one's are in flight, and requests the one after that behind
 // its first fragment reads.
 // What bounds it: per step and CU 2048 cycles of MFMAs per SIMD (32 of 32 cycles for each of its two waves) against 1400 cycles of LDS
-// traffic (128 KiB of fragments and 48 KiB of arriving pieces at 128 bytes a cycle) that overlap only in part.  Measured without epilogue, 2048 rows, cold weights, one chain of sums (us, both planes), this
-// tile / 128 x 256 with 8 waves of 64 x 64 and two blocks per CU: 192 tiles of 6144 x 2560 118 / 127, 608 tiles of
-// 19456 x 2560 370 / 348 where the last of three rounds is 38 % full (hence the split of the last round's tiles, see the
-// launcher); other shapes and orders at 19456 x 2560: 4 waves of 128 x 128 472, waves of 128 x 64 384, fragments read half a
-// step ahead (which needs the next step landed half a step earlier) 384, raised wave priority around the MFMAs 435.
+// traffic (128 KiB of fragments and 48 KiB of arriving pieces at 128 bytes a cycle) that overlap only in part.  Measured without
+// epilogue, 2048 rows, cold weights, one chain of sums (us, both planes), this tile / 128 x 256 with 8 waves of 64 x 64 and two blocks
+// per CU: 192 tiles of 6144 x 2560 118 / 127, 608 tiles of 19456 x 2560 370 / 348 where the last of three rounds is 38 % full (hence
+// the split of the last round's tiles, see the launcher); other shapes and orders at 19456 x 2560: 4 waves of 128 x 128 472, waves of
+// 128 x 64 384, fragments read half a step ahead (which needs the next step landed half a step earlier) 384, raised wave priority
+// around the MFMAs 435.
 // Blocks go round-robin over the 8 compute dies; a die takes a contiguous run of tiles with the row tiles fastest, so a
 // weight byte enters one die's L2 only and its row tiles share it there.
 // Tiles of 128 rows (waves of 64 x 64, a ring of four buffers, 0.8 instead of 1.25 us per step) where they pad a launch's rows less.
