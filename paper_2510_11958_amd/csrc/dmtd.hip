@@ -454,9 +454,10 @@ struct WidePlan { double us; int n_full, ksplit; };
 template <int EPI, int BM>
 WidePlan plan_wide(const dmtd_config& cf, int num_cus, int rows, int nt, int KS) {
   const int tiles = (rows + BM - 1) / BM * nt, slots = num_cus;
-  // a k-step of 32 takes 1.25 us with 256 rows and 0.8 with 128 (measured, cold weights), a block's start and end about 4;
+  // a k-step of 32 takes 1.25 us with 256 rows (1.45 where it is summed by itself) and 0.8 with 128 (measured, cold weights), a
+  // block's start and end about 4;
   // a raw tile's bytes are written and read by blocks all over the chip at about 3.5 TB/s in all; the finishing launch itself 5 us
-  const double step_us = BM == 256 ? 1.25 : 0.8;
+  const double step_us = BM == 256 ? (EPI == EPI_STORE ? 1.45 : 1.25) : 0.8;
   const int part_tiles = (int)std::min<size_t>(gemm_part_floats(cf) / GwTile<BM>::PART, 1 << 20);
   const int whole = EPI == EPI_RESID ? 0 : tiles / slots * slots, left = tiles - whole;
   auto round_us = [&](int ks) { return (left * ks + slots - 1) / slots * (2.0 * KS / ks * step_us + 4.0); };

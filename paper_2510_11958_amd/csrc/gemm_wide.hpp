@@ -20,13 +20,14 @@
 // weight byte enters one die's L2 only and its row tiles share it there.
 // Tiles of 128 rows (waves of 64 x 64, a ring of four buffers, 0.8 instead of 1.25 us per step) where they pad a launch's rows less.
 // Against passes of 128 rows through gemm_mfma.hpp (4B shapes, 2048 rows, us with the finishing launch, before / now):
-// gate/up 660 / 357, QKV 390 / 144, down + O 763 / 297.
+// gate/up 660 / 357, QKV 390 / 133, down + O 763 / 297.
 // Sums: a tile that takes its whole K in one block sums it in one fp32 chain, a rounding per 8 products, 4.4e-7 of the result's norm at
 // K = 2560 in two planes; five parts summed apart (gemm_mfma.hpp with 128 rows) leave 2.0e-7.  In the QKV projection, whose K
-// and V are then rounded to bf16, that decides roundings (STEP_SUMS below): each k-step of 32 is summed by itself and added to the
-// chain, 1.5e-7.  Logits of a prompt of 1003, 2560 wide, against 64 bits with the cache's rounding taken along, 1 / 2 layers:
-// chain 8.5e-5 / 1.15e-4, steps 5.2e-5 / 7.5e-5, 128-row parts 5.2e-5 / 7.5e-5.  It costs 128 additions a step beside 32 MFMAs:
-// QKV 125 -> 144 us with 2048 rows, 1 to 2 % of a pass; in all projections 9 to 10 % at 2560 wide, for no smaller an error.
+// and V are then rounded to bf16, that decides roundings; there a chain has 8 k-steps (tiles of 128 rows) or one (256 rows, 128
+// additions beside 32 MFMAs: 1.45 us per step), about 1.5e-7.  Logits of a prompt of 1003, 2560 wide, against 64 bits with the
+// cache's rounding taken along, 1 / 2 layers: one chain 8.5e-5 / 1.14e-4, short chains 4.0e-5 / 6.2e-5, 128-row parts 5.3e-5 /
+// 7.5e-5.  QKV with 2048 rows, us: one chain 126, short ones 133 (144 in tiles of 256 rows); chains of a step in all projections cost 9
+// to 10 % of a pass at 2560 wide, for no smaller an error.
 #pragma once
 #include "gemm_mfma.hpp"
 
@@ -151,9 +152,9 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
     if (TR == 4) ss += __shfl_xor(ss, 2, 64);
     if (tid % TR == 0) rs_s[tid / TR] = rsqrtf(ss / (float)K + a.eps);
   }
-  // Results that are rounded to 16 bits afterwards (QKV: the cache): a k-step's products are summed by themselves and added to the
-  // chain once, not in its roundings of 8 products at a time
-  constexpr bool STEP_SUMS = EPI == EPI_STORE;
+  // Results that are rounded to 16 bits afterwards (QKV: the cache) are summed in short chains of their own, added to the accumulators
+  // once each: 8 k-steps where the wave has registers for a second set (tiles of 128 rows), one step else
+  constexpr bool SHORT_SUMS = EPI == EPI_STORE;
   auto chunk = [](const bf16_t* q) { return __builtin_bit_cast(bf16x8_t, *(const u32x4*)q); };
   auto mma = [](bf16x8_t wv, bf16x8_t xv, const f32x16& c) {
     return WA ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, xv, c, 0, 0, 0) : __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv, wv, c, 0, 0, 0);
@@ -175,6 +176,17 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
 #pragma unroll
         for (int i = 0; i < 2; ++i) acc[i][j] = mma(f.wf[j], p ? f.xh[i] : f.xl[i], acc[i][j]);
   };
+  constexpr bool KEEP = SHORT_SUMS && BM == 128;      // a second set of accumulators
+  f32x16 part[2][KEEP ? NJ : 1];
+  auto clear = [&](f32x16& c) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) c[e] = 0.f;
+  };
+  if (KEEP)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) clear(part[i][KEEP ? j : 0]);
   int buf = 0, nxt = T::BUF - 1;
   for (int s = s_lo; s < s_hi; ++s) {
     // this step's pieces have landed once all loads but those of the newer steps (BUF - 2 of them, fewer at the end) have
@@ -186,7 +198,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");         // no LDS read of the slice moves above the barrier
     const bf16_t* base = ring + buf * T::STAGE + frag;
-    if constexpr (STEP_SUMS) {
+    if constexpr (SHORT_SUMS) {
       bf16x8_t xf[2][2][2];                // [low, high part][half of the step][row tile]
 #pragma unroll
       for (int p = 0; p < 2; ++p)
@@ -201,27 +213,24 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
       for (int j = 0; j < NJ; ++j) {       // the next tile's weights are read while this one's products run
         const bf16_t* wn = base + wtile(j + 1 < NJ ? j + 1 : j) * 1024;
         const bf16x8_t n0 = chunk(wn), n1 = chunk(wn + 256);
-        f32x16 t[2];
+        const int jp = KEEP ? j : 0;
+        if (!KEEP) { clear(part[0][0]); clear(part[1][0]); }
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          f32x16 z;
+        for (int p = 0; p < 2; ++p)        // low parts first
 #pragma unroll
-          for (int e = 0; e < 16; ++e) z[e] = 0.f;
-          t[i] = mma(w0, xf[0][0][i], z);
-        }
+          for (int c = 0; c < 2; ++c)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) t[i] = mma(w1, xf[0][1][i], t[i]);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) t[i] = mma(w0, xf[1][0][i], t[i]);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) t[i] = mma(w1, xf[1][1][i], t[i]);
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) acc[i][j][e] += t[i][e];
+            for (int i = 0; i < 2; ++i) part[i][jp] = mma(c ? w1 : w0, xf[p][c][i], part[i][jp]);
+        if (!KEEP) { acc[0][j] += part[0][0]; acc[1][j] += part[1][0]; }
         w0 = n0; w1 = n1;
       }
       __builtin_amdgcn_sched_barrier(0);
+      if (KEEP && (((s - s_lo) & 7) == 7 || s + 1 == s_hi)) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) { acc[i][j] += part[i][KEEP ? j : 0]; clear(part[i][KEEP ? j : 0]); }
+      }
     } else {
       Frag f0, f1;
       read(f0, base, 0);

@@ -37,7 +37,8 @@ CASES = {
     # the layouts that the plan of a projection reaches at these sizes: LAYOUTS below
     "tiles_256_whole_and_tail": (S(2, 896, 14, 2, 64, 8896, 17000), 8, 256),
     "tiles_256_qkv_ragged": (S(1, 512, 66, 22, 64, 704, 300), 4, 505),            # 2020 rows: the last row tile has 228, nqkv is 27.5 tiles
-    "tiles_256_qkv_tail_ragged": (S(1, 1024, 93, 31, 64, 704, 300), 4, 449),      # the last row tile has 4 rows, nqkv is 38.75 tiles
+    "tiles_256_qkv_tail_ragged": (S(1, 768, 78, 26, 64, 704, 300), 4, 505),       # nqkv is 32.5 tiles
+    "tiles_128_qkv_tail_ragged": (S(1, 1024, 93, 31, 64, 704, 300), 4, 449),      # the last row tile has 4 rows, nqkv is 38.75 tiles
     "resid_in_two_launches": (S(2, 1024, 4, 2, 64, 128, 300), 5, 400),
     "vectors_38400_hd64_gq8": (S(1, 128, 16, 2, 64, 128, 97), 48, 50),           # 384 blocks of 128, more than a block per CU: one group of waves
 }
@@ -49,7 +50,8 @@ KINDS = {"qkv": 0, "oproj": 1, "gateup": 2, "down": 3, "lmhead": 4}
 LAYOUTS = {
     "tiles_256_whole_and_tail": {"gateup": (2048, 256, 512, 48, 3), "down": (2048, 256, 0, 32, 8), "lmhead": (512, 256, 134, 0, 1)},
     "tiles_256_qkv_ragged": {"qkv": (2020, 256, 224, 0, 1)},
-    "tiles_256_qkv_tail_ragged": {"qkv": (1796, 256, 256, 56, 3)},
+    "tiles_256_qkv_tail_ragged": {"qkv": (2020, 256, 256, 8, 3)},
+    "tiles_128_qkv_tail_ragged": {"qkv": (1796, 128, 512, 73, 3)},
     "resid_in_two_launches": {"oproj": (1536, 128, 0, 48, 1), "down": (1536, 128, 0, 48, 1)},
 }
 
@@ -104,8 +106,8 @@ def test_wide_pass_against_oracle(name):
 @pytest.mark.gpu
 def test_few_cached_values_round_the_other_way():
     """How near the QKV projection's sums are to 64 bits decides how many keys and values round to the other bf16 neighbour: of 2.05 million
-    values 2.3e-4 with K = 2560 summed in five parts (passes of 128 rows), 3.2e-4 to 3.6e-4 in one fp32 chain, 1.7e-4 with each
-    k-step summed by itself.  2.6e-4 is three standard deviations of the count above the first."""
+    values 2.3e-4 with K = 2560 summed in five parts (passes of 128 rows), 3.2e-4 to 3.6e-4 in one fp32 chain, 1.8e-4 in chains of
+    8 k-steps of 32.  2.6e-4 is three standard deviations of the count above the first."""
     import torch
     sh, n = S(1, 2560, 32, 8, 128, 128, 300), 1003
     blob = di.make_weight_blob(sh, seed=31, std=0.02, gain_sigma=0.2)
