@@ -20,14 +20,14 @@
 // weight byte enters one die's L2 only and its row tiles share it there.
 // Tiles of 128 rows (waves of 64 x 64, a ring of four buffers, 0.8 instead of 1.25 us per step) where they pad a launch's rows less.
 // Against passes of 128 rows through gemm_mfma.hpp (4B shapes, 2048 rows, us with the finishing launch, before / now):
-// gate/up 660 / 357, QKV 390 / 133, down + O 763 / 297.
+// gate/up 660 / 357, QKV 390 / 137, down + O 763 / 297.
 // Sums: a tile that takes its whole K in one block sums it in one fp32 chain, a rounding per 8 products, 4.4e-7 of the result's norm at
-// K = 2560 in two planes; five parts summed apart (gemm_mfma.hpp with 128 rows) leave 2.0e-7.  In the QKV projection, whose K
-// and V are then rounded to bf16, that decides roundings; there a chain has 8 k-steps (tiles of 128 rows) or one (256 rows, 128
-// additions beside 32 MFMAs: 1.45 us per step), about 1.5e-7.  Logits of a prompt of 1003, 2560 wide, against 64 bits with the
-// cache's rounding taken along, 1 / 2 layers: one chain 8.5e-5 / 1.14e-4, short chains 4.0e-5 / 6.2e-5, 128-row parts 5.3e-5 /
-// 7.5e-5.  QKV with 2048 rows, us: one chain 126, short ones 133 (144 in tiles of 256 rows); chains of a step in all projections cost 9
-// to 10 % of a pass at 2560 wide, for no smaller an error.
+// K = 2560 in two planes; five parts summed apart (gemm_mfma.hpp with 128 rows) leave 2.0e-7.  In the QKV projection, whose K and V are
+// then rounded to bf16, that decides roundings; there a chain has 4 k-steps (tiles of 128 rows) or one (256 rows, 128 additions beside
+// 32 MFMAs: 1.45 us per step), about 1.3e-7.  Logits of a prompt of 1003, 2560 wide, against 64 bits with the cache's rounding taken
+// along, 1 / 2 layers: one chain 8.5e-5 / 1.14e-4, short chains 5.1e-5 / 7.2e-5, 128-row parts 5.2e-5 / 7.5e-5.  QKV with 2048 rows, us:
+// one chain 126, short ones 137 (8 steps long 132, no nearer than parts at K = 1024; in tiles of 256 rows 144); chains of a step in all
+// projections cost 9 to 10 % of a pass at 2560 wide, for no smaller an error.
 #pragma once
 #include "gemm_mfma.hpp"
 
@@ -153,7 +153,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
     if (tid % TR == 0) rs_s[tid / TR] = rsqrtf(ss / (float)K + a.eps);
   }
   // Results that are rounded to 16 bits afterwards (QKV: the cache) are summed in short chains of their own, added to the accumulators
-  // once each: 8 k-steps where the wave has registers for a second set (tiles of 128 rows), one step else
+  // once each: 4 k-steps where the wave has registers for a second set (tiles of 128 rows), one step else
   constexpr bool SHORT_SUMS = EPI == EPI_STORE;
   auto chunk = [](const bf16_t* q) { return __builtin_bit_cast(bf16x8_t, *(const u32x4*)q); };
   auto mma = [](bf16x8_t wv, bf16x8_t xv, const f32x16& c) {
@@ -225,7 +225,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
         w0 = n0; w1 = n1;
       }
       __builtin_amdgcn_sched_barrier(0);
-      if (KEEP && (((s - s_lo) & 7) == 7 || s + 1 == s_hi)) {
+      if (KEEP && (((s - s_lo) & 3) == 3 || s + 1 == s_hi)) {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll

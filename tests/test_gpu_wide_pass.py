@@ -106,8 +106,8 @@ def test_wide_pass_against_oracle(name):
 @pytest.mark.gpu
 def test_few_cached_values_round_the_other_way():
     """How near the QKV projection's sums are to 64 bits decides how many keys and values round to the other bf16 neighbour: of 2.05 million
-    values 2.3e-4 with K = 2560 summed in five parts (passes of 128 rows), 3.2e-4 to 3.6e-4 in one fp32 chain, 1.8e-4 in chains of
-    8 k-steps of 32.  2.6e-4 is three standard deviations of the count above the first."""
+    values 2.3e-4 with K = 2560 summed in five parts (passes of 128 rows), 3.2e-4 to 3.6e-4 in one fp32 chain, 1.4e-4 in chains of
+    4 k-steps of 32.  2.6e-4 is three standard deviations of the count above the first."""
     import torch
     sh, n = S(1, 2560, 32, 8, 128, 128, 300), 1003
     blob = di.make_weight_blob(sh, seed=31, std=0.02, gain_sigma=0.2)
