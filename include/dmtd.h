@@ -152,7 +152,7 @@ int dmtd_decode(dmtd_ctx* ctx, int32_t tau, int32_t n_late, int32_t n_steps,
  * tokens, so the sequences of one batch may be at different points of their cycles - a sequence starts a new cycle (its
  * pending tokens and its newest token pass the front layers, refilling its own front-layer KV entries) at the step after
  * its own cycle is complete, whatever the others do.  In such a step the sequences that start a cycle pass the front layers
- * (one weight pass per distinct number of pending rows among them), and ALL sequences' newest tokens then share one pass
+ * (in one weight pass where their numbers of pending rows are alike, else a few), and ALL sequences' newest tokens then share one pass
  * through the late layers and the LM head.  tau: HOST int32 [batch], each in [1, 64]; the lengths may change from call to
  * call (a sequence whose cycle already holds tau[b] or more tokens starts a new one at the call's first step).
  * forced_inputs, out_tokens, out_stride (>= n_steps), n_emitted: as for dmtd_decode.  All-or-nothing like dmtd_decode.

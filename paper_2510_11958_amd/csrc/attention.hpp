@@ -239,7 +239,6 @@ __global__ void __launch_bounds__(256) attn_split_kernel(
   const int rpb = QVT / GQ;                                    // rows per block
   const int n_rg = (r_total + rpb - 1) / rpb;
   const int split = blockIdx.x / n_rg, rg = blockIdx.x % n_rg;
-  const int r = min(rpb, r_total - rg * rpb), QV = r * GQ;
   const int key_begin = split * kps;
   const int sl = lane % LPK, grp = wave * GPW + lane / LPK;
   const int my_u = sl >> USH;
@@ -265,13 +264,16 @@ __global__ void __launch_bounds__(256) attn_split_kernel(
   load_kv(key_begin, min(s_max, key_begin + kps));
 
   const int pos_first = row_base(st, sel, offset, bs);
+  const int live = fmap ? live_rows(st, bs, r_total) : r_total; // rows of this sequence; the others of its r_total are dead
+  const int r = min(rpb, live - rg * rpb), QV = r * GQ;
+  if (r <= 0) return;
   const int pos0 = pos_first + rg * rpb;                        // position of this block's first row
   const int ctx = pos0 + r;                                     // keys 0 .. ctx-1 are visible to its last row
   if (key_begin >= ctx) return;                                 // whole range beyond the context (block-uniform)
   const int key_end = min(ctx, key_begin + kps);
   const int n_new = rg * rpb + r;                               // new rows whose keys this block's rows can see
   const bool holds_new = do_append != 2 && key_end > pos_first; // a new position, not yet in the cache, falls into this range
-  const bool writer = do_append == 1 && (rg + 1) * rpb >= r_total;   // the last row group's blocks append to the cache
+  const bool writer = do_append == 1 && (rg + 1) * rpb >= live;   // the last row group's blocks append to the cache
   const float scale = rsqrtf((float)HD);
 
   attn_prepare_rows<CT, HD>(qkv, ldq, q_gain, k_gain, rope_tab, kc, vc, b, g, nh, nkv, s_max, eps, r_total, rg * rpb, QV, n_new, holds_new,

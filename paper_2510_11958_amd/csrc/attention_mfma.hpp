@@ -247,7 +247,7 @@ __global__ void __launch_bounds__(64 * NW) attn_split_mfma_kernel(
   const int rpb = QVT / GQ;                                    // rows per block
   const int n_rg = (r_total + rpb - 1) / rpb;
   const int split = blockIdx.x / n_rg, rg = blockIdx.x % n_rg;
-  const int r = min(rpb, r_total - rg * rpb), QV = r * GQ;
+  const int QV_all = min(rpb, r_total - rg * rpb) * GQ;
   const int key_begin = split * kps;
   const int sl = lane & 15, kq = lane >> 4;
 
@@ -280,16 +280,19 @@ __global__ void __launch_bounds__(64 * NW) attn_split_mfma_kernel(
   load_kv(key_begin + 16 * wave, range_limit);
 
   // the block's query vectors do not depend on the positions: fetched now, next to K and V
-  const AttQueryPre<HD> qpre = attn_preload_query<HD>(qs, (const bf16_t*)q_gain, b, g, GQ, r_total, rg * rpb, QV, tid);
+  const AttQueryPre<HD> qpre = attn_preload_query<HD>(qs, (const bf16_t*)q_gain, b, g, GQ, r_total, rg * rpb, QV_all, tid);
 
   const int pos_first = row_base(st, sel, offset, bs);
+  const int live = fmap ? live_rows(st, bs, r_total) : r_total; // rows of this sequence; the others of its r_total are dead
+  const int r = min(rpb, live - rg * rpb), QV = r * GQ;
+  if (r <= 0) return;
   const int pos0 = pos_first + rg * rpb;                        // position of this block's first row
   const int ctx = pos0 + r;                                     // keys 0 .. ctx-1 are visible to its last row
   if (key_begin >= ctx) return;                                 // whole range beyond the context (block-uniform)
   const int key_end = min(ctx, key_begin + kps);
   const int n_new = rg * rpb + r;                               // new rows whose keys this block's rows can see
   const bool holds_new = do_append != 2 && key_end > pos_first;      // do_append = 2: the rows' keys are in the cache already
-  const bool writer = do_append == 1 && (rg + 1) * rpb >= r_total;   // the last row group's blocks append to the cache
+  const bool writer = do_append == 1 && (rg + 1) * rpb >= live;   // the last row group's blocks append to the cache
 
   attn_prepare_rows_mfma<HD>(qs, (const bf16_t*)q_gain, (const bf16_t*)k_gain, rope_tab, kc, vc, b, g, nh, nkv, s_max, eps, r_total,
                              rg * rpb, QV, n_new, holds_new, writer, pos_first, key_begin, key_end, qhi_s, qlo_s, knew_s, vnew_s, tid, NT / 16, qpre);

@@ -456,8 +456,9 @@ __global__ void __launch_bounds__(256) embed_pack_kernel(
   // the row's values stay in registers between the fp32 store, the packed store and the sum of squares.
   constexpr int NCH = 4;
   __shared__ float wsum[4];
-  const int row = blockIdx.x, i = row % r;
+  const int row = blockIdx.x;
   const int b = fmap ? fmap[row / r] : row / r;
+  const int i = fmap ? min(row % r, live_rows(st, b, r) - 1) : row % r;      // a dead row repeats the newest one
   const int pos = row_base(st, sel, offset, b) + i;
   const bf16_t* src = table + (size_t)tokens[(size_t)b * s_max + pos] * d;
   float* dst = h + (size_t)row * d;
@@ -509,7 +510,7 @@ __global__ void __launch_bounds__(256) take_last_pack_kernel(
     const int* __restrict__ last_pos /* nullable: sequence b's row is the one at explicit position last_pos[b], if in this launch */,
     const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot */, int blocked) {
   const int bl = blockIdx.x, b = fmap ? fmap[bl] : bl;         // source rows by launch sequence, everything else by slot
-  const int i = last_pos ? last_pos[b] - offset : r - 1;
+  const int i = last_pos ? last_pos[b] - offset : (fmap ? live_rows(st, b, r) : r) - 1;
   if (i < 0 || i >= r) return;
   const float* s = src + ((size_t)bl * r + i) * d;
   float* o = dst + (size_t)b * d;

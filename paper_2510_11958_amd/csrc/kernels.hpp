@@ -46,6 +46,14 @@ __device__ __forceinline__ int row_base(const DevState* st, int sel, int offset,
   return (sel == POS_NTOK ? st->n_tok + si.delta : si.front) + offset;
 }
 
+// Rows of sequence slot b in a front pass over some sequences (fmap), which has room for r rows per sequence: its pending tokens and
+// its newest one.  Sequences with fewer rows than r leave the rest of their room dead: such rows pass the projections with
+// whatever they hold (rows do not mix there), the attention neither computes nor appends them, and nobody reads them afterwards.
+__device__ __forceinline__ int live_rows(const DevState* st, int b, int r) {
+  const SeqInfo si = seq_info(st)[b];
+  return min(r, st->n_tok + si.delta - si.front + 1);
+}
+
 __device__ __forceinline__ float bf16_to_f32(bf16_t v) { return __uint_as_float(((uint32_t)v) << 16); }
 
 __device__ __forceinline__ bf16_t f32_to_bf16(float f) {   // round to nearest even
@@ -222,8 +230,9 @@ template <typename WT>
 __global__ void embed_kernel(const WT* __restrict__ table, const int* __restrict__ tokens, int s_max,
                              const DevState* st, int sel, int explicit_pos, int r, int d, float* __restrict__ h,
                              const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot */) {
-  const int row = blockIdx.x, i = row % r;
+  const int row = blockIdx.x;
   const int b = fmap ? fmap[row / r] : row / r;
+  const int i = fmap ? min(row % r, live_rows(st, b, r) - 1) : row % r;      // a dead row repeats the newest one
   const int pos = row_base(st, sel, explicit_pos, b) + i;
   const int tok = tokens[(size_t)b * s_max + pos];
   const WT* src = table + (size_t)tok * d;
@@ -242,7 +251,7 @@ __global__ void take_last_rows_kernel(const float* __restrict__ src, float* dst,
                                       int s_max, const DevState* st, int sel, int explicit_pos, const float* add_rows,
                                       const int* __restrict__ last_pos, const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot */) {
   const int bl = blockIdx.x, b = fmap ? fmap[bl] : bl;         // source rows by launch sequence, everything else by slot
-  const int i = last_pos ? last_pos[b] - explicit_pos : r - 1;
+  const int i = last_pos ? last_pos[b] - explicit_pos : (fmap ? live_rows(st, b, r) : r) - 1;
   if (i < 0 || i >= r) return;
   const float* s = src + ((size_t)bl * r + i) * d;
   float* o = dst + (size_t)b * d;

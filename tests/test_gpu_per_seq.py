@@ -249,3 +249,26 @@ def test_more_step_patterns_than_the_device_table_keeps(use_graphs):
     assert checked > 0
     compare_caches(eng, orcs, sh, n_late, 1e-5)
     print(f"{len(patterns)} distinct mixed patterns, graphs={use_graphs}: worst {worst:.2e}, tokens checked {checked}")
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("taus", [(1, 2, 3, 5, 8, 16), (1,) * 20 + (12,) * 4, (16, 1)], ids=["one_pass", "two_passes", "widest_padding"])
+def test_front_passes_with_room_for_more_rows_than_a_sequence_has(dtype, taus):
+    """Sequences that start a cycle with different numbers of pending tokens share a front pass with room for the largest
+    number (few sequences), or take passes of their own (20 sequences of one row beside 4 of twelve); run up to the last slot
+    of the cache, where a sequence's unused rows lie beyond its end."""
+    sh = di.ModelShape(3, 128, 4, 2, 64, 192, 130, dtype=dtype)
+    B, P, n_late, n = len(taus), 5, 1, 49
+    blob = di.make_weight_blob(sh, seed=3)
+    prompts = di.make_prompts(sh.vocab, B, P, seed=5)
+    toks = forced_string(sh.vocab, B, prompts, P + n)
+    eng = pkg.Engine(engine_config(sh, P + n, B), blob)
+    ocfg = oracle_config(sh)
+    w = O.unpack_weights(blob, ocfg, np.float64)
+    orcs = [O.DmtdOracle(ocfg, w, P + n, np.float64) for _ in range(B)]
+    eng.prefill(prompts)
+    for b, o in enumerate(orcs):
+        o.prefill(prompts[b])
+    _, checked = run_calls(eng, orcs, toks, [(list(taus), 18), (list(taus), 31)], n_late, TOL_F32 if dtype == "fp32" else TOL_BF16)
+    assert checked > 0
+    compare_caches(eng, orcs, sh, n_late, 1e-5 if dtype == "fp32" else 2e-2)
