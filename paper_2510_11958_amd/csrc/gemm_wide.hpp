@@ -6,16 +6,15 @@
 // v_mfma_f32_32x32x16_bf16).  K is walked in steps of 32: weights and both activation planes go from memory straight into
 // LDS (global_load ... lds), 48 pieces of 1 KiB per step, each piece holding 16 rows in the order [16-byte chunk of k][row],
 // which is the order the weights and the blocked activations (packed_at) are stored in; a fragment read then takes 256
-// contiguous bytes per 16 lanes (no bank conflicts).  A ring of three LDS buffers (144 KiB, one block per CU): a step is
-// waited for by the exact count of its loads while the next one's are in flight, and requests the one after that behind
-// its first fragment reads.
-// What bounds it: per step and CU 2048 cycles of MFMAs per SIMD (32 of 32 cycles for each of its two waves) against 1400 cycles of LDS
-// traffic (128 KiB of fragments and 48 KiB of arriving pieces at 128 bytes a cycle) that overlap only in part.  Measured without
-// epilogue, 2048 rows, cold weights, one chain of sums (us, both planes), this tile / 128 x 256 with 8 waves of 64 x 64 and two blocks
-// per CU: 192 tiles of 6144 x 2560 118 / 127, 608 tiles of 19456 x 2560 370 / 348 where the last of three rounds is 38 % full (hence
-// the split of the last round's tiles, see the launcher); other shapes and orders at 19456 x 2560: 4 waves of 128 x 128 472, waves of
-// 128 x 64 384, fragments read half a step ahead (which needs the next step landed half a step earlier) 384, raised wave priority
-// around the MFMAs 435.
+// contiguous bytes per 16 lanes (no bank conflicts).  A ring of three LDS buffers (144 KiB, one block per CU); a step is waited for by the
+// exact count of its loads.  The block's barrier stands in the middle of a step, where the fragments of its second half are in registers
+// and the next step's first ones are read beside the products (see the loop).
+// What bounds it: the card's power.  Gate/up at 2048 rows (608 tiles, 19456 x 2560, cold weights, without the finishing launch), us, barrier in front
+// of a step with all its reads and loads behind it / barrier in the middle: on zeros 263 / 233, on normally distributed data 333 / 314, where
+// the clock falls to 1.9 GHz; one 2560 x 9728 launch in 240 blocks 160 / 154; tiles of 128 rows, 1003 rows of 2560 x 4096 41.3 / 40.2.  With the
+// same tile loaded by every block the launch takes 302, so memory is not it.  Also measured at the middle barrier, no faster: other orders of
+// the products (each weight tile or each row tile held over 4 of them) 312 to 316, raised wave priority 320, 4 waves of 128 x 128 (a quarter
+// less LDS traffic) 5 % slower, tiles of 128 rows in 4 waves of 64 x 128 6 % slower.
 // Blocks go round-robin over the 8 compute dies; a die takes a contiguous run of tiles with the row tiles fastest, so a
 // weight byte enters one die's L2 only and its row tiles share it there.
 // Tiles of 128 rows (waves of 64 x 64, a ring of four buffers, 0.8 instead of 1.25 us per step) where they pad a launch's rows less.
@@ -26,7 +25,7 @@
 // then rounded to bf16, that decides roundings; there a chain has 4 k-steps (tiles of 128 rows) or one (256 rows, 128 additions beside
 // 32 MFMAs: 1.45 us per step), about 1.3e-7.  Logits of a prompt of 1003, 2560 wide, against 64 bits with the cache's rounding taken
 // along, 1 / 2 layers: one chain 8.5e-5 / 1.14e-4, short chains 5.1e-5 / 7.2e-5, 128-row parts 5.2e-5 / 7.5e-5.  QKV with 2048 rows, us:
-// one chain 126, short ones 137 (8 steps long 132, no nearer than parts at K = 1024; in tiles of 256 rows 144); chains of a step in all
+// one chain 126, short ones 137 (before the barrier moved; 8 steps long 132, no nearer than parts at K = 1024; in tiles of 256 rows 144); chains of a step in all
 // projections cost 9 to 10 % of a pass at 2560 wide, for no smaller an error.
 #pragma once
 #include "gemm_mfma.hpp"
@@ -104,20 +103,15 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
 #pragma unroll
   for (int j = 0; j < XP; ++j)
     xsrc[j] = (w >= 4 ? xb_lo_ : xb_) + (size_t)min(mb * T::XT + (XP * w + j) % T::XT, m_tiles - 1) * KS * 1024 + (size_t)s_lo * 512;
+  auto issue_one = [&](int buf, int j) {       // load j of a step into ring buffer buf
+    bf16_t* dst = ring + buf * T::STAGE + (j < 2 ? 2 * w + j : 16 + XP * w + j - 2) * 512;
+    const bf16_t*& src = j < 2 ? wsrc[j] : xsrc[j - 2];
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + lane * 8), (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+    src += 512;
+  };
   auto issue = [&](int buf) {
-    bf16_t* dst = ring + buf * T::STAGE;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(wsrc[j] + lane * 8),
-                                       (__attribute__((address_space(3))) void*)(dst + (2 * w + j) * 512), 16, 0, 0);
-      wsrc[j] += 512;
-    }
-#pragma unroll
-    for (int j = 0; j < XP; ++j) {
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(xsrc[j] + lane * 8),
-                                       (__attribute__((address_space(3))) void*)(dst + (16 + XP * w + j) * 512), 16, 0, 0);
-      xsrc[j] += 512;
-    }
+    for (int j = 0; j < T::LPS; ++j) issue_one(buf, j);
   };
   const int wm = w % T::WM, wn = w / T::WM;
   // 32-row weight tiles of this wave (SwiGLU: NJ / 2 gate tiles and the up tiles of the same outputs)
@@ -159,22 +153,12 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
   auto mma = [](bf16x8_t wv, bf16x8_t xv, const f32x16& c) {
     return WA ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, xv, c, 0, 0, 0) : __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv, wv, c, 0, 0, 0);
   };
-  struct Frag { bf16x8_t xl[2], xh[2], wf[NJ]; };
-  auto read = [&](Frag& f, const bf16_t* base, int c) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) f.xl[i] = chunk(base + (16 + T::XT + (2 * wm + i) * 2) * 512 + c * 256);
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) f.wf[j] = chunk(base + wtile(j) * 1024 + c * 256);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) f.xh[i] = chunk(base + (16 + (2 * wm + i) * 2) * 512 + c * 256);
-  };
-  auto mul = [&](const Frag& f) {
-#pragma unroll
-    for (int p = 0; p < 2; ++p)            // low parts first
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int i = 0; i < 2; ++i) acc[i][j] = mma(f.wf[j], p ? f.xh[i] : f.xl[i], acc[i][j]);
+  // fragments of half a step (16 of k), in order of first use: low parts of the two row tiles, weight tiles, high parts
+  constexpr int NF = 4 + NJ;
+  struct Frag { bf16x8_t f[NF]; };
+  auto read_one = [&](Frag& f, const bf16_t* base, int c, int q) {
+    const int piece = q < 2 ? 16 + T::XT + (2 * wm + q) * 2 : (q < 2 + NJ ? 2 * wtile(q - 2) : 16 + (2 * wm + q - 2 - NJ) * 2);
+    f.f[q] = chunk(base + piece * 512 + c * 256);
   };
   constexpr bool KEEP = SHORT_SUMS && BM == 128;      // a second set of accumulators
   f32x16 part[2][KEEP ? NJ : 1];
@@ -187,18 +171,16 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j) clear(part[i][KEEP ? j : 0]);
-  int buf = 0, nxt = T::BUF - 1;
-  for (int s = s_lo; s < s_hi; ++s) {
-    // this step's pieces have landed once all loads but those of the newer steps (BUF - 2 of them, fewer at the end) have
-    // returned (they return in order); behind the barrier every wave's have, and every wave is done with the buffer that is
-    // filled next.  vmcnt(newer steps x LPS) lgkmcnt(0), expcnt untouched
-    if (T::BUF == 4 && s + 2 < s_hi) __builtin_amdgcn_s_waitcnt(2 * T::LPS | (7 << 4));
-    else if (s + 1 < s_hi) __builtin_amdgcn_s_waitcnt(T::LPS | (7 << 4));
-    else __builtin_amdgcn_s_waitcnt(7 << 4);
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");         // no LDS read of the slice moves above the barrier
-    const bf16_t* base = ring + buf * T::STAGE + frag;
-    if constexpr (SHORT_SUMS) {
+  if constexpr (SHORT_SUMS && !KEEP) {
+    int buf = 0, nxt = T::BUF - 1;
+    for (int s = s_lo; s < s_hi; ++s) {
+      // this step's pieces have landed once all loads but the newer step's have returned (they return in order); behind the barrier
+      // every wave's have, and every wave is done with the buffer that is filled next.  vmcnt(LPS) lgkmcnt(0), expcnt untouched
+      if (s + 1 < s_hi) __builtin_amdgcn_s_waitcnt(T::LPS | (7 << 4));
+      else __builtin_amdgcn_s_waitcnt(7 << 4);
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");         // no LDS read of the slice moves above the barrier
+      const bf16_t* base = ring + buf * T::STAGE + frag;
       bf16x8_t xf[2][2][2];                // [low, high part][half of the step][row tile]
 #pragma unroll
       for (int p = 0; p < 2; ++p)
@@ -213,38 +195,81 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
       for (int j = 0; j < NJ; ++j) {       // the next tile's weights are read while this one's products run
         const bf16_t* wn = base + wtile(j + 1 < NJ ? j + 1 : j) * 1024;
         const bf16x8_t n0 = chunk(wn), n1 = chunk(wn + 256);
-        const int jp = KEEP ? j : 0;
-        if (!KEEP) { clear(part[0][0]); clear(part[1][0]); }
+        clear(part[0][0]); clear(part[1][0]);
 #pragma unroll
         for (int p = 0; p < 2; ++p)        // low parts first
 #pragma unroll
           for (int c = 0; c < 2; ++c)
 #pragma unroll
-            for (int i = 0; i < 2; ++i) part[i][jp] = mma(c ? w1 : w0, xf[p][c][i], part[i][jp]);
-        if (!KEEP) { acc[0][j] += part[0][0]; acc[1][j] += part[1][0]; }
+            for (int i = 0; i < 2; ++i) part[i][0] = mma(c ? w1 : w0, xf[p][c][i], part[i][0]);
+        acc[0][j] += part[0][0]; acc[1][j] += part[1][0];
         w0 = n0; w1 = n1;
       }
       __builtin_amdgcn_sched_barrier(0);
+      buf = buf + 1 == T::BUF ? 0 : buf + 1;
+      nxt = nxt + 1 == T::BUF ? 0 : nxt + 1;
+    }
+  } else {
+    // A step's two halves: while the products of one run, the fragments of the next are read, one beside every NJ / 4 products.  The
+    // barrier stands between the halves.  Behind it the second half's fragments are in registers, so the matrix cores go on at
+    // once; every wave is done reading this step's buffer, so it is refilled (a load beside every pair of products: together they would
+    // hold the wave up, the memory pipe takes a load per 16 cycles of a CU); and the next step has landed for every wave.
+    // vmcnt(newer steps x LPS) lgkmcnt(0), expcnt untouched: loads return in order, BUF - 2 newer steps are on their way (at the end fewer,
+    // then all loads are waited for).
+    constexpr int VM = (T::BUF - 2) * T::LPS;
+    static_assert(VM < 16, "the counter wait's low field");
+    auto half = [&](const Frag& f, auto beside) {
+#pragma unroll
+      for (int q = 0; q < 2 * NJ; ++q) {
+        const int p = q / NJ, j = q % NJ;    // low parts first
+        beside(q);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          f32x16& c = KEEP ? part[i][KEEP ? j : 0] : acc[i][j];
+          c = mma(f.f[2 + j], f.f[p ? 2 + NJ + i : i], c);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    // the reads (n = NF) or loads (n = LPS) beside products pair q of 2 NJ, the last pair taking what is left
+    auto share = [](int q, int n, auto f) {
+      if (q < n) f(q);
+      if (q == 2 * NJ - 1)
+#pragma unroll
+        for (int z = 2 * NJ; z < n; ++z) f(z);
+    };
+    Frag f0, f1;
+    if (s_hi - s_lo >= T::BUF - 1) __builtin_amdgcn_s_waitcnt(VM | (7 << 4));
+    else __builtin_amdgcn_s_waitcnt(7 << 4);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");           // no LDS read of a slice moves above the barrier
+#pragma unroll
+    for (int q = 0; q < NF; ++q) read_one(f0, ring + frag, 0, q);
+    if (s_hi - s_lo > T::BUF - 1) issue(T::BUF - 1);
+    int buf = 0;
+    for (int s = s_lo; s < s_hi; ++s) {
+      const int nxt = buf + 1 == T::BUF ? 0 : buf + 1;
+      const bf16_t* base = ring + buf * T::STAGE + frag;
+      const bf16_t* next = ring + nxt * T::STAGE + frag;
+      __builtin_amdgcn_sched_barrier(0);
+      half(f0, [&](int q) { share(q, NF, [&](int z) { read_one(f1, base, 1, z); }); });
+      if (s + T::BUF - 1 < s_hi) __builtin_amdgcn_s_waitcnt(VM | (7 << 4));
+      else __builtin_amdgcn_s_waitcnt(7 << 4);
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      const bool more = s + 1 < s_hi, fill = s + T::BUF < s_hi;
+      half(f1, [&](int q) {
+        if (more) share(q, NF, [&](int z) { read_one(f0, next, 0, z); });
+        if (fill) share(q, T::LPS, [&](int z) { issue_one(buf, z); });
+      });
       if (KEEP && (((s - s_lo) & 3) == 3 || s + 1 == s_hi)) {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
           for (int j = 0; j < NJ; ++j) { acc[i][j] += part[i][KEEP ? j : 0]; clear(part[i][KEEP ? j : 0]); }
       }
-    } else {
-      Frag f0, f1;
-      read(f0, base, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      if (s + T::BUF - 1 < s_hi) issue(nxt);
-      read(f1, base, 1);
-      __builtin_amdgcn_sched_barrier(0);
-      mul(f0);
-      __builtin_amdgcn_sched_barrier(0);
-      mul(f1);
-      __builtin_amdgcn_sched_barrier(0);
+      buf = nxt;
     }
-    buf = buf + 1 == T::BUF ? 0 : buf + 1;
-    nxt = nxt + 1 == T::BUF ? 0 : nxt + 1;
   }
 
   // lane (column n = lane % 32 of a weight tile): element e of acc[i][j] is row 32 i + 8 (e / 4) + 4 (lane / 32) + e % 4 of the wave
