@@ -20,6 +20,10 @@
 // before the first one is needed.  The kernel boundary makes the partials visible across the chip
 // (fences and same-kernel grid barriers were measured to cost far more on this chip).
 //
+// What bounds it on a small model is the chain position -> rotary table -> queries -> scores -> totals of one block: what does not depend on
+// the position is loaded ahead of it, sixteen vectors are prepared at a time, and sums across lanes are exchanges between
+// registers (tiny model, 33 to 48 keys, 1 or 2 rows: 8.7 us with shuffles and a wave per vector, 6.4 now).
+//
 // Keys beyond the current context inside a block's range are loaded (they lie inside the cache
 // allocation) and masked; ranges wholly beyond the context exit early and are skipped by the merge.
 #pragma once
@@ -33,6 +37,17 @@ constexpr int ATT_MAX_SPLITS = 64;
 // Keys a block covers per iteration: 16 lane groups x 4 keys (head_dim 128) or 32 x 4 (head_dim 64).
 template <int HD> struct AttKeysPerIter { static constexpr int value = 4 * (64 / (HD / 8)) * 4; };
 
+
+// f over the keys of a wave: a value per lane slice that holds a key (2 or 4 neighbouring lanes each), every lane gets the result
+template <int HD, typename F> __device__ __forceinline__ float key_reduce(float v, F f) {
+  if (HD == 64) v = f(v, lane_dpp<kDppQuad2>(v));
+  v = f(v, lane_dpp<kDppHalfMirror>(v));        // quads hold one value each: lane ^ 4
+  v = f(v, lane_dpp<kDppRor8>(v));
+  LanePair<float> p = halves<16>(v, v);
+  v = f(p.x, p.y);
+  p = halves<32>(v, v);
+  return f(p.x, p.y);
+}
 
 // One block iteration of the running softmax: 4 keys per lane group (kf, vf: this lane's 8 dims of
 // each), scored against every query vector.  After the in-group reduction lane slice sl holds the
@@ -55,23 +70,23 @@ for (int qv = 0; qv < QVT; ++qv) {
       for (int e = 0; e < 8; ++e) d += q[qv][e] * kf[u][e];
       s4[u] = d;
     }
-    // sum over the lane group; the 4 keys' sums end up in 4 different lane slices
+    // sum over the lane group; the 4 keys' sums end up in 4 different lane slices (the mirror pairs a lane with one whose lower
+    // bits are flipped too: the steps behind it sum over those)
     {
+      constexpr int X1 = LPK == 16 ? kDppRor8 : kDppHalfMirror, X2 = LPK == 16 ? kDppHalfMirror : kDppQuad2;
       const bool up1 = (sl & (LPK / 2)) != 0;
-      const float a0 = (up1 ? s4[2] : s4[0]) + __shfl_xor(up1 ? s4[0] : s4[2], LPK / 2, 64);
-      const float a1 = (up1 ? s4[3] : s4[1]) + __shfl_xor(up1 ? s4[1] : s4[3], LPK / 2, 64);
+      const float a0 = (up1 ? s4[2] : s4[0]) + lane_dpp<X1>(up1 ? s4[0] : s4[2]);
+      const float a1 = (up1 ? s4[3] : s4[1]) + lane_dpp<X1>(up1 ? s4[1] : s4[3]);
       const bool up2 = (sl & (LPK / 4)) != 0;
-      float s = (up2 ? a1 : a0) + __shfl_xor(up2 ? a0 : a1, LPK / 4, 64);
-#pragma unroll
-      for (int o = LPK / 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+      float s = (up2 ? a1 : a0) + lane_dpp<X2>(up2 ? a0 : a1);
+      if (LPK == 16) s += lane_dpp<kDppQuad2>(s);
+      s += lane_dpp<kDppQuad1>(s);
       s4[0] = s;
     }
     // causal and range mask: row i = qv / GQ sees keys <= pos0 + i
     float s = s4[0];
     if (my_key >= key_end || my_key > pos0 + qv / GQ) s = -INFINITY;
-    float mx = s;
-#pragma unroll
-    for (int o = LPK / 4; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));   // over keys and lane groups
+    const float mx = key_reduce<HD>(s, [](float a, float b) { return fmaxf(a, b); });   // over keys and lane groups
     const float m_new = fmaxf(m[qv], mx);
     if (m_new != -INFINITY) {
       const float sc = __expf(m[qv] - m_new);           // exp(-inf) = 0 on the first visible key
@@ -89,25 +104,29 @@ for (int qv = 0; qv < QVT; ++qv) {
 }
 }
 
-// End of a wave's key loop: l summed over the distinct (lane group, key) holders, acc over the lane groups.
+// End of a wave's key loop: l summed over the keys, acc over the lane groups.  The sum over the groups halves the values a lane
+// holds at each step: lane (slice sl, group grp) ends up with output dims 8 sl + e .. of query qv in acc[qv][0 ..], AttOut<HD> of them from
+// e = AttOut<HD>::first(lane) on.
+template <int HD> struct AttOut {
+  static constexpr int n = HD == 64 ? 1 : 2;
+  static __device__ __forceinline__ int first(int lane) { return (lane >> 5) * 4 + ((lane >> 4) & 1) * 2 + (HD == 64 ? (lane >> 3) & 1 : 0); }
+};
 template <int HD, int QVT>
-__device__ __forceinline__ void attn_wave_totals(float (&l)[QVT], float (&acc)[QVT][8]) {
-  constexpr int LPK = HD / 8;
-#pragma unroll
-  for (int qv = 0; qv < QVT; ++qv) {
-    float v = l[qv];
-#pragma unroll
-    for (int o = LPK / 4; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
-    l[qv] = v;
-  }
+__device__ __forceinline__ void attn_wave_totals(float (&l)[QVT], float (&acc)[QVT][8], int QV, int lane) {
 #pragma unroll
   for (int qv = 0; qv < QVT; ++qv)
+    if (qv < QV) {
+      l[qv] = key_reduce<HD>(l[qv], [](float a, float b) { return a + b; });
+      float (&v)[8] = acc[qv];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      float v = acc[qv][e];
+      for (int e = 0; e < 4; ++e) { const LanePair<float> p = halves<32>(v[e], v[e + 4]); v[e] = p.x + p.y; }
 #pragma unroll
-      for (int o = LPK; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
-      acc[qv][e] = v;
+      for (int e = 0; e < 2; ++e) { const LanePair<float> p = halves<16>(v[e], v[e + 2]); v[e] = p.x + p.y; }
+      if (HD == 64) {
+        const bool up = (lane & 8) != 0;
+        const float send = up ? v[0] : v[1], keep = up ? v[1] : v[0];
+        v[0] = keep + lane_dpp<kDppRor8>(send);
+      }
     }
 }
 
@@ -122,60 +141,21 @@ __global__ void rope_table_kernel(const double* __restrict__ inv_freq, float2* _
   }
 }
 
-// Per-head RMSNorm + RoPE (pair (i, i + HD/2), cos/sin from the table) of a block's QV query vectors
-// (rows row0 .. of the launch, GQ heads each, scaled by 1/sqrt(HD)) into q_s and, if the block's key
-// range holds new positions, of the launch's first n_new keys and values into knew_s / vnew_s, rounded
-// to the cache's type; the writer block also stores them to the cache.  Called by all 4 waves of a block.
-template <typename CT, int HD>
-__device__ __forceinline__ void attn_prepare_rows(
-    const float* __restrict__ qkv, int ldq, const void* __restrict__ q_gain, const void* __restrict__ k_gain,
-    const float2* __restrict__ rope_tab, CT* __restrict__ kc, CT* __restrict__ vc, int b, int g, int nh, int nkv, int s_max,
-    float eps, int r_total, int row0, int QV, int n_new, bool holds_new, bool writer, int pos_first, int key_begin, int key_end,
-    float (*q_s)[HD], float (*knew_s)[HD], float (*vnew_s)[HD], int lane, int wave) {
-  constexpr int half = HD / 2;
-  const int GQ = nh / nkv;
-  const float scale = rsqrtf((float)HD);
-  const bool act = lane < half;
-  const int n_vec = QV + (holds_new ? 2 * n_new : 0);         // queries, new keys, new values
-  for (int v = wave; v < n_vec; v += 4) {
-    if (v < QV + n_new) {
-      const bool is_q = v < QV;
-      const int row = is_q ? row0 + v / GQ : v - QV;          // row of the launch
-      const int hcol = is_q ? g * GQ + v % GQ : nh + g;
-      const float* src = qkv + (size_t)(b * r_total + row) * ldq + (size_t)hcol * HD;
-      float x0 = act ? src[lane] : 0.f, x1 = act ? src[lane + half] : 0.f;
-      const float rs = rsqrtf(wave_sum(x0 * x0 + x1 * x1) / (float)HD + eps);
-      if (act) {
-        const CT* gn = (const CT*)(is_q ? q_gain : k_gain);
-        x0 *= rs * Elem<CT>::to_f32(gn[lane]);
-        x1 *= rs * Elem<CT>::to_f32(gn[lane + half]);
-        const float2 cs = rope_tab[(size_t)(pos_first + row) * half + lane];
-        const float c = cs.x, sf = cs.y;
-        const float y0 = x0 * c - x1 * sf, y1 = x1 * c + x0 * sf;
-        if (is_q) {
-          q_s[v][lane] = y0 * scale; q_s[v][lane + half] = y1 * scale;
-        } else {
-          const CT c0 = Elem<CT>::from_f32(y0), c1 = Elem<CT>::from_f32(y1);
-          knew_s[row][lane] = Elem<CT>::to_f32(c0); knew_s[row][lane + half] = Elem<CT>::to_f32(c1);
-          const int key = pos_first + row;
-          if (writer && key >= key_begin && key < key_end) {
-            CT* dst = kc + (((size_t)b * nkv + g) * s_max + key) * HD;
-            dst[lane] = c0; dst[lane + half] = c1;
-          }
-        }
-      }
-    } else {
-      const int row = v - QV - n_new, key = pos_first + row;
-      const float* src = qkv + (size_t)(b * r_total + row) * ldq + (size_t)(nh + nkv + g) * HD;
-      CT* dst = vc + (((size_t)b * nkv + g) * s_max + key) * HD;
-      const bool wr = writer && key >= key_begin && key < key_end;
-      for (int k = lane; k < HD; k += 64) {
-        const CT cv = Elem<CT>::from_f32(src[k]);
-        vnew_s[row][k] = Elem<CT>::to_f32(cv);
-        if (wr) dst[k] = cv;
-      }
-    }
-  }
+// A vector of the prologue (a query, a new key or a new value of one head) is handled by 16 neighbouring lanes; lane l holds the
+// rotary pairs (HL l + e, HD/2 + HL l + e), e < HL.
+template <int HD> struct AttRow {
+  static constexpr int HL = HD / 32;
+  typedef float vec __attribute__((ext_vector_type(HD / 32)));
+  vec a, b;
+  __device__ __forceinline__ void load(const float* p, int l) { a = *(const vec*)(p + HL * l); b = *(const vec*)(p + HD / 2 + HL * l); }
+};
+// Sum over the 16 lanes of a DPP row by rotations (every lane ends up with the total).
+__device__ __forceinline__ float row16_sum(float v) {
+  v += lane_dpp<0x128>(v);
+  v += lane_dpp<0x124>(v);
+  v += lane_dpp<0x122>(v);
+  v += lane_dpp<0x121>(v);
+  return v;
 }
 
 // QK-RMSNorm + RoPE + KV append as a launch of its own, for passes that carry more rows per sequence than an attention
@@ -208,17 +188,17 @@ __global__ void __launch_bounds__(64) kv_append_kernel(
   for (int k = lane; k < HD; k += 64) vd[k] = Elem<CT>::from_f32(vsrc[k]);
 }
 
-template <typename CT, int HD, int QVT>
+template <int HD, int QVT>
 __global__ void __launch_bounds__(256) attn_split_kernel(
     const float* __restrict__ qkv, int ldq, const void* __restrict__ q_gain, const void* __restrict__ k_gain,
-    const float2* __restrict__ rope_tab /* [s_max][HD / 2] (cos, sin) of position * theta^(-2i/HD) */, CT* __restrict__ kc, CT* __restrict__ vc,
+    const float2* __restrict__ rope_tab /* [s_max][HD / 2] (cos, sin) of position * theta^(-2i/HD) */, float* __restrict__ kc, float* __restrict__ vc,
     float* __restrict__ part_o, float* __restrict__ part_ml, int nh, int nkv, int s_max, float eps,
     int kps /* keys per range, a multiple of the block iteration */, int n_splits, int qv_stride,
     const DevState* st, int sel, int offset, int r_total,
     int do_append /* 1: the launch appends its rows' keys and values; 0: it scores them from its inputs and leaves the cache untouched (measurement); 2: they are in the cache already */,
     const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot (cache rows, positions) */,
     float* __restrict__ out, int ldo /* nullable: one range, no merge launch follows */) {
-  typedef typename Elem<CT>::Raw Raw;
+  typedef Elem<float>::Raw Raw;
   constexpr int LPK = HD / 8;          // lanes per key (16 or 8)
   constexpr int GPW = 64 / LPK;        // lane groups per wave (4 or 8)
   constexpr int NG = 4 * GPW;          // lane groups per block
@@ -242,24 +222,38 @@ __global__ void __launch_bounds__(256) attn_split_kernel(
   const int key_begin = split * kps;
   const int sl = lane % LPK, grp = wave * GPW + lane / LPK;
   const int my_u = sl >> USH;
+  // the rows this block prepares if every row is alive: its queries, then the new keys and values its queries may see
+  const int QV_all = min(rpb, r_total - rg * rpb) * GQ, new_all = min(r_total, (rg + 1) * rpb);
+  const int vl = tid & 15, vg = tid >> 4;              // lane of a 16-lane row; row of the block
+  AttRow<HD> x0, gq, gk;
+  auto vec_src = [&](int v) {                          // vector v of the prologue
+    const bool is_q = v < QV_all, is_k = v < QV_all + new_all;
+    const int row = is_q ? rg * rpb + v / GQ : (is_k ? v - QV_all : v - QV_all - new_all);
+    return qkv + (size_t)(b * r_total + row) * ldq + (size_t)(is_q ? g * GQ + v % GQ : (is_k ? nh + g : nh + nkv + g)) * HD;
+  };
+  // the first vector and the gains: what does not depend on the position is on its way before that is known
+  x0.load(vec_src(min(vg, QV_all + 2 * new_all - 1)), vl);
+  gq.load((const float*)q_gain, vl);
+  gk.load((const float*)k_gain, vl);
 
-  __shared__ float q_s[QVT][HD];
-  __shared__ float knew_s[NEW_MAX][HD], vnew_s[NEW_MAX][HD];
+  __shared__ __attribute__((aligned(16))) float q_s[QVT][HD];
+  __shared__ __attribute__((aligned(16))) float knew_s[NEW_MAX][HD], vnew_s[NEW_MAX][HD];
   __shared__ float wacc[4][QVT][HD];
   __shared__ float wm[4][QVT], wl[4][QVT];
 
   // K/V of the first iteration: addresses depend on the launch only
-  const CT* kbase = kc + (((size_t)b * nkv + g) * s_max) * HD + sl * 8;
-  const CT* vbase = vc + (((size_t)b * nkv + g) * s_max) * HD + sl * 8;
+  const float* kbase = kc + (((size_t)b * nkv + g) * s_max) * HD + sl * 8;
+  const float* vbase = vc + (((size_t)b * nkv + g) * s_max) * HD + sl * 8;
   Raw kr[U], vr[U];
+  int loaded = 0;                      // the limit of the keys in kr and vr
   auto load_kv = [&](int it0, int limit) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int key = it0 + u * NG + grp;
-      const bool ok = key < limit;
-      kr[u] = ok ? Elem<CT>::load_raw(kbase + (size_t)key * HD) : Elem<CT>::zero_raw();
-      vr[u] = ok ? Elem<CT>::load_raw(vbase + (size_t)key * HD) : Elem<CT>::zero_raw();
+      const int key = min(it0 + u * NG + grp, limit - 1);      // unconditional; a key beyond the limit becomes zero when it is used
+      kr[u] = Elem<float>::load_raw(kbase + (size_t)key * HD);
+      vr[u] = Elem<float>::load_raw(vbase + (size_t)key * HD);
     }
+    loaded = limit;
   };
   load_kv(key_begin, min(s_max, key_begin + kps));
 
@@ -274,10 +268,51 @@ __global__ void __launch_bounds__(256) attn_split_kernel(
   const int n_new = rg * rpb + r;                               // new rows whose keys this block's rows can see
   const bool holds_new = do_append != 2 && key_end > pos_first; // a new position, not yet in the cache, falls into this range
   const bool writer = do_append == 1 && (rg + 1) * rpb >= live;   // the last row group's blocks append to the cache
-  const float scale = rsqrtf((float)HD);
 
-  attn_prepare_rows<CT, HD>(qkv, ldq, q_gain, k_gain, rope_tab, kc, vc, b, g, nh, nkv, s_max, eps, r_total, rg * rpb, QV, n_new, holds_new,
-                            writer, pos_first, key_begin, key_end, q_s, knew_s, vnew_s, lane, wave);
+  // Per-head RMSNorm + RoPE (cos/sin from the table) of the block's queries, scaled by 1/sqrt(HD), into q_s and, if the range holds new
+  // positions, of the launch's new keys, and the new values, into knew_s / vnew_s; the writer also stores them to the cache.
+  // Sixteen vectors at a time.
+  {
+    constexpr int HL = AttRow<HD>::HL, half = HD / 2;
+    const float scale = rsqrtf((float)HD);
+    const int n_vec = QV_all + (holds_new ? 2 * new_all : 0);
+    for (int v = vg; v < n_vec; v += 16) {
+      const bool is_q = v < QV_all, is_k = !is_q && v < QV_all + new_all;
+      const int row = is_q ? rg * rpb + v / GQ : (is_k ? v - QV_all : v - QV_all - new_all);
+      AttRow<HD> x = x0;
+      if (v != vg) x.load(vec_src(v), vl);
+      if (row >= live) continue;
+      const int key = pos_first + row;
+      const bool wr = !is_q && writer && key >= key_begin && key < key_end;
+      const size_t at = (((size_t)b * nkv + g) * s_max + key) * HD + HL * vl;
+      typename AttRow<HD>::vec ya = x.a, yb = x.b;
+      if (is_q || is_k) {
+        float ss = 0.f;
+#pragma unroll
+        for (int e = 0; e < HL; ++e) ss += x.a[e] * x.a[e] + x.b[e] * x.b[e];
+        const float rs = rsqrtf(row16_sum(ss) / (float)HD + eps);
+        const float2* rp = rope_tab + (size_t)key * half + HL * vl;
+#pragma unroll
+        for (int e = 0; e < HL; ++e) {
+          const float2 cs = rp[e];
+          const float a0 = x.a[e] * (rs * (is_q ? gq.a[e] : gk.a[e])), a1 = x.b[e] * (rs * (is_q ? gq.b[e] : gk.b[e]));
+          ya[e] = a0 * cs.x - a1 * cs.y;
+          yb[e] = a1 * cs.x + a0 * cs.y;
+        }
+      }
+      typedef typename AttRow<HD>::vec vec;
+      if (is_q) {
+        *(vec*)&q_s[v][HL * vl] = ya * scale; *(vec*)&q_s[v][half + HL * vl] = yb * scale;
+      } else {
+        float (*dst)[HD] = is_k ? knew_s : vnew_s;
+        *(vec*)&dst[row][HL * vl] = ya; *(vec*)&dst[row][half + HL * vl] = yb;
+        if (wr) {
+          float* c = (is_k ? kc : vc) + at;
+          *(vec*)c = ya; *(vec*)(c + half) = yb;
+        }
+      }
+    }
+  }
   __syncthreads();
 
   float q[QVT][8];
@@ -296,7 +331,11 @@ __global__ void __launch_bounds__(256) attn_split_kernel(
   for (int it0 = key_begin; it0 < key_end; it0 += KPI) {
     float kf[U][8], vf[U][8];
 #pragma unroll
-    for (int u = 0; u < U; ++u) { Elem<CT>::unpack(kr[u], kf[u]); Elem<CT>::unpack(vr[u], vf[u]); }
+    for (int u = 0; u < U; ++u) {
+      const bool ok = it0 + u * NG + grp < loaded;
+      Elem<float>::unpack(ok ? kr[u] : Elem<float>::zero_raw(), kf[u]);
+      Elem<float>::unpack(ok ? vr[u] : Elem<float>::zero_raw(), vf[u]);
+    }
     if (it0 + KPI < key_end) load_kv(it0 + KPI, key_end);       // next iteration's keys fly during the scoring
     if (holds_new) {
       // new positions: key and value come from LDS, not from the cache slot (written by another block, or not yet)
@@ -312,16 +351,14 @@ __global__ void __launch_bounds__(256) attn_split_kernel(
     attn_accumulate<HD, QVT>(q, kf, vf, it0 + my_u * NG + grp, key_end, pos0, GQ, QV, lane, sl, m, l, acc);
   }
 
-  attn_wave_totals<HD, QVT>(l, acc);
-  if (lane < LPK) {
+  attn_wave_totals<HD, QVT>(l, acc, QV, lane);
 #pragma unroll
-    for (int qv = 0; qv < QVT; ++qv)
-      if (qv < QV) {
+  for (int qv = 0; qv < QVT; ++qv)
+    if (qv < QV) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) wacc[wave][qv][sl * 8 + e] = acc[qv][e];
-        if (lane == 0) { wm[wave][qv] = m[qv]; wl[wave][qv] = l[qv]; }
-      }
-  }
+      for (int e = 0; e < AttOut<HD>::n; ++e) wacc[wave][qv][sl * 8 + AttOut<HD>::first(lane) + e] = acc[qv][e];
+      if (lane == 0) { wm[wave][qv] = m[qv]; wl[wave][qv] = l[qv]; }
+    }
   __syncthreads();
   // partials are indexed by the launch-wide query-vector number row * GQ + head
   const size_t slot = (((size_t)b * nkv + g) * ATT_MAX_SPLITS + split) * qv_stride + (size_t)rg * rpb * GQ;

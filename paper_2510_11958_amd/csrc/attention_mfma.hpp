@@ -31,19 +31,6 @@
 
 namespace dmtd {
 
-// Sum over the 16 lanes of a DPP row by rotations (every lane ends up with the total).
-template <int N>
-__device__ __forceinline__ float row_ror_f32(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xF, 0xF, false));
-}
-__device__ __forceinline__ float row16_sum(float v) {
-  v += row_ror_f32<8>(v);
-  v += row_ror_f32<4>(v);
-  v += row_ror_f32<2>(v);
-  v += row_ror_f32<1>(v);
-  return v;
-}
-
 typedef short bf16x4s_t __attribute__((ext_vector_type(4)));      // operand of the 16x16x16 bf16 matrix instruction
 constexpr int ATT_QPAD = 8;     // bf16 elements of padding per LDS query row
 
@@ -358,8 +345,7 @@ __global__ void __launch_bounds__(64 * NW) attn_split_mfma_kernel(
       if (key >= key_end || key > my_row_pos || sl >= QV) sc[j] = -INFINITY;
       mx = fmaxf(mx, sc[j]);
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    mx = column_max(mx);
     const float m_new = fmaxf(m_run, mx);
     float p[4] = {0.f, 0.f, 0.f, 0.f};
     float resc = 1.f;
@@ -402,8 +388,7 @@ __global__ void __launch_bounds__(64 * NW) attn_split_mfma_kernel(
     }
   }
   // per-wave totals: l summed over the 4 kq lanes of a query
-  l_run += __shfl_xor(l_run, 16, 64);
-  l_run += __shfl_xor(l_run, 32, 64);
+  l_run = column_sum(l_run);
   if (kq == 0 && sl < QV) { wm[wave][sl] = m_run; wl[wave][sl] = l_run; }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {

@@ -143,7 +143,7 @@ __global__ void __launch_bounds__(256 * KG, HD == 64 && KG == 1 ? 3 : 2) attn_pr
     for (int t = 0; t < T; ++t)
 #pragma unroll
       for (int e = 0; e < 8; ++e) ss += x[t][e] * x[t][e];
-    ss += __shfl_xor(ss, 32, 64);
+    ss = pair_sum<32>(ss);
     const float rs = rsqrtf(ss / (float)HD + eps);
     const float scale = rsqrtf((float)HD) * 1.4426950408889634f;
     const float2* rp = rope_tab + (size_t)my_pos * (HD / 2) + 8 * hi;
@@ -223,7 +223,7 @@ __global__ void __launch_bounds__(256 * KG, HD == 64 && KG == 1 ? 3 : 2) attn_pr
     for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[0][e]);
 #pragma unroll
     for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[1][e]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    mx = pair_max<32>(mx);
     const float m_new = fmaxf(m_run, mx);       // -inf: the odd tiles so far hold no key this row sees
     const float m_use = m_new == -INFINITY ? 0.f : m_new;
     if (__any(m_new > m_run)) {
@@ -290,7 +290,7 @@ __global__ void __launch_bounds__(256 * KG, HD == 64 && KG == 1 ? 3 : 2) attn_pr
     asm volatile("" ::: "memory");
     walk(std::integral_constant<bool, true>());
   }
-  l_run += __shfl_xor(l_run, 32, 64);
+  l_run = pair_sum<32>(l_run);
   if constexpr (KG == 2) {
   // the odd tiles' results go through LDS (the ring is free: every wave is past the last tile's barrier) to the even tiles' waves
   float* mine = (float*)attn_dyn_smem + (size_t)w * (DT * 16 + 2) * 64 + lane;

@@ -356,6 +356,22 @@ const void* norm_gain_for_layer(const dmtd_ctx* c, int l) {   // gain of the nor
 
 template <typename WT, int M, int EPI, bool NORM>
 hipError_t launch_gemv(dmtd_ctx* c, GemvArgs a, int groups) {
+  // Short rows go through gemv_direct_kernel, which holds a wave's weights and rows in registers: four chunks of 256 fill 128 of them.
+  // us per step of 4 layers, gemv_rows_kernel / here (with the attention of the same change): 256 wide 78.8 / 50, 32000 entries 117 / 79,
+  // 16 sequences 291 / 74; 1024 wide, 1 row 174 / 141, 4 to 12 rows 213 / 101; 151936 entries, 2 layers 184 / 171.
+  if (a.K <= 1024) {
+    constexpr int RPW = EPI == EPI_SWIGLU ? 2 : 4;
+    const dim3 grid((a.N + 4 * RPW - 1) / (4 * RPW), groups);
+    auto go = [&](auto its) {
+      hipLaunchKernelGGL((gemv_direct_kernel<M, EPI, NORM, decltype(its)::value>), grid, dim3(256), 0, c->stream, (const float*)a.W, (const float*)a.W2,
+                         a.x, (const float*)a.gain, a.y, a.ldx, a.ldy, a.N, a.K, a.eps, a.amax, a.amax_ld);
+      return hipGetLastError();
+    };
+    if (a.K <= 256) return go(std::integral_constant<int, 1>());
+    if (a.K <= 512) return go(std::integral_constant<int, 2>());
+    if (a.K <= 768) return go(std::integral_constant<int, 3>());
+    return go(std::integral_constant<int, 4>());
+  }
   // narrow outputs with long rows: the waves of a block split K
   if constexpr ((EPI == EPI_RESID || EPI == EPI_STORE) && !NORM) {
     if (a.K >= 1024 && a.N <= 8192) {
@@ -707,14 +723,14 @@ hipError_t launch_gateup(dmtd_ctx* c, MfmaArgs a, int rows) {
 // a3 + a4: QK-RMSNorm, RoPE, KV append and split-K attention in one launch over static key ranges, then the merge.
 // The ranges follow from the context bucket (c->att_bucket, 256 or a multiple of 512 that covers the context), so a
 // captured step stays valid until the sequence grows into the next bucket.
-template <typename CT, typename OT, int HD, int QVT>
-void launch_attention_t(dmtd_ctx* c, int l, const float* qkv, OT* attn, OT* attn_lo, int sel, int offset, int r, int append) {
+template <int HD, int QVT>
+void launch_attention_t(dmtd_ctx* c, int l, const float* qkv, float* attn, int sel, int offset, int r, int append) {
   const dmtd_config& cf = c->cfg;
   const int B = c->batch, nqkv = (cf.n_q_heads + 2 * cf.n_kv_heads) * HD, qd = cf.n_q_heads * HD;
   const int gq = cf.n_q_heads / cf.n_kv_heads, rpb = QVT / gq, n_rg = (r + rpb - 1) / rpb;
   constexpr int KPI = AttKeysPerIter<HD>::value;
-  CT* kc = (CT*)(c->ws + c->o.kv + (size_t)l * c->o.kv_layer_stride);
-  CT* vc = (CT*)(c->ws + c->o.kv + (size_t)l * c->o.kv_layer_stride + c->o.kv_v_off);
+  float* kc = (float*)(c->ws + c->o.kv + (size_t)l * c->o.kv_layer_stride);
+  float* vc = (float*)(c->ws + c->o.kv + (size_t)l * c->o.kv_layer_stride + c->o.kv_v_off);
   const LayerW& w = c->layers[l];
   // keys per range: one block iteration while that keeps the ranges within the partials buffer and puts no
   // more than about four blocks on every CU; longer ranges (several iterations) for long contexts or big batches
@@ -725,17 +741,17 @@ void launch_attention_t(dmtd_ctx* c, int l, const float* qkv, OT* attn, OT* attn
   if (want_splits < 1) want_splits = 1;
   int kps = ((bucket + want_splits - 1) / want_splits + KPI - 1) / KPI * KPI;
   // short contexts: one range of at most two block iterations instead of the merge launch (4.4 us; an iteration takes about 2)
-  const bool one = std::is_same<OT, float>::value && bucket <= 2 * KPI;
+  const bool one = bucket <= 2 * KPI;
   if (one) kps = bucket;
   const int ns = (bucket + kps - 1) / kps;
   float* po = c->part_o;
   float* pml = c->part_ml;
   const DevState* st = dev_state(c);
-  hipLaunchKernelGGL((attn_split_kernel<CT, HD, QVT>), dim3(ns * n_rg, cf.n_kv_heads, B), dim3(256), 0, c->stream, qkv, nqkv,
+  hipLaunchKernelGGL((attn_split_kernel<HD, QVT>), dim3(ns * n_rg, cf.n_kv_heads, B), dim3(256), 0, c->stream, qkv, nqkv,
                      w.q_norm, w.k_norm, (const float2*)(c->ws + c->o.rope_tab), kc, vc, po, pml, cf.n_q_heads, cf.n_kv_heads,
-                     cf.max_seq_len, cf.rms_eps, kps, ns, c->part_rows * gq, st, sel, offset, r, append, c->fmap, one ? (float*)attn : (float*)nullptr, qd);
+                     cf.max_seq_len, cf.rms_eps, kps, ns, c->part_rows * gq, st, sel, offset, r, append, c->fmap, one ? attn : (float*)nullptr, qd);
   if (one) return;
-  hipLaunchKernelGGL((attn_merge_kernel<HD, OT>), dim3(r, cf.n_q_heads, B), dim3(256), 0, c->stream, po, pml, attn, attn_lo, qd,
+  hipLaunchKernelGGL((attn_merge_kernel<HD, float>), dim3(r, cf.n_q_heads, B), dim3(256), 0, c->stream, po, pml, attn, (float*)nullptr, qd,
                      cf.n_q_heads, cf.n_kv_heads, kps, ns, c->part_rows * gq, st, sel, offset, r, c->fmap, blocked_rows(c, B * r));
 }
 
@@ -864,17 +880,18 @@ hipError_t launch_attention(dmtd_ctx* c, int l, const float* qkv, OT* attn, OT* 
     }
     if (cf.head_dim == 128) return launch_attention_mfma_t<OT, 128>(c, l, qkv, attn, attn_lo, sel, offset, r, append);
     return launch_attention_mfma_t<OT, 64>(c, l, qkv, attn, attn_lo, sel, offset, r, append);
-  }
-  const int want = c->share_kv ? r * gq : gq;
-  const int qvt = want <= 4 ? 4 : (want <= 8 ? 8 : 16);
-  if (cf.head_dim == 128) {
-    if (qvt == 4) launch_attention_t<CT, OT, 128, 4>(c, l, qkv, attn, attn_lo, sel, offset, r, append);
-    else if (qvt == 8) launch_attention_t<CT, OT, 128, 8>(c, l, qkv, attn, attn_lo, sel, offset, r, append);
-    else launch_attention_t<CT, OT, 128, 16>(c, l, qkv, attn, attn_lo, sel, offset, r, append);
   } else {
-    if (qvt == 4) launch_attention_t<CT, OT, 64, 4>(c, l, qkv, attn, attn_lo, sel, offset, r, append);
-    else if (qvt == 8) launch_attention_t<CT, OT, 64, 8>(c, l, qkv, attn, attn_lo, sel, offset, r, append);
-    else launch_attention_t<CT, OT, 64, 16>(c, l, qkv, attn, attn_lo, sel, offset, r, append);
+    const int want = c->share_kv ? r * gq : gq;
+    const int qvt = want <= 4 ? 4 : (want <= 8 ? 8 : 16);
+    if (cf.head_dim == 128) {
+      if (qvt == 4) launch_attention_t<128, 4>(c, l, qkv, attn, sel, offset, r, append);
+      else if (qvt == 8) launch_attention_t<128, 8>(c, l, qkv, attn, sel, offset, r, append);
+      else launch_attention_t<128, 16>(c, l, qkv, attn, sel, offset, r, append);
+    } else {
+      if (qvt == 4) launch_attention_t<64, 4>(c, l, qkv, attn, sel, offset, r, append);
+      else if (qvt == 8) launch_attention_t<64, 8>(c, l, qkv, attn, sel, offset, r, append);
+      else launch_attention_t<64, 16>(c, l, qkv, attn, sel, offset, r, append);
+    }
   }
   return hipGetLastError();
 }

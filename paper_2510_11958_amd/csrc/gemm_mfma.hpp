@@ -347,8 +347,7 @@ __global__ void __launch_bounds__(64 * gemm_waves(CG, EPI)) gemm_mfma_kernel(
         }
         if (EPI == EPI_RESID) {
           // sum of squares of the 16 outputs of this tile for activation row m: over the 4 kg lanes
-          hsq += __shfl_xor(hsq, 16, 64);
-          hsq += __shfl_xor(hsq, 32, 64);
+          hsq = column_sum(hsq);
           if (mact && tv[j] && kg == 0) a.ssp_next[(size_t)tile[j] * a.ssp_ld + m] = hsq;
         }
         if (EPI == EPI_LOGITS && best != 0ull) atomicMax(&key_s[m], best);

@@ -142,8 +142,8 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
       for (int u = 0; u < 8; ++u)
         if (p0 + TR * u < a.n_parts) ss += v[u];
     }
-    ss += __shfl_xor(ss, 1, 64);
-    if (TR == 4) ss += __shfl_xor(ss, 2, 64);
+    ss += lane_dpp<kDppQuad1>(ss);
+    if (TR == 4) ss += lane_dpp<kDppQuad2>(ss);
     if (tid % TR == 0) rs_s[tid / TR] = rsqrtf(ss / (float)K + a.eps);
   }
   // Results that are rounded to 16 bits afterwards (QKV: the cache) are summed in short chains of their own, added to the accumulators
@@ -367,8 +367,7 @@ __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part
   if (NORM) {
     float ss = 0.f;
     for (int p = lane >> 4; p < a.n_parts; p += 4) ss += a.ssp[(size_t)p * a.ssp_ld + mc];
-    ss += __shfl_xor(ss, 16, 64);
-    ss += __shfl_xor(ss, 32, 64);
+    ss = column_sum(ss);
     rs = rsqrtf(ss / (float)a.K + a.eps);
   }
   float hsq = 0.f;
@@ -439,8 +438,7 @@ __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part
   }
   if (EPI == EPI_RESID) {
     // one sum of squares per row and tile of 256 outputs
-    hsq += __shfl_xor(hsq, 16, 64);
-    hsq += __shfl_xor(hsq, 32, 64);
+    hsq = column_sum(hsq);
     if (lane < 16) ss_s[w][lane] = hsq;
     __syncthreads();
     if (tid < 16 && act) a.ssp_next[(size_t)nb * a.ssp_ld + m] = ss_s[0][tid] + ss_s[1][tid] + ss_s[2][tid] + ss_s[3][tid];

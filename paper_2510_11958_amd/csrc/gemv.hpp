@@ -13,6 +13,7 @@
 //                       outputs with long rows (O projection, down projection), where
 //                       whole-row waves would leave most of the chip idle.  Each lane keeps
 //                       its own slices of the activation rows in registers.
+//  gemv_direct_kernel : short rows (K <= 1024) of an fp32 model: nothing through LDS, no barrier, every load issued at once.
 #pragma once
 #include "kernels.hpp"
 
@@ -32,27 +33,36 @@ struct GemvArgs {
   int amax_ld;
 };
 
-// Sum V (a power of two <= 64) per-lane values over the 64 lanes with V - 1 + (6 - log2 V)
-// shuffles: at each of the first log2 V steps a lane hands half of its values to its
+// Sum V (4, 8 or 16) per-lane values over the 64 lanes with V - 1 + (6 - log2 V) exchanges: at each of the first log2 V steps a lane hands half of its values to its
 // partner and keeps the other half.  Afterwards lane L holds, in v[0], the wave total of
 // the value with index L >> (6 - log2 V).
 template <int V>
 __device__ __forceinline__ float wave_reduce_multi(float (&v)[V], int lane) {
-  static_assert(V >= 1 && V <= 64 && (V & (V - 1)) == 0, "V must be a power of two");
-  constexpr int LOG = V == 1 ? 0 : V == 2 ? 1 : V == 4 ? 2 : V == 8 ? 3 : V == 16 ? 4 : V == 32 ? 5 : 6;
+  static_assert(V == 4 || V == 8 || V == 16, "two to four halvings");
 #pragma unroll
-  for (int s = 0; s < LOG; ++s) {
-    const int o = 32 >> s, n = V >> s;
-    const bool up = (lane & o) != 0;
+  for (int i = 0; i < V / 2; ++i) { const LanePair<float> p = halves<32>(v[i], v[i + V / 2]); v[i] = p.x + p.y; }
 #pragma unroll
-    for (int i = 0; i < n / 2; ++i) {
-      const float send = up ? v[i] : v[i + n / 2];
-      const float keep = up ? v[i + n / 2] : v[i];
-      v[i] = keep + __shfl_xor(send, o, 64);
+  for (int i = 0; i < V / 4; ++i) { const LanePair<float> p = halves<16>(v[i], v[i + V / 4]); v[i] = p.x + p.y; }
+  if constexpr (V >= 8) {
+    const bool up = (lane & 8) != 0;
+#pragma unroll
+    for (int i = 0; i < V / 8; ++i) {
+      const float send = up ? v[i] : v[i + V / 8], keep = up ? v[i + V / 8] : v[i];
+      v[i] = keep + lane_dpp<kDppRor8>(send);
     }
+  } else {
+    v[0] += lane_dpp<kDppRor8>(v[0]);
   }
-#pragma unroll
-  for (int s = LOG; s < 6; ++s) v[0] += __shfl_xor(v[0], 32 >> s, 64);
+  // the mirror pairs lane with lane ^ 7: a lane of the other quad, over which the last two steps sum anyway
+  if constexpr (V == 16) {
+    const bool up = (lane & 4) != 0;
+    const float send = up ? v[0] : v[1], keep = up ? v[1] : v[0];
+    v[0] = keep + lane_dpp<kDppHalfMirror>(send);
+  } else {
+    v[0] += lane_dpp<kDppHalfMirror>(v[0]);
+  }
+  v[0] += lane_dpp<kDppQuad2>(v[0]);
+  v[0] += lane_dpp<kDppQuad1>(v[0]);
   return v[0];
 }
 
@@ -193,6 +203,105 @@ __global__ void __launch_bounds__(256) gemv_rows_kernel(GemvArgs a) {
     if (owner && best != 0ull) atomicMax(&best_s[my_m], best);
     __syncthreads();
     if (tid < M && best_s[tid] != 0ull) atomicMax(a.amax + (size_t)(blockIdx.x % AMAX_CELLS) * a.amax_ld + tid, best_s[tid]);
+  }
+}
+
+// Short rows (K <= 256 ITS) of a small fp32 model, whose launches are bound by latency: kernel start, one round trip to
+// memory, the reduction.  A wave owns 4 outputs (SwiGLU: the gate and up rows of 2) and M activation rows; it loads its weights, the
+// rows, the norm's gain and the residual values it adds to, all at once, computes the rows' sums of squares by itself, and scales its sums
+// by 1/rms at the end.  No LDS, no barrier, no load behind another (gemv_rows_kernel has three round trips: rows, gain, residual).
+// Tiny model (256 wide, SwiGLU width 768, cache resident), us per launch with 2 rows, gemv_rows_kernel / here: QKV 4.9 / 2.5, O 4.5 / 3.9,
+// gate/up 4.9 / 3.1, down 4.5 / 2.9, LM head (1024 entries, 1 row) 5.0 / 3.0; 32 rows: gate/up 23.4 / 4.3, QKV 9.1 / 3.3.
+template <int M, int EPI, bool NORM, int ITS>
+__global__ void __launch_bounds__(256) gemv_direct_kernel(const float* __restrict__ W, const float* __restrict__ W2, const float* __restrict__ x, const float* __restrict__ gain,
+                                                          float* y, int ldx, int ldy, int N, int K, float eps, unsigned long long* amax, int amax_ld) {
+  constexpr int MP = PadRows<M>::MP, V = 4 * MP;
+  constexpr int LOGV = V == 4 ? 2 : V == 8 ? 3 : 4;
+  constexpr int RPW = EPI == EPI_SWIGLU ? 2 : 4;
+  x += (size_t)blockIdx.y * M * ldx;                 // group of M activation rows
+  y += (size_t)blockIdx.y * M * ldy;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n0 = (blockIdx.x * 4 + wave) * RPW;
+  f32x4 w[4][ITS], xv[M][ITS], g[ITS];
+#pragma unroll
+  for (int it = 0; it < ITS; ++it) {
+    const int k = it * 256 + lane * 4, kc = k < K ? k : 0;     // unconditional loads from a clamped index
+#pragma unroll
+    for (int m = 0; m < M; ++m) xv[m][it] = *(const f32x4*)(x + (size_t)m * ldx + kc);
+    if (NORM) g[it] = *(const f32x4*)(gain + kc);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float* row = EPI == EPI_SWIGLU ? (r < 2 ? W : W2) + (size_t)min(n0 + (r & 1), N - 1) * K : W + (size_t)min(n0 + r, N - 1) * K;
+      w[r][it] = *(const f32x4*)(row + kc);
+    }
+  }
+  const int my_idx = lane >> (6 - LOGV);             // value this lane owns after the reduction
+  const int my_r = my_idx >> PadRows<M>::SH, my_m = my_idx & (MP - 1);
+  const bool owner = (lane & ((64 >> LOGV) - 1)) == 0 && my_m < M && n0 + my_r < N && (EPI != EPI_SWIGLU || my_r < 2);
+  float* dst = y + (size_t)(my_m < M ? my_m : 0) * ldy + min(n0 + my_r, N - 1);
+  float res = 0.f;
+  if (EPI == EPI_RESID) res = *dst;
+#pragma unroll
+  for (int it = 0; it < ITS; ++it)
+    if (it * 256 + lane * 4 >= K) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) w[r][it] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int m = 0; m < M; ++m) xv[m][it] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  float rs = 1.f;
+  if (NORM) {
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      float ss = 0.f;
+#pragma unroll
+      for (int it = 0; it < ITS; ++it) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ss += xv[m][it][e] * xv[m][it][e];
+        xv[m][it] *= g[it];
+      }
+      ss = wave_sum(ss);
+      rs = my_m == m ? ss : rs;
+    }
+    rs = rsqrtf(rs / (float)K + eps);
+  }
+  float acc[V];
+#pragma unroll
+  for (int i = 0; i < V; ++i) acc[i] = 0.f;
+#pragma unroll
+  for (int it = 0; it < ITS; ++it)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int m = 0; m < M; ++m)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[r * MP + m] += w[r][it][e] * xv[m][it][e];
+  const float tot = wave_reduce_multi<V>(acc, lane) * rs;
+  if (EPI == EPI_SWIGLU) {
+    // the lower half of the wave holds the gate sums of outputs n0, n0 + 1, the upper one the up sums
+    const float up = halves<32>(tot, tot).y;         // lower lanes: the upper ones' values
+    if (owner) *dst = tot / (1.0f + __expf(-tot)) * up;
+  } else if (EPI == EPI_RESID) {
+    if (owner) *dst = res + tot;
+  } else if (owner) {
+    *dst = tot;
+  }
+  if (EPI == EPI_LOGITS) {
+    __shared__ unsigned long long best_s[4][MP];
+    // the wave's best of row my_m: its four outputs sit in the lanes my_m apart by MP groups
+    unsigned long long best = owner ? argmax_key(tot, n0 + my_r) : 0ull;
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      const unsigned long long b = wave_max_key(my_m == m ? best : 0ull);
+      if (lane == 0) best_s[wave][m] = b;
+    }
+    __syncthreads();
+    if (threadIdx.x < M) {
+      const int m = threadIdx.x;
+      const unsigned long long a = best_s[0][m] > best_s[1][m] ? best_s[0][m] : best_s[1][m], b = best_s[2][m] > best_s[3][m] ? best_s[2][m] : best_s[3][m];
+      const unsigned long long best_m = a > b ? a : b;
+      if (best_m != 0ull) atomicMax(amax + (size_t)(blockIdx.x % AMAX_CELLS) * amax_ld + blockIdx.y * M + m, best_m);
+    }
   }
 }
 

@@ -400,10 +400,10 @@ __global__ void __launch_bounds__(64 * NWT) gemv_mfma_kernel(const bf16_t* W_, c
     }
     if (EPI == EPI_RESID) {
       // sum of squares of the tile's 16 outputs of column c: its 16 neighbouring lanes (inactive ones hold 0)
-      hsq += __shfl_xor(hsq, 1, 64);
-      hsq += __shfl_xor(hsq, 2, 64);
-      hsq += __shfl_xor(hsq, 4, 64);
-      hsq += __shfl_xor(hsq, 8, 64);
+      hsq += lane_dpp<kDppQuad1>(hsq);
+      hsq += lane_dpp<kDppQuad2>(hsq);
+      hsq += lane_dpp<kDppHalfMirror>(hsq);      // the quads hold one value each by now
+      hsq += lane_dpp<kDppRor8>(hsq);
       if (row == 0 && c < M) a.ssp_next[(size_t)tile * a.ssp_ld + c] = hsq;
     }
   }

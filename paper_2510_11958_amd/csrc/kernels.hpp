@@ -104,16 +104,52 @@ template <> struct Elem<bf16_t> {
   }
 };
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+// Exchanges between lanes without LDS (a shuffle is a round trip to the LDS unit, about 100 cycles of latency; these are
+// register instructions of 4 to 8).  lane_dpp: the DPP controls row_ror:n (0x120 + n, rotation within 16 lanes), row_half_mirror (0x141,
+// lane ^ 7) and quad_perm.  halves32 / halves16 return {the lower 32 (16 of each 32) lanes of a, those of b in the upper ones' place} and
+// {the upper lanes of a in the lower ones' place, those of b}: the sum of the two is one step of a butterfly over two values, and with a = b
+// a lane and its partner lane ^ 32 (^ 16).
+constexpr int kDppQuad1 = 0xB1, kDppQuad2 = 0x4E, kDppHalfMirror = 0x141, kDppRor4 = 0x124, kDppRor8 = 0x128;
+template <int CTRL> __device__ __forceinline__ uint32_t lane_dpp(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false); }
+template <int CTRL> __device__ __forceinline__ float lane_dpp(float v) { return __uint_as_float(lane_dpp<CTRL>(__float_as_uint(v))); }
+template <int CTRL> __device__ __forceinline__ unsigned long long lane_dpp(unsigned long long v) {
+  return ((unsigned long long)lane_dpp<CTRL>((uint32_t)(v >> 32)) << 32) | lane_dpp<CTRL>((uint32_t)v);
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+template <typename T> struct LanePair { T x, y; };
+template <int O> __device__ __forceinline__ LanePair<uint32_t> halves(uint32_t a, uint32_t b) {      // O: 32 or 16
+  if constexpr (O == 32) { const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false); return {r[0], r[1]}; }
+  else { const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false); return {r[0], r[1]}; }
 }
+template <int O> __device__ __forceinline__ LanePair<float> halves(float a, float b) {
+  const LanePair<uint32_t> r = halves<O>(__float_as_uint(a), __float_as_uint(b));
+  return {__uint_as_float(r.x), __uint_as_float(r.y)};
+}
+template <int O> __device__ __forceinline__ LanePair<unsigned long long> halves(unsigned long long a, unsigned long long b) {
+  const LanePair<uint32_t> h = halves<O>((uint32_t)(a >> 32), (uint32_t)(b >> 32)), l = halves<O>((uint32_t)a, (uint32_t)b);
+  return {((unsigned long long)h.x << 32) | l.x, ((unsigned long long)h.y << 32) | l.y};
+}
+// f over the 64 lanes (commutative; every lane gets the result), in the order of a butterfly over 32, 16, 8, 4, 2, 1: behind the step
+// over 8 the values repeat every 8 lanes, so the rotation by 4 is the exchange with lane ^ 4.
+template <typename T, typename F> __device__ __forceinline__ T wave_reduce(T v, F f) {
+  LanePair<T> p = halves<32>(v, v);
+  v = f(p.x, p.y);
+  p = halves<16>(v, v);
+  v = f(p.x, p.y);
+  v = f(v, lane_dpp<kDppRor8>(v));
+  v = f(v, lane_dpp<kDppRor4>(v));
+  v = f(v, lane_dpp<kDppQuad2>(v));
+  return f(v, lane_dpp<kDppQuad1>(v));
+}
+__device__ __forceinline__ float wave_sum(float v) { return wave_reduce(v, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); }); }
+__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long key) {
+  return wave_reduce(key, [](unsigned long long a, unsigned long long b) { return a > b ? a : b; });
+}
+// over a lane and its partner lane ^ O (32 or 16); column_*: over the four lanes of a column of a 16-wide matrix-core result
+template <int O> __device__ __forceinline__ float pair_sum(float v) { const LanePair<float> p = halves<O>(v, v); return p.x + p.y; }
+template <int O> __device__ __forceinline__ float pair_max(float v) { const LanePair<float> p = halves<O>(v, v); return fmaxf(p.x, p.y); }
+__device__ __forceinline__ float column_sum(float v) { return pair_sum<32>(pair_sum<16>(v)); }
+__device__ __forceinline__ float column_max(float v) { return pair_max<32>(pair_max<16>(v)); }
 
 // ---------------------------------------------------------------- small kernels
 
@@ -203,11 +239,7 @@ __global__ void __launch_bounds__(1024) finish_step_kernel(DevState* st, unsigne
       best = amax[(size_t)lane * amax_ld + b];
       amax[(size_t)lane * amax_ld + b] = 0ull;
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const unsigned long long other = __shfl_xor(best, o, 64);
-      if (other > best) best = other;
-    }
+    best = wave_max_key(best);
     if (lane == 0 && write_tokens) {
       const int tok = argmax_key_index(best);
       emitted[step * batch + b] = tok;
@@ -308,14 +340,6 @@ __device__ __forceinline__ unsigned long long draw_base(const SampleCfg* cfg, co
   const unsigned long long seed = ((unsigned long long)cfg->seed_hi << 32) | cfg->seed_lo;
   const unsigned long long stream = ((unsigned long long)(unsigned int)b << 32) | (unsigned int)(st->n_tok + seq_info(st)[b].delta);
   return splitmix_mix(splitmix_mix(seed + 0x9E3779B97F4A7C15ull) ^ (stream * 0xD6E8FEB86659FD93ull));
-}
-__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long key) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned long long other = __shfl_xor(key, o, 64);
-    if (other > key) key = other;
-  }
-  return key;
 }
 
 // Token selection by sampling, after the LM head: the row at position st->n_tok of sequence b draws its token from

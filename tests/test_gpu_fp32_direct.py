@@ -1,0 +1,43 @@
+"""GPU parity of the fp32 kernels at the edges of their sizes: projection rows of one to four chunks of 256 values and beyond (whole and
+ragged chunks, outputs that do not fill a wave's four), 1 to 4 activation rows and groups of them; attention rows of 16 lanes for
+both head sizes, queries per KV head from 1 to 16, one range and several, and more rows than a block prepares at a time.
+
+Tolerance: that of the other fp32 parity tests, 1e-4 of the largest logit (sums in another order: 3e-7 measured).
+"""
+import numpy as np
+import pytest
+
+import dmtd_inputs as di
+from parity_util import Pair
+
+pytestmark = pytest.mark.gpu
+
+S = di.ModelShape
+CASES = {
+    # name: (layers, hidden, query heads, KV heads, head dim, SwiGLU width, vocabulary), batch, prompt, tau
+    "k8_16": ((2, 8, 1, 1, 64, 16, 33), 1, 3, 3),
+    "k256_768": ((3, 256, 4, 2, 64, 768, 1024), 1, 33, 4),
+    "k200_264": ((2, 200, 2, 1, 128, 264, 130), 1, 7, 2),
+    "k264_512_rows_8": ((2, 264, 8, 8, 64, 512, 131), 2, 6, 4),
+    "k520_776_gq3": ((2, 520, 6, 2, 64, 776, 259), 3, 5, 2),
+    "k1024_1032_gq16": ((2, 1024, 16, 1, 64, 1032, 130), 1, 5, 3),
+    "k1032_1024_gq5_hd128": ((2, 1032, 10, 2, 128, 1024, 130), 1, 9, 5),
+    "ranges_hd64": ((2, 64, 4, 1, 64, 96, 130), 1, 500, 3),
+    "ranges_hd128_rows_2_4": ((2, 64, 8, 4, 128, 96, 130), 2, 300, 2),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_fp32_sizes_against_the_oracle(name):
+    dims, batch, n, tau = CASES[name]
+    sh, steps = S(*dims, dtype="fp32"), 2 * tau + 1
+    blob = di.make_weight_blob(sh, seed=3, std=0.05, gain_sigma=0.2)
+    prompts = di.make_prompts(sh.vocab, batch, n, seed=5)
+    cont = di.make_continuation(sh.vocab, batch, n + steps + 2, seed=1001)
+    toks = [np.concatenate([prompts[b], cont[b]])[:n + steps + 2] for b in range(batch)]
+    p = Pair(sh, blob, n + steps + 2, batch=batch)
+    p.prefill(prompts)
+    for _ in range(steps):
+        p.step_forced(tau, 1, toks)
+    assert p.worst < 1e-4, p.worst
+    p.compare_kv(1e-5)
