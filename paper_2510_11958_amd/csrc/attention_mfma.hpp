@@ -72,17 +72,21 @@ __device__ __forceinline__ void attn_load_vec(const QkvSrc& q, int row_g, int co
     pa[ks] = *(const fvec_t*)p; pb[ks] = *(const fvec_t*)(p + half);
   }
   float ss = 0.f;
-  for (int p0 = 0; p0 < q.n_parts; p0 += 64) {
-    float sp[4];
+  auto sum_parts = [&](int p0, auto n_c) {      // 16 n of the producer's parts: one per lane, n loads in flight
+    constexpr int n = decltype(n_c)::value;
+    float sp[n];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < n; ++j) {
       const int pi = p0 + l + 16 * j;
       sp[j] = q.ssp[(size_t)(pi < q.n_parts ? pi : q.n_parts - 1) * q.ssp_ld + row_g];
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < n; ++j)
       if (p0 + l + 16 * j < q.n_parts) ss += sp[j];
-  }
+  };
+  if (q.n_parts <= 16) sum_parts(0, std::integral_constant<int, 1>());            // behind a finishing launch or the embedding
+  else
+    for (int p0 = 0; p0 < q.n_parts; p0 += 64) sum_parts(p0, std::integral_constant<int, 4>());
   const float rs = rsqrtf(row16_sum(ss) * q.inv_k + q.eps);
   fvec_t sa = pa[0], sb = pb[0];
 #pragma unroll

@@ -170,23 +170,33 @@ __global__ void __launch_bounds__(64 * gemm_waves(CG, EPI)) gemm_mfma_kernel(
 
   if (NORM && !SPLITK) {
     // the rows' 1/rms while the first weights are on their way: wave w takes rows w, w + waves, ..., its lanes the producer's
-    // partial sums of squares, four loads per lane in flight (one thread per row walking all parts in turn cost every block
+    // partial sums of squares, those of up to four rows in flight (one thread per row walking all parts in turn cost every block
     // of the LM head ~160 dependent loads in its epilogue: 210 us per launch in the step against 147 with a single part)
-    for (int m = w; m < M; m += GEMM_WAVES) {
-      float sacc = 0.f;
+    constexpr int RM = BM / GEMM_WAVES < 4 ? BM / GEMM_WAVES : 4;
+    for (int m0 = w; m0 < M; m0 += RM * GEMM_WAVES) {
+      float sacc[RM];
+#pragma unroll
+      for (int u = 0; u < RM; ++u) sacc[u] = 0.f;
       for (int p0 = 0; p0 < a.n_parts; p0 += 256) {
-        float v4[4];
+        float v[RM][4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int p = p0 + lane + 64 * j;
-          v4[j] = a.ssp[(size_t)(p < a.n_parts ? p : a.n_parts - 1) * a.ssp_ld + m];
-        }
+        for (int u = 0; u < RM; ++u)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (p0 + lane + 64 * j < a.n_parts) sacc += v4[j];
+          for (int j = 0; j < 4; ++j) {
+            const int p = p0 + lane + 64 * j;
+            v[u][j] = a.ssp[(size_t)(p < a.n_parts ? p : a.n_parts - 1) * a.ssp_ld + min(m0 + u * GEMM_WAVES, M - 1)];
+          }
+#pragma unroll
+        for (int u = 0; u < RM; ++u)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (p0 + lane + 64 * j < a.n_parts) sacc[u] += v[u][j];
       }
-      sacc = wave_sum(sacc);
-      if (lane == 0) rs_s[m] = rsqrtf(sacc / (float)K + a.eps);
+#pragma unroll
+      for (int u = 0; u < RM; ++u) {
+        const float s = wave_sum(sacc[u]);
+        if (lane == 0 && m0 + u * GEMM_WAVES < M) rs_s[m0 + u * GEMM_WAVES] = rsqrtf(s / (float)K + a.eps);
+      }
     }
   }
 
