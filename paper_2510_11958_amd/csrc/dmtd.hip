@@ -903,10 +903,17 @@ hipError_t embed_rows(dmtd_ctx* c, Rows& R, int sel, int offset, int r, int next
   const dmtd_config& cf = c->cfg;
   const int rows = c->batch * r;
   if (c->packed) {
-    hipLaunchKernelGGL(embed_pack_kernel, dim3(rows), dim3(256), 0, c->stream, (const bf16_t*)c->embed, dev_tokens(c),
-                       cf.max_seq_len, dev_state(c), sel, offset, r, cf.hidden, R.h, (const bf16_t*)norm_gain_for_layer(c, next_layer),
-                       R.xb, R.xb_lo, R.ssp, c->fmap, blocked_rows(c, rows));
-    R.n_parts = 1;
+    // a prefill pass has few blocks of 16 rows: its columns in four parts; a step's late rows may come from the front layers too, in one
+    const int parts = blocked_rows(c, rows) && sel == POS_EXPLICIT ? 4 : 1;
+    if (blocked_rows(c, rows))
+      hipLaunchKernelGGL(embed_pack_blocked_kernel, dim3((rows + 15) / 16, parts), dim3(256), 0, c->stream, (const bf16_t*)c->embed, dev_tokens(c),
+                         cf.max_seq_len, dev_state(c), sel, offset, r, cf.hidden, R.h, (const bf16_t*)norm_gain_for_layer(c, next_layer),
+                         R.xb, R.xb_lo, R.ssp, c->ssp_ld, c->fmap, rows);
+    else
+      hipLaunchKernelGGL(embed_pack_kernel, dim3(rows), dim3(256), 0, c->stream, (const bf16_t*)c->embed, dev_tokens(c),
+                         cf.max_seq_len, dev_state(c), sel, offset, r, cf.hidden, R.h, (const bf16_t*)norm_gain_for_layer(c, next_layer),
+                         R.xb, R.xb_lo, R.ssp, c->fmap);
+    R.n_parts = parts;
   } else {
     hipLaunchKernelGGL(embed_kernel<float>, dim3(rows), dim3(256), 0, c->stream, (const float*)c->embed, dev_tokens(c),
                        cf.max_seq_len, dev_state(c), sel, offset, r, cf.hidden, R.h, c->fmap);

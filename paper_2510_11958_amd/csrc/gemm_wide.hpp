@@ -346,7 +346,9 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
 // Second stage of the tiles whose K was split over blocks (and of every residual tile): epilogue(sum of the parts, in order).  A
 // block takes 16 rows of a tile, a wave 16 rows x 32 outputs at a time: lane (row = lane % 16, chunk = lane / 16) has 8
 // consecutive outputs, so a wave writes 1 KiB of contiguous blocked layout per plane.  (Row by row, 4 outputs per thread, the
-// blocked stores are 16-byte pieces: 38 us for 2048 x 2560 from 3 parts.)
+// blocked stores are 16-byte pieces: 38 us for 2048 x 2560 from 3 parts.)  With 2048 rows memory bounds it (126 MB in 25 us); with a few
+// hundred the round trips do, so every load is issued ahead of the first sum (us, one round of 4 parts of a group at a time / now: residual,
+// 256 rows of 1024 10.2 / 8.6, 1003 rows of 2560 20.6 / 19.3, gate/up 2048 rows 15.8 / 12.0, QKV 13.3 / 10.1).
 template <int EPI, bool NORM, int BM>
 __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part_, int M_, int N_, int n_full_, int n_tail_, int ksplit_, int mt_, int nt_,
                                                                MfmaArgs a) {
@@ -361,45 +363,70 @@ __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part
   const bool act = m < M;
   const int mc = act ? m : M - 1;
   constexpr int GROUPS = EPI == EPI_SWIGLU ? 1 : 2;      // groups of 32 outputs per wave
-  constexpr int PRE = 4;                                 // parts fetched at once
+  constexpr int PRE = EPI == EPI_RESID ? 6 : 4;          // parts of every group fetched at once
   const size_t step = (size_t)n_tail_ * PART;
+  float ssv[4];                                          // the row's partial sums of squares, 16 of them up front
+  if (NORM)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) ssv[j] = a.ssp[(size_t)min((lane >> 4) + 4 * j, a.n_parts - 1) * a.ssp_ld + mc];
+  float hsq = 0.f;
+  // all loads of all groups first: the residual rows, the gains, and up to PRE parts (a group beyond N repeats the first)
+  const int c0 = nb * (EPI == EPI_SWIGLU ? 128 : GW_BN);
+  f32x4 sum[GROUPS][2], sum2[1][2], res[GROUPS][2];
+  u32x4 gain[GROUPS];
+  const float* src[GROUPS];
+#pragma unroll
+  for (int gi = 0; gi < GROUPS; ++gi) {
+    const int lg = (w * GROUPS + gi) * 32, lc = (c0 + lg < N ? lg : 0) + c8;
+    src[gi] = part_ + (size_t)blockIdx.x * PART + (size_t)r * GW_BN + lc;
+    sum[gi][0] = sum[gi][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (EPI == EPI_RESID) {
+      res[gi][0] = *(const f32x4*)(a.y + (size_t)mc * a.ldy + c0 + lc);
+      res[gi][1] = *(const f32x4*)(a.y + (size_t)mc * a.ldy + c0 + lc + 4);
+      gain[gi] = *(const u32x4*)(a.g_next + c0 + lc);
+    }
+  }
+  sum2[0][0] = sum2[0][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto add_parts = [&](int k0, auto n_c) {
+    constexpr int n = decltype(n_c)::value;
+    f32x4 x[GROUPS][n][2], z[EPI == EPI_SWIGLU ? n : 1][2];
+#pragma unroll
+    for (int gi = 0; gi < GROUPS; ++gi)
+#pragma unroll
+      for (int k = 0; k < n; ++k) {
+        const float* q = src[gi] + (size_t)(k0 + k) * step;
+        x[gi][k][0] = *(const f32x4*)q; x[gi][k][1] = *(const f32x4*)(q + 4);
+        if (EPI == EPI_SWIGLU) { z[k][0] = *(const f32x4*)(q + 128); z[k][1] = *(const f32x4*)(q + 132); }
+      }
+#pragma unroll
+    for (int gi = 0; gi < GROUPS; ++gi)
+#pragma unroll
+      for (int k = 0; k < n; ++k) {
+        sum[gi][0] += x[gi][k][0]; sum[gi][1] += x[gi][k][1];
+        if (EPI == EPI_SWIGLU) { sum2[0][0] += z[k][0]; sum2[0][1] += z[k][1]; }
+      }
+  };
+  int k0 = 0;
+  for (; k0 + PRE <= ksplit_; k0 += PRE) add_parts(k0, std::integral_constant<int, PRE>());
+  static_for<1, PRE>([&](auto n) {
+    if (ksplit_ - k0 == decltype(n)::value) add_parts(k0, n);
+  });
   float rs = 1.f;
   if (NORM) {
     float ss = 0.f;
-    for (int p = lane >> 4; p < a.n_parts; p += 4) ss += a.ssp[(size_t)p * a.ssp_ld + mc];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) ss += (lane >> 4) + 4 * j < a.n_parts ? ssv[j] : 0.f;
+    for (int p = (lane >> 4) + 16; p < a.n_parts; p += 4) ss += a.ssp[(size_t)p * a.ssp_ld + mc];
     ss = column_sum(ss);
     rs = rsqrtf(ss / (float)a.K + a.eps);
   }
-  float hsq = 0.f;
 #pragma unroll
   for (int gi = 0; gi < GROUPS; ++gi) {
-    const int lc = (w * GROUPS + gi) * 32 + c8;                              // output inside the tile
-    const int n = nb * (EPI == EPI_SWIGLU ? 128 : GW_BN) + lc;
+    const int n = c0 + (w * GROUPS + gi) * 32 + c8;
     if (n - c8 >= N) continue;                                               // N is a multiple of 64 here: whole groups
-    const float* p = part_ + (size_t)blockIdx.x * PART + (size_t)r * GW_BN + lc;
-    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0, u0 = s0, u1 = s0;
-    f32x4 h0 = s0, h1 = s0;
-    u32x4 graw = {0, 0, 0, 0};
-    if (EPI == EPI_RESID) {
-      h0 = *(const f32x4*)(a.y + (size_t)mc * a.ldy + n);
-      h1 = *(const f32x4*)(a.y + (size_t)mc * a.ldy + n + 4);
-      graw = *(const u32x4*)(a.g_next + n);
-    }
-    for (int k0 = 0; k0 < ksplit_; k0 += PRE) {
-      f32x4 x0[PRE], x1[PRE], z0[PRE], z1[PRE];
-#pragma unroll
-      for (int k = 0; k < PRE; ++k) {
-        const float* q = p + (size_t)min(k0 + k, ksplit_ - 1) * step;
-        x0[k] = *(const f32x4*)q; x1[k] = *(const f32x4*)(q + 4);
-        if (EPI == EPI_SWIGLU) { z0[k] = *(const f32x4*)(q + 128); z1[k] = *(const f32x4*)(q + 132); }
-      }
-#pragma unroll
-      for (int k = 0; k < PRE; ++k)
-        if (k0 + k < ksplit_) {
-          s0 += x0[k]; s1 += x1[k];
-          if (EPI == EPI_SWIGLU) { u0 += z0[k]; u1 += z1[k]; }
-        }
-    }
+    const f32x4 s0 = sum[gi][0], s1 = sum[gi][1], u0 = sum2[0][0], u1 = sum2[0][1];
+    f32x4 h0 = res[gi][0], h1 = res[gi][1];
+    const u32x4 graw = gain[gi];
     float v[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
     if (EPI == EPI_STORE) {
       if (act) {

@@ -451,7 +451,7 @@ __device__ __forceinline__ void pack_row_for_norm(const float* __restrict__ h, c
 __global__ void __launch_bounds__(256) embed_pack_kernel(
     const bf16_t* __restrict__ table, const int* __restrict__ tokens, int s_max, const DevState* st, int sel, int offset,
     int r, int d, float* __restrict__ h, const bf16_t* __restrict__ gain, bf16_t* __restrict__ xb, bf16_t* __restrict__ xb_lo,
-    float* __restrict__ ssp, const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot */, int blocked) {
+    float* __restrict__ ssp, const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot */) {
   // One pass, 8 elements (16 bytes of the table row) per thread and turn, up to NCH turns' loads in flight at once;
   // the row's values stay in registers between the fp32 store, the packed store and the sum of squares.
   constexpr int NCH = 4;
@@ -491,7 +491,7 @@ __global__ void __launch_bounds__(256) embed_pack_kernel(
         }
         *(f32x4*)(dst + (size_t)c * 8) = f32x4{v[0], v[1], v[2], v[3]};
         *(f32x4*)(dst + (size_t)c * 8 + 4) = f32x4{v[4], v[5], v[6], v[7]};
-        const size_t at = packed_at(blocked, row, c * 8, d);
+        const size_t at = (size_t)row * d + c * 8;
         *(u32x4*)(xb + at) = u32x4{hi[0], hi[1], hi[2], hi[3]};
         *(u32x4*)(xb_lo + at) = u32x4{lo[0], lo[1], lo[2], lo[3]};
       }
@@ -501,6 +501,65 @@ __global__ void __launch_bounds__(256) embed_pack_kernel(
   if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = ss;
   __syncthreads();
   if (threadIdx.x == 0) ssp[row] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+}
+
+// The same for passes whose packed rows are in blocks of 16 x 32: a block takes 16 rows and a part of the columns (blockIdx.y; a partial sum
+// of squares each), a wave 32 columns of all 16 rows at a time,
+// lane (row = lane % 16, chunk = lane / 16), so that its packed stores are 1 KiB of contiguous memory (row by row they are 16-byte
+// pieces; us for 2048 / 1003 rows of 2560, row by row 33.5 / 18, here 15.6 / 11.2; bound by memory, 42 MB written for 2048).
+__global__ void __launch_bounds__(256) embed_pack_blocked_kernel(
+    const bf16_t* __restrict__ table, const int* __restrict__ tokens, int s_max, const DevState* st, int sel, int offset,
+    int r, int d, float* __restrict__ h, const bf16_t* __restrict__ gain, bf16_t* __restrict__ xb, bf16_t* __restrict__ xb_lo,
+    float* __restrict__ ssp, int ssp_ld, const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot */, int rows) {
+  constexpr int NCH = 4;                         // turns whose loads are in flight at once
+  __shared__ float wsum[4][16];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int row = blockIdx.x * 16 + (lane & 15), rc = min(row, rows - 1), c8 = (lane >> 4) * 8;
+  const int b = fmap ? fmap[rc / r] : rc / r;
+  const int i = fmap ? min(rc % r, live_rows(st, b, r) - 1) : rc % r;      // a dead row repeats the newest one
+  const int pos = row_base(st, sel, offset, b) + i;
+  const bf16_t* src = table + (size_t)tokens[(size_t)b * s_max + pos] * d + c8;
+  float* dst = h + (size_t)rc * d + c8;
+  const int g_all = d >> 5, g_hi = g_all * ((int)blockIdx.y + 1) / (int)gridDim.y;      // d is a multiple of 64 on this path
+  float ss = 0.f;
+  for (int g0 = g_all * (int)blockIdx.y / (int)gridDim.y + w; g0 < g_hi; g0 += 4 * NCH) {
+    u32x4 tv[NCH], gv[NCH];
+#pragma unroll
+    for (int u = 0; u < NCH; ++u) {
+      const int c = (g0 + u * 4 < g_hi ? g0 + u * 4 : g0) * 32;
+      tv[u] = *(const u32x4*)(src + c);
+      gv[u] = *(const u32x4*)(gain + c8 + c);
+    }
+#pragma unroll
+    for (int u = 0; u < NCH; ++u) {
+      const int c = (g0 + u * 4) * 32;
+      if (g0 + u * 4 < g_hi && row < rows) {
+        float v[8], g[8];
+        Elem<bf16_t>::unpack(tv[u], v);
+        Elem<bf16_t>::unpack(gv[u], g);
+        uint32_t hi[4], lo[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x = v[2 * e] * g[2 * e], y = v[2 * e + 1] * g[2 * e + 1];
+          hi[e] = pack_bf16x2(x, y);
+          lo[e] = pack_bf16x2(x - __uint_as_float(hi[e] << 16), y - __uint_as_float(hi[e] & 0xFFFF0000u));
+          ss += v[2 * e] * v[2 * e] + v[2 * e + 1] * v[2 * e + 1];
+        }
+        *(f32x4*)(dst + c) = f32x4{v[0], v[1], v[2], v[3]};
+        *(f32x4*)(dst + c + 4) = f32x4{v[4], v[5], v[6], v[7]};
+        const size_t at = packed_at(1, row, c + c8, d);
+        *(u32x4*)(xb + at) = u32x4{hi[0], hi[1], hi[2], hi[3]};
+        *(u32x4*)(xb_lo + at) = u32x4{lo[0], lo[1], lo[2], lo[3]};
+      }
+    }
+  }
+  ss = column_sum(ss);
+  if (lane < 16) wsum[w][lane] = ss;
+  __syncthreads();
+  if (threadIdx.x < 16 && row < rows) {
+    const int m = threadIdx.x;
+    ssp[(size_t)blockIdx.y * ssp_ld + row] = wsum[0][m] + wsum[1][m] + wsum[2][m] + wsum[3][m];
+  }
 }
 
 __global__ void __launch_bounds__(256) take_last_pack_kernel(
