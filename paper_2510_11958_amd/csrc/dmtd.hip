@@ -480,7 +480,7 @@ WidePlan plan_wide(const dmtd_config& cf, int num_cus, int rows, int nt, int KS)
   auto parts_us = [&](int ks) { return left * ks * (GwTile<BM>::PART * 4) / 3.5e6 + 5.0; };
   WidePlan p{round_us(1) + (EPI == EPI_RESID ? parts_us(1) : 0.0), EPI == EPI_RESID ? 0 : tiles, 1};
   if (EPI == EPI_RESID && left > part_tiles) p.us = 1e30;            // the raw sums do not fit
-  if (EPI != EPI_LOGITS)
+  if (EPI != EPI_LOGITS && EPI != EPI_NLL)
     for (int ks = 2; ks <= kGemmMaxSplit && ks * 4 <= KS && left > 0 && (long)left * ks <= part_tiles; ++ks) {      // at least 8 steps per part
       const double us = round_us(ks) + parts_us(ks);
       if (us < p.us * 0.97) p = WidePlan{us, whole, ks};
@@ -501,7 +501,7 @@ hipError_t launch_wide_tiles(dmtd_ctx* c, const MfmaArgs& g, int nt, const WideP
   }
   hipLaunchKernelGGL(kern, dim3(p.n_full + n_tail * p.ksplit), dim3(64 * GW_WAVES), GwTile<BM>::LDS, c->stream, g.W, g.W2, g.xb, g.xb_lo,
                      g.M, g.N, g.K, p.n_full, n_tail, p.ksplit, mt, nt, g);
-  if constexpr (EPI != EPI_LOGITS) {
+  if constexpr (EPI != EPI_LOGITS && EPI != EPI_NLL) {
     if (n_tail > 0)
       hipLaunchKernelGGL((gemm_wide_finish_kernel<EPI, NORM, BM>), dim3(n_tail, BM / 16), dim3(256), 0, c->stream, (const float*)g.part,
                          g.M, g.N, p.n_full, n_tail, p.ksplit, mt, nt, g);
@@ -1441,6 +1441,37 @@ hipError_t enqueue_masked_head(dmtd_ctx* c, const Rows& R, int m0 /* a multiple 
   return hipGetLastError();
 }
 
+// The same for all rows of a chunk that went through the wide GEMM, without their logits: the LM head's tiles leave per row what the loss and
+// the greedy choice need (EPI_NLL).  Against 512 rows of logits at a time and a launch
+// that reads them again (2046 rows, 2560 wide, 152k entries): four times 781 + 67 us before, 2741 + 12 now: no logits written, the weights read once, and
+// 4752 tiles in 19 rounds of the chip where 1188 took 5.
+// The results live in the layers' scratch, like the logits do; false: they do not fit (a vocabulary of a few entries).
+bool masked_nll_fits(const dmtd_ctx* c, int rows) {
+  const dmtd_config& cf = c->cfg;
+  const size_t nt = (size_t)(cf.vocab + GW_BN - 1) / GW_BN, ld = ((size_t)rows + 15) / 16 * 16;
+  return blocked_rows(c, rows) && ld * (nt * GwTile<128>::WN * sizeof(float2) + 16) <= (size_t)head_row_capacity(cf, c->wide_rows) * cf.vocab * 4;
+}
+hipError_t enqueue_masked_nll(dmtd_ctx* c, const Rows& R, int rows, int p0, int r, int n) {
+  const dmtd_config& cf = c->cfg;
+  const WideChoice w = choose_wide<EPI_NLL>(cf, c->num_cus, rows, cf.vocab, cf.hidden);
+  const int ld = (rows + 15) / 16 * 16, n_parts = w.nt * (w.bm == 128 ? GwTile<128>::WN : GwTile<256>::WN);
+  char* base = c->ws + c->o.logits_rows;
+  float2* part = (float2*)base;
+  unsigned long long* keys = (unsigned long long*)(part + (size_t)n_parts * ld);
+  float* zt = (float*)(keys + ld);
+  int* target = (int*)(zt + ld);
+  hipLaunchKernelGGL(nll_targets_kernel, dim3((rows + 255) / 256), dim3(256), 0, c->stream, (const int*)dev_tokens(c), cf.max_seq_len, rows, p0, r, n, target, keys);
+  MfmaArgs a{};
+  a.W = c->lm_head_sw; a.xb = R.xb; a.xb_lo = R.xb_lo; a.ldxb = cf.hidden; a.M = rows; a.N = cf.vocab; a.K = cf.hidden; a.ssp = R.ssp; a.n_parts = R.n_parts;
+  a.ssp_ld = c->ssp_ld; a.eps = cf.rms_eps; a.blocked = 1;
+  a.part = (float*)part; a.ldp = ld; a.amax = keys; a.ssp_next = zt; a.g_next = (const bf16_t*)target;
+  const hipError_t e = w.bm == 128 ? launch_wide_tiles<EPI_NLL, true, 128>(c, a, w.nt, w.p) : launch_wide_tiles<EPI_NLL, true, 256>(c, a, w.nt, w.p);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(nll_merge_kernel, dim3((rows + 7) / 8), dim3(256), 0, c->stream, (const float2*)part, n_parts, ld, (const int*)target, (const float*)zt,
+                     (const unsigned long long*)keys, cf.max_seq_len, rows, p0, r, (float*)(c->ws + c->o.nll), (int*)(c->ws + c->o.best));
+  return hipGetLastError();
+}
+
 // One launch of one kernel kind on layer l, for dmtd_time_kernel.  Outputs go to scratch
 // buffers only (never the late rows, the caches, the token history or the scheduler state).
 hipError_t time_one(dmtd_ctx* c, int kind, int l, int rows) {
@@ -2258,6 +2289,10 @@ int dmtd_masked_forward(dmtd_ctx* c, const int32_t* tokens, int32_t batch, int32
     Rows R = front_rows(c);
     e = enqueue_masked_chunk(c, R, p0, r, n_late);
     const int rows = batch * r, head = head_row_capacity(cf, c->wide_rows);
+    if (!logits && masked_nll_fits(c, rows)) {
+      if (e == hipSuccess) e = enqueue_masked_nll(c, R, rows, p0, r, n);
+      continue;
+    }
     for (int m0 = 0; m0 < rows && e == hipSuccess; m0 += head) {
       const int m1 = std::min(rows, m0 + head);
       e = enqueue_masked_head(c, R, m0, m1 - m0, p0, r, n);

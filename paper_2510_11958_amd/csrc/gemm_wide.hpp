@@ -68,7 +68,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
                                                                 int M_, int N_, int K_, int n_full_, int n_tail_, int ksplit_, int mt_, int nt_, MfmaArgs a) {
   // which operand gives the result's rows: with the weights there a lane holds 4 consecutive outputs of one activation row (8-byte
   // pieces of the blocked layout, 512 contiguous bytes per two row groups and store), else 16 rows of one output (128 bytes of a row)
-  constexpr bool WA = EPI == EPI_SWIGLU;
+  constexpr bool WA = EPI == EPI_SWIGLU || EPI == EPI_NLL;
   typedef GwTile<BM> T;
   constexpr int NJ = T::NJ;
   extern __shared__ float4 gemm_dyn_smem[];
@@ -274,7 +274,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
 
   // lane (column n = lane % 32 of a weight tile): element e of acc[i][j] is row 32 i + 8 (e / 4) + 4 (lane / 32) + e % 4 of the wave
   const int m_w = mb * BM + wm * 64, m_l = 4 * (lane >> 5), col = lane & 31;
-  if (EPI != EPI_LOGITS && pl.tail) {
+  if (EPI != EPI_LOGITS && EPI != EPI_NLL && pl.tail) {
     // raw sums [BM rows][256 outputs] (SwiGLU: 128 gate, 128 up) of this part of K, for the finishing kernel
     float* part = a.part + ((size_t)pl.ks * n_tail_ + (pl.t - n_full_)) * T::PART + (size_t)(wm * 64) * GW_BN;
 #pragma unroll
@@ -295,6 +295,73 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
   if (EPI == EPI_LOGITS && tid < BM) key_s[tid] = 0ull;
   __syncthreads();
   const int r_w = wm * 64 + m_l;
+  if constexpr (EPI == EPI_NLL) {
+    // What the loss and the greedy choice need of this wave's 32 NJ entries, the logits themselves go nowhere: per row the largest one and
+    // the sum of exponentials against it, the target's logit if it is here, and the best entry's key.  A lane has 16 NJ entries of
+    // row 32 i + lane % 32, 32 j + 8 q + 4 (lane / 32) + 0..3 from n_w on; the row's others are with lane ^ 32.
+    const int n_w = nb * GW_BN + 32 * NJ * wn;
+    const int* target = (const int*)a.g_next;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int m = m_w + 32 * i + col, mc = min(m, M - 1);
+      const bool act = m < M;
+      const unsigned long long seen = a.amax[mc];          // maybe an older value: then the search below runs once too often
+      const int rel = target[mc] - n_w - m_l;
+      const float rs = rs_s[wm * 64 + 32 * i + col];
+      float mx = -INFINITY;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[i][j] *= rs;
+      if (n_w + 32 * NJ > N) {                             // entries beyond the vocabulary
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            if (n_w + m_l + 32 * j + 8 * (e >> 2) + (e & 3) >= N) acc[i][j][e] = -INFINITY;
+      }
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) mx = fmaxf(mx, acc[i][j][e]);
+      mx = pair_max<32>(mx);
+      const float mu = mx == -INFINITY ? 0.f : mx;
+      float s = 0.f;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s += __expf(acc[i][j][e] - mu);
+      s = pair_sum<32>(s);
+      if (act && lane < 32) ((float2*)a.part)[(size_t)(nb * T::WN + wn) * a.ldp + m] = make_float2(mx, s);
+      const bool hit = act && rel >= 0 && rel < 32 * NJ && !(rel & 4);
+      if (__any(hit)) {                                    // a target: seldom
+        float z = 0.f;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) z = rel == 32 * j + 8 * (e >> 2) + (e & 3) ? acc[i][j][e] : z;
+        if (hit) a.ssp_next[m] = z;
+      }
+      // the best entry, where the row's largest value reaches the best so far: about one wave in three with a large vocabulary (a sum
+      // that is not a number hides what the maximum may have left out, and zeros of either sign are told apart by their keys only)
+      const bool need = act && (!(s == s) || mx == 0.f || ordered_bits(mx) >= (uint32_t)(seen >> 32));
+      if (__any(need)) {
+        uint32_t bo = 0u;
+        int bi = 0;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int n = n_w + m_l + 32 * j + 8 * (e >> 2) + (e & 3);
+            const uint32_t o = ordered_bits(acc[i][j][e]);
+            if (n < N && o > bo) { bo = o; bi = n; }       // entries in rising order: the first of equal ones stays
+          }
+        unsigned long long key = ((unsigned long long)bo << 32) | (uint32_t)(0x7FFFFFFF - bi);
+        const LanePair<unsigned long long> p = halves<32>(key, key);
+        key = p.x > p.y ? p.x : p.y;
+        if (need && lane < 32) atomicMax(a.amax + m, key);
+      }
+    }
+    return;
+  }
   if (EPI == EPI_SWIGLU) {
     // activation row 32 i + lane % 32 of the wave, outputs 32 j + 8 q + 4 (lane / 32) + 0..3 of its 32 HJ
 #pragma unroll

@@ -19,7 +19,7 @@
 
 namespace dmtd {
 
-enum GemvEpi : int { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
+enum GemvEpi : int { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3, EPI_NLL = 4 /* wide GEMM only */ };
 
 struct GemvArgs {
   const void* W;        // [N, K]; for SWIGLU the gate matrix

@@ -132,7 +132,8 @@ struct MfmaArgs {
   unsigned long long* amax;   // LOGITS: selection keys [AMAX_CELLS, amax_ld], already offset to this launch's rows
   int amax_ld;
   int blocked;           // layout of xb and yb (packed_at): 0 row-major, 1 blocks of 16 x 32 (wide GEMM and its finishing launch only)
-  float* part;           // tiled kernel with K split over blocks: partial sums [ksplit][M][ldp]
+  float* part;           // tiled kernel with K split over blocks: partial sums [ksplit][M][ldp].  EPI_NLL: (maximum, sum) pairs [parts][ldp], with the
+                         // rows' targets (int) in g_next, the targets' logits in ssp_next and the rows' best keys in amax
   int ksplit, ldp;
 };
 // Every projection launch carries these.  With the 80 bytes of a MergeSrc among them, launches outside a graph took longer at small

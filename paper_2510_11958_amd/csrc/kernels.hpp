@@ -217,10 +217,12 @@ constexpr int AMAX_CELLS = 64;       // the LM head's blocks spread a sequence's
 // Greedy selection keys: a logit and its vocabulary index packed into one 64-bit integer whose
 // unsigned order is (larger logit first, then lower index), so an integer max over any
 // partition of the vocabulary, in any order, gives the argmax with ties to the lowest index.
-__device__ __forceinline__ unsigned long long argmax_key(float v, int idx) {
+__device__ __forceinline__ uint32_t ordered_bits(float v) {
   const uint32_t u = __float_as_uint(v);
-  const uint32_t ordered = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-  return ((unsigned long long)ordered << 32) | (uint32_t)(0x7FFFFFFF - idx);
+  return u ^ ((uint32_t)((int)u >> 31) | 0x80000000u);
+}
+__device__ __forceinline__ unsigned long long argmax_key(float v, int idx) {
+  return ((unsigned long long)ordered_bits(v) << 32) | (uint32_t)(0x7FFFFFFF - idx);
 }
 __device__ __forceinline__ int argmax_key_index(unsigned long long key) { return 0x7FFFFFFF - (int)(uint32_t)(key & 0xFFFFFFFFu); }
 
@@ -563,6 +565,52 @@ __global__ void __launch_bounds__(1024) nll_rows_kernel(const float* __restrict_
     if (pos + 1 < n) out = __logf(tot) + top - z[tokens[(size_t)b * s_max + pos + 1]];
     nll[(size_t)b * s_max + pos] = out;
   }
+}
+
+// The same from the wide GEMM's per-row results (EPI_NLL), which never writes the logits.  nll_targets_kernel, before it: every row's
+// target (-1: none) and an empty best key.  nll_merge_kernel, behind it: the parts' (largest logit, sum of exponentials against it) pairs
+// part[p][ld] added up against the row's largest; 8 rows per block, 32 threads a row, a fixed order.
+__global__ void nll_targets_kernel(const int* __restrict__ tokens, int s_max, int rows, int p0, int r, int n, int* __restrict__ target, unsigned long long* __restrict__ keys) {
+  const int row = blockIdx.x * blockDim.x + threadIdx.x;
+  if (row >= rows) return;
+  const int b = row / r, pos = p0 + row - b * r;
+  target[row] = pos + 1 < n ? tokens[(size_t)b * s_max + pos + 1] : -1;
+  keys[row] = 0ull;
+}
+__global__ void __launch_bounds__(256) nll_merge_kernel(const float2* __restrict__ part, int n_parts, int ld, const int* __restrict__ target, const float* __restrict__ z_target,
+                                                        const unsigned long long* __restrict__ keys, int s_max, int rows, int p0, int r,
+                                                        float* __restrict__ nll, int* __restrict__ best) {
+  constexpr int U = 8;                     // parts in flight per thread
+  __shared__ float m_s[32][8], s_s[32][8];
+  const int i = threadIdx.x & 7, t = threadIdx.x >> 3, row = blockIdx.x * 8 + i, rc = min(row, rows - 1);
+  float mx = -INFINITY, s = 0.f;
+  for (int q0 = t; q0 < n_parts; q0 += 32 * U) {
+    float2 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = part[(size_t)min(q0 + 32 * u, n_parts - 1) * ld + rc];
+    float m8 = mx;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (q0 + 32 * u >= n_parts) v[u] = make_float2(-INFINITY, 0.f);
+      m8 = fmaxf(m8, v[u].x);
+    }
+    const float mu = m8 == -INFINITY ? 0.f : m8;
+    s *= __expf(mx - mu);
+#pragma unroll
+    for (int u = 0; u < U; ++u) s += v[u].y * __expf(v[u].x - mu);
+    mx = m8;
+  }
+  m_s[t][i] = mx;
+  s_s[t][i] = s;
+  __syncthreads();
+  if (t != 0 || row >= rows) return;
+  float top = m_s[0][i];
+  for (int k = 1; k < 32; ++k) top = fmaxf(top, m_s[k][i]);
+  float tot = 0.f;
+  for (int k = 0; k < 32; ++k) tot += s_s[k][i] * __expf(m_s[k][i] - (top == -INFINITY ? 0.f : top));
+  const int b = row / r, pos = p0 + row - b * r;
+  best[(size_t)b * s_max + pos] = argmax_key_index(keys[row]);
+  nll[(size_t)b * s_max + pos] = target[row] >= 0 ? __logf(tot) + top - z_target[row] : 0.f;
 }
 
 // Eq. 6 per sequence: the mean of the summands of the n-1 positions that have a successor (fixed summation order).
