@@ -470,13 +470,15 @@ struct WidePlan { double us; int n_full, ksplit; };
 template <int EPI, int BM>
 WidePlan plan_wide(const dmtd_config& cf, int num_cus, int rows, int nt, int KS) {
   const int tiles = (rows + BM - 1) / BM * nt, slots = num_cus;
-  // a k-step of 32 takes 1.25 us with 256 rows (1.45 where it is summed by itself) and 0.8 with 128 (measured, cold weights), a
-  // block's start and end about 4;
+  // a k-step of 32 takes 0.8 us with 128 rows; with 256 it takes 1.3, and 1.45 in long runs, where the card lowers its clock (also where
+  // it is summed by itself); a block's start and end take about 4 us.  Fitted to 300 measured launches of five widths from 200 to 2048
+  // rows: with one figure of 1.25 a launch was 0.7 % slower than its better tile on average and up to 14 % (2560 wide, us, tiles of
+  // 256 / 128: down with 896 rows 97 / 89, 1003 rows 98 / 95, O with 1400 rows 74 / 66; 1536 wide, down with 1003 rows 66 / 60), now 0.4 %;
   // a raw tile's bytes are written and read by blocks all over the chip at about 3.5 TB/s in all; the finishing launch itself 5 us
-  const double step_us = BM == 256 ? (EPI == EPI_STORE ? 1.45 : 1.25) : 0.8;
+  auto step_us = [&](int ks) { return BM == 128 ? 0.8 : (EPI == EPI_STORE || 2 * KS >= 40 * ks ? 1.45 : 1.3); };
   const int part_tiles = (int)std::min<size_t>(gemm_part_floats(cf) / GwTile<BM>::PART, 1 << 20);
   const int whole = EPI == EPI_RESID ? 0 : tiles / slots * slots, left = tiles - whole;
-  auto round_us = [&](int ks) { return (left * ks + slots - 1) / slots * (2.0 * KS / ks * step_us + 4.0); };
+  auto round_us = [&](int ks) { return (left * ks + slots - 1) / slots * (2.0 * KS / ks * step_us(ks) + 4.0); };
   auto parts_us = [&](int ks) { return left * ks * (GwTile<BM>::PART * 4) / 3.5e6 + 5.0; };
   WidePlan p{round_us(1) + (EPI == EPI_RESID ? parts_us(1) : 0.0), EPI == EPI_RESID ? 0 : tiles, 1};
   if (EPI == EPI_RESID && left > part_tiles) p.us = 1e30;            // the raw sums do not fit
@@ -485,7 +487,7 @@ WidePlan plan_wide(const dmtd_config& cf, int num_cus, int rows, int nt, int KS)
       const double us = round_us(ks) + parts_us(ks);
       if (us < p.us * 0.97) p = WidePlan{us, whole, ks};
     }
-  p.us += whole / slots * (2.0 * KS * step_us + 4.0);
+  p.us += whole / slots * (2.0 * KS * step_us(1) + 4.0);
   return p;
 }
 
