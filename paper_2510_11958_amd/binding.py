@@ -167,16 +167,27 @@ class Engine:
         rc = self.lib.dmtd_create(C.byref(cc), self._weights.data_ptr(), wbytes, self._workspace.data_ptr(), nbytes,
                                   C.byref(self._h))
         self._check_create(rc)
-        # Page-locked memory for the logits' copy to the host, lent to the caller one array at a time (see logits()).  us per call,
-        # pageable / page-locked: 32 x 151936 1100 / 350, 8 x 151936 270 / 97, 1 x 151936 35 / 21.
-        nbytes = 4 * cfg.max_batch * cfg.vocab
-        if nbytes <= self._PINNED_LIMIT:
-            try:
-                self._pinned = torch.empty((cfg.max_batch, cfg.vocab), dtype=torch.float32, pin_memory=True)
-            except RuntimeError:
-                pass                    # no page-locked memory to be had: pageable arrays, as beyond the limit
 
     _PINNED_LIMIT = 64 << 20
+
+    def _host_logits(self, batch: int) -> np.ndarray:
+        """An array [batch, vocab] for the logits' copy to the host: page-locked memory that the engine holds from the first call on, lent
+        to the caller one array at a time, else pageable.  us per call, pageable / page-locked: 32 x 151936 1100 / 350,
+        8 x 151936 270 / 97, 1 x 151936 35 / 21."""
+        shape = (self.cfg.max_batch, self.cfg.vocab)
+        with self._lock:
+            if self._pinned is None and not self.cfg.dry_run and 4 * shape[0] * shape[1] <= self._PINNED_LIMIT:
+                import torch
+                try:
+                    self._pinned = torch.empty(shape, dtype=torch.float32, pin_memory=True)
+                except RuntimeError:    # no page-locked memory to be had
+                    self._pinned = False
+            # free when the array lent last, and every view of it (a view keeps its array alive), is gone
+            if self._pinned is not None and self._pinned is not False and (self._lent is None or self._lent() is None):
+                out = self._pinned[:batch].numpy()
+                self._lent = weakref.ref(out)
+                return out
+        return np.empty((batch, self.cfg.vocab), np.float32)
 
     def _check_create(self, rc):
         if rc != DMTD_OK:
@@ -286,14 +297,7 @@ class Engine:
 
     def logits(self) -> np.ndarray:
         B = getattr(self, "_batch", 1)
-        out = None
-        with self._lock:
-            # the page-locked array is free when the one lent last, and every view of it (a view keeps its array alive), is gone
-            if self._pinned is not None and (self._lent is None or self._lent() is None):
-                out = self._pinned[:B].numpy()
-                self._lent = weakref.ref(out)
-        if out is None:
-            out = np.empty((B, self.cfg.vocab), np.float32)
+        out = self._host_logits(B)
         self._check(self.lib.dmtd_logits(self._h, out.ctypes.data_as(C.POINTER(C.c_float)), out.size))
         return out
 
