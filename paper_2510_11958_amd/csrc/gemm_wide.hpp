@@ -17,9 +17,9 @@
 // less LDS traffic) 5 % slower, tiles of 128 rows in 4 waves of 64 x 128 6 % slower.
 // Blocks go round-robin over the 8 compute dies; a die takes a contiguous run of tiles with the row tiles fastest, so a
 // weight byte enters one die's L2 only and its row tiles share it there.
-// Tiles of 128 rows (waves of 64 x 64, a ring of four buffers, 0.8 instead of 1.25 us per step) where they pad a launch's rows less.
+// Tiles of 128 rows (waves of 64 x 64, a ring of four buffers, 0.8 instead of 1.3 us per step) where they pad a launch's rows less.
 // Against passes of 128 rows through gemm_mfma.hpp (4B shapes, 2048 rows, us with the finishing launch, before / now):
-// gate/up 660 / 357, QKV 390 / 137, down + O 763 / 297.
+// gate/up 660 / 336, QKV 390 / 128, down + O 763 / 282.
 // Sums: a tile that takes its whole K in one block sums it in one fp32 chain, a rounding per 8 products, 4.4e-7 of the result's norm at
 // K = 2560 in two planes; five parts summed apart (gemm_mfma.hpp with 128 rows) leave 2.0e-7.  In the QKV projection, whose K and V are
 // then rounded to bf16, that decides roundings; there a chain has 4 k-steps (tiles of 128 rows) or one (256 rows, 128 additions beside
