@@ -11,7 +11,6 @@ import ctypes as C
 import dataclasses
 import os
 import threading
-import weakref
 
 import numpy as np
 
@@ -140,7 +139,7 @@ class Engine:
         self.cfg = cfg
         self._h = C.c_void_p()
         self._weights = self._workspace = None
-        self._pinned = self._lent = None
+        self._stage = None
         self._lock = threading.Lock()
         if cfg.dry_run:
             cc = cfg.to_c(0)
@@ -168,26 +167,19 @@ class Engine:
                                   C.byref(self._h))
         self._check_create(rc)
 
-    _PINNED_LIMIT = 64 << 20
+    _STAGE_LIMIT = 64 << 20
 
-    def _host_logits(self, batch: int) -> np.ndarray:
-        """An array [batch, vocab] for the logits' copy to the host: page-locked memory that the engine holds from the first call on, lent
-        to the caller one array at a time, else pageable.  us per call, pageable / page-locked: 32 x 151936 1100 / 350,
-        8 x 151936 270 / 97, 1 x 151936 35 / 21."""
+    def _logits_stage(self):
+        """Page-locked memory [max_batch, vocab] that the logits' copy from the GPU goes through, the engine's own from the first call to
+        ``close``; None where it would be too large."""
         shape = (self.cfg.max_batch, self.cfg.vocab)
-        with self._lock:
-            if self._pinned is None and not self.cfg.dry_run and 4 * shape[0] * shape[1] <= self._PINNED_LIMIT:
-                import torch
-                try:
-                    self._pinned = torch.empty(shape, dtype=torch.float32, pin_memory=True)
-                except RuntimeError:    # no page-locked memory to be had
-                    self._pinned = False
-            # free when the array lent last, and every view of it (a view keeps its array alive), is gone
-            if self._pinned is not None and self._pinned is not False and (self._lent is None or self._lent() is None):
-                out = self._pinned[:batch].numpy()
-                self._lent = weakref.ref(out)
-                return out
-        return np.empty((batch, self.cfg.vocab), np.float32)
+        if self._stage is None and not self.cfg.dry_run and 4 * shape[0] * shape[1] <= self._STAGE_LIMIT:
+            import torch
+            try:
+                self._stage = torch.empty(shape, dtype=torch.float32, device="cpu", pin_memory=True)
+            except RuntimeError:    # no page-locked memory to be had
+                self._stage = False
+        return None if self._stage is None or self._stage is False else self._stage
 
     def _check_create(self, rc):
         if rc != DMTD_OK:
@@ -201,6 +193,7 @@ class Engine:
         if self._h:
             self.lib.dmtd_destroy(self._h)
             self._h = C.c_void_p()
+        self._stage = None
 
     def __del__(self):
         try:
@@ -296,9 +289,20 @@ class Engine:
             torch.cuda.synchronize()
 
     def logits(self) -> np.ndarray:
+        """The most recent step's logits, ``[batch, vocab]``, in pageable memory of the caller's own.
+
+        The page-locked staging memory never leaves the engine: an upload of the result that does not wait
+        (``torch.from_numpy(...).to("cuda", non_blocking=True)``) would still read it while the next call writes it.  Up to 64 MiB of it stay
+        locked from the first call to ``close``.  us per call, straight into pageable memory / staged: 32 x 151936 1109 / 484, 8 x 151936 276 / 134, 1 x 151936 41 / 35."""
         B = getattr(self, "_batch", 1)
-        out = self._host_logits(B)
-        self._check(self.lib.dmtd_logits(self._h, out.ctypes.data_as(C.POINTER(C.c_float)), out.size))
+        out = np.empty((B, self.cfg.vocab), np.float32)
+        with self._lock:
+            stage = self._logits_stage()
+            at = out.ctypes.data if stage is None else stage.data_ptr()
+            self._check(self.lib.dmtd_logits(self._h, C.cast(at, C.POINTER(C.c_float)), out.size))
+            if stage is not None:
+                import torch
+                torch.from_numpy(out).copy_(stage[:B])
         return out
 
     def state(self):
