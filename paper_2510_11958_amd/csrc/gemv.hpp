@@ -206,7 +206,7 @@ __global__ void __launch_bounds__(256) gemv_rows_kernel(GemvArgs a) {
   }
 }
 
-// Short rows (K <= 256 ITS) of a small fp32 model, whose launches are bound by latency: kernel start, one round trip to
+// Short rows (256 (ITS - 1) < K <= 256 ITS) of a small fp32 model, whose launches are bound by latency: kernel start, one round trip to
 // memory, the reduction.  A wave owns 4 outputs (SwiGLU: the gate and up rows of 2) and M activation rows; it loads its weights, the
 // rows, the norm's gain and the residual values it adds to, all at once, computes the rows' sums of squares by itself, and scales its sums
 // by 1/rms at the end.  No LDS, no barrier, no load behind another (gemv_rows_kernel has three round trips: rows, gain, residual).
@@ -259,6 +259,10 @@ __global__ void __launch_bounds__(256) gemv_direct_kernel(const float* __restric
 #pragma unroll
         for (int e = 0; e < 4; ++e) ss += xv[m][it][e] * xv[m][it][e];
         xv[m][it] *= g[it];
+        // (0 times an infinite gain is not 0: the lanes behind the row are cleared again; only the last chunk has any)
+        if (it == ITS - 1)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) xv[m][it][e] = it * 256 + lane * 4 < K ? xv[m][it][e] : 0.f;
       }
       ss = wave_sum(ss);
       rs = my_m == m ? ss : rs;

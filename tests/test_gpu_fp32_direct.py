@@ -8,7 +8,8 @@ import numpy as np
 import pytest
 
 import dmtd_inputs as di
-from parity_util import Pair
+from parity_util import Pair, engine_config
+import paper_2510_11958_amd as pkg
 
 pytestmark = pytest.mark.gpu
 
@@ -41,3 +42,20 @@ def test_fp32_sizes_against_the_oracle(name):
         p.step_forced(tau, 1, toks)
     assert p.worst < 1e-4, p.worst
     p.compare_kv(1e-5)
+
+
+@pytest.mark.parametrize("hidden", [8, 200, 256, 264, 1000, 1032])
+def test_infinite_gain_stays_with_its_element(hidden):
+    """The final norm's first gain is infinite: every logit is infinite with the sign of its weight times the element, and none of the
+    lanes whose values lie beyond the row makes a NaN of it."""
+    sh = S(1, hidden, 1, 1, 64, 64, 130, dtype="fp32")
+    blob = di.make_weight_blob(sh, seed=3, std=0.05)
+    table = blob[:sh.vocab * hidden].reshape(sh.vocab, hidden)
+    blob[-hidden] = np.inf
+    assert (table[:, 0] != 0).all()
+    eng = pkg.Engine(engine_config(sh, 16), blob)
+    first = eng.prefill(di.make_prompts(sh.vocab, 1, 5, seed=5))
+    z = eng.logits()[0]
+    assert np.isinf(z).all()
+    assert abs((np.sign(z) * np.sign(table[:, 0])).sum()) == sh.vocab
+    assert first[0] == np.argmax(z)
