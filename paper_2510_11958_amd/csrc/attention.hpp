@@ -38,6 +38,20 @@ constexpr int ATT_MAX_SPLITS = 64;
 template <int HD> struct AttKeysPerIter { static constexpr int value = 4 * (64 / (HD / 8)) * 4; };
 
 
+// Which key range and row group of a sequence a block of a decode attention launch takes.  Grid: (ranges x row groups, KV heads,
+// sequences); the row groups are fastest: those of a range read the same keys at about the same time.  In a front pass over some sequences
+// (fmap) most row groups behind the first may be dead (live_rows); there the ranges are fastest, and the groups
+// begin at another one for every KV head and sequence.  With the row groups fastest, blocks going round-robin over the 8 dies, two
+// or four row groups left the living ones to 4 or 2 dies (1536 wide, 8 sequences of 2 rows beside one of 8, us per step of 4 layers with 8k / 32k
+// keys: 200 / 313, here 194 / 285; a pass of its own for the longer one 200 / 288).
+// MAP, here and in the kernels: such a pass.  Told apart by the pointer, every launch's prologue took 0.2 to 0.5 us longer.
+struct AttPlace { int split, rg; };
+template <bool MAP> __device__ __forceinline__ AttPlace att_place(int n_splits, int n_rg) {
+  const int x = blockIdx.x;
+  if (MAP) return AttPlace{x % n_splits, (int)(x / n_splits + blockIdx.y + blockIdx.z) % n_rg};
+  return AttPlace{x / n_rg, x % n_rg};
+}
+
 // f over the keys of a wave: a value per lane slice that holds a key (2 or 4 neighbouring lanes each), every lane gets the result
 template <int HD, typename F> __device__ __forceinline__ float key_reduce(float v, F f) {
   if (HD == 64) v = f(v, lane_dpp<kDppQuad2>(v));
@@ -188,7 +202,7 @@ __global__ void __launch_bounds__(64) kv_append_kernel(
   for (int k = lane; k < HD; k += 64) vd[k] = Elem<CT>::from_f32(vsrc[k]);
 }
 
-template <int HD, int QVT>
+template <int HD, int QVT, bool MAP>
 __global__ void __launch_bounds__(256) attn_split_kernel(
     const float* __restrict__ qkv, int ldq, const void* __restrict__ q_gain, const void* __restrict__ k_gain,
     const float2* __restrict__ rope_tab /* [s_max][HD / 2] (cos, sin) of position * theta^(-2i/HD) */, float* __restrict__ kc, float* __restrict__ vc,
@@ -196,7 +210,7 @@ __global__ void __launch_bounds__(256) attn_split_kernel(
     int kps /* keys per range, a multiple of the block iteration */, int n_splits, int qv_stride,
     const DevState* st, int sel, int offset, int r_total,
     int do_append /* 1: the launch appends its rows' keys and values; 0: it scores them from its inputs and leaves the cache untouched (measurement); 2: they are in the cache already */,
-    const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot (cache rows, positions) */,
+    const int* __restrict__ fmap /* MAP: launch sequence -> sequence slot (cache rows, positions) */,
     float* __restrict__ out, int ldo /* nullable: one range, no merge launch follows */) {
   typedef Elem<float>::Raw Raw;
   constexpr int LPK = HD / 8;          // lanes per key (16 or 8)
@@ -209,16 +223,18 @@ __global__ void __launch_bounds__(256) attn_split_kernel(
   constexpr int NEW_MAX = 16;          // rows a launch can carry
 
   const int g = blockIdx.y, b = blockIdx.z;
-  // rows and partials are indexed by the launch's sequence number b, the cache and the positions by the sequence's slot:
-  // the cache pointers are moved so that index b lands on the slot
-  const int bs = fmap ? fmap[b] : b;
-  kc += (ptrdiff_t)(bs - b) * nkv * s_max * HD;
-  vc += (ptrdiff_t)(bs - b) * nkv * s_max * HD;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int GQ = nh / nkv;
   const int rpb = QVT / GQ;                                    // rows per block
   const int n_rg = (r_total + rpb - 1) / rpb;
-  const int split = blockIdx.x / n_rg, rg = blockIdx.x % n_rg;
+  const AttPlace pl = att_place<MAP>(n_splits, n_rg);
+  const int split = pl.split, rg = pl.rg;
+  // rows and partials are indexed by the launch's sequence number b, the cache and the positions by the sequence's slot:
+  // the cache pointers are moved so that index b lands on the slot
+  const int bs = MAP ? fmap[b] : b;
+  kc += (ptrdiff_t)(bs - b) * nkv * s_max * HD;
+  vc += (ptrdiff_t)(bs - b) * nkv * s_max * HD;
+  if (MAP && rg > 0 && rg * rpb >= live_rows(st, bs, r_total)) return;      // no row of its own; the first group has one
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int key_begin = split * kps;
   const int sl = lane % LPK, grp = wave * GPW + lane / LPK;
   const int my_u = sl >> USH;
@@ -258,7 +274,7 @@ __global__ void __launch_bounds__(256) attn_split_kernel(
   load_kv(key_begin, min(s_max, key_begin + kps));
 
   const int pos_first = row_base(st, sel, offset, bs);
-  const int live = fmap ? live_rows(st, bs, r_total) : r_total; // rows of this sequence; the others of its r_total are dead
+  const int live = MAP ? live_rows(st, bs, r_total) : r_total; // rows of this sequence; the others of its r_total are dead
   const int r = min(rpb, live - rg * rpb), QV = r * GQ;
   if (r <= 0) return;
   const int pos0 = pos_first + rg * rpb;                        // position of this block's first row
@@ -388,11 +404,11 @@ __global__ void __launch_bounds__(256) attn_split_kernel(
 // 4 consecutive d of the ranges group, group + NG, ...; every load is issued before the first one is needed; the
 // maximum and the denominator are wave reductions over one lane per range; the groups' sums are added in group
 // order through LDS (deterministic).
-template <int HD, typename OT>   // OT: float, or bf16_t (the packed input of the O projection: high parts to out, low parts to out_lo)
+template <int HD, typename OT, bool MAP>   // OT: float, or bf16_t (the packed input of the O projection: high parts to out, low parts to out_lo)
 __global__ void __launch_bounds__(256) attn_merge_kernel(
     const float* __restrict__ part_o, const float* __restrict__ part_ml, OT* __restrict__ out, OT* __restrict__ out_lo, int ldo,
     int nh, int nkv, int kps, int n_splits, int qv_stride, const DevState* st, int sel, int offset, int r_total,
-    const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot (positions) */, int blocked /* layout of a bf16 output (packed_at) */) {
+    const int* __restrict__ fmap /* MAP: launch sequence -> sequence slot (positions) */, int blocked /* layout of a bf16 output (packed_at) */) {
   constexpr int T4 = HD / 4;              // threads per group: one per 4 consecutive d
   constexpr int NG = 256 / T4;            // groups (8 or 16); group sg takes ranges sg, sg + NG, ...
   constexpr int PRE = 4;                  // ranges per thread fetched before anything is waited for (4 * NG >= 32 ranges)
@@ -401,6 +417,8 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(
   const int tid = threadIdx.x;
   const int GQ = nh / nkv, g = head / GQ, j = head % GQ;
   const int sg = tid / T4, d = (tid % T4) * 4;
+  const int bs = MAP ? fmap[b] : b;
+  if (MAP && i > 0 && i >= live_rows(st, bs, r_total)) return;       // a dead row; the first is alive
   __shared__ float f_s[ATT_MAX_SPLITS];
   __shared__ float inv_l_s;
   __shared__ __attribute__((aligned(16))) float red[NG][HD];
@@ -421,7 +439,7 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(
     const int uc = sg + u * NG < n_splits ? u : 0;
     ov[u] = *(const f32x4*)(po + uc * po_step);
   }
-  const int pos_row = row_base(st, sel, offset, fmap ? fmap[b] : b) + i;    // row i sees keys 0 .. pos_row
+  const int pos_row = row_base(st, sel, offset, bs) + i;    // row i sees keys 0 .. pos_row
   const int n_act = min(n_splits, pos_row / kps + 1);   // ranges that hold keys visible to row i; later ones hold stale partials
   if (tid < 64) {
     // the first wave holds one range per lane: maximum and weighted sum by shuffles (a fixed tree: deterministic)

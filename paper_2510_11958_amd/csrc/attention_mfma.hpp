@@ -209,13 +209,13 @@ __device__ __forceinline__ void attn_prepare_rows_mfma(
 // sequence), so the block's result is the attention output itself: it is normalised and written as the packed input
 // of the O projection (high parts to out, low parts to out_lo) and no merge kernel follows.  The waves' partial
 // results meet in dynamic shared memory: NW * QV * HD floats (QV = the block's query vectors).
-template <int HD, int NW, bool FINAL>
+template <int HD, int NW, bool FINAL, bool MAP>
 __global__ void __launch_bounds__(64 * NW) attn_split_mfma_kernel(
     // in order of first use: the leading 16 dwords of scalars arrive in registers with the wave (kernel-argument preload;
     // an argument struct ends it, so QkvSrc comes last), the rest after a load from the argument buffer
     bf16_t* __restrict__ kc, bf16_t* __restrict__ vc, int nh, int nkv, int s_max,
     int kps /* keys per range, a multiple of 16 * NW */, int r_total,
-    const int* __restrict__ fmap /* nullable: launch sequence -> sequence slot (cache rows, positions) */,
+    const int* __restrict__ fmap /* MAP: launch sequence -> sequence slot (cache rows, positions) */,
     const DevState* st, int sel, int offset, int n_splits, const void* __restrict__ q_gain,
     const void* __restrict__ k_gain, const float2* __restrict__ rope_tab,
     float* __restrict__ part_o, float* __restrict__ part_ml, float eps, int qv_stride, int do_append,
@@ -228,16 +228,18 @@ __global__ void __launch_bounds__(64 * NW) attn_split_mfma_kernel(
   typedef unsigned int vraw_t __attribute__((ext_vector_type(DPL / 2)));   // DPL bf16 values
 
   const int g = blockIdx.y, b = blockIdx.z;
-  // rows and partials are indexed by the launch's sequence number b, the cache and the positions by the sequence's slot:
-  // the cache pointers are moved so that index b lands on the slot (no load, no wait, when there is no map)
-  const int bs = fmap ? fmap[b] : b;
-  kc += (ptrdiff_t)(bs - b) * nkv * s_max * HD;
-  vc += (ptrdiff_t)(bs - b) * nkv * s_max * HD;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int GQ = nh / nkv;
   const int rpb = QVT / GQ;                                    // rows per block
   const int n_rg = (r_total + rpb - 1) / rpb;
-  const int split = blockIdx.x / n_rg, rg = blockIdx.x % n_rg;
+  const AttPlace pl = att_place<MAP>(n_splits, n_rg);
+  const int split = pl.split, rg = pl.rg;
+  // rows and partials are indexed by the launch's sequence number b, the cache and the positions by the sequence's slot:
+  // the cache pointers are moved so that index b lands on the slot (no load, no wait, when there is no map)
+  const int bs = MAP ? fmap[b] : b;
+  kc += (ptrdiff_t)(bs - b) * nkv * s_max * HD;
+  vc += (ptrdiff_t)(bs - b) * nkv * s_max * HD;
+  if (MAP && rg > 0 && rg * rpb >= live_rows(st, bs, r_total)) return;      // no row of its own; the first group has one
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int QV_all = min(rpb, r_total - rg * rpb) * GQ;
   const int key_begin = split * kps;
   const int sl = lane & 15, kq = lane >> 4;
@@ -274,7 +276,7 @@ __global__ void __launch_bounds__(64 * NW) attn_split_mfma_kernel(
   const AttQueryPre<HD> qpre = attn_preload_query<HD>(qs, (const bf16_t*)q_gain, b, g, GQ, r_total, rg * rpb, QV_all, tid);
 
   const int pos_first = row_base(st, sel, offset, bs);
-  const int live = fmap ? live_rows(st, bs, r_total) : r_total; // rows of this sequence; the others of its r_total are dead
+  const int live = MAP ? live_rows(st, bs, r_total) : r_total; // rows of this sequence; the others of its r_total are dead
   const int r = min(rpb, live - rg * rpb), QV = r * GQ;
   if (r <= 0) return;
   const int pos0 = pos_first + rg * rpb;                        // position of this block's first row

@@ -205,6 +205,7 @@ struct dmtd_ctx {
   int late_batch = 0;         // a front pass over some sequences: sequences of the whole batch (0: all are in the pass)
   int resid_parts = 0;        // partial sums of squares per row the last residual projection left for the next norm
   const int* fmap = nullptr;  // launches of a front pass over SOME sequences: launch sequence -> sequence slot (device); null = all, in order
+  const int* live = nullptr;  // ... and the rows each of them has (host; the launch has room for the largest number); null = all rows of the launch
   const unsigned char* full_mask = nullptr;   // the step's bookkeeping: which sequences close their refill gap (device); null = all or none
   // sequences at different points of their cycles (dmtd_decode_per_seq): per-sequence phase and front position (in the
   // counters' coordinates); while `diverged` the single-phase calls are refused
@@ -437,6 +438,16 @@ hipError_t gemv_rows(dmtd_ctx* c, GemvArgs a, int rows) {
 
 // ---------------------------------------------------- packed path: MFMA weight streaming
 
+// Row groups (of rpb rows) of an attention launch with r rows per sequence that have a row in them: what its key ranges are chosen by.
+// The groups that a front pass has room for beyond a sequence's own rows leave at once (live_rows); counted with the others they
+// left those fewer and longer ranges (512 wide, one KV head, 65k keys, 4 sequences of 1 row beside one of 12: 300 us per step of 6 layers, 284 now).
+long row_groups(const dmtd_ctx* c, int r, int rpb) {
+  if (!c->live) return (long)c->batch * ((r + rpb - 1) / rpb);
+  long n = 0;
+  for (int b = 0; b < c->batch; ++b) n += (c->live[b] + rpb - 1) / rpb;
+  return n;
+}
+
 // nw waves split K for each matrix: the smallest of {2, 4, 8} (SwiGLU: {2, 4, 5}) that lets a wave
 // hold its k-range in one round of PF k-steps, else the largest with several rounds.
 // More than 16 rows go through the LDS-tiled kernel, up to kGemmRows per pass (each pass streams the matrix once).
@@ -446,11 +457,13 @@ bool attention_single_range(const dmtd_ctx* c, int r) {
   const dmtd_config& cf = c->cfg;
   const int gq = cf.n_q_heads / cf.n_kv_heads, rpb = 16 / gq, n_rg = (r + rpb - 1) / rpb;
   const long blocks = (long)cf.n_kv_heads * c->batch * n_rg;
-  if (r > c->part_rows || blocks >= c->num_cus) return true;         // more rows than the ranges' partials are laid out for: one range
+  if (r > c->part_rows || cf.n_kv_heads * row_groups(c, r, rpb) >= c->num_cus) return true;         // more rows than the ranges' partials are laid out for: one range
   // Fewer blocks than CUs, short contexts: a block walks 128 keys in about 1.4 us (2.3 us with 8 blocks on the chip), the merge
   // launch and, with K-split QKV sums, their finishing launch cost 4-9 us.  us per step of 8 layers, one range / ranges + merge:
   // 64 blocks (batch 8), 2560 wide: 100 keys 485 / 523, 400 keys 519 / 526, 900 keys 592 / 580; 1024 wide: 250 / 272, 288 / 276,
   // 355 / 324; 128 blocks: 400 keys 572 / 626 and 346 / 381, 900 keys 639 / 653 and 421 / 408; 8 blocks: 400 keys 483 / 434.
+  // (Blocks of dead row groups count here: the merge and the finishing launch carry their rows too.  2560 wide, 300 keys, 8
+  // sequences of 2 rows beside one of 8, us per step of 4 layers: 208, by the living alone 212.)
   return c->att_bucket <= 4 * blocks;
 }
 
@@ -737,7 +750,7 @@ void launch_attention_t(dmtd_ctx* c, int l, const float* qkv, float* attn, int s
   // keys per range: one block iteration while that keeps the ranges within the partials buffer and puts no
   // more than about four blocks on every CU; longer ranges (several iterations) for long contexts or big batches
   const int bucket = c->att_bucket;
-  long per_split_blocks = (long)cf.n_kv_heads * B * n_rg;
+  const long per_split_blocks = cf.n_kv_heads * row_groups(c, r, rpb);
   int want_splits = (int)((4L * c->num_cus + per_split_blocks - 1) / per_split_blocks);
   if (want_splits > ATT_MAX_SPLITS) want_splits = ATT_MAX_SPLITS;
   if (want_splits < 1) want_splits = 1;
@@ -749,11 +762,13 @@ void launch_attention_t(dmtd_ctx* c, int l, const float* qkv, float* attn, int s
   float* po = c->part_o;
   float* pml = c->part_ml;
   const DevState* st = dev_state(c);
-  hipLaunchKernelGGL((attn_split_kernel<HD, QVT>), dim3(ns * n_rg, cf.n_kv_heads, B), dim3(256), 0, c->stream, qkv, nqkv,
+  const auto split_kern = c->fmap ? attn_split_kernel<HD, QVT, true> : attn_split_kernel<HD, QVT, false>;
+  hipLaunchKernelGGL(split_kern, dim3(ns * n_rg, cf.n_kv_heads, B), dim3(256), 0, c->stream, qkv, nqkv,
                      w.q_norm, w.k_norm, (const float2*)(c->ws + c->o.rope_tab), kc, vc, po, pml, cf.n_q_heads, cf.n_kv_heads,
                      cf.max_seq_len, cf.rms_eps, kps, ns, c->part_rows * gq, st, sel, offset, r, append, c->fmap, one ? attn : (float*)nullptr, qd);
   if (one) return;
-  hipLaunchKernelGGL((attn_merge_kernel<HD, float>), dim3(r, cf.n_q_heads, B), dim3(256), 0, c->stream, po, pml, attn, (float*)nullptr, qd,
+  const auto merge_kern = c->fmap ? attn_merge_kernel<HD, float, true> : attn_merge_kernel<HD, float, false>;
+  hipLaunchKernelGGL(merge_kern, dim3(r, cf.n_q_heads, B), dim3(256), 0, c->stream, po, pml, attn, (float*)nullptr, qd,
                      cf.n_q_heads, cf.n_kv_heads, kps, ns, c->part_rows * gq, st, sel, offset, r, c->fmap, blocked_rows(c, B * r));
 }
 
@@ -761,8 +776,8 @@ void launch_attention_t(dmtd_ctx* c, int l, const float* qkv, float* attn, int s
 struct AttRanges { int kps, ns; };
 AttRanges attention_ranges(const dmtd_ctx* c, int r) {
   const dmtd_config& cf = c->cfg;
-  const int gq = cf.n_q_heads / cf.n_kv_heads, rpb = 16 / gq, n_rg = (r + rpb - 1) / rpb;
-  const long per_split_blocks = (long)cf.n_kv_heads * c->batch * n_rg;
+  const int gq = cf.n_q_heads / cf.n_kv_heads;
+  const long per_split_blocks = cf.n_kv_heads * row_groups(c, r, 16 / gq);
   int want_splits = (int)((4L * c->num_cus + per_split_blocks - 1) / per_split_blocks);
   if (want_splits > ATT_MAX_SPLITS) want_splits = ATT_MAX_SPLITS;
   if (want_splits < 1) want_splits = 1;
@@ -805,12 +820,12 @@ hipError_t launch_attention_mfma_t(dmtd_ctx* c, int l, const float* qkv, OT* att
     constexpr int NW = 8;
     const int kps = (c->att_bucket + 16 * NW - 1) / (16 * NW) * (16 * NW);
     const size_t lds = (size_t)NW * qv_max * HD * 4;
-    auto kern = attn_split_mfma_kernel<HD, NW, true>;
-    static bool big_lds = false;
-    if (lds > 32 * 1024 && !big_lds) {
+    const auto kern = c->fmap ? attn_split_mfma_kernel<HD, NW, true, true> : attn_split_mfma_kernel<HD, NW, true, false>;
+    static bool big_lds[2] = {false, false};
+    if (lds > 32 * 1024 && !big_lds[c->fmap != nullptr]) {
       hipError_t ae = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, NW * 16 * HD * 4);
       if (ae != hipSuccess) return ae;
-      big_lds = true;
+      big_lds[c->fmap != nullptr] = true;
     }
     hipLaunchKernelGGL(kern, dim3(n_rg, cf.n_kv_heads, B), dim3(64 * NW), lds, c->stream,
                        kc, vc, cf.n_q_heads, cf.n_kv_heads, cf.max_seq_len, kps, r, c->fmap, st, sel, offset, 1, w.q_norm,
@@ -820,7 +835,8 @@ hipError_t launch_attention_mfma_t(dmtd_ctx* c, int l, const float* qkv, OT* att
   }
   const AttRanges ar = attention_ranges(c, r);
   const int kps = ar.kps, ns = ar.ns;
-  hipLaunchKernelGGL((attn_split_mfma_kernel<HD, 4, false>), dim3(ns * n_rg, cf.n_kv_heads, B), dim3(256), (size_t)4 * qv_max * HD * 4, c->stream,
+  const auto split_kern = c->fmap ? attn_split_mfma_kernel<HD, 4, false, true> : attn_split_mfma_kernel<HD, 4, false, false>;
+  hipLaunchKernelGGL(split_kern, dim3(ns * n_rg, cf.n_kv_heads, B), dim3(256), (size_t)4 * qv_max * HD * 4, c->stream,
                      kc, vc, cf.n_q_heads, cf.n_kv_heads, cf.max_seq_len, kps, r, c->fmap, st, sel, offset, ns, w.q_norm,
                      w.k_norm, (const float2*)(c->ws + c->o.rope_tab), po, pml, cf.rms_eps, c->part_rows * gq, append,
                      (bf16_t*)nullptr, (bf16_t*)nullptr, 0, 0, qs);
@@ -828,7 +844,8 @@ hipError_t launch_attention_mfma_t(dmtd_ctx* c, int l, const float* qkv, OT* att
     c->merge_pending = merge_source(c, r, ar, sel, offset);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL((attn_merge_kernel<HD, OT>), dim3(r, cf.n_q_heads, B), dim3(256), 0, c->stream, po, pml, attn, attn_lo, qd,
+  const auto merge_kern = c->fmap ? attn_merge_kernel<HD, OT, true> : attn_merge_kernel<HD, OT, false>;
+  hipLaunchKernelGGL(merge_kern, dim3(r, cf.n_q_heads, B), dim3(256), 0, c->stream, po, pml, attn, attn_lo, qd,
                      cf.n_q_heads, cf.n_kv_heads, kps, ns, c->part_rows * gq, st, sel, offset, r, c->fmap, blocked_rows(c, B * r));
   return hipGetLastError();
 }
@@ -1195,8 +1212,9 @@ hipError_t enqueue_step(dmtd_ctx* c, bool full, int r, int n_late) {
 // over those sequences only (full_list: their slots, sorted by row count; groups: see front_groups) - and every
 // sequence's newest token then shares ONE pass through the late layers and the LM head: the late layers read the front
 // output for the former and the raw embedding for the others (Eq. 4).
-hipError_t enqueue_step_mixed(dmtd_ctx* c, const std::vector<std::pair<int, int>>& groups /* (rows, sequences) */, int n_late,
-                              const int* full_list, const unsigned char* full_mask) {
+hipError_t enqueue_step_mixed(dmtd_ctx* c, const std::vector<std::pair<int, int>>& groups /* (rows, sequences) */,
+                              const std::vector<int>& full_rows /* of the sequences in full_list */, int n_late, const int* full_list,
+                              const unsigned char* full_mask) {
   const dmtd_config& cf = c->cfg;
   const int F = cf.n_layers - n_late, B = c->batch;
   Rows front = front_rows(c), late = late_rows(c);
@@ -1208,12 +1226,14 @@ hipError_t enqueue_step_mixed(dmtd_ctx* c, const std::vector<std::pair<int, int>
     c->batch = n;
     c->late_batch = B;
     c->fmap = full_list + first;
+    c->live = full_rows.data() + first;
     e = embed_rows(c, front, POS_NFRONT, 0, r, 0);
     for (int l = 0; l < F && e == hipSuccess; ++l) e = run_layer(c, l, front, r, POS_NFRONT, 0);
     if (e == hipSuccess) e = take_last_rows(c, front, late, r, cf.full_pos_add_embed ? 1 : 0, POS_NFRONT, 0, F);
     c->batch = B;
     c->late_batch = 0;
     c->fmap = nullptr;
+    c->live = nullptr;
     if (e != hipSuccess) return e;
     first += n;
   }
@@ -1231,11 +1251,11 @@ hipError_t enqueue_step_mixed(dmtd_ctx* c, const std::vector<std::pair<int, int>
 // So a run is worth a pass of its own only if it saves more than some 70 rows of padding; the cut with the least sum is taken.  (An
 // fp32 model's projections take 4 rows per weight stream, so padding costs it more: 8 rows.)  2560 wide, 5 sequences with cycles of 1 to
 // 4 tokens, 24 steps: a pass per row count 19.0 ms for the whole request, its prefill included, one pass per step 16.3 ms.
-std::vector<std::pair<int, int>> front_groups(const std::vector<int>& order, const std::vector<int>& rows, bool packed) {
+std::vector<std::pair<int, int>> front_groups(const std::vector<int>& rows /* ascending */, bool packed) {
   const long kPassCost = packed ? 70 : 8;      // rows that cost as much as another pass
   std::vector<std::pair<int, int>> counts, groups;      // (rows, sequences): the distinct row counts; the passes
-  for (int b : order) {
-    if (counts.empty() || counts.back().first != rows[b]) counts.emplace_back(rows[b], 0);
+  for (int r : rows) {
+    if (counts.empty() || counts.back().first != r) counts.emplace_back(r, 0);
     counts.back().second += 1;
   }
   const int n = (int)counts.size();
@@ -2016,6 +2036,8 @@ int dmtd_decode_per_seq(dmtd_ctx* c, const int32_t* tau, int32_t n_late, int32_t
       std::vector<int> order;
       for (int b = 0; b < B; ++b) if (rows[i][b] > 0) order.push_back(b);
       std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return rows[i][x] < rows[i][y]; });
+      std::vector<int> order_rows;
+      for (int b : order) order_rows.push_back(rows[i][b]);
       // the pattern's device image: the list (ints) and the mask (bytes); cached patterns keep their slot for good (graphs
       // refer to it), the last slot serves patterns beyond the table, without a graph
       auto it = c->pattern_ids.find(rows[i]);
@@ -2037,7 +2059,7 @@ int dmtd_decode_per_seq(dmtd_ctx* c, const int32_t* tau, int32_t n_late, int32_t
       const int* list_dev = (const int*)img_dev;
       const unsigned char* mask_dev = (const unsigned char*)img_dev + (size_t)4 * cf.max_batch;
       if (!cf.use_graphs || !cached) {
-        hipError_t e = enqueue_step_mixed(c, front_groups(order, rows[i], c->packed), n_late, list_dev, mask_dev);
+        hipError_t e = enqueue_step_mixed(c, front_groups(order_rows, c->packed), order_rows, n_late, list_dev, mask_dev);
         if (e != hipSuccess) { c->err = std::string("mixed step: ") + hipGetErrorString(e); rc = DMTD_EHIP; }
         continue;
       }
@@ -2047,7 +2069,7 @@ int dmtd_decode_per_seq(dmtd_ctx* c, const int32_t* tau, int32_t n_late, int32_t
         hipGraph_t graph = nullptr;
         hipError_t e0 = hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal);
         if (e0 != hipSuccess) { c->err = std::string("hipStreamBeginCapture: ") + hipGetErrorString(e0); rc = DMTD_EHIP; break; }
-        hipError_t e = enqueue_step_mixed(c, front_groups(order, rows[i], c->packed), n_late, list_dev, mask_dev);
+        hipError_t e = enqueue_step_mixed(c, front_groups(order_rows, c->packed), order_rows, n_late, list_dev, mask_dev);
         hipError_t e2 = hipStreamEndCapture(c->stream, &graph);
         if (e != hipSuccess || e2 != hipSuccess) {
           if (graph) (void)hipGraphDestroy(graph);

@@ -272,3 +272,27 @@ def test_front_passes_with_room_for_more_rows_than_a_sequence_has(dtype, taus):
     _, checked = run_calls(eng, orcs, toks, [(list(taus), 18), (list(taus), 31)], n_late, TOL_F32 if dtype == "fp32" else TOL_BF16)
     assert checked > 0
     compare_caches(eng, orcs, sh, n_late, 1e-5 if dtype == "fp32" else 2e-2)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("heads,kv_heads,hd,P,taus", [(14, 2, 64, 700, (2, 2, 2, 12)), (8, 1, 64, 300, (3, 1, 9, 2)), (16, 4, 128, 1100, (1, 8, 8)),
+                                                      (64, 16, 64, 40, (4, 4, 4, 12))],
+                         ids=["gq7_6_groups_ranges", "one_kv_head_5_groups", "gq4_2_groups_hd128", "3_groups_one_range"])
+def test_row_groups_without_a_row_of_their_own(dtype, heads, kv_heads, hd, P, taus):
+    """A front pass with room for several row groups (16 query vectors per KV head each) per sequence, of which some sequences fill
+    the first only, over one key range and over several: the living groups are spread over the launch by KV head and sequence."""
+    sh = di.ModelShape(2, 128, heads, kv_heads, hd, 192, 130, dtype=dtype)
+    B, n = len(taus), 26
+    blob = di.make_weight_blob(sh, seed=3)
+    prompts = di.make_prompts(sh.vocab, B, P, seed=5)
+    toks = forced_string(sh.vocab, B, prompts, P + n)
+    eng = pkg.Engine(engine_config(sh, P + n, B), blob)
+    ocfg = oracle_config(sh)
+    w = O.unpack_weights(blob, ocfg, np.float64)
+    orcs = [O.DmtdOracle(ocfg, w, P + n, np.float64) for _ in range(B)]
+    eng.prefill(prompts)
+    for b, o in enumerate(orcs):
+        o.prefill(prompts[b])
+    _, checked = run_calls(eng, orcs, toks, [(list(taus), 13), (list(taus), 13)], 1, TOL_F32 if dtype == "fp32" else TOL_BF16)
+    assert checked > 0
+    compare_caches(eng, orcs, sh, 1, 1e-5 if dtype == "fp32" else 2e-2)
