@@ -249,6 +249,12 @@ int dmtd_time_kernel(dmtd_ctx* ctx, int32_t kind, int32_t rows, int32_t reps, fl
  * Errors: DMTD_EINVAL (also an fp32 model, and rows <= 192). */
 int dmtd_wide_plan(const dmtd_config* cfg, int32_t kind, int32_t rows, int32_t num_cus, int32_t plan[5]);
 
+/* How the sequences that start a cycle in one step of dmtd_decode_per_seq pass the front layers: rows HOST int32 [n], each sequence's
+ * pending tokens and its newest one (1 to 16), in any order.  n_passes receives the number of passes; plan HOST int32 [2 n]: for pass i
+ * plan[2 i] the rows it has room for per sequence and plan[2 i + 1] its sequences, those with the fewest rows first.  Needs no GPU and
+ * changes nothing, like dmtd_wide_plan.  Errors: DMTD_EINVAL. */
+int dmtd_front_plan(const dmtd_config* cfg, const int32_t* rows, int32_t n, int32_t* plan, int32_t* n_passes);
+
 /* ExDy variant (Sec. 2.1, the paragraph before Eq. 5; layer allocations of Sec. 3.3): the in-cycle tokens
  * reuse the first n_early (encoding) layers as well as the last n_late (decoding) layers, i.e. h_masked is built
  * from h_enc instead of h_emb.  A late-only step then runs layers [0, n_early) and [L - n_late, L) on its token

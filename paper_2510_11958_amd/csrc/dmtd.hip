@@ -1245,27 +1245,37 @@ hipError_t enqueue_step_mixed(dmtd_ctx* c, const std::vector<std::pair<int, int>
   return e;
 }
 
+// What a front pass with that many rows costs.  bf16, us per layer: the attention and the launches 25, the layer's weights, and little
+// per row, dead or alive, as long as the projections stay in the same kernel: beyond 64 and beyond 128 rows the tiled one takes longer steps.
+// (Projections alone, us with 1 / 16 / 64 / 72 / 128 / 136 rows: 2560 wide 42 / 54 / 81 / 98 / 113 / 163, 1536 29 / 37 / 62 / 75 / 84 / 121, 1024
+// 18 / 27 / 50 / 59 / 70 / 102, 896 20 / 26 / 54 / 68 / 80 / 108, 512 wide with one KV head 17 / 19 / 43 / 52 / 57 / 84.  With one price for every width
+// and row, 70 rows a pass, 8 sequences of 2 rows beside one of 8 went together in narrow models too; us per step of 6 layers, a pass per row count /
+// together: 896 wide, 300 keys 162 / 171, 8k keys 191 / 202, 512 wide 132 / 138.)
+// fp32, in rows: the projections take 4 rows per weight stream, a pass costs as much as 8.
+double front_pass_cost(const dmtd_config& cf, int rows) {
+  if (cf.dtype == DMTD_DTYPE_F32) return 8.0 + rows;
+  const double weight_us = (double)swizzled_layer_elems(cf) * 2 / 6.0e6;
+  return 25.0 + weight_us + 0.5 * rows + (rows > 64 ? 10.0 : 0.0) + (rows > 128 && rows <= kTiledRows ? 25.0 : 0.0);
+}
+
 // The front passes of such a step: the sequences that start a cycle, sorted by row count, cut into runs; a run passes the front
-// layers together, with room for its largest row count per sequence (live_rows).  A pass costs its stream of weights and launches and
-// then little per row, dead or alive: a 2560-wide layer takes about 50 us plus 0.65 us per row up to 192 rows, a 1024-wide one 27 + 0.3.
-// So a run is worth a pass of its own only if it saves more than some 70 rows of padding; the cut with the least sum is taken.  (An
-// fp32 model's projections take 4 rows per weight stream, so padding costs it more: 8 rows.)  2560 wide, 5 sequences with cycles of 1 to
-// 4 tokens, 24 steps: a pass per row count 19.0 ms for the whole request, its prefill included, one pass per step 16.3 ms.
-std::vector<std::pair<int, int>> front_groups(const std::vector<int>& rows /* ascending */, bool packed) {
-  const long kPassCost = packed ? 70 : 8;      // rows that cost as much as another pass
+// layers together, with room for its largest row count per sequence (live_rows).  The cut with the least cost is taken.
+// 2560 wide, 5 sequences with cycles of 1 to 4 tokens, 24 steps: a pass per row count 19.0 ms for the whole request, its prefill included,
+// one pass per step 16.3 ms.
+std::vector<std::pair<int, int>> front_groups(const dmtd_config& cf, const std::vector<int>& rows /* ascending */) {
   std::vector<std::pair<int, int>> counts, groups;      // (rows, sequences): the distinct row counts; the passes
   for (int r : rows) {
     if (counts.empty() || counts.back().first != r) counts.emplace_back(r, 0);
     counts.back().second += 1;
   }
   const int n = (int)counts.size();
-  std::vector<long> cost(n + 1, 0);   // cost[i]: the first i counts
+  std::vector<double> cost(n + 1, 0.0);   // cost[i]: the first i counts
   std::vector<int> from(n + 1, 0);
   for (int i = 1; i <= n; ++i) {
-    long seqs = 0;
+    int seqs = 0;
     for (int j = i - 1; j >= 0; --j) {
       seqs += counts[j].second;
-      const long v = cost[j] + kPassCost + seqs * counts[i - 1].first;
+      const double v = cost[j] + front_pass_cost(cf, seqs * counts[i - 1].first);
       if (j == i - 1 || v < cost[i]) { cost[i] = v; from[i] = j; }
     }
   }
@@ -2059,7 +2069,7 @@ int dmtd_decode_per_seq(dmtd_ctx* c, const int32_t* tau, int32_t n_late, int32_t
       const int* list_dev = (const int*)img_dev;
       const unsigned char* mask_dev = (const unsigned char*)img_dev + (size_t)4 * cf.max_batch;
       if (!cf.use_graphs || !cached) {
-        hipError_t e = enqueue_step_mixed(c, front_groups(order_rows, c->packed), order_rows, n_late, list_dev, mask_dev);
+        hipError_t e = enqueue_step_mixed(c, front_groups(cf, order_rows), order_rows, n_late, list_dev, mask_dev);
         if (e != hipSuccess) { c->err = std::string("mixed step: ") + hipGetErrorString(e); rc = DMTD_EHIP; }
         continue;
       }
@@ -2069,7 +2079,7 @@ int dmtd_decode_per_seq(dmtd_ctx* c, const int32_t* tau, int32_t n_late, int32_t
         hipGraph_t graph = nullptr;
         hipError_t e0 = hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal);
         if (e0 != hipSuccess) { c->err = std::string("hipStreamBeginCapture: ") + hipGetErrorString(e0); rc = DMTD_EHIP; break; }
-        hipError_t e = enqueue_step_mixed(c, front_groups(order_rows, c->packed), order_rows, n_late, list_dev, mask_dev);
+        hipError_t e = enqueue_step_mixed(c, front_groups(cf, order_rows), order_rows, n_late, list_dev, mask_dev);
         hipError_t e2 = hipStreamEndCapture(c->stream, &graph);
         if (e != hipSuccess || e2 != hipSuccess) {
           if (graph) (void)hipGraphDestroy(graph);
@@ -2279,6 +2289,18 @@ int dmtd_wide_plan(const dmtd_config* cfg, int32_t kind, int32_t rows, int32_t n
   plan[2] = w.p.n_full;
   plan[3] = (w.pass + w.bm - 1) / w.bm * w.nt - w.p.n_full;
   plan[4] = w.p.ksplit;
+  return DMTD_OK;
+}
+
+int dmtd_front_plan(const dmtd_config* cfg, const int32_t* rows, int32_t n, int32_t* plan, int32_t* n_passes) {
+  std::string why;
+  if (!rows || !plan || !n_passes || !valid_config(cfg, why) || n < 1 || n > cfg->max_batch) return DMTD_EINVAL;
+  std::vector<int> sorted(rows, rows + n);
+  std::sort(sorted.begin(), sorted.end());
+  if (sorted.front() < 1 || sorted.back() > kMaxRows) return DMTD_EINVAL;
+  const std::vector<std::pair<int, int>> groups = front_groups(*cfg, sorted);
+  for (size_t i = 0; i < groups.size(); ++i) { plan[2 * i] = groups[i].first; plan[2 * i + 1] = groups[i].second; }
+  *n_passes = (int32_t)groups.size();
   return DMTD_OK;
 }
 

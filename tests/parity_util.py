@@ -1,5 +1,7 @@
 """Helpers shared by the GPU parity tests: build the HIP engine and the CPU oracle from the same
 seeded inputs and compare them step by step."""
+import ctypes as C
+
 import numpy as np
 
 import dmtd_inputs as di
@@ -18,6 +20,15 @@ def engine_config(sh, max_seq_len, max_batch=1, **kw):
 def oracle_config(sh, **kw):
     return O.OracleConfig(sh.n_layers, sh.hidden, sh.n_q_heads, sh.n_kv_heads, sh.head_dim, sh.intermediate, sh.vocab,
                           sh.rms_eps, sh.rope_theta, sh.tied_embeddings, **kw)
+
+
+def front_plan(cfg, rows):
+    """The front passes of a step in which sequences with that many rows start a cycle: [(room per sequence, sequences), ...]."""
+    r, plan, n = np.asarray(rows, np.int32), np.zeros(2 * len(rows), np.int32), C.c_int32()
+    i32 = C.POINTER(C.c_int32)
+    rc = pkg.load_library().dmtd_front_plan(C.byref(cfg.to_c()), r.ctypes.data_as(i32), len(r), plan.ctypes.data_as(i32), C.byref(n))
+    assert rc == pkg.DMTD_OK
+    return [tuple(int(v) for v in p) for p in plan.reshape(-1, 2)[:n.value]]
 
 
 def norm_err(z_gpu, z_ref):

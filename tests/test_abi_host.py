@@ -363,3 +363,45 @@ def test_weight_image_starts_1_kib_off_a_multiple_of_2():
         layer = image((h + 2 * k) * hd, d) + image(d, h * hd) + 2 * image(ff, d) + image(d, ff)
         start = lib.dmtd_workspace_bytes(C.byref(cfg.to_c())) - (layer * L + image(vocab, d))
         assert start % 2048 == 1024, (cfg, start % 2048)
+
+
+WIDTHS = {2560: (32, 8, 128, 9728), 1536: (12, 2, 128, 8960), 1024: (16, 8, 128, 3072), 896: (14, 2, 64, 4864)}
+
+
+@pytest.mark.parametrize("hidden,rows,passes", [
+    (2560, [2] * 8 + [8], [(8, 9)]), (1536, [2] * 8 + [8], [(8, 9)]),           # wide: a pass costs its stream of weights
+    (1024, [8] + [2] * 8, [(2, 8), (8, 1)]), (896, [2] * 8 + [8], [(2, 8), (8, 1)]),      # narrow: 72 rows cost more than 16 and 8
+    (2560, [1] * 12 + [6], [(6, 13)]), (896, [1] * 12 + [6], [(1, 12), (6, 1)]),
+    (2560, [1, 2, 3, 4, 3], [(4, 5)]), (896, [3, 2, 3, 4, 1], [(4, 5)]),
+    (2560, [1] * 20 + [12] * 4, [(1, 20), (12, 4)]),
+    (1024, [1, 16], [(16, 2)]), (1024, [5], [(5, 1)]), (1024, [4] * 3, [(4, 3)]),
+])
+def test_front_plan(hidden, rows, passes):
+    """Which sequences pass the front layers together: decided by what the passes cost with that many rows, by the model's width."""
+    from parity_util import front_plan
+    assert front_plan(pkg.ModelConfig(4, hidden, *WIDTHS[hidden], 1000, max_batch=32), rows) == passes
+
+
+def test_front_plan_covers_every_sequence():
+    from parity_util import front_plan
+    rng = np.random.RandomState(3)
+    for dtype in ("bf16", "fp32"):
+        cfg = pkg.ModelConfig(2, 128, 4, 2, 64, 192, 130, dtype=dtype, max_batch=64)
+        for _ in range(200):
+            rows = rng.randint(1, 17, rng.randint(1, 65))
+            plan, left = front_plan(cfg, rows), sorted(rows.tolist())
+            for room, seqs in plan:
+                assert left[seqs - 1] == room and (len(left) == seqs or left[seqs] > room)      # whole row counts, no room to spare
+                left = left[seqs:]
+            assert not left
+
+
+def test_front_plan_argument_errors():
+    lib, n, plan = pkg.load_library(), C.c_int32(), (C.c_int32 * 8)()
+    cfg = pkg.ModelConfig(2, 128, 4, 2, 64, 192, 130, max_batch=4).to_c()
+    rows = (C.c_int32 * 5)(1, 2, 3, 4, 5)
+    assert lib.dmtd_front_plan(C.byref(cfg), rows, 4, plan, C.byref(n)) == pkg.DMTD_OK
+    for args in ((None, rows, 4, plan, C.byref(n)), (C.byref(cfg), None, 4, plan, C.byref(n)), (C.byref(cfg), rows, 0, plan, C.byref(n)),
+                 (C.byref(cfg), rows, 5, plan, C.byref(n)), (C.byref(cfg), rows, 4, None, C.byref(n)), (C.byref(cfg), rows, 4, plan, None),
+                 (C.byref(cfg), (C.c_int32 * 2)(0, 1), 2, plan, C.byref(n)), (C.byref(cfg), (C.c_int32 * 2)(1, 17), 2, plan, C.byref(n))):
+        assert lib.dmtd_front_plan(*args) == pkg.DMTD_EINVAL
