@@ -1251,9 +1251,11 @@ hipError_t enqueue_step_mixed(dmtd_ctx* c, const std::vector<std::pair<int, int>
 // 18 / 27 / 50 / 59 / 70 / 102, 896 20 / 26 / 54 / 68 / 80 / 108, 512 wide with one KV head 17 / 19 / 43 / 52 / 57 / 84.  With one price for every width
 // and row, 70 rows a pass, 8 sequences of 2 rows beside one of 8 went together in narrow models too; us per step of 6 layers, a pass per row count /
 // together: 896 wide, 300 keys 162 / 171, 8k keys 191 / 202, 512 wide 132 / 138.)
-// fp32, in rows: the projections take 4 rows per weight stream, a pass costs as much as 8.
+// fp32, in rows: rows up to 1024 wide go through gemv_direct_kernel, whose launches cost more than another group of 4 rows; wider ones
+// take 4 rows per weight stream.  us per step, a pass priced at 8 / 24 rows: 16 sequences in cycles of 1 to 8, 64 wide 125 / 112, 256 wide 138 / 124,
+// 512 167 / 155, 1024 321 / 321, 1536 697 / 740, 2048 745 / 797; cycles of 1, 2, 4 and 6, 1024 wide 180 / 173, 1536 305 / 315.
 double front_pass_cost(const dmtd_config& cf, int rows) {
-  if (cf.dtype == DMTD_DTYPE_F32) return 8.0 + rows;
+  if (cf.dtype == DMTD_DTYPE_F32) return (cf.hidden <= 1024 ? 24.0 : 8.0) + rows;
   const double weight_us = (double)swizzled_layer_elems(cf) * 2 / 6.0e6;
   return 25.0 + weight_us + 0.5 * rows + (rows > 64 ? 10.0 : 0.0) + (rows > 128 && rows <= kTiledRows ? 25.0 : 0.0);
 }

@@ -382,6 +382,15 @@ def test_front_plan(hidden, rows, passes):
     assert front_plan(pkg.ModelConfig(4, hidden, *WIDTHS[hidden], 1000, max_batch=32), rows) == passes
 
 
+@pytest.mark.parametrize("hidden,rows,passes", [
+    (1024, [1, 2, 4, 6], [(6, 4)]), (1032, [1, 2, 4, 6], [(2, 2), (6, 2)]),       # short rows: a pass costs as much as 24 rows, else 8
+    (256, [1, 16], [(16, 2)]), (2048, [1, 16], [(1, 1), (16, 1)]), (1024, [1] * 16 + [8], [(1, 16), (8, 1)]),
+])
+def test_front_plan_fp32(hidden, rows, passes):
+    from parity_util import front_plan
+    assert front_plan(pkg.ModelConfig(4, hidden, 4, 2, 64, 768, 1000, dtype="fp32", max_batch=32), rows) == passes
+
+
 def test_front_plan_covers_every_sequence():
     from parity_util import front_plan
     rng = np.random.RandomState(3)
