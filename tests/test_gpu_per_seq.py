@@ -10,7 +10,7 @@ import torch
 
 import dmtd_inputs as di
 from oracle import dmtd_oracle as O
-from parity_util import MARGIN, engine_config, norm_err, oracle_config, top2_margin
+from parity_util import MARGIN, engine_config, front_plan, norm_err, oracle_config, top2_margin
 import paper_2510_11958_amd as pkg
 
 pytestmark = pytest.mark.gpu
@@ -252,13 +252,19 @@ def test_more_step_patterns_than_the_device_table_keeps(use_graphs):
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
-@pytest.mark.parametrize("taus", [(1, 2, 3, 5, 8, 16), (1,) * 20 + (12,) * 4, (16, 1)], ids=["one_pass", "two_passes", "widest_padding"])
-def test_front_passes_with_room_for_more_rows_than_a_sequence_has(dtype, taus):
+@pytest.mark.parametrize("taus,plans", [
+    ((1, 2, 3, 5, 8, 16), {(1, 2, 3, 8): [(8, 4)], (1, 2, 3, 5): [(5, 4)], (1, 2, 3, 8, 16): [(3, 3), (16, 2)]}),
+    ((1,) * 20 + (12,) * 4, {(1,) * 20 + (12,) * 4: [(1, 20), (12, 4)]}),
+    ((16, 1), {(1, 16): [(16, 2)]}),
+], ids=["shared_and_cut", "20_of_1_row_apart_from_4_of_12", "1_row_beside_16"])
+def test_front_passes_with_room_for_more_rows_than_a_sequence_has(dtype, taus, plans):
     """Sequences that start a cycle with different numbers of pending tokens share a front pass with room for the largest
     number (few sequences), or take passes of their own (20 sequences of one row beside 4 of twelve); run up to the last slot
-    of the cache, where a sequence's unused rows lie beyond its end."""
+    of the cache, where a sequence's unused rows lie beyond its end.  plans: the passes of some of the steps, by their row counts."""
     sh = di.ModelShape(3, 128, 4, 2, 64, 192, 130, dtype=dtype)
     B, P, n_late, n = len(taus), 5, 1, 49
+    for rows, passes in plans.items():
+        assert front_plan(engine_config(sh, P + n, B), rows) == passes, rows
     blob = di.make_weight_blob(sh, seed=3)
     prompts = di.make_prompts(sh.vocab, B, P, seed=5)
     toks = forced_string(sh.vocab, B, prompts, P + n)
@@ -275,14 +281,15 @@ def test_front_passes_with_room_for_more_rows_than_a_sequence_has(dtype, taus):
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
-@pytest.mark.parametrize("heads,kv_heads,hd,P,taus", [(14, 2, 64, 700, (2, 2, 2, 12)), (8, 1, 64, 300, (3, 1, 9, 2)), (16, 4, 128, 1100, (1, 8, 8)),
-                                                      (64, 16, 64, 40, (4, 4, 4, 12))],
+@pytest.mark.parametrize("heads,kv_heads,hd,P,taus", [(14, 2, 64, 700, (2, 2, 12)), (8, 1, 64, 300, (3, 1, 9, 2)), (16, 4, 128, 1100, (1, 8, 8)),
+                                                      (64, 16, 64, 40, (4, 4, 12))],
                          ids=["gq7_6_groups_ranges", "one_kv_head_5_groups", "gq4_2_groups_hd128", "3_groups_one_range"])
 def test_row_groups_without_a_row_of_their_own(dtype, heads, kv_heads, hd, P, taus):
     """A front pass with room for several row groups (16 query vectors per KV head each) per sequence, of which some sequences fill
     the first only, over one key range and over several: the living groups are spread over the launch by KV head and sequence."""
     sh = di.ModelShape(2, 128, heads, kv_heads, hd, 192, 130, dtype=dtype)
     B, n = len(taus), 26
+    assert front_plan(engine_config(sh, P + n, B), taus) == [(max(taus), B)]      # where all start a cycle: one pass
     blob = di.make_weight_blob(sh, seed=3)
     prompts = di.make_prompts(sh.vocab, B, P, seed=5)
     toks = forced_string(sh.vocab, B, prompts, P + n)
