@@ -292,6 +292,11 @@ int dmtd_set_sampling(dmtd_ctx* ctx, float temperature, int32_t top_k, uint64_t 
 int dmtd_masked_forward(dmtd_ctx* ctx, const int32_t* tokens, int32_t batch, int32_t n, const uint8_t* mask, int32_t n_late,
                         float* nll, int32_t* best, float* logits, size_t logits_elems, float* loss);
 
+/* How dmtd_masked_forward over batch sequences of n tokens passes the layers, with a workspace of dmtd_workspace_bytes: plan[0] positions
+ * per sequence of its first pass; plan[1] 1 if that pass, when no logits are asked for, ends in the tiles of dmtd_wide_plan (DMTD_K_LMHEAD, all rows
+ * of the pass) without writing logits, 0 if it holds logits of some rows at a time.  Needs no GPU.  Errors: DMTD_EINVAL. */
+int dmtd_score_plan(const dmtd_config* cfg, int32_t batch, int32_t n, int32_t plan[2]);
+
 /* Back to the state right after dmtd_create (caches are treated as empty). */
 int dmtd_reset(dmtd_ctx* ctx);
 

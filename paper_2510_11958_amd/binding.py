@@ -85,6 +85,8 @@ def load_library():
     lib.dmtd_wide_plan.argtypes = [P(_Config), C.c_int32, C.c_int32, C.c_int32, P(C.c_int32)]
     lib.dmtd_front_plan.restype = C.c_int
     lib.dmtd_front_plan.argtypes = [P(_Config), P(C.c_int32), C.c_int32, P(C.c_int32), P(C.c_int32)]
+    lib.dmtd_score_plan.restype = C.c_int
+    lib.dmtd_score_plan.argtypes = [P(_Config), C.c_int32, C.c_int32, P(C.c_int32)]
     lib.dmtd_set_n_early.restype = C.c_int
     lib.dmtd_set_n_early.argtypes = [C.c_void_p, C.c_int32]
     lib.dmtd_set_sampling.restype = C.c_int

@@ -495,7 +495,7 @@ WidePlan plan_wide(const dmtd_config& cf, int num_cus, int rows, int nt, int KS)
   auto parts_us = [&](int ks) { return left * ks * (GwTile<BM>::PART * 4) / 3.5e6 + 5.0; };
   WidePlan p{round_us(1) + (EPI == EPI_RESID ? parts_us(1) : 0.0), EPI == EPI_RESID ? 0 : tiles, 1};
   if (EPI == EPI_RESID && left > part_tiles) p.us = 1e30;            // the raw sums do not fit
-  if (EPI != EPI_LOGITS && EPI != EPI_NLL)
+  if (EPI != EPI_LOGITS)
     for (int ks = 2; ks <= kGemmMaxSplit && ks * 4 <= KS && left > 0 && (long)left * ks <= part_tiles; ++ks) {      // at least 8 steps per part
       const double us = round_us(ks) + parts_us(ks);
       if (us < p.us * 0.97) p = WidePlan{us, whole, ks};
@@ -1480,14 +1480,13 @@ hipError_t enqueue_masked_head(dmtd_ctx* c, const Rows& R, int m0 /* a multiple 
 // that reads them again (2046 rows, 2560 wide, 152k entries): four times 781 + 67 us before, 2741 + 12 now: no logits written, the weights read once, and
 // 4752 tiles in 19 rounds of the chip where 1188 took 5.
 // The results live in the layers' scratch, like the logits do; false: they do not fit (a vocabulary of a few entries).
-bool masked_nll_fits(const dmtd_ctx* c, int rows) {
-  const dmtd_config& cf = c->cfg;
+bool masked_nll_fits(const dmtd_config& cf, int wide_rows, int rows) {
   const size_t nt = (size_t)(cf.vocab + GW_BN - 1) / GW_BN, ld = ((size_t)rows + 15) / 16 * 16;
-  return blocked_rows(c, rows) && ld * (nt * GwTile<128>::WN * sizeof(float2) + 16) <= (size_t)head_row_capacity(cf, c->wide_rows) * cf.vocab * 4;
+  return cf.dtype == DMTD_DTYPE_BF16 && rows > kTiledRows && ld * (nt * GwTile<128>::WN * sizeof(float2) + 16) <= (size_t)head_row_capacity(cf, wide_rows) * cf.vocab * 4;
 }
 hipError_t enqueue_masked_nll(dmtd_ctx* c, const Rows& R, int rows, int p0, int r, int n) {
   const dmtd_config& cf = c->cfg;
-  const WideChoice w = choose_wide<EPI_NLL>(cf, c->num_cus, rows, cf.vocab, cf.hidden);
+  const WideChoice w = choose_wide<EPI_LOGITS>(cf, c->num_cus, rows, cf.vocab, cf.hidden);      // the same tiles, all whole
   const int ld = (rows + 15) / 16 * 16, n_parts = w.nt * (w.bm == 128 ? GwTile<128>::WN : GwTile<256>::WN);
   char* base = c->ws + c->o.logits_rows;
   float2* part = (float2*)base;
@@ -2306,6 +2305,14 @@ int dmtd_front_plan(const dmtd_config* cfg, const int32_t* rows, int32_t n, int3
   return DMTD_OK;
 }
 
+int dmtd_score_plan(const dmtd_config* cfg, int32_t batch, int32_t n, int32_t plan[2]) {
+  std::string why;
+  if (!plan || !valid_config(cfg, why) || batch < 1 || batch > cfg->max_batch || n < 1 || n > cfg->max_seq_len) return DMTD_EINVAL;
+  plan[0] = std::min(n, pass_positions(*cfg, kWideRows, batch));
+  plan[1] = masked_nll_fits(*cfg, kWideRows, batch * plan[0]) ? 1 : 0;
+  return DMTD_OK;
+}
+
 int dmtd_masked_forward(dmtd_ctx* c, const int32_t* tokens, int32_t batch, int32_t n, const uint8_t* mask, int32_t n_late,
                         float* nll, int32_t* best, float* logits, size_t logits_elems, float* loss) {
   if (!c) return DMTD_EINVAL;
@@ -2337,7 +2344,7 @@ int dmtd_masked_forward(dmtd_ctx* c, const int32_t* tokens, int32_t batch, int32
     Rows R = front_rows(c);
     e = enqueue_masked_chunk(c, R, p0, r, n_late);
     const int rows = batch * r, head = head_row_capacity(cf, c->wide_rows);
-    if (!logits && masked_nll_fits(c, rows)) {
+    if (!logits && masked_nll_fits(cf, c->wide_rows, rows)) {
       if (e == hipSuccess) e = enqueue_masked_nll(c, R, rows, p0, r, n);
       continue;
     }

@@ -63,7 +63,7 @@ def test_cases_reach_the_layouts_they_are_there_for(name):
     cfg = engine_config(sh, n + 2, batch).to_c()
     for kind, want in LAYOUTS[name].items():
         plan = (C.c_int32 * 5)()
-        rows = batch * n if kind != "lmhead" else min(batch * n, 512)      # a scoring pass holds the logits of 512 rows at a time
+        rows = batch * n if kind != "lmhead" else min(batch * n, 512)      # a scoring pass that is asked for logits, as here, holds those of 512 rows at a time
         assert pkg.load_library().dmtd_wide_plan(C.byref(cfg), KINDS[kind], rows, 256, plan) == pkg.DMTD_OK
         assert tuple(plan) == want, kind
 
