@@ -305,7 +305,8 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
     for (int i = 0; i < 2; ++i) {
       const int m = m_w + 32 * i + col, mc = min(m, M - 1);
       const bool act = m < M;
-      const unsigned long long seen = a.amax[mc];          // maybe an older value: then the search below runs once too often
+      // other blocks raise it meanwhile: with an older value the search below runs once too often
+      const unsigned long long seen = __hip_atomic_load(a.amax + mc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const int rel = target[mc] - n_w - m_l;
       const float rs = rs_s[wm * 64 + 32 * i + col];
       float mx = -INFINITY;
