@@ -355,7 +355,7 @@ const void* norm_gain_for_layer(const dmtd_ctx* c, int l) {   // gain of the nor
 
 // ------------------------------------------------------- fp32 path: FMA weight streaming
 
-template <typename WT, int M, int EPI, bool NORM>
+template <int M, int EPI, bool NORM>
 hipError_t launch_gemv(dmtd_ctx* c, GemvArgs a, int groups) {
   // Short rows go through gemv_direct_kernel, which holds a wave's weights and rows in registers: four chunks of 256 fill 128 of them.
   // us per step of 4 layers, gemv_rows_kernel / here (with the attention of the same change): 256 wide 78.8 / 50, 32000 entries 117 / 79,
@@ -375,19 +375,19 @@ hipError_t launch_gemv(dmtd_ctx* c, GemvArgs a, int groups) {
   }
   // narrow outputs with long rows: the waves of a block split K
   if constexpr ((EPI == EPI_RESID || EPI == EPI_STORE) && !NORM) {
-    if (a.K >= 1024 && a.N <= 8192) {
+    if (a.N <= 8192) {
       if (a.K <= 4 * 2 * 512) {
-        hipLaunchKernelGGL((gemv_ksplit_kernel<WT, M, EPI, 2, 4, 1>), dim3((a.N + 3) / 4, groups), dim3(256), 0, c->stream, a);
+        hipLaunchKernelGGL((gemv_ksplit_kernel<float, M, EPI, 2, 4, 1>), dim3((a.N + 3) / 4, groups), dim3(256), 0, c->stream, a);
         return hipGetLastError();
       }
       if (a.K <= 4 * 5 * 512) {
-        hipLaunchKernelGGL((gemv_ksplit_kernel<WT, M, EPI, 5, 4, 1>), dim3((a.N + 3) / 4, groups), dim3(256), 0, c->stream, a);
+        hipLaunchKernelGGL((gemv_ksplit_kernel<float, M, EPI, 5, 4, 1>), dim3((a.N + 3) / 4, groups), dim3(256), 0, c->stream, a);
         return hipGetLastError();
       }
     }
   }
   const size_t lds = (size_t)M * a.K * 4;
-  auto kern = gemv_rows_kernel<WT, M, EPI, NORM, 5>;
+  auto kern = gemv_rows_kernel<float, M, EPI, NORM, 5>;
   static int occ_cache = -1;
   static size_t occ_lds = 0;
   if (lds > 160 * 1024 - 4096) return hipErrorInvalidValue;
@@ -411,7 +411,7 @@ hipError_t launch_gemv(dmtd_ctx* c, GemvArgs a, int groups) {
   return hipGetLastError();
 }
 
-template <typename WT, int EPI, bool NORM>
+template <int EPI, bool NORM>
 hipError_t gemv_rows(dmtd_ctx* c, GemvArgs a, int rows) {
   // Groups of kGemvRows rows, all full groups in one launch (a group per grid row), the rest in another.  One launch per group
   // had the groups wait for each other on a model whose weights sit in cache: the tiny model's 32-row
@@ -425,10 +425,10 @@ hipError_t gemv_rows(dmtd_ctx* c, GemvArgs a, int rows) {
     if (a.amax) g.amax = a.amax + m0;
     hipError_t e;
     switch (m) {
-      case 1: e = launch_gemv<WT, 1, EPI, NORM>(c, g, 1); break;
-      case 2: e = launch_gemv<WT, 2, EPI, NORM>(c, g, 1); break;
-      case 3: e = launch_gemv<WT, 3, EPI, NORM>(c, g, 1); break;
-      default: e = launch_gemv<WT, 4, EPI, NORM>(c, g, groups); break;
+      case 1: e = launch_gemv<1, EPI, NORM>(c, g, 1); break;
+      case 2: e = launch_gemv<2, EPI, NORM>(c, g, 1); break;
+      case 3: e = launch_gemv<3, EPI, NORM>(c, g, 1); break;
+      default: e = launch_gemv<4, EPI, NORM>(c, g, groups); break;
     }
     if (e != hipSuccess) return e;
     m0 += groups > 0 ? groups * kGemvRows : m;
@@ -1047,23 +1047,23 @@ hipError_t run_layer(dmtd_ctx* c, int l, Rows& R, int r, int sel, int offset) {
   a.eps = cf.rms_eps;
   // a2: RMSNorm + fused QKV projection (q, k, v are contiguous in the blob)
   a.W = w.q; a.gain = w.attn_norm; a.x = R.h; a.ldx = d; a.y = qkv; a.ldy = nqkv; a.N = nqkv; a.K = d;
-  if ((e = gemv_rows<float, EPI_STORE, true>(c, a, rows)) != hipSuccess) return e;
+  if ((e = gemv_rows<EPI_STORE, true>(c, a, rows)) != hipSuccess) return e;
   // a3 + a4: QK-RMSNorm + RoPE + KV append + split-K attention, then the merge
   if (r > kMaxRows && (e = launch_kv_append<float>(c, l, qkv, sel, offset, r)) != hipSuccess) return e;
   if ((e = launch_attention<float, float>(c, l, qkv, attn, (float*)nullptr, sel, offset, r, r > kMaxRows ? 2 : 1)) != hipSuccess) return e;
   // a5: O projection + residual
   a = GemvArgs{};
   a.W = w.o; a.x = attn; a.ldx = qd; a.y = R.h; a.ldy = d; a.N = d; a.K = qd;
-  if ((e = gemv_rows<float, EPI_RESID, false>(c, a, rows)) != hipSuccess) return e;
+  if ((e = gemv_rows<EPI_RESID, false>(c, a, rows)) != hipSuccess) return e;
   // a6: RMSNorm + gate/up + SwiGLU
   a = GemvArgs{};
   a.eps = cf.rms_eps;
   a.W = w.gate; a.W2 = w.up; a.gain = w.mlp_norm; a.x = R.h; a.ldx = d; a.y = mlp; a.ldy = ff; a.N = ff; a.K = d;
-  if ((e = gemv_rows<float, EPI_SWIGLU, true>(c, a, rows)) != hipSuccess) return e;
+  if ((e = gemv_rows<EPI_SWIGLU, true>(c, a, rows)) != hipSuccess) return e;
   // a7: down projection + residual
   a = GemvArgs{};
   a.W = w.down; a.x = mlp; a.ldx = ff; a.y = R.h; a.ldy = d; a.N = d; a.K = ff;
-  return gemv_rows<float, EPI_RESID, false>(c, a, rows);
+  return gemv_rows<EPI_RESID, false>(c, a, rows);
 }
 
 // a9, first part: final RMSNorm + LM head (Eq. 5) of n_rows rows into logits [n_rows, vocab], selection keys into amax
@@ -1082,7 +1082,7 @@ hipError_t head_logits(dmtd_ctx* c, const Rows& R, int n_rows, float* logits, un
   a.W = c->lm_head; a.gain = c->final_norm; a.x = R.h; a.ldx = cf.hidden;
   a.y = logits; a.ldy = cf.vocab; a.N = cf.vocab; a.K = cf.hidden;
   a.amax = amax; a.amax_ld = amax_ld;
-  return gemv_rows<float, EPI_LOGITS, true>(c, a, n_rows);
+  return gemv_rows<EPI_LOGITS, true>(c, a, n_rows);
 }
 
 // a9: final RMSNorm + LM head + greedy selection for one row per sequence; then the step's bookkeeping
@@ -1587,16 +1587,16 @@ hipError_t time_one(dmtd_ctx* c, int kind, int l, int rows) {
   switch (kind) {
     case DMTD_K_QKV:
       a.W = w.q; a.gain = w.attn_norm; a.x = R.h; a.ldx = d; a.y = qkv; a.ldy = nqkv; a.N = nqkv; a.K = d;
-      return gemv_rows<float, EPI_STORE, true>(c, a, rows);
+      return gemv_rows<EPI_STORE, true>(c, a, rows);
     case DMTD_K_OPROJ:
       a.W = w.o; a.x = attn; a.ldx = qd; a.y = R.h; a.ldy = d; a.N = d; a.K = qd;
-      return gemv_rows<float, EPI_RESID, false>(c, a, rows);
+      return gemv_rows<EPI_RESID, false>(c, a, rows);
     case DMTD_K_GATEUP:
       a.W = w.gate; a.W2 = w.up; a.gain = w.mlp_norm; a.x = R.h; a.ldx = d; a.y = mlp; a.ldy = ff; a.N = ff; a.K = d;
-      return gemv_rows<float, EPI_SWIGLU, true>(c, a, rows);
+      return gemv_rows<EPI_SWIGLU, true>(c, a, rows);
     default:
       a.W = w.down; a.x = mlp; a.ldx = ff; a.y = R.h; a.ldy = d; a.N = d; a.K = ff;
-      return gemv_rows<float, EPI_RESID, false>(c, a, rows);
+      return gemv_rows<EPI_RESID, false>(c, a, rows);
   }
 }
 

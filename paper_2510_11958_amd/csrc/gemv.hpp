@@ -13,7 +13,8 @@
 //                       outputs with long rows (O projection, down projection), where
 //                       whole-row waves would leave most of the chip idle.  Each lane keeps
 //                       its own slices of the activation rows in registers.
-//  gemv_direct_kernel : short rows (K <= 1024) of an fp32 model: nothing through LDS, no barrier, every load issued at once.
+//  gemv_direct_kernel : short rows (K <= 1024) of an fp32 model: no LDS and no barrier on the way to the sums, every load issued at once
+//                       (the LM head's selection keys meet in LDS behind one barrier).
 #pragma once
 #include "kernels.hpp"
 
@@ -209,7 +210,8 @@ __global__ void __launch_bounds__(256) gemv_rows_kernel(GemvArgs a) {
 // Short rows (256 (ITS - 1) < K <= 256 ITS) of a small fp32 model, whose launches are bound by latency: kernel start, one round trip to
 // memory, the reduction.  A wave owns 4 outputs (SwiGLU: the gate and up rows of 2) and M activation rows; it loads its weights, the
 // rows, the norm's gain and the residual values it adds to, all at once, computes the rows' sums of squares by itself, and scales its sums
-// by 1/rms at the end.  No LDS, no barrier, no load behind another (gemv_rows_kernel has three round trips: rows, gain, residual).
+// by 1/rms at the end.  No LDS, no barrier (but for the LM head's keys, at the end), no load behind another (gemv_rows_kernel has three round
+// trips: rows, gain, residual).
 // Tiny model (256 wide, SwiGLU width 768, cache resident), us per launch with 2 rows, gemv_rows_kernel / here: QKV 4.9 / 2.5, O 4.5 / 3.9,
 // gate/up 4.9 / 3.1, down 4.5 / 2.9, LM head (1024 entries, 1 row) 5.0 / 3.0; 32 rows: gate/up 23.4 / 4.3, QKV 9.1 / 3.3.
 template <int M, int EPI, bool NORM, int ITS>
