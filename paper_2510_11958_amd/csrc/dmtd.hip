@@ -38,8 +38,9 @@ constexpr int kPassRows = 128;       // activation rows (all sequences together)
 // larger than passes of 128 rows did; with less workspace the passes are shorter.
 constexpr int kWideRows = 2048;
 constexpr int kHeadRows = 512;       // rows of a whole-sequence pass whose logits are held at a time (0.3 GB at a 152k vocabulary)
-// Up to this many rows go through the LDS-tiled kernel in passes, more through the wide GEMM (all four projections of a layer at
-// 4B shapes, us: 160 rows 172 / 190, 192 rows 191 / 190, 256 rows 220 / 190 with tiles of 256 rows)
+// Up to this many rows go through the LDS-tiled kernel in passes of 128, more through the wide GEMM.  All four projections of a layer with their
+// finishing launches, us, tiled / wide: 2560 wide, 128 rows 111 / 120, 144 rows 163 / 150, 192 rows 188 / 153; 1024 wide 70 / 76, 100 / 81, 117 / 85.
+// The line stems from tiles of 256 rows only (192 rows 191 / 190); with those of 128 the kernels meet at 128 rows.
 constexpr int kTiledRows = 192;
 // Rows per sequence and in all that a decode step may carry: what the attention's partial results are laid out for.
 inline int step_row_capacity(int max_batch) { return max_batch * kMaxRows > kPassRows ? max_batch * kMaxRows : kPassRows; }
