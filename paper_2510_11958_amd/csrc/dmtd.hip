@@ -481,19 +481,24 @@ bool mfma_rows_fit(const dmtd_ctx* c, int rows, int N, int K, int n_parts) {
 // cost.  The residual projections go through the finishing kernel whole (their few tiles are nearly always split, and it
 // owns their epilogue).
 struct WidePlan { double us; int n_full, ksplit; };
-template <int EPI, int BM>
+template <int EPI, int BM, int BN>
 WidePlan plan_wide(const dmtd_config& cf, int num_cus, int rows, int nt, int KS) {
+  typedef GwTile<BM, BN> T;
   const int tiles = (rows + BM - 1) / BM * nt, slots = num_cus;
   // a k-step of 32 takes 0.8 us with 128 rows; with 256 it takes 1.3, and 1.45 in long runs, where the card lowers its clock (also where
   // it is summed by itself); a block's start and end take about 4 us.  Fitted to 300 measured launches of five widths from 200 to 2048
   // rows: with one figure of 1.25 a launch was 0.7 % slower than its better tile on average and up to 14 % (2560 wide, us, tiles of
   // 256 / 128: down with 896 rows 97 / 89, 1003 rows 98 / 95, O with 1400 rows 74 / 66; 1536 wide, down with 1003 rows 66 / 60), now 0.4 %;
-  // a raw tile's bytes are written and read by blocks all over the chip at about 3.5 TB/s in all; the finishing launch itself 5 us
-  auto step_us = [&](int ks) { return BM == 128 ? 0.8 : (EPI == EPI_STORE || 2 * KS >= 40 * ks ? 1.45 : 1.3); };
-  const int part_tiles = (int)std::min<size_t>(gemm_part_floats(cf) / GwTile<BM>::PART, 1 << 20);
+  // a raw tile's bytes are written and read by blocks all over the chip at about 3.5 TB/s in all; the finishing launch itself 5 us.
+  // Against 256 weight rows a step of 320 takes 1.28 times as long, one of 192 0.93 times (1.86, 1.31 to 1.4; 0.75 with 128 rows).
+  auto step_us = [&](int ks) {
+    const double whole = BM == 128 ? 0.8 : (EPI == EPI_STORE || 2 * KS >= 40 * ks ? 1.45 : 1.3);
+    return BN == GW_BN ? whole : (BN == 320 ? 1.28 : 0.93) * whole;
+  };
+  const int part_tiles = (int)std::min<size_t>(gemm_part_floats(cf) / T::PART, 1 << 20);
   const int whole = EPI == EPI_RESID ? 0 : tiles / slots * slots, left = tiles - whole;
   auto round_us = [&](int ks) { return (left * ks + slots - 1) / slots * (2.0 * KS / ks * step_us(ks) + 4.0); };
-  auto parts_us = [&](int ks) { return left * ks * (GwTile<BM>::PART * 4) / 3.5e6 + 5.0; };
+  auto parts_us = [&](int ks) { return left * ks * (T::PART * 4) / 3.5e6 + 5.0; };
   WidePlan p{round_us(1) + (EPI == EPI_RESID ? parts_us(1) : 0.0), EPI == EPI_RESID ? 0 : tiles, 1};
   if (EPI == EPI_RESID && left > part_tiles) p.us = 1e30;            // the raw sums do not fit
   if (EPI != EPI_LOGITS)
@@ -505,38 +510,59 @@ WidePlan plan_wide(const dmtd_config& cf, int num_cus, int rows, int nt, int KS)
   return p;
 }
 
-template <int EPI, bool NORM, int BM>
+template <int EPI, bool NORM, int BM, int BN>
 hipError_t launch_wide_tiles(dmtd_ctx* c, const MfmaArgs& g, int nt, const WidePlan& p) {
+  typedef GwTile<BM, BN> T;
   const int mt = (g.M + BM - 1) / BM, n_tail = mt * nt - p.n_full;
-  auto kern = gemm_wide_mfma_kernel<EPI, NORM, BM>;
+  auto kern = gemm_wide_mfma_kernel<EPI, NORM, BM, BN>;
   static bool big_lds = false;
   if (!big_lds) {
-    hipError_t ae = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)GwTile<BM>::LDS);
+    hipError_t ae = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::LDS);
     if (ae != hipSuccess) return ae;
     big_lds = true;
   }
-  hipLaunchKernelGGL(kern, dim3(p.n_full + n_tail * p.ksplit), dim3(64 * GW_WAVES), GwTile<BM>::LDS, c->stream, g.W, g.W2, g.xb, g.xb_lo,
+  hipLaunchKernelGGL(kern, dim3(p.n_full + n_tail * p.ksplit), dim3(64 * GW_WAVES), T::LDS, c->stream, g.W, g.W2, g.xb, g.xb_lo,
                      g.M, g.N, g.K, p.n_full, n_tail, p.ksplit, mt, nt, g);
   if constexpr (EPI != EPI_LOGITS && EPI != EPI_NLL) {
     if (n_tail > 0)
-      hipLaunchKernelGGL((gemm_wide_finish_kernel<EPI, NORM, BM>), dim3(n_tail, BM / 16), dim3(256), 0, c->stream, (const float*)g.part,
+      hipLaunchKernelGGL((gemm_wide_finish_kernel<EPI, NORM, BM, BN>), dim3(n_tail, BM / 16), dim3(256), 0, c->stream, (const float*)g.part,
                          g.M, g.N, p.n_full, n_tail, p.ksplit, mt, nt, g);
   }
   return hipGetLastError();
 }
 
-// How a launch of `rows` rows of an [N, K] projection is laid out: rows of a launch, and the tile height with its plan
-struct WideChoice { int nt, pass, bm; WidePlan p; };
+// How a launch of `rows` rows of an [N, K] projection is laid out: rows of a launch, and the tile (rows bm, weight rows bn, nt of them along
+// the outputs) with its plan
+struct WideChoice { int nt, pass, bm, bn; WidePlan p; };
+template <int EPI> int wide_col_tiles(int N, int bn) { const int out = EPI == EPI_SWIGLU ? bn / 2 : bn; return (N + out - 1) / out; }
 template <int EPI>
 WideChoice choose_wide(const dmtd_config& cf, int num_cus, int rows, int N, int K) {
   WideChoice w{};
-  w.nt = EPI == EPI_SWIGLU ? (N + 127) / 128 : (N + GW_BN - 1) / GW_BN;
-  const int part_tiles = (int)std::min<size_t>(gemm_part_floats(cf) / GwTile<256>::PART, 1 << 20);      // at least nt
+  w.nt = wide_col_tiles<EPI>(N, GW_BN);
+  w.bn = GW_BN;
+  const int part_tiles = (int)std::min<size_t>(gemm_part_floats(cf) / GwTile<256, GW_BN>::PART, 1 << 20);      // at least nt
   w.pass = rows;
   if (EPI == EPI_RESID && (long)(rows + 255) / 256 * w.nt > part_tiles) w.pass = part_tiles / w.nt * 256;
-  const WidePlan p256 = plan_wide<EPI, 256>(cf, num_cus, w.pass, w.nt, K / 64), p128 = plan_wide<EPI, 128>(cf, num_cus, w.pass, w.nt, K / 64);
+  const WidePlan p256 = plan_wide<EPI, 256, GW_BN>(cf, num_cus, w.pass, w.nt, K / 64), p128 = plan_wide<EPI, 128, GW_BN>(cf, num_cus, w.pass, w.nt, K / 64);
   w.bm = p128.us < p256.us ? 128 : 256;
   w.p = w.bm == 128 ? p128 : p256;
+  // Other widths, all tiles whole, where they fill more than 7/8 of their rounds of the chip (us, 256 / other: gate/up with 320, 1003 rows of 2560
+  // 172 / 152, 2048 rows 321 / 298, 1536 wide, 1003 rows 109 / 89, 896 wide, 2048 rows 78 / 61; with 192, 2048 wide, 1536 rows 138 / 115, 1024 wide,
+  // 2048 rows 49 / 44; QKV with 192 of 128 rows, 1003 rows of 2560 67 / 63, of 256 rows, 2048 rows 124 / 120; less full: gate/up with 320, 2048 wide,
+  // 2048 rows, 312 of 512 blocks 170 / 213, 1400 rows of 2560, 366 of 512 241 / 276).
+  if constexpr (EPI == EPI_STORE || EPI == EPI_SWIGLU) {
+    auto other = [&](auto bm_c, auto bn_c) {
+      constexpr int BM = decltype(bm_c)::value, BN = decltype(bn_c)::value;
+      const int nt = wide_col_tiles<EPI>(N, BN), tiles = (rows + BM - 1) / BM * nt, rounds = (tiles + num_cus - 1) / num_cus;
+      const WidePlan p = plan_wide<EPI, BM, BN>(cf, num_cus, rows, nt, K / 64);
+      if (p.ksplit == 1 && tiles * 8L > rounds * (long)num_cus * 7 && p.us < w.p.us) w = WideChoice{nt, rows, BM, BN, p};
+    };
+    typedef std::integral_constant<int, 128> i128; typedef std::integral_constant<int, 192> i192;
+    typedef std::integral_constant<int, 256> i256; typedef std::integral_constant<int, 320> i320;
+    other(i256(), i192());
+    if constexpr (EPI == EPI_STORE) other(i128(), i192());
+    else other(i256(), i320());
+  }
   return w;
 }
 
@@ -556,7 +582,14 @@ hipError_t launch_wide(dmtd_ctx* c, const MfmaArgs& a, int rows) {
     if (a.ssp_next) g.ssp_next = a.ssp_next + m0;
     if (a.amax) g.amax = a.amax + m0;
     g.part = c->gemm_part;
-    const hipError_t e = w.bm == 128 ? launch_wide_tiles<EPI, NORM, 128>(c, g, w.nt, w.p) : launch_wide_tiles<EPI, NORM, 256>(c, g, w.nt, w.p);
+    hipError_t e = hipErrorInvalidValue;
+    if (w.bn == GW_BN) e = w.bm == 128 ? launch_wide_tiles<EPI, NORM, 128, GW_BN>(c, g, w.nt, w.p) : launch_wide_tiles<EPI, NORM, 256, GW_BN>(c, g, w.nt, w.p);
+    if constexpr (EPI == EPI_STORE || EPI == EPI_SWIGLU)
+      if (w.bn == 192 && w.bm == 256) e = launch_wide_tiles<EPI, NORM, 256, 192>(c, g, w.nt, w.p);
+    if constexpr (EPI == EPI_STORE)
+      if (w.bn == 192 && w.bm == 128) e = launch_wide_tiles<EPI, NORM, 128, 192>(c, g, w.nt, w.p);
+    if constexpr (EPI == EPI_SWIGLU)
+      if (w.bn == 320) e = launch_wide_tiles<EPI, NORM, 256, 320>(c, g, w.nt, w.p);
     if (e != hipSuccess) return e;
   }
   if (EPI == EPI_RESID) c->resid_parts = w.nt;
@@ -1483,12 +1516,12 @@ hipError_t enqueue_masked_head(dmtd_ctx* c, const Rows& R, int m0 /* a multiple 
 // The results live in the layers' scratch, like the logits do; false: they do not fit (a vocabulary of a few entries).
 bool masked_nll_fits(const dmtd_config& cf, int wide_rows, int rows) {
   const size_t nt = (size_t)(cf.vocab + GW_BN - 1) / GW_BN, ld = ((size_t)rows + 15) / 16 * 16;
-  return cf.dtype == DMTD_DTYPE_BF16 && rows > kTiledRows && ld * (nt * GwTile<128>::WN * sizeof(float2) + 16) <= (size_t)head_row_capacity(cf, wide_rows) * cf.vocab * 4;
+  return cf.dtype == DMTD_DTYPE_BF16 && rows > kTiledRows && ld * (nt * GwTile<128, GW_BN>::WN * sizeof(float2) + 16) <= (size_t)head_row_capacity(cf, wide_rows) * cf.vocab * 4;
 }
 hipError_t enqueue_masked_nll(dmtd_ctx* c, const Rows& R, int rows, int p0, int r, int n) {
   const dmtd_config& cf = c->cfg;
   const WideChoice w = choose_wide<EPI_LOGITS>(cf, c->num_cus, rows, cf.vocab, cf.hidden);      // the same tiles, all whole
-  const int ld = (rows + 15) / 16 * 16, n_parts = w.nt * (w.bm == 128 ? GwTile<128>::WN : GwTile<256>::WN);
+  const int ld = (rows + 15) / 16 * 16, n_parts = w.nt * (w.bm == 128 ? GwTile<128, GW_BN>::WN : GwTile<256, GW_BN>::WN);
   char* base = c->ws + c->o.logits_rows;
   float2* part = (float2*)base;
   unsigned long long* keys = (unsigned long long*)(part + (size_t)n_parts * ld);
@@ -1499,7 +1532,7 @@ hipError_t enqueue_masked_nll(dmtd_ctx* c, const Rows& R, int rows, int p0, int 
   a.W = c->lm_head_sw; a.xb = R.xb; a.xb_lo = R.xb_lo; a.ldxb = cf.hidden; a.M = rows; a.N = cf.vocab; a.K = cf.hidden; a.ssp = R.ssp; a.n_parts = R.n_parts;
   a.ssp_ld = c->ssp_ld; a.eps = cf.rms_eps; a.blocked = 1;
   a.part = (float*)part; a.ldp = ld; a.amax = keys; a.ssp_next = zt; a.g_next = (const bf16_t*)target;
-  const hipError_t e = w.bm == 128 ? launch_wide_tiles<EPI_NLL, true, 128>(c, a, w.nt, w.p) : launch_wide_tiles<EPI_NLL, true, 256>(c, a, w.nt, w.p);
+  const hipError_t e = w.bm == 128 ? launch_wide_tiles<EPI_NLL, true, 128, GW_BN>(c, a, w.nt, w.p) : launch_wide_tiles<EPI_NLL, true, 256, GW_BN>(c, a, w.nt, w.p);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(nll_merge_kernel, dim3((rows + 7) / 8), dim3(256), 0, c->stream, (const float2*)part, n_parts, ld, (const int*)target, (const float*)zt,
                      (const unsigned long long*)keys, cf.max_seq_len, rows, p0, r, (float*)(c->ws + c->o.nll), (int*)(c->ws + c->o.best));

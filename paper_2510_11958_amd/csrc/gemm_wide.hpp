@@ -2,8 +2,9 @@
 // steps carry more than 192 rows): y[m, n] = sum_k W[n, k] * x[m, k] with x in two bf16 planes (see gemv_mfma.hpp).
 //
 // With hundreds of rows the projection is a matrix-core problem, not a weight stream.  A block computes a tile of 256
-// rows x 256 weight rows (SwiGLU: 128 gate and the same 128 up rows) with 8 waves of 64 x 128 (2 x 4 tiles of
-// v_mfma_f32_32x32x16_bf16).  K is walked in steps of 32: weights and both activation planes go from memory straight into
+// rows x 256 weight rows (SwiGLU: 128 gate and the same 128 up rows, 16 of each in turn) with 8 waves of 64 x 128 (2 x 4 tiles of
+// v_mfma_f32_32x32x16_bf16).  Gate/up also comes with 320 and 192 weight rows, QKV with 192, where these leave fewer CUs idle
+// (choose_wide); 320 is what the registers (240 of 256) and LDS (157 of 160 KiB) hold, and the fragments read per product are a tenth fewer.  K is walked in steps of 32: weights and both activation planes go from memory straight into
 // LDS (global_load ... lds), 48 pieces of 1 KiB per step, each piece holding 16 rows in the order [16-byte chunk of k][row],
 // which is the order the weights and the blocked activations (packed_at) are stored in; a fragment read then takes 256
 // contiguous bytes per 16 lanes (no bank conflicts).  A ring of three LDS buffers (144 KiB, one block per CU); a step is waited for by the
@@ -19,6 +20,8 @@
 // less LDS traffic) 5 % slower, tiles of 128 rows in 4 waves of 64 x 128 6 % slower.
 // Blocks go round-robin over the 8 compute dies; a die takes a contiguous run of tiles with the row tiles fastest, so a
 // weight byte enters one die's L2 only and its row tiles share it there.
+// A block costs 10 to 13 us beside its steps; of the SwiGLU epilogue's 6, its divisions and 8-byte stores took 3 (1003 rows of 2560, 320 weight rows, us
+// with them / now 156 / 153).  Without loads, reads and barriers in the loop the products alone take 140 there, on zeros 113.
 // Tiles of 128 rows (waves of 64 x 64, a ring of four buffers, 0.8 instead of 1.3 us per step) where they pad a launch's rows less.
 // Against passes of 128 rows through gemm_mfma.hpp (4B shapes, 2048 rows, us with the finishing launch, before / now):
 // gate/up 660 / 336, QKV 390 / 128, down + O 763 / 282.
@@ -34,15 +37,19 @@
 
 namespace dmtd {
 
-constexpr int GW_BN = 256;                   // weight rows of a block's tile (SwiGLU: 128 gate and 128 up rows)
+constexpr int GW_BN = 256;                   // weight rows of a block's tile (SwiGLU: gate and up rows together), unless the plan takes another width
 constexpr int GW_WAVES = 8;
-// The tile's shape by its activation rows BM: waves along the rows and the weight rows (64 rows each), 32-wide weight tiles per
-// wave, LDS buffers, 1 KiB pieces of a step (16 of weights, BM / 16 per activation plane), loads a wave issues per step.
-template <int BM> struct GwTile {
-  static constexpr int WM = BM / 64, WN = GW_WAVES / WM, NJ = GW_BN / 32 / WN, BUF = BM == 256 ? 3 : 4;
-  static constexpr int XT = BM / 16, PIECES = 16 + 2 * XT, STAGE = PIECES * 512, LPS = PIECES / GW_WAVES;
+// The tile's shape by its activation rows BM and weight rows BN: waves along the rows and the weight rows, tiles of 32 rows (RT) and of 32
+// weight rows (NJ) per wave, LDS buffers, 1 KiB pieces of a step (BN / 16 of weights, BM / 16 per activation plane), loads a wave issues
+// per step (waves below HEAVY; the others one less).
+template <int BM, int BN> struct GwTile {
+  static constexpr int WM = BM == 256 || BN % 256 != 0 ? 4 : 2, WN = GW_WAVES / WM, RT = BM / 32 / WM, NJ = BN / 32 / WN, BUF = BM == 256 ? 3 : 4;
+  static constexpr int WP = BN / 16, XT = BM / 16, PIECES = WP + 2 * XT, STAGE = PIECES * 512, LPS = (PIECES + GW_WAVES - 1) / GW_WAVES;
+  static constexpr int HEAVY = PIECES - (LPS - 1) * GW_WAVES;
   static constexpr size_t LDS = (size_t)BUF * STAGE * 2;
-  static constexpr int PART = BM * GW_BN;    // floats of a tile's raw sums
+  static constexpr int PART = BM * BN;       // floats of a tile's raw sums
+  static_assert(WM * RT * 32 == BM && WN * NJ * 32 == BN, "a tile is whole waves");
+  static_assert(LDS + 2048 <= 160 * 1024, "a CU's LDS");
 };
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -65,14 +72,14 @@ __device__ __forceinline__ GwPlace gw_place(int id, int blocks, int n_full, int 
   return p;
 }
 
-template <int EPI, bool NORM, int BM>
+template <int EPI, bool NORM, int BM, int BN>
 __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const bf16_t* W_, const bf16_t* W2_, const bf16_t* xb_, const bf16_t* xb_lo_,
                                                                 int M_, int N_, int K_, int n_full_, int n_tail_, int ksplit_, int mt_, int nt_, MfmaArgs a) {
   // which operand gives the result's rows: with the weights there a lane holds 4 consecutive outputs of one activation row (8-byte
   // pieces of the blocked layout, 512 contiguous bytes per two row groups and store), else 16 rows of one output (128 bytes of a row)
   constexpr bool WA = EPI == EPI_SWIGLU || EPI == EPI_NLL;
-  typedef GwTile<BM> T;
-  constexpr int NJ = T::NJ;
+  typedef GwTile<BM, BN> T;
+  constexpr int NJ = T::NJ, RT = T::RT;
   extern __shared__ float4 gemm_dyn_smem[];
   bf16_t* ring = (bf16_t*)gemm_dyn_smem;
   __shared__ float rs_s[BM];
@@ -87,42 +94,39 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
   const int s_hi = pl.tail ? 2 * (int)((long)(pl.ks + 1) * KS / ksplit_) : 2 * KS;
   const int n_tiles = (N + 15) >> 4;
 
-  // loads: wave w brings weight pieces 2w, 2w + 1 and XP activation pieces from XP w on (waves 0-3 the high plane) of every step;
-  // the bases are uniform over the wave, a lane adds its 16 bytes.  Weight tiles beyond N and activation tiles beyond M repeat
-  // the last one, and the last activation tile's rows beyond M hold whatever the buffer held: each is an output row of its
-  // own that is never stored.
-  const bf16_t* wsrc[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int p = 2 * w + j;
-    int gt = EPI == EPI_SWIGLU ? nb * 8 + (p & 7) : nb * 16 + p;
-    if (gt >= n_tiles) gt = n_tiles - 1;
-    wsrc[j] = ((EPI == EPI_SWIGLU && p >= 8) ? W2_ : W_) + ((size_t)gt * KS) * 1024 + (size_t)s_lo * 512;
-  }
+  // loads: wave w brings pieces w, w + 8, ... of every step, which are the weights' (SwiGLU: 16 gate rows and the up rows of the same outputs
+  // in turn), the high plane's and the low plane's; the bases are uniform over the wave, a lane adds its 16 bytes.  Weight tiles beyond
+  // N and activation tiles beyond M repeat the last one, and the last activation tile's rows beyond M hold whatever the buffer
+  // held: each is an output row of its own that is never stored.
   const int m_tiles = (M + 15) >> 4;
-  constexpr int XP = T::LPS - 2;
-  const bf16_t* xsrc[XP];
+  const bf16_t* src[T::LPS];
+  int slot[T::LPS];                            // the piece's place in a buffer
 #pragma unroll
-  for (int j = 0; j < XP; ++j)
-    xsrc[j] = (w >= 4 ? xb_lo_ : xb_) + (size_t)min(mb * T::XT + (XP * w + j) % T::XT, m_tiles - 1) * KS * 1024 + (size_t)s_lo * 512;
+  for (int j = 0; j < T::LPS; ++j) {
+    const int p = min(w + GW_WAVES * j, T::PIECES - 1), q = p - T::WP;
+    const bool up = EPI == EPI_SWIGLU && p >= T::WP / 2;
+    const int gt = min(EPI == EPI_SWIGLU ? nb * (BN / 32) + p - (up ? T::WP / 2 : 0) : nb * T::WP + p, n_tiles - 1);
+    const bf16_t* base = p < T::WP ? (up ? W2_ : W_) : (q >= T::XT ? xb_lo_ : xb_);
+    const int tile = p < T::WP ? gt : min(mb * T::XT + (q >= T::XT ? q - T::XT : q), m_tiles - 1);
+    src[j] = base + (size_t)tile * KS * 1024 + (size_t)s_lo * 512;
+    slot[j] = EPI == EPI_SWIGLU && p < T::WP ? (up ? 2 * p - T::WP + 1 : 2 * p) : w + GW_WAVES * j;
+  }
   auto issue_one = [&](int buf, int j) {       // load j of a step into ring buffer buf
-    bf16_t* dst = ring + buf * T::STAGE + (j < 2 ? 2 * w + j : 16 + XP * w + j - 2) * 512;
-    const bf16_t*& src = j < 2 ? wsrc[j] : xsrc[j - 2];
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + lane * 8), (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
-    src += 512;
+    if (j == T::LPS - 1 && T::HEAVY < GW_WAVES && w >= T::HEAVY) return;
+    bf16_t* dst = ring + buf * T::STAGE + slot[j] * 512;
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[j] + lane * 8), (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+    src[j] += 512;
   };
   auto issue = [&](int buf) {
 #pragma unroll
     for (int j = 0; j < T::LPS; ++j) issue_one(buf, j);
   };
   const int wm = w % T::WM, wn = w / T::WM;
-  // 32-row weight tiles of this wave (SwiGLU: NJ / 2 gate tiles and the up tiles of the same outputs)
-  constexpr int HJ = NJ / 2;
-  auto wtile = [&](int j) { return EPI == EPI_SWIGLU ? (j / HJ) * 4 + HJ * wn + j % HJ : NJ * wn + j; };
+  auto wtile = [&](int j) { return NJ * wn + j; };     // 32-row weight tiles of this wave (SwiGLU: 16 gate rows, then the up rows of the same outputs)
   const int frag = ((lane >> 4) & 1) * 512 + (lane >> 5) * 128 + (lane & 15) * 8;   // this lane's 16 bytes of a 32-row tile, k chunk 0
-  f32x16 acc[2][NJ];
+  f32x16 acc[RT][NJ];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < RT; ++i)
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -156,30 +160,39 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
     return WA ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, xv, c, 0, 0, 0) : __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv, wv, c, 0, 0, 0);
   };
   // fragments of half a step (16 of k), in order of first use: low parts of the two row tiles, weight tiles, high parts
-  constexpr int NF = 4 + NJ;
+  constexpr int NF = 2 * RT + NJ;
   struct Frag { bf16x8_t f[NF]; };
   auto read_one = [&](Frag& f, const bf16_t* base, int c, int q) {
-    const int piece = q < 2 ? 16 + T::XT + (2 * wm + q) * 2 : (q < 2 + NJ ? 2 * wtile(q - 2) : 16 + (2 * wm + q - 2 - NJ) * 2);
+    const int piece = q < RT ? T::WP + T::XT + (RT * wm + q) * 2 : (q < RT + NJ ? 2 * wtile(q - RT) : T::WP + (RT * wm + q - RT - NJ) * 2);
     f.f[q] = chunk(base + piece * 512 + c * 256);
   };
   constexpr bool KEEP = SHORT_SUMS && BM == 128;      // a second set of accumulators
-  f32x16 part[2][KEEP ? NJ : 1];
+  f32x16 part[KEEP ? RT : 1][KEEP ? NJ : 1];
   auto clear = [&](f32x16& c) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) c[e] = 0.f;
   };
   if (KEEP)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j) clear(part[i][KEEP ? j : 0]);
+  // the loads of a step have returned once all but those of `newer` newer steps have (they return in order); none newer for certain: all
+  // vmcnt(loads) lgkmcnt(0), expcnt untouched
+  auto wait_but = [&](auto newer_c) {
+    constexpr int newer = decltype(newer_c)::value;
+    static_assert(newer * T::LPS < 16, "the counter wait's low field");
+    if (newer == 0 || T::HEAVY == GW_WAVES || w < T::HEAVY) __builtin_amdgcn_s_waitcnt(newer * T::LPS | (7 << 4));
+    else __builtin_amdgcn_s_waitcnt(newer * (T::LPS - 1) | (7 << 4));
+  };
+  const auto wait_all = std::integral_constant<int, 0>();
   if constexpr (SHORT_SUMS && !KEEP) {
+    static_assert(RT == 2, "two row tiles");
     int buf = 0, nxt = T::BUF - 1;
     for (int s = s_lo; s < s_hi; ++s) {
-      // this step's pieces have landed once all loads but the newer step's have returned (they return in order); behind the barrier
-      // every wave's have, and every wave is done with the buffer that is filled next.  vmcnt(LPS) lgkmcnt(0), expcnt untouched
-      if (s + 1 < s_hi) __builtin_amdgcn_s_waitcnt(T::LPS | (7 << 4));
-      else __builtin_amdgcn_s_waitcnt(7 << 4);
+      // this step's pieces have landed; behind the barrier every wave's have, and every wave is done with the buffer that is filled next
+      if (s + 1 < s_hi) wait_but(std::integral_constant<int, 1>());
+      else wait_but(wait_all);
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");         // no LDS read of the slice moves above the barrier
       const bf16_t* base = ring + buf * T::STAGE + frag;
@@ -189,7 +202,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
 #pragma unroll
         for (int c = 0; c < 2; ++c)
 #pragma unroll
-          for (int i = 0; i < 2; ++i) xf[p][c][i] = chunk(base + (16 + (1 - p) * T::XT + (2 * wm + i) * 2) * 512 + c * 256);
+          for (int i = 0; i < 2; ++i) xf[p][c][i] = chunk(base + (T::WP + (1 - p) * T::XT + (2 * wm + i) * 2) * 512 + c * 256);
       bf16x8_t w0 = chunk(base + wtile(0) * 1024), w1 = chunk(base + wtile(0) * 1024 + 256);
       __builtin_amdgcn_sched_barrier(0);
       if (s + T::BUF - 1 < s_hi) issue(nxt);
@@ -197,14 +210,15 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
       for (int j = 0; j < NJ; ++j) {       // the next tile's weights are read while this one's products run
         const bf16_t* wn = base + wtile(j + 1 < NJ ? j + 1 : j) * 1024;
         const bf16x8_t n0 = chunk(wn), n1 = chunk(wn + 256);
-        clear(part[0][0]); clear(part[1][0]);
+        f32x16 sum[2];
+        clear(sum[0]); clear(sum[1]);
 #pragma unroll
         for (int p = 0; p < 2; ++p)        // low parts first
 #pragma unroll
           for (int c = 0; c < 2; ++c)
 #pragma unroll
-            for (int i = 0; i < 2; ++i) part[i][0] = mma(c ? w1 : w0, xf[p][c][i], part[i][0]);
-        acc[0][j] += part[0][0]; acc[1][j] += part[1][0];
+            for (int i = 0; i < 2; ++i) sum[i] = mma(c ? w1 : w0, xf[p][c][i], sum[i]);
+        acc[0][j] += sum[0]; acc[1][j] += sum[1];
         w0 = n0; w1 = n1;
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -216,19 +230,17 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
     // barrier stands between the halves.  Behind it the second half's fragments are in registers, so the matrix cores go on at
     // once; every wave is done reading this step's buffer, so it is refilled (a load beside every pair of products: together they would
     // hold the wave up, the memory pipe takes a load per 16 cycles of a CU); and the next step has landed for every wave.
-    // vmcnt(newer steps x LPS) lgkmcnt(0), expcnt untouched: loads return in order, BUF - 2 newer steps are on their way (at the end fewer,
-    // then all loads are waited for).
-    constexpr int VM = (T::BUF - 2) * T::LPS;
-    static_assert(VM < 16, "the counter wait's low field");
+    // BUF - 2 newer steps are on their way (at the end fewer, then all loads are waited for).
+    const auto newer = std::integral_constant<int, T::BUF - 2>();
     auto half = [&](const Frag& f, auto beside) {
 #pragma unroll
       for (int q = 0; q < 2 * NJ; ++q) {
         const int p = q / NJ, j = q % NJ;    // low parts first
         beside(q);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          f32x16& c = KEEP ? part[i][KEEP ? j : 0] : acc[i][j];
-          c = mma(f.f[2 + j], f.f[p ? 2 + NJ + i : i], c);
+        for (int i = 0; i < RT; ++i) {
+          f32x16& c = KEEP ? part[KEEP ? i : 0][KEEP ? j : 0] : acc[i][j];
+          c = mma(f.f[RT + j], f.f[p ? RT + NJ + i : i], c);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -241,8 +253,8 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
         for (int z = 2 * NJ; z < n; ++z) f(z);
     };
     Frag f0, f1;
-    if (s_hi - s_lo >= T::BUF - 1) __builtin_amdgcn_s_waitcnt(VM | (7 << 4));
-    else __builtin_amdgcn_s_waitcnt(7 << 4);
+    if (s_hi - s_lo >= T::BUF - 1) wait_but(newer);
+    else wait_but(wait_all);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");           // no LDS read of a slice moves above the barrier
 #pragma unroll
@@ -255,8 +267,8 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
       const bf16_t* next = ring + nxt * T::STAGE + frag;
       __builtin_amdgcn_sched_barrier(0);
       half(f0, [&](int q) { share(q, NF, [&](int z) { read_one(f1, base, 1, z); }); });
-      if (s + T::BUF - 1 < s_hi) __builtin_amdgcn_s_waitcnt(VM | (7 << 4));
-      else __builtin_amdgcn_s_waitcnt(7 << 4);
+      if (s + T::BUF - 1 < s_hi) wait_but(newer);
+      else wait_but(wait_all);
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
       const bool more = s + 1 < s_hi, fill = s + T::BUF < s_hi;
@@ -266,7 +278,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
       });
       if (KEEP && (((s - s_lo) & 3) == 3 || s + 1 == s_hi)) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < RT; ++i)
 #pragma unroll
           for (int j = 0; j < NJ; ++j) { acc[i][j] += part[i][KEEP ? j : 0]; clear(part[i][KEEP ? j : 0]); }
       }
@@ -275,42 +287,42 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
   }
 
   // lane (column n = lane % 32 of a weight tile): element e of acc[i][j] is row 32 i + 8 (e / 4) + 4 (lane / 32) + e % 4 of the wave
-  const int m_w = mb * BM + wm * 64, m_l = 4 * (lane >> 5), col = lane & 31;
+  const int m_w = mb * BM + wm * 32 * RT, m_l = 4 * (lane >> 5), col = lane & 31;
   if (EPI != EPI_LOGITS && EPI != EPI_NLL && pl.tail) {
-    // raw sums [BM rows][256 outputs] (SwiGLU: 128 gate, 128 up) of this part of K, for the finishing kernel
-    float* part = a.part + ((size_t)pl.ks * n_tail_ + (pl.t - n_full_)) * T::PART + (size_t)(wm * 64) * GW_BN;
+    // raw sums [BM rows][BN weight rows] of this part of K, for the finishing kernel
+    float* part = a.part + ((size_t)pl.ks * n_tail_ + (pl.t - n_full_)) * T::PART + (size_t)(wm * 32 * RT) * BN;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
         if (WA) {
 #pragma unroll
           for (int q = 0; q < 4; ++q)
-            *(f32x4*)(part + (32 * i + col) * GW_BN + wtile(j) * 32 + 8 * q + m_l) = f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+            *(f32x4*)(part + (32 * i + col) * BN + wtile(j) * 32 + 8 * q + m_l) = f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
         } else {
 #pragma unroll
-          for (int e = 0; e < 16; ++e) part[(32 * i + 8 * (e >> 2) + m_l + (e & 3)) * GW_BN + wtile(j) * 32 + col] = acc[i][j][e];
+          for (int e = 0; e < 16; ++e) part[(32 * i + 8 * (e >> 2) + m_l + (e & 3)) * BN + wtile(j) * 32 + col] = acc[i][j][e];
         }
       }
     return;
   }
   if (EPI == EPI_LOGITS && tid < BM) key_s[tid] = 0ull;
   __syncthreads();
-  const int r_w = wm * 64 + m_l;
+  const int r_w = wm * 32 * RT + m_l;
   if constexpr (EPI == EPI_NLL) {
     // What the loss and the greedy choice need of this wave's 32 NJ entries, the logits themselves go nowhere: per row the largest one and
     // the sum of exponentials against it, the target's logit if it is here, and the best entry's key.  A lane has 16 NJ entries of
     // row 32 i + lane % 32, 32 j + 8 q + 4 (lane / 32) + 0..3 from n_w on; the row's others are with lane ^ 32.
-    const int n_w = nb * GW_BN + 32 * NJ * wn;
+    const int n_w = nb * BN + 32 * NJ * wn;
     const int* target = (const int*)a.g_next;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < RT; ++i) {
       const int m = m_w + 32 * i + col, mc = min(m, M - 1);
       const bool act = m < M;
       // other blocks raise it meanwhile: with an older value the search below runs once too often
       const unsigned long long seen = __hip_atomic_load(a.amax + mc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const int rel = target[mc] - n_w - m_l;
-      const float rs = rs_s[wm * 64 + 32 * i + col];
+      const float rs = rs_s[wm * 32 * RT + 32 * i + col];
       float mx = -INFINITY;
 #pragma unroll
       for (int j = 0; j < NJ; ++j) acc[i][j] *= rs;
@@ -366,31 +378,43 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
     return;
   }
   if (EPI == EPI_SWIGLU) {
-    // activation row 32 i + lane % 32 of the wave, outputs 32 j + 8 q + 4 (lane / 32) + 0..3 of its 32 HJ
+    // activation row 32 i + lane % 32 of the wave, outputs 16 j + 8 q + 4 (lane / 32) + 0..3 of its 16 NJ; lanes 32 apart then exchange halves, so
+    // that the lower one stores the 8 outputs of q = 0 and the upper one those of q = 1
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < RT; ++i) {
       const int m = m_w + 32 * i + col;
-      const float rs = rs_s[wm * 64 + 32 * i + col];
+      const float rs = rs_s[wm * 32 * RT + 32 * i + col];
 #pragma unroll
-      for (int jq = 0; jq < 4 * HJ; ++jq) {
-        const int j = jq >> 2, q = jq & 3, n = nb * 128 + wn * 32 * HJ + 32 * j + 8 * q + m_l;
-        bf16_t hi[4], lo[4];
+      for (int j = 0; j < NJ; ++j) {
+        const int n = nb * (BN / 2) + wtile(j) * 16 + 8 * (lane >> 5);
+        uint32_t hi[2][2], lo[2][2];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float gt = acc[i][j][4 * q + e] * rs, up = acc[i][j + HJ][4 * q + e] * rs;
-          split_bf16(gt / (1.0f + __expf(-gt)) * up, hi[e], lo[e]);
-        }
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            float v[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              // the reciprocal is good to one unit in the last place, 2^-7 of what the two bf16 parts keep
+              const float gt = acc[i][j][4 * q + 2 * h + e] * rs, up = acc[i][j][8 + 4 * q + 2 * h + e] * rs;
+              v[e] = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * up;
+            }
+            hi[q][h] = pack_bf16x2(v[0], v[1]);
+            lo[q][h] = pack_bf16x2(v[0] - __uint_as_float(hi[q][h] << 16), v[1] - __uint_as_float(hi[q][h] & 0xFFFF0000u));
+          }
+        const LanePair<uint32_t> h0 = halves<32>(hi[0][0], hi[1][0]), h1 = halves<32>(hi[0][1], hi[1][1]);
+        const LanePair<uint32_t> l0 = halves<32>(lo[0][0], lo[1][0]), l1 = halves<32>(lo[0][1], lo[1][1]);
         if (m < M && n < N) {
           const size_t at = packed_at(1, m, n, a.ldyb);
-          *(uint2*)(a.yb + at) = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
-          *(uint2*)(a.yb_lo + at) = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
+          *(u32x4*)(a.yb + at) = u32x4{h0.x, h1.x, h0.y, h1.y};
+          *(u32x4*)(a.yb_lo + at) = u32x4{l0.x, l1.x, l0.y, l1.y};
         }
       }
     }
     return;
   }
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < RT; ++i)
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int ml = 32 * i + 8 * (e >> 2) + (e & 3), m = m_w + m_l + ml;
@@ -398,7 +422,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
       unsigned long long best = 0ull;
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
-        const int n = nb * GW_BN + wtile(j) * 32 + col;
+        const int n = nb * BN + wtile(j) * 32 + col;
         const float v = acc[i][j][e] * rs;
         if (m < M && n < N) {
           a.y[(size_t)m * a.ldy + n] = v;
@@ -419,7 +443,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
 // blocked stores are 16-byte pieces: 38 us for 2048 x 2560 from 3 parts.)  With 2048 rows memory bounds it (126 MB in 25 us); with a few
 // hundred the round trips do, so every load is issued ahead of the first sum (us, one round of 4 parts of a group at a time / now: residual,
 // 256 rows of 1024 10.2 / 8.6, 1003 rows of 2560 20.6 / 19.3, gate/up 2048 rows 15.8 / 12.0, QKV 13.3 / 10.1).
-template <int EPI, bool NORM, int BM>
+template <int EPI, bool NORM, int BM, int BN>
 __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part_, int M_, int N_, int n_full_, int n_tail_, int ksplit_, int mt_, int nt_,
                                                                MfmaArgs a) {
   __shared__ float ss_s[4][16];
@@ -428,11 +452,11 @@ __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part
   const int per_group = 8 * nt_, grp = t / per_group, in = t - grp * per_group, rows = min(8, mt_ - grp * 8);
   const int nb = in / rows, mb = grp * 8 + in - nb * rows;
   const int r = blockIdx.y * 16 + (lane & 15), m = mb * BM + r, c8 = (lane >> 4) * 8;
-  constexpr int PART = GwTile<BM>::PART;
+  constexpr int PART = GwTile<BM, BN>::PART;
   if (mb * BM + (int)blockIdx.y * 16 >= M) return;
   const bool act = m < M;
   const int mc = act ? m : M - 1;
-  constexpr int GROUPS = EPI == EPI_SWIGLU ? 1 : 2;      // groups of 32 outputs per wave
+  constexpr int OUT = EPI == EPI_SWIGLU ? BN / 2 : BN, ALL = OUT / 32, GROUPS = (ALL + 3) / 4;      // outputs of a tile; groups of 32 of them, per wave
   constexpr int PRE = EPI == EPI_RESID ? 6 : 4;          // parts of every group fetched at once
   const size_t step = (size_t)n_tail_ * PART;
   float ssv[4];                                          // the row's partial sums of squares, 16 of them up front
@@ -441,39 +465,40 @@ __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part
     for (int j = 0; j < 4; ++j) ssv[j] = a.ssp[(size_t)min((lane >> 4) + 4 * j, a.n_parts - 1) * a.ssp_ld + mc];
   float hsq = 0.f;
   // all loads of all groups first: the residual rows, the gains, and up to PRE parts (a group beyond N repeats the first)
-  const int c0 = nb * (EPI == EPI_SWIGLU ? 128 : GW_BN);
-  f32x4 sum[GROUPS][2], sum2[1][2], res[GROUPS][2];
+  const int c0 = nb * OUT;
+  f32x4 sum[GROUPS][2], sum2[EPI == EPI_SWIGLU ? GROUPS : 1][2], res[GROUPS][2];
   u32x4 gain[GROUPS];
   const float* src[GROUPS];
 #pragma unroll
   for (int gi = 0; gi < GROUPS; ++gi) {
-    const int lg = (w * GROUPS + gi) * 32, lc = (c0 + lg < N ? lg : 0) + c8;
-    src[gi] = part_ + (size_t)blockIdx.x * PART + (size_t)r * GW_BN + lc;
+    const int lg = (w * GROUPS + gi) * 32, lc = (w * GROUPS + gi < ALL && c0 + lg < N ? lg : 0) + c8;
+    // SwiGLU: 16 gate sums, then the up sums of the same outputs
+    src[gi] = part_ + (size_t)blockIdx.x * PART + (size_t)r * BN + (EPI == EPI_SWIGLU ? (lc & ~15) * 2 + (lc & 15) : lc);
     sum[gi][0] = sum[gi][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (EPI == EPI_SWIGLU) sum2[gi][0] = sum2[gi][1] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (EPI == EPI_RESID) {
       res[gi][0] = *(const f32x4*)(a.y + (size_t)mc * a.ldy + c0 + lc);
       res[gi][1] = *(const f32x4*)(a.y + (size_t)mc * a.ldy + c0 + lc + 4);
       gain[gi] = *(const u32x4*)(a.g_next + c0 + lc);
     }
   }
-  sum2[0][0] = sum2[0][1] = f32x4{0.f, 0.f, 0.f, 0.f};
   auto add_parts = [&](int k0, auto n_c) {
     constexpr int n = decltype(n_c)::value;
-    f32x4 x[GROUPS][n][2], z[EPI == EPI_SWIGLU ? n : 1][2];
+    f32x4 x[GROUPS][n][2], z[EPI == EPI_SWIGLU ? GROUPS : 1][EPI == EPI_SWIGLU ? n : 1][2];
 #pragma unroll
     for (int gi = 0; gi < GROUPS; ++gi)
 #pragma unroll
       for (int k = 0; k < n; ++k) {
         const float* q = src[gi] + (size_t)(k0 + k) * step;
         x[gi][k][0] = *(const f32x4*)q; x[gi][k][1] = *(const f32x4*)(q + 4);
-        if (EPI == EPI_SWIGLU) { z[k][0] = *(const f32x4*)(q + 128); z[k][1] = *(const f32x4*)(q + 132); }
+        if (EPI == EPI_SWIGLU) { z[gi][k][0] = *(const f32x4*)(q + 16); z[gi][k][1] = *(const f32x4*)(q + 20); }
       }
 #pragma unroll
     for (int gi = 0; gi < GROUPS; ++gi)
 #pragma unroll
       for (int k = 0; k < n; ++k) {
         sum[gi][0] += x[gi][k][0]; sum[gi][1] += x[gi][k][1];
-        if (EPI == EPI_SWIGLU) { sum2[0][0] += z[k][0]; sum2[0][1] += z[k][1]; }
+        if (EPI == EPI_SWIGLU) { sum2[gi][0] += z[gi][k][0]; sum2[gi][1] += z[gi][k][1]; }
       }
   };
   int k0 = 0;
@@ -493,8 +518,9 @@ __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part
 #pragma unroll
   for (int gi = 0; gi < GROUPS; ++gi) {
     const int n = c0 + (w * GROUPS + gi) * 32 + c8;
-    if (n - c8 >= N) continue;                                               // N is a multiple of 64 here: whole groups
-    const f32x4 s0 = sum[gi][0], s1 = sum[gi][1], u0 = sum2[0][0], u1 = sum2[0][1];
+    if (w * GROUPS + gi >= ALL || n - c8 >= N) continue;                     // N is a multiple of 64 here: whole groups
+    const int g2 = EPI == EPI_SWIGLU ? gi : 0;
+    const f32x4 s0 = sum[gi][0], s1 = sum[gi][1], u0 = sum2[g2][0], u1 = sum2[g2][1];
     f32x4 h0 = res[gi][0], h1 = res[gi][1];
     const u32x4 graw = gain[gi];
     float v[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
@@ -534,7 +560,7 @@ __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part
     }
   }
   if (EPI == EPI_RESID) {
-    // one sum of squares per row and tile of 256 outputs
+    // one sum of squares per row and tile
     hsq = column_sum(hsq);
     if (lane < 16) ss_s[w][lane] = hsq;
     __syncthreads();

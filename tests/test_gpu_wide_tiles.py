@@ -1,0 +1,50 @@
+"""GPU parity of the wide GEMM's tiles of 192 and 320 weight rows (gate/up and QKV projections that fill the chip with them), where the last
+tile along the rows and the last one along the outputs are partly empty, against the CPU oracle.
+
+Tolerance: that of the other bf16 parity tests (2e-2 of the largest logit); a wrong row, output or gate/up pair is an error of order one.
+"""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+import dmtd_inputs as di
+import paper_2510_11958_amd as pkg
+from oracle import dmtd_oracle as O
+from parity_util import engine_config, norm_err, oracle_config
+
+S = di.ModelShape
+# name: (shape, batch, positions), kind of projection, (rows per launch, rows of a tile, whole tiles, tiles of a second launch, parts of K)
+CASES = {
+    "gateup_320": (S(1, 1024, 4, 2, 64, 4800, 300), 4, 505, 2, (2020, 256, 240, 0, 1)),            # 30 x 160 outputs
+    "gateup_320_ragged": (S(1, 704, 4, 2, 64, 4544, 300), 4, 449, 2, (1796, 256, 232, 0, 1)),      # 28.4 tiles; 4 rows in the last row tile
+    "gateup_192": (S(1, 1088, 4, 2, 64, 2752, 300), 4, 505, 2, (2020, 256, 232, 0, 1)),            # 28.7 tiles of 96 outputs; K = 17 x 64
+    "qkv_192_of_256": (S(1, 1024, 51, 17, 64, 64, 300), 4, 505, 0, (2020, 256, 232, 0, 1)),        # 28.3 tiles
+    "qkv_192_of_128": (S(1, 1600, 51, 17, 64, 64, 300), 1, 1003, 0, (1003, 128, 232, 0, 1)),       # a short last row tile of 107
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_cases_reach_the_tiles_they_are_there_for(name):
+    """Runs without a GPU: the number of whole tiles tells the width."""
+    sh, batch, n, kind, want = CASES[name]
+    plan = (C.c_int32 * 5)()
+    assert pkg.load_library().dmtd_wide_plan(C.byref(engine_config(sh, n + 2, batch).to_c()), kind, batch * n, 256, plan) == pkg.DMTD_OK
+    assert tuple(plan) == want
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", list(CASES))
+def test_wide_tiles_against_oracle(name):
+    sh, batch, n, _, _ = CASES[name]
+    blob = di.make_weight_blob(sh, seed=31, std=0.04, gain_sigma=0.2)
+    toks = di.make_prompts(sh.vocab, batch, n, seed=5)
+    mask = O.inference_mask(n, n // 2, 3)
+    eng = pkg.Engine(engine_config(sh, n + 2, batch), blob)
+    got = eng.masked_forward(toks, mask, 1, want_logits=True)["logits"]
+    ocfg = oracle_config(sh)
+    w = O.unpack_weights(blob, ocfg)
+    for b in range(batch):
+        ref = O.masked_forward(toks[b], mask, 1, w, ocfg)
+        worst = max(norm_err(got[b, i], ref[i]) for i in range(n))
+        assert worst < 2e-2, (b, worst)
