@@ -18,8 +18,14 @@
 // K goes from the cache straight into LDS (global_load ... lds; rows of HD with their 16-byte chunks permuted by the key
 // number), V through registers, transposed on the way (4 keys x HD/16 dims per thread, 8-byte pieces of 4 keys permuted by
 // the dim): fragment reads of both spread over all banks.  Two buffers of each; the next tile's loads fly during a tile.
-// What bounds it: the matrix cores (40 MFMAs of 32 cycles per 32 keys and wave at HD = 128) with the softmax and the
-// three-way split (about as many vector cycles) beside them in the other resident block's waves.
+// What bounds it: the matrix cores (40 MFMAs of 32 cycles per 32 keys and wave at HD = 128; they work 68 % of the time against 8k keys) at
+// the clock the card's power leaves them (1.83 GHz there), and the softmax and three-way split, about 0.8 times as many vector cycles.
+// So a tile's work is laid out by hand: a K fragment is read a step, a V fragment three products ahead of its use, the next tile's
+// loads are issued one beside each step of the scores, and the exponentials and parts of a contraction step stand six vector
+// instructions beside each product of the step before.  2048 rows behind 0 / 2k / 4k / 6k keys (the passes of a prompt of 8192), us per
+// launch: read and waited for in place 115 / 252 / 392 / 523; in this order 108 / 245 / 378 / 510; the blocks paired long with short
+// (launcher) 97 / 231 / 367 / 500; loads' addresses from two registers a tile 93 / 220 / 347 / 475; rescaling only beyond AP_SLACK
+// 90 / 213 / 339 / 466.  Wave priorities (by block, or raised around the softmax) changed nothing.
 // Against the decode kernel (attention_mfma.hpp, one pass over K and V per 16 query vectors, the same products) on the same passes,
 // 32/8 heads of 128, us per launch: one prompt of 1003 111 -> 52; 2048 rows against 2k to 8k keys 1044 -> 322 (the prompt of
 // 8192, 2 layers: 14.5 -> 8.8 ms); 32 prompts of 2048 in passes of 64 rows 386 -> 90; one prompt of 400 33 -> 28.
@@ -35,12 +41,13 @@ namespace dmtd {
 // dynamic LDS: per group two buffers of K and V tiles
 constexpr size_t attn_prefill_lds(int hd, int kg) { return (size_t)kg * 4 * 64 * hd * 2; }
 constexpr int AP_QV = 128, AP_KT = 64;       // query vectors of a block, keys of a tile
+constexpr float AP_SLACK = 8.f;              // growth of a row's largest score, in powers of two, that its sums are not rescaled for
 
 template <int HD, int KG>
 __global__ void __launch_bounds__(256 * KG, HD == 64 && KG == 1 ? 3 : 2) attn_prefill_mfma_kernel(
     const float* __restrict__ qkv, int ldq, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc, int nh, int nkv, int s_max,
     int r_total, const DevState* st, int sel, int offset, const bf16_t* __restrict__ q_gain, const float2* __restrict__ rope_tab,
-    float eps, bf16_t* __restrict__ out, bf16_t* __restrict__ out_lo, int ldo, int blocked) {
+    float eps, bf16_t* __restrict__ out, bf16_t* __restrict__ out_lo, int ldo, int blocked, int n_down) {
   constexpr int T = HD / 16;           // MFMA steps over d for the scores
   constexpr int DT = HD / 32;          // 32-dim tiles of the output
   constexpr int DV = HD / 16;          // dims of V a thread carries
@@ -53,7 +60,8 @@ __global__ void __launch_bounds__(256 * KG, HD == 64 && KG == 1 ? 3 : 2) attn_pr
   const int tid = threadIdx.x, lane = tid & 63;
   const int w8 = __builtin_amdgcn_readfirstlane(tid >> 6), w = w8 & 3, kg = KG == 2 ? w8 >> 2 : 0;      // wave of its group; group (tiles of that parity)
   bf16_t* ring = (bf16_t*)attn_dyn_smem + kg * 4 * TILE;                // the group's buffers: K, K, V^T, V^T
-  const int g = blockIdx.x, b = blockIdx.y, qt = gridDim.z - 1 - blockIdx.z;      // the tiles with the most keys start first
+    // the tiles with the most keys start first; behind n_down of them the shortest first (see the launcher)
+  const int g = blockIdx.x, b = blockIdx.y, z = blockIdx.z, qt = z < n_down ? (int)gridDim.z - 1 - z : z - n_down;
   const int GQ = nh / nkv, rpb = AP_QV / GQ, row0 = qt * rpb;
   const int rows = min(rpb, r_total - row0);
   const int hi = lane >> 5, qv = 32 * w + (lane & 31);
@@ -65,28 +73,29 @@ __global__ void __launch_bounds__(256 * KG, HD == 64 && KG == 1 ? 3 : 2) attn_pr
   kc += ((size_t)b * nkv + g) * s_max * HD;
   vc += ((size_t)b * nkv + g) * s_max * HD;
 
-  // The loads' addresses are worked out anew from the lane number in every tile: kept in registers through the loop they would
-  // push the kernel beyond the 256 that two blocks per CU allow.
+  // Piece i of a wave's share of a K tile holds keys (w KI + i) * 64 / CH + ln / CH, a chunk of one per lane ln, permuted by the key number.
+  // The walk hands the lane number in anew for every tile: what follows from it, kept in registers through the loop, would push the kernel
+  // beyond the 256 that two blocks per CU allow.
+  auto load_k_piece = [&](int ln, int base, int buf, int i) {
+    static_assert(64 / CH <= CH, "the permutation of a piece is that of piece 0, exclusive-or its first key");
+    const int k0 = ln / CH, c0 = (ln % CH) ^ k0, ki = (w * KI + i) * (64 / CH);
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(kc + (uint32_t)(min(base + ki + k0, key_end - 1) * HD + (c0 ^ (ki & (CH - 1))) * 8)),
+                                     (__attribute__((address_space(3))) void*)(ring + buf * TILE + (w * KI + i) * 512), 16, 0, 0);
+  };
   auto load_k = [&](int base, int buf) {
-    int ln = lane;
-    asm volatile("" : "+v"(ln));
 #pragma unroll
-    for (int i = 0; i < KI; ++i) {
-      const int J = w * KI + i, k = J * (64 / CH) + ln / CH, c = (ln % CH) ^ (k & (CH - 1));
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(kc + (uint32_t)(min(base + k, key_end - 1) * HD + c * 8)),
-                                       (__attribute__((address_space(3))) void*)(ring + buf * TILE + J * 512), 16, 0, 0);
-    }
+    for (int i = 0; i < KI; ++i) load_k_piece(lane, base, buf, i);
   };
   // this thread's 4 keys of a tile, its dims, and where its pieces go in a V^T row: 16 keys' groups of 4 in the order 0, 2, 1, 3, so
   // that the two groups a lane of the PV product needs (kg, kg + 2) are one 16-byte slot; slots permuted by the dim
   const int kgp = lane & 15, dg = w * 4 + (lane >> 4), vslot = 2 * (kgp >> 2) + (kgp & 1), vhalf = ((kgp >> 1) & 1) * 4;
   vraw_t vr[4];
+  auto load_v_piece = [&](int ln, int base, int m) {
+    vr[m] = *(const vraw_t*)(vc + (uint32_t)(min(base + 4 * (ln & 15) + m, key_end - 1) * HD + (w * 4 + (ln >> 4)) * DV));
+  };
   auto load_v = [&](int base) {
-    int ln = lane;
-    asm volatile("" : "+v"(ln));
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
-      vr[m] = *(const vraw_t*)(vc + (uint32_t)(min(base + 4 * (ln & 15) + m, key_end - 1) * HD + (w * 4 + (ln >> 4)) * DV));
+    for (int m = 0; m < 4; ++m) load_v_piece(lane, base, m);
   };
   auto drop_bad = [&](int base) {       // values from poison_s on that are not finite become 0
 #pragma unroll
@@ -97,17 +106,18 @@ __global__ void __launch_bounds__(256 * KG, HD == 64 && KG == 1 ? 3 : 2) attn_pr
           vr[m][u] = ((vr[m][u] & 0x7F80u) == 0x7F80u ? 0u : vr[m][u] & 0xFFFFu) | ((vr[m][u] & 0x7F800000u) == 0x7F800000u ? 0u : vr[m][u] & 0xFFFF0000u);
       }
   };
+  auto store_v_piece = [&](int buf, int u) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int d = dg * DV + 2 * u + h;
+      const unsigned int s = h ? 0x07060302u : 0x05040100u;
+      *(uint2*)(ring + (2 + buf) * TILE + d * AP_KT + ((vslot ^ ((d >> 1) & 7)) * 8 + vhalf)) =
+          make_uint2(__builtin_amdgcn_perm(vr[1][u], vr[0][u], s), __builtin_amdgcn_perm(vr[3][u], vr[2][u], s));
+    }
+  };
   auto store_v = [&](int buf) {
 #pragma unroll
-    for (int u = 0; u < DV / 2; ++u) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int d = dg * DV + 2 * u + h;
-        const unsigned int s = h ? 0x07060302u : 0x05040100u;
-        *(uint2*)(ring + (2 + buf) * TILE + d * AP_KT + ((vslot ^ ((d >> 1) & 7)) * 8 + vhalf)) =
-            make_uint2(__builtin_amdgcn_perm(vr[1][u], vr[0][u], s), __builtin_amdgcn_perm(vr[3][u], vr[2][u], s));
-      }
-    }
+    for (int u = 0; u < DV / 2; ++u) store_v_piece(buf, u);
   };
   const int n_tiles = (key_end + AP_KT - 1) / AP_KT;
   if (kg < n_tiles) { load_k(kg * AP_KT, 0); load_v(kg * AP_KT); }
@@ -192,25 +202,45 @@ __global__ void __launch_bounds__(256 * KG, HD == 64 && KG == 1 ? 3 : 2) attn_pr
   auto walk = [&](auto drop_c) {
   constexpr bool DROP = decltype(drop_c)::value;
   for (int it = 0; KG * it < n_tiles; ++it) {
-    const int buf = it & 1, base = (KG * it + kg) * AP_KT;
-    const bool more = KG * (it + 1) + kg < n_tiles;
-    if (more) { load_k(base + KG * AP_KT, buf ^ 1); load_v(base + KG * AP_KT); }
+    const int buf = it & 1, base = (KG * it + kg) * AP_KT, ahead = base + KG * AP_KT;
     if (KG * it + kg < n_tiles) {       // uniform over the wave; every wave meets the barrier below
+    // Fragment offsets: chunk 2 t + hi of a K row and slot 2 q + hi of a V^T row, permuted, differ from chunk and slot hi by an exclusive or
+    int ko = (lane & 31) * HD + ((hi ^ (lane & (CH - 1))) << 3), vo = (lane & 31) * AP_KT + ((hi ^ ((lane >> 1) & 7)) << 3);
+    int ln = lane;
+    asm volatile("" : "+v"(ko), "+v"(vo), "+v"(ln));
+    const bf16_t* kb = ring + buf * TILE;
+    const bf16_t* vb = ring + (2 + buf) * TILE;
+    auto read_k = [&](int k, int t) { return __builtin_bit_cast(bf16x8_t, *(const u32x4*)(kb + (ko ^ (t << 4)) + k * 32 * HD)); };
+    auto read_v = [&](int q, int t) { return __builtin_bit_cast(bf16x8_t, *(const u32x4*)(vb + (vo ^ (q << 4)) + t * 32 * AP_KT)); };
     // scores (in units of log2) of keys base + 32 k + 8 (e / 4) + 4 hi + e % 4 for the lane's query
     f32x16 s[2];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < 2; ++k)
 #pragma unroll
       for (int e = 0; e < 16; ++e) s[k][e] = 0.f;
-      const int key = 32 * k + (lane & 31);
-      const bf16_t* kp = ring + buf * TILE + key * HD;
+    bf16x8_t kf[2][2];
+    kf[0][0] = read_k(0, 0);
+    kf[0][1] = read_k(1, 0);
+    constexpr int LD = KI + 4;          // loads of the next tile (beyond the last: its last key again, never used), shared out over the steps
 #pragma unroll
-      for (int t = 0; t < T; ++t) {
-        const bf16x8_t kf = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(kp + (((2 * t + hi) ^ (key & (CH - 1))) << 3)));
-        s[k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, ql[t], s[k], 0, 0, 0);
-        s[k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qh[t], s[k], 0, 0, 0);
+    for (int t = 0; t < T; ++t) {
+      if (t + 1 < T) {
+        kf[(t + 1) & 1][0] = read_k(0, t + 1);
+        kf[(t + 1) & 1][1] = read_k(1, t + 1);
       }
+      s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t & 1][0], ql[t], s[0], 0, 0, 0);
+      s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t & 1][1], ql[t], s[1], 0, 0, 0);
+#pragma unroll
+      for (int z = t * LD / T; z < (t + 1) * LD / T; ++z) {
+        if (z < KI) load_k_piece(ln, ahead, buf ^ 1, z);
+        else load_v_piece(ln, ahead, z - KI);
+      }
+      s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t & 1][0], qh[t], s[0], 0, 0, 0);
+      s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t & 1][1], qh[t], s[1], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
+    bf16x8_t vf[2];
+    vf[0] = read_v(0, 0);
     if (base + AP_KT > pos0 + 1) {      // keys beyond some row's position in this tile
 #pragma unroll
       for (int k = 0; k < 2; ++k)
@@ -224,10 +254,13 @@ __global__ void __launch_bounds__(256 * KG, HD == 64 && KG == 1 ? 3 : 2) attn_pr
 #pragma unroll
     for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[1][e]);
     mx = pair_max<32>(mx);
-    const float m_new = fmaxf(m_run, mx);       // -inf: the odd tiles so far hold no key this row sees
-    const float m_use = m_new == -INFINITY ? 0.f : m_new;
-    if (__any(m_new > m_run)) {
-      const float f = __builtin_amdgcn_exp2f(m_run - m_use);
+    // The reference the exponentials are taken against follows the largest score only when that has grown by more than AP_SLACK: a
+    // probability may then be as large as 2^AP_SLACK, with the same relative error, and most tiles leave the accumulators alone.
+    // Each row decides by its own scores, so its bits do not depend on its neighbours.  -inf: the odd tiles so far hold no key this row sees
+    const bool grown = mx > m_run + AP_SLACK;
+    if (__any(grown)) {
+      const float m_new = grown ? mx : m_run;
+      const float f = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.f : m_new));
       l_run *= f;
 #pragma unroll
       for (int t = 0; t < DT; ++t)
@@ -235,46 +268,55 @@ __global__ void __launch_bounds__(256 * KG, HD == 64 && KG == 1 ? 3 : 2) attn_pr
         for (int e = 0; e < 16; ++e) acc[t][e] *= f;
       m_run = m_new;
     }
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        s[k][e] = __builtin_amdgcn_exp2f(s[k][e] - m_use);
-        l_run += s[k][e];
+    const float m_use = m_run == -INFINITY ? 0.f : m_run;
+    // The 8 probabilities of a contraction step q as three bf16 parts (truncated leading 8 bits, the next 8, the rest: exact), pair j of them
+    // in three pieces of about six vector instructions
+    uint32_t pp[2][3][4];
+    float r0[4], r1[4];
+    auto piece = [&](int q, int j, int z) {
+      const int e = 8 * (q & 1) + 2 * j;
+      const float a = s[q >> 1][e], d = s[q >> 1][e + 1];
+      if (z == 0) {
+        s[q >> 1][e] = __builtin_amdgcn_exp2f(a - m_use);
+        s[q >> 1][e + 1] = __builtin_amdgcn_exp2f(d - m_use);
+      } else if (z == 1) {
+        l_run += a;
+        l_run += d;
+        pp[q & 1][0][j] = __builtin_amdgcn_perm(__float_as_uint(d), __float_as_uint(a), 0x07060302u);
+        r0[j] = a - __uint_as_float(__float_as_uint(a) & 0xFFFF0000u);
+        r1[j] = d - __uint_as_float(__float_as_uint(d) & 0xFFFF0000u);
+      } else {
+        pp[q & 1][1][j] = __builtin_amdgcn_perm(__float_as_uint(r1[j]), __float_as_uint(r0[j]), 0x07060302u);
+        const float a2 = r0[j] - __uint_as_float(__float_as_uint(r0[j]) & 0xFFFF0000u), d2 = r1[j] - __uint_as_float(__float_as_uint(r1[j]) & 0xFFFF0000u);
+        pp[q & 1][2][j] = __builtin_amdgcn_perm(__float_as_uint(d2), __float_as_uint(a2), 0x07060302u);
       }
+    };
+    constexpr int PG = 4 / DT;          // pairs of the next step beside a V fragment's three products
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int z = 0; z < 3; ++z)
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        // the 8 probabilities of this contraction step as three bf16 parts (truncated leading 8 bits, the next 8, the rest: exact)
-        uint32_t p1[4], p2[4], p3[4];
+      for (int j = 0; j < 4; ++j) piece(0, j, z);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float a = s[k][8 * c + 2 * e], d = s[k][8 * c + 2 * e + 1];
-          const float a1 = a - __uint_as_float(__float_as_uint(a) & 0xFFFF0000u), d1 = d - __uint_as_float(__float_as_uint(d) & 0xFFFF0000u);
-          const float a2 = a1 - __uint_as_float(__float_as_uint(a1) & 0xFFFF0000u), d2 = d1 - __uint_as_float(__float_as_uint(d1) & 0xFFFF0000u);
-          p1[e] = __builtin_amdgcn_perm(__float_as_uint(d), __float_as_uint(a), 0x07060302u);
-          p2[e] = __builtin_amdgcn_perm(__float_as_uint(d1), __float_as_uint(a1), 0x07060302u);
-          p3[e] = __builtin_amdgcn_perm(__float_as_uint(d2), __float_as_uint(a2), 0x07060302u);
-        }
-        const bf16x8_t f1 = __builtin_bit_cast(bf16x8_t, u32x4{p1[0], p1[1], p1[2], p1[3]});
-        const bf16x8_t f2 = __builtin_bit_cast(bf16x8_t, u32x4{p2[0], p2[1], p2[2], p2[3]});
-        const bf16x8_t f3 = __builtin_bit_cast(bf16x8_t, u32x4{p3[0], p3[1], p3[2], p3[3]});
-        const int slot = 4 * k + 2 * c + hi;
+    for (int q = 0; q < 4; ++q) {
 #pragma unroll
-        for (int t = 0; t < DT; ++t) {
-          const int d = 32 * t + (lane & 31);
-          const bf16x8_t vf = __builtin_bit_cast(bf16x8_t, *(const u32x4*)(ring + (2 + buf) * TILE + d * AP_KT + ((slot ^ ((d >> 1) & 7)) << 3)));
-          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, f3, acc[t], 0, 0, 0);
-          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, f2, acc[t], 0, 0, 0);
-          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, f1, acc[t], 0, 0, 0);
+      for (int t = 0; t < DT; ++t) {
+        const int n = q * DT + t;
+        if (n + 1 < 4 * DT) vf[(n + 1) & 1] = read_v((n + 1) / DT, (n + 1) % DT);
+#pragma unroll
+        for (int z = 0; z < 3; ++z) {
+          const uint32_t* f = pp[q & 1][2 - z];
+          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[n & 1], __builtin_bit_cast(bf16x8_t, u32x4{f[0], f[1], f[2], f[3]}), acc[t], 0, 0, 0);
+          if (q < 3) {
+#pragma unroll
+            for (int j = 0; j < PG; ++j) piece(q + 1, t * PG + j, z);
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
     }
-    }
-    if (more) {
-      if (DROP) drop_bad(base + KG * AP_KT);
-      store_v(buf ^ 1);
+    if (DROP) drop_bad(ahead);
+    store_v(buf ^ 1);
     }
     __builtin_amdgcn_s_waitcnt(7 << 4);
     __builtin_amdgcn_s_barrier();

@@ -894,6 +894,12 @@ hipError_t launch_attention_prefill(dmtd_ctx* c, int l, const float* qkv, bf16_t
   const bf16_t* vc = (const bf16_t*)(c->ws + c->o.kv + (size_t)l * c->o.kv_layer_stride + c->o.kv_v_off);
   // KV heads fastest: with 8 of them a compute die's blocks share one head's keys and values in its L2
   const dim3 grid(cf.n_kv_heads, c->batch, (r + rpb - 1) / rpb);
+  // Blocks of later rows have more keys.  Two blocks share a CU, so up to 2 num_cus of them are all resident from the start and nothing
+  // evens out what a CU got: the first round of the CUs goes from the longest down, the second from the shortest up, and a CU's
+  // two come to about the same (2048 rows behind 0 / 6k keys, all from the longest down 108 / 510 us, so 97 / 500, long and short in
+  // turn 123 / 538).  More blocks than that start as others end, longest first.
+  const int per_z = (int)(grid.x * grid.y);
+  const int n_down = (long)per_z * grid.z <= 2L * c->num_cus ? std::min((int)grid.z, (c->num_cus + per_z - 1) / per_z) : (int)grid.z;
   auto launch = [&](auto kg_c) -> hipError_t {
     constexpr int KG = decltype(kg_c)::value;
     auto kern = attn_prefill_mfma_kernel<HD, KG>;
@@ -905,7 +911,7 @@ hipError_t launch_attention_prefill(dmtd_ctx* c, int l, const float* qkv, bf16_t
     }
     hipLaunchKernelGGL(kern, grid, dim3(256 * KG), attn_prefill_lds(HD, KG), c->stream, qkv, nqkv, kc, vc,
                        cf.n_q_heads, cf.n_kv_heads, cf.max_seq_len, r, (const DevState*)dev_state(c), sel, offset, (const bf16_t*)c->layers[l].q_norm,
-                       (const float2*)(c->ws + c->o.rope_tab), cf.rms_eps, attn, attn_lo, cf.n_q_heads * HD, blocked_rows(c, c->batch * r));
+                       (const float2*)(c->ws + c->o.rope_tab), cf.rms_eps, attn, attn_lo, cf.n_q_heads * HD, blocked_rows(c, c->batch * r), n_down);
     return hipGetLastError();
   };
   return (long)grid.x * grid.y * grid.z <= c->num_cus ? launch(std::integral_constant<int, 2>()) : launch(std::integral_constant<int, 1>());
