@@ -15,7 +15,10 @@
 // the clock falls to 1.9 GHz; one 2560 x 9728 launch in 240 blocks 160 / 154; tiles of 128 rows, 1003 rows of 2560 x 4096 41.3 / 40.2.  With the
 // same tile loaded by every block the launch takes 302, so memory is not it.  But at that clock a loop of nothing but MFMAs on random
 // operands does 1.7 PFLOP/s, and a launch 1.0 to 1.2 with its matrix cores idle for 29 to 39 % of a busy CU's time: a step's barrier and reads, a
-// block's start and end, and rounds that are not full (192 blocks of QKV at 2048 rows, a round of split tails behind a full one).  Also measured at the middle barrier, no faster: other orders of
+// block's start and end, and rounds that are not full (192 blocks of QKV at 2048 rows, a round of split tails behind a full one).  Of a launch's end the stores are the most: 50
+// MB of QKV sums or 63 MB of raw ones take 10 to 12 us with the matrix cores idle.  Reads two at a time behind their pairs of products, without a branch each (2048 rows of 2560, us
+// before / now): gate/up 301 / 294, down 158 / 154; QKV with its loop laid out likewise 121 / 116 (without any loads 100, the same tile for every
+// block 114, chains of both row tiles in turn 116).  Also measured at the middle barrier, no faster: other orders of
 // the products (each weight tile or each row tile held over 4 of them) 312 to 316, raised wave priority 320, 4 waves of 128 x 128 (a quarter
 // less LDS traffic) 5 % slower, tiles of 128 rows in 4 waves of 64 x 128 6 % slower.
 // Blocks go round-robin over the 8 compute dies; a die takes a contiguous run of tiles with the row tiles fastest, so a
@@ -187,46 +190,83 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
   };
   const auto wait_all = std::integral_constant<int, 0>();
   if constexpr (SHORT_SUMS && !KEEP) {
+    // A step's weight tiles one after the other, its activation fragments in registers all the while.  A tile's eight products are two chains, one per
+    // row tile, and a chain is added to the accumulators beside the next one's products, three products after its end.  The barrier
+    // stands in front of the last tile, whose weights are in registers: behind it each fragment's last product is followed by
+    // the read of the next step's, and this step's buffer is refilled.
     static_assert(RT == 2, "two row tiles");
-    int buf = 0, nxt = T::BUF - 1;
+    constexpr int NW = NJ % 2 ? 3 : 2;       // weight fragments' places: a tile's are free when the tile NW further is read
+    bf16x8_t xf[2][2][2], wf[NW][2];         // [low, high part][half of the step][row tile]; [place][half]
+    f32x16 sum[2];
+    clear(sum[0]); clear(sum[1]);
+    float total[2][NJ][16];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) total[0][j][e] = total[1][j][e] = 0.f;
+    auto read_x = [&](const bf16_t* base, int p, int c, int i) { xf[p][c][i] = chunk(base + (T::WP + (1 - p) * T::XT + (2 * wm + i) * 2) * 512 + c * 256); };
+    auto read_w = [&](const bf16_t* base, int j, int c) { wf[j % NW][c] = chunk(base + wtile(j) * 1024 + c * 256); };
+    if (s_hi - s_lo >= T::BUF - 1) wait_but(std::integral_constant<int, T::BUF - 2>());
+    else wait_but(wait_all);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");           // no LDS read of a slice moves above the barrier
+#pragma unroll
+    for (int u = 0; u < 8; ++u) read_x(ring + frag, (u >> 1) & 1, u & 1, u >> 2);
+    read_w(ring + frag, 0, 0);
+    read_w(ring + frag, 0, 1);
+    if (s_hi - s_lo > T::BUF - 1) issue(T::BUF - 1);
+    int buf = 0;
     for (int s = s_lo; s < s_hi; ++s) {
-      // this step's pieces have landed; behind the barrier every wave's have, and every wave is done with the buffer that is filled next
-      if (s + 1 < s_hi) wait_but(std::integral_constant<int, 1>());
-      else wait_but(wait_all);
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");         // no LDS read of the slice moves above the barrier
+      const int nxt = buf + 1 == T::BUF ? 0 : buf + 1;
       const bf16_t* base = ring + buf * T::STAGE + frag;
-      bf16x8_t xf[2][2][2];                // [low, high part][half of the step][row tile]
-#pragma unroll
-      for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-          for (int i = 0; i < 2; ++i) xf[p][c][i] = chunk(base + (T::WP + (1 - p) * T::XT + (2 * wm + i) * 2) * 512 + c * 256);
-      bf16x8_t w0 = chunk(base + wtile(0) * 1024), w1 = chunk(base + wtile(0) * 1024 + 256);
+      const bf16_t* next = ring + nxt * T::STAGE + frag;
+      const bool fill = s + T::BUF < s_hi;
       __builtin_amdgcn_sched_barrier(0);
-      if (s + T::BUF - 1 < s_hi) issue(nxt);
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) {       // the next tile's weights are read while this one's products run
-        const bf16_t* wn = base + wtile(j + 1 < NJ ? j + 1 : j) * 1024;
-        const bf16x8_t n0 = chunk(wn), n1 = chunk(wn + 256);
-        f32x16 sum[2];
-        clear(sum[0]); clear(sum[1]);
+      for (int j = 0; j < NJ; ++j) {
+        const bool last = j + 1 == NJ;
+        if (last) {
+          if (s + T::BUF - 1 < s_hi) wait_but(std::integral_constant<int, T::BUF - 2>());
+          else wait_but(wait_all);
+          __builtin_amdgcn_s_barrier();
+          asm volatile("" ::: "memory");
+        }
 #pragma unroll
-        for (int p = 0; p < 2; ++p)        // low parts first
+        for (int u = 0; u < 8; ++u) {
+          const int i = u >> 2, p = (u >> 1) & 1, c = u & 1;      // low parts first
+          f32x16 from = sum[i];
+          if ((u & 3) == 0) clear(from);
+          sum[i] = mma(wf[j % NW][c], xf[p][c][i], from);
+          __builtin_amdgcn_sched_barrier(0);
+          if (!last) {
+            if (u < 2) read_w(base, j + 1, u);
+          } else {
+            read_x(next, p, c, i);           // behind the last step nobody uses what is read
+            if (u >= 6) read_w(next, 0, u - 6);
+            if (fill && u < T::LPS) issue_one(buf, u);
+          }
+          const int pi = i ^ 1, pj = i ? j : (j + NJ - 1) % NJ;      // the chain before
+          if ((u & 3) > 1) {                 // (pinned: the compiler would gather the additions of a step behind a branch)
+            float* t = &total[pi][pj][((u & 3) - 2) * 8];
 #pragma unroll
-          for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int i = 0; i < 2; ++i) sum[i] = mma(c ? w1 : w0, xf[p][c][i], sum[i]);
-        acc[0][j] += sum[0]; acc[1][j] += sum[1];
-        w0 = n0; w1 = n1;
+            for (int e = 0; e < 8; ++e) t[e] += sum[pi][((u & 3) - 2) * 8 + e];
+            asm volatile("" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]), "+v"(t[4]), "+v"(t[5]), "+v"(t[6]), "+v"(t[7]));
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
-      __builtin_amdgcn_sched_barrier(0);
-      buf = buf + 1 == T::BUF ? 0 : buf + 1;
-      nxt = nxt + 1 == T::BUF ? 0 : nxt + 1;
+      buf = nxt;
     }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        acc[0][j][e] = total[0][j][e];
+        acc[1][j][e] = total[1][j][e] + (j == NJ - 1 ? sum[1][e] : 0.f);
+      }
   } else {
-    // A step's two halves: while the products of one run, the fragments of the next are read, one beside every NJ / 4 products.  The
+    // A step's two halves: while the products of one run, the fragments of the next are read.  Reads and loads stand behind a pair of products, not in
+    // front: the compiler waits for all reads at a product that needs one, also for those it has just issued.  The
     // barrier stands between the halves.  Behind it the second half's fragments are in registers, so the matrix cores go on at
     // once; every wave is done reading this step's buffer, so it is refilled (a load beside every pair of products: together they would
     // hold the wave up, the memory pipe takes a load per 16 cycles of a CU); and the next step has landed for every wave.
@@ -236,21 +276,25 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
 #pragma unroll
       for (int q = 0; q < 2 * NJ; ++q) {
         const int p = q / NJ, j = q % NJ;    // low parts first
-        beside(q);
 #pragma unroll
         for (int i = 0; i < RT; ++i) {
           f32x16& c = KEEP ? part[KEEP ? i : 0][KEEP ? j : 0] : acc[i][j];
           c = mma(f.f[RT + j], f.f[p ? RT + NJ + i : i], c);
         }
         __builtin_amdgcn_sched_barrier(0);
+        beside(q);
+        __builtin_amdgcn_sched_barrier(0);
       }
     };
-    // the reads (n = NF) or loads (n = LPS) beside products pair q of 2 NJ, the last pair taking what is left
-    auto share = [](int q, int n, auto f) {
-      if (q < n) f(q);
-      if (q == 2 * NJ - 1)
+    // the reads of the next fragments behind products pair q, two at a time, so that the last is back well before it is needed; the
+    // loads of a step, one behind each pair
+    auto reads = [&](Frag& f, const bf16_t* base, int c, int q) {
 #pragma unroll
-        for (int z = 2 * NJ; z < n; ++z) f(z);
+      for (int z = 2 * q; z < (q == 2 * NJ - 1 ? NF : min(2 * q + 2, NF)); ++z) read_one(f, base, c, z);
+    };
+    auto loads = [&](int buf, int q) {
+#pragma unroll
+      for (int z = q; z < (q == 2 * NJ - 1 ? T::LPS : min(q + 1, T::LPS)); ++z) issue_one(buf, z);
     };
     Frag f0, f1;
     if (s_hi - s_lo >= T::BUF - 1) wait_but(newer);
@@ -266,15 +310,15 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
       const bf16_t* base = ring + buf * T::STAGE + frag;
       const bf16_t* next = ring + nxt * T::STAGE + frag;
       __builtin_amdgcn_sched_barrier(0);
-      half(f0, [&](int q) { share(q, NF, [&](int z) { read_one(f1, base, 1, z); }); });
+      half(f0, [&](int q) { reads(f1, base, 1, q); });
       if (s + T::BUF - 1 < s_hi) wait_but(newer);
       else wait_but(wait_all);
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
-      const bool more = s + 1 < s_hi, fill = s + T::BUF < s_hi;
+      const bool fill = s + T::BUF < s_hi;
       half(f1, [&](int q) {
-        if (more) share(q, NF, [&](int z) { read_one(f0, next, 0, z); });
-        if (fill) share(q, T::LPS, [&](int z) { issue_one(buf, z); });
+        reads(f0, next, 0, q);               // behind the last step nobody uses what is read
+        if (fill) loads(buf, q);
       });
       if (KEEP && (((s - s_lo) & 3) == 3 || s + 1 == s_hi)) {
 #pragma unroll
