@@ -627,9 +627,10 @@ hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows, const MergeSrc& merge 
                                                : (EPI == EPI_SWIGLU && out_tiles >= 2 * c->num_cus && (size_t)rows * 4 * a.K >= (size_t)50 * 1024);
   const bool fits = a.ldxb == a.K && !prefers_tiled && mfma_rows_fit(c, rows, a.N, a.K, NORM ? a.n_parts : 0);
   // one launch of the tiled kernel; with 64 and more rows its ring of activation slices is dynamic LDS beyond the default limit
-#define DMTD_LAUNCH_GEMM(CG_, SPLIT_, GRID_)                                                                                   \
+#define DMTD_LAUNCH_GEMM(CG_, SPLIT_, GRID_) DMTD_LAUNCH_GEMM_W(CG_, SPLIT_, GRID_, gemm_waves(CG_, EPI))
+#define DMTD_LAUNCH_GEMM_W(CG_, SPLIT_, GRID_, WAVES_)                                                                         \
   do {                                                                                                                         \
-    auto kern = gemm_mfma_kernel<EPI, NORM, CG_, SPLIT_>;                                                                      \
+    auto kern = gemm_mfma_kernel<EPI, NORM, CG_, SPLIT_, WAVES_>;                                                              \
     constexpr size_t dyn = gemm_dyn_lds(CG_);                                                                                  \
     static bool big_lds = false;                                                                                               \
     if (dyn > 0 && !big_lds) {                                                                                                 \
@@ -637,11 +638,17 @@ hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows, const MergeSrc& merge 
       if (ae != hipSuccess) return ae;                                                                                         \
       big_lds = true;                                                                                                          \
     }                                                                                                                          \
-    hipLaunchKernelGGL(kern, GRID_, dim3(64 * gemm_waves(CG_, EPI)), dyn, c->stream, g.W, g.W2, g.xb, g.xb_lo, g.M, g.N, g.K, \
+    hipLaunchKernelGGL(kern, GRID_, dim3(64 * (WAVES_)), dyn, c->stream, g.W, g.W2, g.xb, g.xb_lo, g.M, g.N, g.K, \
                        g.ldxb, g.ksplit, g);                                                                                   \
   } while (0)
   if (!fits) {
     const int n_tiles = (a.N + 15) / 16;
+    // An LM head with 17 to 32 rows: two blocks share a CU, of 8 waves or of kLmWaves; those that take fewer rounds of the chip for their waves (us, 8 /
+    // 10 waves, 32 rows: 2560 wide, 140000 entries 142 / 132, 151936, 1.16 and 0.93 rounds, 148 / 140, 163840 155 / 148; 1024 wide 68 / 58, 70 / 62, 76 / 66;
+    // up to 131072 entries are one round either way, 163841 to 262144 two).
+    // The wider ones walk K in whole rounds of their pipeline.
+    const auto lm_cost = [&](int waves) { return (n_tiles + 4 * waves * c->num_cus - 1) / (4 * waves * c->num_cus) * waves; };
+    const bool lm_wide = KS % gemm_pf(2, EPI_LOGITS) == 0 && lm_cost(kLmWaves) < lm_cost(8);
     for (int m0 = 0; m0 < rows; m0 += kGemmRows) {
       MfmaArgs g = a;
       g.M = rows - m0 < kGemmRows ? rows - m0 : kGemmRows;
@@ -696,7 +703,9 @@ hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows, const MergeSrc& merge 
         }
       } else {
         if (cg == 1) DMTD_LAUNCH_GEMM(1, false, ggrid);
-        else if (cg == 2) DMTD_LAUNCH_GEMM(2, false, ggrid);
+        else if (EPI == EPI_LOGITS && cg == 2 && lm_wide) {
+          if constexpr (EPI == EPI_LOGITS) DMTD_LAUNCH_GEMM_W(2, false, dim3((n_tiles + 2 * kLmWaves - 1) / (2 * kLmWaves)), kLmWaves);
+        } else if (cg == 2) DMTD_LAUNCH_GEMM(2, false, ggrid);
         else if (cg == 4) DMTD_LAUNCH_GEMM(4, false, ggrid);
         else DMTD_LAUNCH_GEMM(8, false, ggrid);
       }

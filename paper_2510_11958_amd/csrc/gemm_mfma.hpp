@@ -74,13 +74,17 @@ constexpr int gemm_pf(int cg, int epi) { return epi == EPI_LOGITS && cg == 2 ? 2
 // dynamic LDS of a launch (bytes): the ring of activation slices
 constexpr size_t gemm_dyn_lds(int cg) { return gemm_uses_dma(cg) ? (size_t)(gemm_pf(cg) + 1) * 2 * cg * 16 * 64 * 2 : 0; }
 
-template <int EPI, bool NORM, int CG, bool SPLITK>
-__global__ void __launch_bounds__(64 * gemm_waves(CG, EPI)) gemm_mfma_kernel(
+// Waves of the wider blocks of an LM head with 17 to 32 rows.  It reads memory at its rate while all CUs have blocks; a second round of few blocks is what
+// it waits for: 594 blocks of 8 waves on 512 places at 151936 entries, 475 of 10, which two to a CU fit with 96 registers (148 -> 140 us).
+constexpr int kLmWaves = 10;
+
+template <int EPI, bool NORM, int CG, bool SPLITK, int WAVES = gemm_waves(CG, EPI)>
+__global__ void __launch_bounds__(64 * WAVES, WAVES == kLmWaves ? 2 * kLmWaves / 4 : 0) gemm_mfma_kernel(
     // what the prologue needs first, as leading scalars: they arrive in registers with the wave (kernel-argument preload), the
     // struct's fields only after a load from the argument buffer (~1 us before the first weight could be requested)
     const bf16_t* W_, const bf16_t* W2_, const bf16_t* xb_, const bf16_t* xb_lo_, int M_, int N_, int K_, int ldxb_, int ksplit_,
     MfmaArgs a) {
-  constexpr int GEMM_WAVES = gemm_waves(CG, EPI);
+  constexpr int GEMM_WAVES = WAVES;
   constexpr int BM = CG * 16;            // activation rows (MFMA columns) per pass
   // k-steps in flight: 3; 2 with 64 and more rows, where the accumulators leave fewer registers (measured at 4B shapes, 64 rows:
   // gate/up 37.4 against 38.8 us, QKV 19.9 against 21.9)
@@ -89,8 +93,9 @@ __global__ void __launch_bounds__(64 * gemm_waves(CG, EPI)) gemm_mfma_kernel(
   constexpr int LDB = 72;                // LDS row (register-staged slices): 64 values + 8 of padding
   constexpr int NT = 64 * GEMM_WAVES;
   constexpr int PIECES = 2 * BM * 8;     // 16-byte pieces of one k-step's activation slice (2 planes)
-  constexpr int PPT = PIECES / NT;       // per thread
-  static_assert(PIECES % NT == 0, "pieces per thread");
+  constexpr int PPT = (PIECES + NT - 1) / NT;       // per thread
+  constexpr bool ODD = PIECES % NT != 0; // the last threads have a piece less: they load one all the same (within the rows) and drop it
+  static_assert(!ODD || (!DMA && PPT == 1), "pieces per thread");
   constexpr int NBUF = PF + 1;           // DMA: slices in the ring
   constexpr int SLICE = 2 * BM * 64;     // DMA: bf16 elements of a slice (both planes, rows of 64)
   constexpr int LPS = PPT + 4;           // loads a thread issues per k-step (slice pieces, then 2 tiles x 2 halves of weights)
@@ -226,7 +231,8 @@ __global__ void __launch_bounds__(64 * gemm_waves(CG, EPI)) gemm_mfma_kernel(
     } else {
       buf = &bs[s & 1][0][0][0];
 #pragma unroll
-      for (int i = 0; i < PPT; ++i) *(u32x4*)(buf + bdst[i]) = Bq[slot][i];
+      for (int i = 0; i < PPT; ++i)
+        if (!ODD || tid < PIECES) *(u32x4*)(buf + bdst[i]) = Bq[slot][i];
       __syncthreads();
     }
 #pragma unroll
@@ -267,7 +273,9 @@ __global__ void __launch_bounds__(64 * gemm_waves(CG, EPI)) gemm_mfma_kernel(
     });
   };
   const int rem = s_hi - s0;
-  if (rem >= PF) {
+  if constexpr (WAVES == kLmWaves) {
+    tail(std::integral_constant<int, PF>());       // whole rounds only (the launcher): the copies of the others would not fit its registers
+  } else if (rem >= PF) {
     static_for<PF, 2 * PF>([&](auto r) {
       if (rem == decltype(r)::value) tail(r);
     });
