@@ -702,7 +702,13 @@ hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows, const MergeSrc& merge 
           }
         }
       } else {
-        if (cg == 1) DMTD_LAUNCH_GEMM(1, false, ggrid);
+        // Gate/up whose blocks of 4 waves are a quarter to a half of the CUs: blocks of 2 (us, 8 / 12 / 16 rows, 4 waves / 2: 2048 wide, 384 tiles, 96
+        // blocks 15.2 / 15.9 / 15.6, now 11.8 / 13.1 / 12.5; 1536 wide, 560 tiles, 140 blocks 14.0 / 13.8 / 14.2 against 14.0 / 15.9 / 16.8; 2560 wide, 608
+        // 19.6 / 20.4 / 21.0 against 22.4 / 23.8 / 25.0: each block draws the activations once more; 1024 wide, 16 rows, 48 blocks 6.0 / 6.2)
+        const bool gu_narrow = EPI == EPI_SWIGLU && cg == 1 && 4 * (int)ggrid.x > c->num_cus && 2 * (int)ggrid.x <= c->num_cus;
+        if (gu_narrow) {
+          if constexpr (EPI == EPI_SWIGLU) DMTD_LAUNCH_GEMM_W(1, false, dim3((n_tiles + 1) / 2), 2);
+        } else if (cg == 1) DMTD_LAUNCH_GEMM(1, false, ggrid);
         else if (EPI == EPI_LOGITS && cg == 2 && lm_wide) {
           if constexpr (EPI == EPI_LOGITS) DMTD_LAUNCH_GEMM_W(2, false, dim3((n_tiles + 2 * kLmWaves - 1) / (2 * kLmWaves)), kLmWaves);
         } else if (cg == 2) DMTD_LAUNCH_GEMM(2, false, ggrid);
