@@ -14,7 +14,7 @@
 // of a step with all its reads and loads behind it / barrier in the middle: on zeros 263 / 233, on normally distributed data 333 / 314, where
 // the clock falls to 1.9 GHz; one 2560 x 9728 launch in 240 blocks 160 / 154; tiles of 128 rows, 1003 rows of 2560 x 4096 41.3 / 40.2.  With the
 // same tile loaded by every block the launch takes 302, so memory is not it.  But at that clock a loop of nothing but MFMAs on random
-// operands does 1.7 PFLOP/s, and a launch 1.0 to 1.2 with its matrix cores idle for 29 to 39 % of a busy CU's time: a step's barrier and reads, a
+// operands does 1.7 PFLOP/s, and a launch 1.1 to 1.36 with its matrix cores idle for 17 % (gate/up, down) to 35 % (QKV) of a busy CU's time: a step's barrier and reads, a
 // block's start and end, and rounds that are not full (192 blocks of QKV at 2048 rows, a round of split tails behind a full one).  Of a launch's end the stores are the most: 50
 // MB of QKV sums or 63 MB of raw ones take 10 to 12 us with the matrix cores idle.  Reads two at a time behind their pairs of products, without a branch each (2048 rows of 2560, us
 // before / now): gate/up 301 / 294, down 158 / 154; QKV with its loop laid out likewise 121 / 116 (without any loads 100, the same tile for every
@@ -31,7 +31,7 @@
 // Sums: a tile that takes its whole K in one block sums it in one fp32 chain, a rounding per 8 products, 4.4e-7 of the result's norm at
 // K = 2560 in two planes; five parts summed apart (gemm_mfma.hpp with 128 rows) leave 2.0e-7.  In the QKV projection, whose K and V are
 // then rounded to bf16, that decides roundings; there a chain has 4 k-steps (tiles of 128 rows) or one (256 rows, 128 additions beside
-// 32 MFMAs: 1.45 us per step), about 1.3e-7 (low and high parts alternate by half steps: 2 % more than with a step's low parts first).  Logits of a prompt of 1003, 2560 wide, against 64 bits with the cache's rounding taken
+// 32 MFMAs), about 1.3e-7 (low and high parts alternate by half steps: 2 % more than with a step's low parts first).  Logits of a prompt of 1003, 2560 wide, against 64 bits with the cache's rounding taken
 // along, 1 / 2 layers: one chain 8.5e-5 / 1.14e-4, short chains 5.1e-5 / 7.2e-5, 128-row parts 5.2e-5 / 7.5e-5.  QKV, us, one chain /
 // short ones: 2048 rows of 2560 118 / 123, 1003 rows 61 / 65, 2048 rows of 1024 34.4 / 35.8 (chains of 8 steps are no nearer than parts at K = 1024).
 // Chains of a step in all projections cost 9 to 10 % of a pass at 2560 wide, for no smaller an error.
