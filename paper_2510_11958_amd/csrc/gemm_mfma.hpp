@@ -315,10 +315,7 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == kLmWaves ? 2 * kLmWaves /
       if (mact && tv[0]) {
         float u[4];
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          const float gt = acc[0][g][jj] * rs, up = acc[1][g][jj] * rs;
-          u[jj] = gt / (1.0f + __expf(-gt)) * up;
-        }
+        for (int jj = 0; jj < 4; ++jj) u[jj] = swiglu(acc[0][g][jj] * rs, acc[1][g][jj] * rs);
         bf16_t hi[4], lo[4];
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) split_bf16(u[jj], hi[jj], lo[jj]);
@@ -442,7 +439,7 @@ __global__ void __launch_bounds__(256) gemm_finish_kernel(const float* part_, co
     } else {
       if (EPI == EPI_SWIGLU) {
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) { const float gt = v[jj] * rs; o[jj] = gt / (1.0f + __expf(-gt)) * (v2[jj] * rs); }
+        for (int jj = 0; jj < 4; ++jj) o[jj] = swiglu(v[jj] * rs, v2[jj] * rs);
       } else {
         h4.x += v[0]; h4.y += v[1]; h4.z += v[2]; h4.w += v[3];
         *(float4*)(a.y + (size_t)m * a.ldy + n0) = h4;

@@ -23,8 +23,8 @@
 // less LDS traffic) 5 % slower, tiles of 128 rows in 4 waves of 64 x 128 6 % slower.
 // Blocks go round-robin over the 8 compute dies; a die takes a contiguous run of tiles with the row tiles fastest, so a
 // weight byte enters one die's L2 only and its row tiles share it there.
-// A block costs 10 to 13 us beside its steps; of the SwiGLU epilogue's 6, its divisions and 8-byte stores took 3 (1003 rows of 2560, 320 weight rows, us
-// with them / now 156 / 153).  Without loads, reads and barriers in the loop the products alone take 140 there, on zeros 113.
+// A block costs 10 to 13 us beside its steps; of the SwiGLU epilogue's 6, its divisions are 2 to 4 (us, v_rcp_f32 in their place / divisions: 1003
+// rows of 2560 149 / 152, 2048 rows 287 / 291).  Without loads, reads and barriers in the loop the products alone take 140 there, on zeros 113.
 // Tiles of 128 rows (waves of 64 x 64, a ring of four buffers, 0.8 instead of 1.3 us per step) where they pad a launch's rows less.
 // Against passes of 128 rows through gemm_mfma.hpp (4B shapes, 2048 rows, us with the finishing launch, before / now):
 // gate/up 660 / 336, QKV 390 / 128, down + O 763 / 282.
@@ -438,11 +438,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
           for (int h = 0; h < 2; ++h) {
             float v[2];
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-              // the reciprocal is good to one unit in the last place, 2^-7 of what the two bf16 parts keep
-              const float gt = acc[i][j][4 * q + 2 * h + e] * rs, up = acc[i][j][8 + 4 * q + 2 * h + e] * rs;
-              v[e] = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * up;
-            }
+            for (int e = 0; e < 2; ++e) v[e] = swiglu(acc[i][j][4 * q + 2 * h + e] * rs, acc[i][j][8 + 4 * q + 2 * h + e] * rs);
             hi[q][h] = pack_bf16x2(v[0], v[1]);
             lo[q][h] = pack_bf16x2(v[0] - __uint_as_float(hi[q][h] << 16), v[1] - __uint_as_float(hi[q][h] & 0xFFFF0000u));
           }
@@ -578,7 +574,7 @@ __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part
     if (EPI == EPI_SWIGLU) {
       const float up[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
 #pragma unroll
-      for (int e = 0; e < 8; ++e) { const float gt = v[e] * rs; v[e] = gt / (1.0f + __expf(-gt)) * (up[e] * rs); }
+      for (int e = 0; e < 8; ++e) v[e] = swiglu(v[e] * rs, up[e] * rs);
     } else {
       h0 += s0; h1 += s1;
       if (act) {

@@ -43,6 +43,9 @@ __device__ __forceinline__ void split_bf16(float v, bf16_t& hi, bf16_t& lo) {
   hi = to_bf16_hw(v);
   lo = to_bf16_hw(v - bf16_to_f32(hi));
 }
+// SwiGLU of a gate and an up value: the same bits on every route a row may take (v_rcp_f32, good to one unit in the last place, in some of them
+// would change the low part of one value in 110)
+__device__ __forceinline__ float swiglu(float gate, float up) { return gate / (1.0f + __expf(-gate)) * up; }
 
 constexpr int MFMA_MAX_WAVES = 16;   // waves that split K for one tile
 
@@ -388,7 +391,7 @@ __global__ void __launch_bounds__(64 * NWT) gemv_mfma_kernel(const bf16_t* W_, c
 #pragma unroll
         for (int ww = 0; ww < nw; ++ww) v1 += red[MATS - 1][ww][c][row];
         v1 *= rs;
-        split_bf16(v0 / (1.0f + __expf(-v0)) * v1, a.yb[(size_t)c * a.ldyb + n], a.yb_lo[(size_t)c * a.ldyb + n]);
+        split_bf16(swiglu(v0, v1), a.yb[(size_t)c * a.ldyb + n], a.yb_lo[(size_t)c * a.ldyb + n]);
       } else if (EPI == EPI_RESID) {
         const float hn = hpre[q] + v0;
         a.y[(size_t)c * a.ldy + n] = hn;
