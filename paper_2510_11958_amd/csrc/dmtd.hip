@@ -33,8 +33,8 @@ constexpr int kGemvRows = 4;         // activation rows per FMA weight-streaming
 constexpr int kMaxRows = 16;         // rows per sequence one pass through the layers may carry
 constexpr int kPassRows = 128;       // activation rows (all sequences together) a prefill or whole-sequence pass of an fp32 model carries
 // The same for a bf16 model.  Its wide GEMM (gemm_wide.hpp) is bound by the matrix cores, so a pass should fill the chip with
-// its tiles whatever the projection: 2048 rows give gate/up 608 tiles of 256 x 256 at 4B shapes, QKV 192 and O and down 80 (their K is
-// split over the 256 CUs).  The activation buffers of such a pass and 512 rows of logits make a 4B context of one sequence 137 MB
+// its tiles whatever the projection: 2048 rows give gate/up 608 tiles of 256 x 256 at 4B shapes (512 whole, 96 in two parts of K), QKV 384 of
+// 128 x 256 and O and down 80 (their K is split over the 256 CUs).  The activation buffers of such a pass and 512 rows of logits make a 4B context of one sequence 137 MB
 // larger than passes of 128 rows did; with less workspace the passes are shorter.
 constexpr int kWideRows = 2048;
 constexpr int kHeadRows = 512;       // rows of a whole-sequence pass whose logits are held at a time (0.3 GB at a 152k vocabulary)
@@ -490,10 +490,10 @@ WidePlan plan_wide(const dmtd_config& cf, int num_cus, int rows, int nt, int KS)
   // rows: with one figure of 1.25 a launch was 0.7 % slower than its better tile on average and up to 14 % (2560 wide, us, tiles of
   // 256 / 128: down with 896 rows 97 / 89, 1003 rows 98 / 95, O with 1400 rows 74 / 66; 1536 wide, down with 1003 rows 66 / 60), now 0.4 %;
   // a raw tile's bytes are written and read by blocks all over the chip at about 3.5 TB/s in all; the finishing launch itself 5 us.
-  // Against 256 weight rows a step of 320 takes 1.28 times as long, one of 192 0.93 times (1.86, 1.31 to 1.4; 0.75 with 128 rows).
+  // Against 256 weight rows a step of 192 takes 0.93 times as long (1.31 to 1.4; 0.75 with 128 rows).
   auto step_us = [&](int ks) {
     const double whole = BM == 128 ? 0.8 : (EPI == EPI_STORE || 2 * KS >= 40 * ks ? 1.45 : 1.3);
-    return BN == GW_BN ? whole : (BN == 320 ? 1.28 : 0.93) * whole;
+    return BN == GW_BN ? whole : 0.93 * whole;
   };
   const int part_tiles = (int)std::min<size_t>(gemm_part_floats(cf) / T::PART, 1 << 20);
   const int whole = EPI == EPI_RESID ? 0 : tiles / slots * slots, left = tiles - whole;
@@ -546,22 +546,19 @@ WideChoice choose_wide(const dmtd_config& cf, int num_cus, int rows, int N, int 
   const WidePlan p256 = plan_wide<EPI, 256, GW_BN>(cf, num_cus, w.pass, w.nt, K / 64), p128 = plan_wide<EPI, 128, GW_BN>(cf, num_cus, w.pass, w.nt, K / 64);
   w.bm = p128.us < p256.us ? 128 : 256;
   w.p = w.bm == 128 ? p128 : p256;
-  // Other widths, all tiles whole, where they fill more than 7/8 of their rounds of the chip (us, 256 / other: gate/up with 320, 1003 rows of 2560
-  // 172 / 152, 2048 rows 321 / 298, 1536 wide, 1003 rows 109 / 89, 896 wide, 2048 rows 78 / 61; with 192, 2048 wide, 1536 rows 138 / 115, 1024 wide,
-  // 2048 rows 49 / 44; QKV with 192 of 128 rows, 1003 rows of 2560 67 / 63, of 256 rows, 2048 rows 124 / 120; less full: gate/up with 320, 2048 wide,
-  // 2048 rows, 312 of 512 blocks 170 / 213, 1400 rows of 2560, 366 of 512 241 / 276).
+  // 192 weight rows where all tiles of 256 are whole, of the same height, and these fill more than 7/8 of their rounds of the chip: a sum is
+  // then the same chain over all of K either way.  (Where tiles of 256 are split, their sums in parts are nearer to 64 bits: see gemm_wide.hpp.)
   if constexpr (EPI == EPI_STORE || EPI == EPI_SWIGLU) {
-    auto other = [&](auto bm_c, auto bn_c) {
-      constexpr int BM = decltype(bm_c)::value, BN = decltype(bn_c)::value;
+    const WideChoice base = w;
+    auto narrow = [&](auto bm_c) {
+      constexpr int BM = decltype(bm_c)::value, BN = 192;
+      if (base.bm != BM || base.p.ksplit > 1) return;
       const int nt = wide_col_tiles<EPI>(N, BN), tiles = (rows + BM - 1) / BM * nt, rounds = (tiles + num_cus - 1) / num_cus;
       const WidePlan p = plan_wide<EPI, BM, BN>(cf, num_cus, rows, nt, K / 64);
       if (p.ksplit == 1 && tiles * 8L > rounds * (long)num_cus * 7 && p.us < w.p.us) w = WideChoice{nt, rows, BM, BN, p};
     };
-    typedef std::integral_constant<int, 128> i128; typedef std::integral_constant<int, 192> i192;
-    typedef std::integral_constant<int, 256> i256; typedef std::integral_constant<int, 320> i320;
-    other(i256(), i192());
-    if constexpr (EPI == EPI_STORE) other(i128(), i192());
-    else other(i256(), i320());
+    narrow(std::integral_constant<int, 256>());
+    if constexpr (EPI == EPI_STORE) narrow(std::integral_constant<int, 128>());
   }
   return w;
 }
@@ -588,8 +585,6 @@ hipError_t launch_wide(dmtd_ctx* c, const MfmaArgs& a, int rows) {
       if (w.bn == 192 && w.bm == 256) e = launch_wide_tiles<EPI, NORM, 256, 192>(c, g, w.nt, w.p);
     if constexpr (EPI == EPI_STORE)
       if (w.bn == 192 && w.bm == 128) e = launch_wide_tiles<EPI, NORM, 128, 192>(c, g, w.nt, w.p);
-    if constexpr (EPI == EPI_SWIGLU)
-      if (w.bn == 320) e = launch_wide_tiles<EPI, NORM, 256, 320>(c, g, w.nt, w.p);
     if (e != hipSuccess) return e;
   }
   if (EPI == EPI_RESID) c->resid_parts = w.nt;

@@ -3,8 +3,9 @@
 //
 // With hundreds of rows the projection is a matrix-core problem, not a weight stream.  A block computes a tile of 256
 // rows x 256 weight rows (SwiGLU: 128 gate and the same 128 up rows, 16 of each in turn) with 8 waves of 64 x 128 (2 x 4 tiles of
-// v_mfma_f32_32x32x16_bf16).  Gate/up also comes with 320 and 192 weight rows, QKV with 192, where these leave fewer CUs idle
-// (choose_wide); 320 is what the registers (240 of 256) and LDS (157 of 160 KiB) hold, and the fragments read per product are a tenth fewer.  K is walked in steps of 32: weights and both activation planes go from memory straight into
+// v_mfma_f32_32x32x16_bf16).  Gate/up and QKV also come with 192 weight rows, where these leave fewer CUs idle
+// (choose_wide).  Tiles of 320 weight rows, all that the registers (240 of 256) and LDS hold, would take gate/up of 1003 rows of 2560 in one round of whole
+// tiles (160 -> 149 us, 2048 rows 305 -> 287); they are not here, since they sum in one chain what 256 sum in five parts (below).  K is walked in steps of 32: weights and both activation planes go from memory straight into
 // LDS (global_load ... lds), 48 pieces of 1 KiB per step, each piece holding 16 rows in the order [16-byte chunk of k][row],
 // which is the order the weights and the blocked activations (packed_at) are stored in; a fragment read then takes 256
 // contiguous bytes per 16 lanes (no bank conflicts).  A ring of three LDS buffers (144 KiB, one block per CU); a step is waited for by the
@@ -24,7 +25,8 @@
 // Blocks go round-robin over the 8 compute dies; a die takes a contiguous run of tiles with the row tiles fastest, so a
 // weight byte enters one die's L2 only and its row tiles share it there.
 // A block costs 10 to 13 us beside its steps; of the SwiGLU epilogue's 6, its divisions are 2 to 4 (us, v_rcp_f32 in their place / divisions: 1003
-// rows of 2560 149 / 152, 2048 rows 287 / 291).  Without loads, reads and barriers in the loop the products alone take 140 there, on zeros 113.
+// rows of 2560 149 / 152, 2048 rows 287 / 291).  Without loads, reads and barriers in the loop the products alone take
+// 140 of these 152, on zeros 113.
 // Tiles of 128 rows (waves of 64 x 64, a ring of four buffers, 0.8 instead of 1.3 us per step) where they pad a launch's rows less.
 // Against passes of 128 rows through gemm_mfma.hpp (4B shapes, 2048 rows, us with the finishing launch, before / now):
 // gate/up 660 / 336, QKV 390 / 128, down + O 763 / 282.

@@ -104,12 +104,14 @@ def test_wide_pass_against_oracle(name):
 
 
 @pytest.mark.gpu
-def test_few_cached_values_round_the_other_way():
+@pytest.mark.parametrize("n,limit", [(1003, 2.6e-4), (2048, 1.8e-4)])
+def test_few_cached_values_round_the_other_way(n, limit):
     """How near the QKV projection's sums are to 64 bits decides how many keys and values round to the other bf16 neighbour: of 2.05 million
     values 2.3e-4 with K = 2560 summed in five parts (passes of 128 rows), 3.2e-4 to 3.6e-4 in one fp32 chain, 1.4e-4 in chains of
-    4 k-steps of 32.  2.6e-4 is three standard deviations of the count above the first."""
+    4 k-steps of 32.  2.6e-4 is three standard deviations of the count above the first.  Of 4.19 million values at 2048 rows 1.67e-4 and 1.51e-4
+    (keys, values) in chains of 4 k-steps; 1.8e-4 is two standard deviations above, and chains of one step in tiles of 192 weight rows leave 1.87e-4."""
     import torch
-    sh, n = S(1, 2560, 32, 8, 128, 128, 300), 1003
+    sh = S(1, 2560, 32, 8, 128, 128, 300)
     blob = di.make_weight_blob(sh, seed=31, std=0.02, gain_sigma=0.2)
     toks = di.make_prompts(sh.vocab, 1, n, seed=5)
     eng = pkg.Engine(engine_config(sh, n + 2), blob)
@@ -122,7 +124,7 @@ def test_few_cached_values_round_the_other_way():
         want = torch.from_numpy(np.ascontiguousarray(np.transpose(ref[:n], (1, 0, 2)))).to(torch.bfloat16).float().numpy()
         share = float((got[which] != want).mean())
         print(("keys", "values")[which], f"{share:.2e}")
-        assert share < 2.6e-4, (which, share)
+        assert share < limit, (which, share)
 
 
 @pytest.mark.gpu

@@ -1,5 +1,6 @@
-"""GPU parity of the wide GEMM's tiles of 192 and 320 weight rows (gate/up and QKV projections that fill the chip with them), where the last
-tile along the rows and the last one along the outputs are partly empty, against the CPU oracle.
+"""GPU parity of the wide GEMM's tiles of 192 weight rows (gate/up and QKV projections that fill the chip with them), where the last
+tile along the rows and the last one along the outputs are partly empty, against the CPU oracle; and of gate/up launches whose tiles of 256
+weight rows stay, the last of them summed in parts.
 
 Tolerance: that of the other bf16 parity tests (2e-2 of the largest logit); a wrong row, output or gate/up pair is an error of order one.
 """
@@ -16,8 +17,8 @@ from parity_util import engine_config, norm_err, oracle_config
 S = di.ModelShape
 # name: (shape, batch, positions), kind of projection, (rows per launch, rows of a tile, whole tiles, tiles of a second launch, parts of K)
 CASES = {
-    "gateup_320": (S(1, 1024, 4, 2, 64, 4800, 300), 4, 505, 2, (2020, 256, 240, 0, 1)),            # 30 x 160 outputs
-    "gateup_320_ragged": (S(1, 704, 4, 2, 64, 4544, 300), 4, 449, 2, (1796, 256, 232, 0, 1)),      # 28.4 tiles; 4 rows in the last row tile
+    "gateup_in_parts": (S(1, 1024, 4, 2, 64, 4800, 300), 4, 505, 2, (2020, 256, 256, 48, 3)),
+    "gateup_in_parts_ragged": (S(1, 704, 4, 2, 64, 4544, 300), 4, 449, 2, (1796, 256, 256, 32, 2)),      # 35.5 tiles; 4 rows in the last row tile
     "gateup_192": (S(1, 1088, 4, 2, 64, 2752, 300), 4, 505, 2, (2020, 256, 232, 0, 1)),            # 28.7 tiles of 96 outputs; K = 17 x 64
     "qkv_192_of_256": (S(1, 1024, 51, 17, 64, 64, 300), 4, 505, 0, (2020, 256, 232, 0, 1)),        # 28.3 tiles
     "qkv_192_of_128": (S(1, 1600, 51, 17, 64, 64, 300), 1, 1003, 0, (1003, 128, 232, 0, 1)),       # a short last row tile of 107
@@ -31,6 +32,27 @@ def test_cases_reach_the_tiles_they_are_there_for(name):
     plan = (C.c_int32 * 5)()
     assert pkg.load_library().dmtd_wide_plan(C.byref(engine_config(sh, n + 2, batch).to_c()), kind, batch * n, 256, plan) == pkg.DMTD_OK
     assert tuple(plan) == want
+
+
+# (shape, kind, rows): launches whose 256-wide tiles are partly summed in parts of K, and where 192 or 320 weight rows would give whole tiles
+IN_PARTS = {
+    (S(1, 2560, 32, 8, 128, 9728, 300), 2, 1003): (1003, 256, 256, 48, 5),
+    (S(1, 2560, 32, 8, 128, 9728, 300), 2, 2048): (2048, 256, 512, 96, 2),
+    (S(1, 2560, 32, 8, 128, 9728, 300), 0, 2048): (2048, 128, 256, 128, 2),
+    (S(1, 2048, 16, 8, 128, 6144, 300), 2, 1536): (1536, 256, 256, 32, 5),
+    (S(1, 1536, 12, 2, 128, 8960, 300), 2, 1003): (1003, 256, 256, 24, 5),
+    (S(1, 896, 14, 2, 64, 4864, 300), 2, 2048): (2048, 256, 256, 48, 3),
+}
+
+
+@pytest.mark.parametrize("case", list(IN_PARTS), ids=lambda c: f"{c[0].hidden}_kind{c[1]}_{c[2]}")
+def test_another_width_keeps_the_parts_of_a_sum(case):
+    """Runs without a GPU.  A sum in parts is nearer to 64 bits than one chain over all of K (2.0e-7 of its norm in five parts against 4.4e-7,
+    K = 2560): a width that would turn the one into the other is not taken."""
+    sh, kind, rows = case
+    plan = (C.c_int32 * 5)()
+    assert pkg.load_library().dmtd_wide_plan(C.byref(engine_config(sh, 2100).to_c()), kind, rows, 256, plan) == pkg.DMTD_OK
+    assert tuple(plan) == IN_PARTS[case]
 
 
 @pytest.mark.gpu
