@@ -514,6 +514,7 @@ template <int EPI, bool NORM, int BM, int BN>
 hipError_t launch_wide_tiles(dmtd_ctx* c, const MfmaArgs& g, int nt, const WidePlan& p) {
   typedef GwTile<BM, BN> T;
   const int mt = (g.M + BM - 1) / BM, n_tail = mt * nt - p.n_full;
+  if (BN != GW_BN && n_tail > 0) return hipErrorInvalidValue;      // tiles of another width are whole (choose_wide)
   auto kern = gemm_wide_mfma_kernel<EPI, NORM, BM, BN>;
   static bool big_lds = false;
   if (!big_lds) {
@@ -523,9 +524,9 @@ hipError_t launch_wide_tiles(dmtd_ctx* c, const MfmaArgs& g, int nt, const WideP
   }
   hipLaunchKernelGGL(kern, dim3(p.n_full + n_tail * p.ksplit), dim3(64 * GW_WAVES), T::LDS, c->stream, g.W, g.W2, g.xb, g.xb_lo,
                      g.M, g.N, g.K, p.n_full, n_tail, p.ksplit, mt, nt, g);
-  if constexpr (EPI != EPI_LOGITS && EPI != EPI_NLL) {
+  if constexpr (EPI != EPI_LOGITS && EPI != EPI_NLL && BN == GW_BN) {
     if (n_tail > 0)
-      hipLaunchKernelGGL((gemm_wide_finish_kernel<EPI, NORM, BM, BN>), dim3(n_tail, BM / 16), dim3(256), 0, c->stream, (const float*)g.part,
+      hipLaunchKernelGGL((gemm_wide_finish_kernel<EPI, NORM, BM>), dim3(n_tail, BM / 16), dim3(256), 0, c->stream, (const float*)g.part,
                          g.M, g.N, p.n_full, n_tail, p.ksplit, mt, nt, g);
   }
   return hipGetLastError();

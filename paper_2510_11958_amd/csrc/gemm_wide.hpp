@@ -334,8 +334,8 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
 
   // lane (column n = lane % 32 of a weight tile): element e of acc[i][j] is row 32 i + 8 (e / 4) + 4 (lane / 32) + e % 4 of the wave
   const int m_w = mb * BM + wm * 32 * RT, m_l = 4 * (lane >> 5), col = lane & 31;
-  if (EPI != EPI_LOGITS && EPI != EPI_NLL && pl.tail) {
-    // raw sums [BM rows][BN weight rows] of this part of K, for the finishing kernel
+  if (EPI != EPI_LOGITS && EPI != EPI_NLL && BN == GW_BN && pl.tail) {
+    // raw sums [BM rows][256 weight rows] of this part of K, for the finishing kernel
     float* part = a.part + ((size_t)pl.ks * n_tail_ + (pl.t - n_full_)) * T::PART + (size_t)(wm * 32 * RT) * BN;
 #pragma unroll
     for (int i = 0; i < RT; ++i)
@@ -485,7 +485,7 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
 // blocked stores are 16-byte pieces: 38 us for 2048 x 2560 from 3 parts.)  With 2048 rows memory bounds it (126 MB in 25 us); with a few
 // hundred the round trips do, so every load is issued ahead of the first sum (us, one round of 4 parts of a group at a time / now: residual,
 // 256 rows of 1024 10.2 / 8.6, 1003 rows of 2560 20.6 / 19.3, gate/up 2048 rows 15.8 / 12.0, QKV 13.3 / 10.1).
-template <int EPI, bool NORM, int BM, int BN>
+template <int EPI, bool NORM, int BM>
 __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part_, int M_, int N_, int n_full_, int n_tail_, int ksplit_, int mt_, int nt_,
                                                                MfmaArgs a) {
   __shared__ float ss_s[4][16];
@@ -494,11 +494,11 @@ __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part
   const int per_group = 8 * nt_, grp = t / per_group, in = t - grp * per_group, rows = min(8, mt_ - grp * 8);
   const int nb = in / rows, mb = grp * 8 + in - nb * rows;
   const int r = blockIdx.y * 16 + (lane & 15), m = mb * BM + r, c8 = (lane >> 4) * 8;
-  constexpr int PART = GwTile<BM, BN>::PART;
+  constexpr int PART = GwTile<BM, GW_BN>::PART;
   if (mb * BM + (int)blockIdx.y * 16 >= M) return;
   const bool act = m < M;
   const int mc = act ? m : M - 1;
-  constexpr int OUT = EPI == EPI_SWIGLU ? BN / 2 : BN, ALL = OUT / 32, GROUPS = (ALL + 3) / 4;      // outputs of a tile; groups of 32 of them, per wave
+  constexpr int OUT = EPI == EPI_SWIGLU ? GW_BN / 2 : GW_BN, GROUPS = OUT / 128;      // outputs of a tile; groups of 32 of them per wave
   constexpr int PRE = EPI == EPI_RESID ? 6 : 4;          // parts of every group fetched at once
   const size_t step = (size_t)n_tail_ * PART;
   float ssv[4];                                          // the row's partial sums of squares, 16 of them up front
@@ -508,39 +508,39 @@ __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part
   float hsq = 0.f;
   // all loads of all groups first: the residual rows, the gains, and up to PRE parts (a group beyond N repeats the first)
   const int c0 = nb * OUT;
-  f32x4 sum[GROUPS][2], sum2[EPI == EPI_SWIGLU ? GROUPS : 1][2], res[GROUPS][2];
+  f32x4 sum[GROUPS][2], sum2[2], res[GROUPS][2];
   u32x4 gain[GROUPS];
   const float* src[GROUPS];
 #pragma unroll
   for (int gi = 0; gi < GROUPS; ++gi) {
-    const int lg = (w * GROUPS + gi) * 32, lc = (w * GROUPS + gi < ALL && c0 + lg < N ? lg : 0) + c8;
+    const int lg = (w * GROUPS + gi) * 32, lc = (c0 + lg < N ? lg : 0) + c8;
     // SwiGLU: 16 gate sums, then the up sums of the same outputs
-    src[gi] = part_ + (size_t)blockIdx.x * PART + (size_t)r * BN + (EPI == EPI_SWIGLU ? (lc & ~15) * 2 + (lc & 15) : lc);
+    src[gi] = part_ + (size_t)blockIdx.x * PART + (size_t)r * GW_BN + (EPI == EPI_SWIGLU ? (lc & ~15) * 2 + (lc & 15) : lc);
     sum[gi][0] = sum[gi][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (EPI == EPI_SWIGLU) sum2[gi][0] = sum2[gi][1] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (EPI == EPI_RESID) {
       res[gi][0] = *(const f32x4*)(a.y + (size_t)mc * a.ldy + c0 + lc);
       res[gi][1] = *(const f32x4*)(a.y + (size_t)mc * a.ldy + c0 + lc + 4);
       gain[gi] = *(const u32x4*)(a.g_next + c0 + lc);
     }
   }
+  sum2[0] = sum2[1] = f32x4{0.f, 0.f, 0.f, 0.f};
   auto add_parts = [&](int k0, auto n_c) {
     constexpr int n = decltype(n_c)::value;
-    f32x4 x[GROUPS][n][2], z[EPI == EPI_SWIGLU ? GROUPS : 1][EPI == EPI_SWIGLU ? n : 1][2];
+    f32x4 x[GROUPS][n][2], z[EPI == EPI_SWIGLU ? n : 1][2];
 #pragma unroll
     for (int gi = 0; gi < GROUPS; ++gi)
 #pragma unroll
       for (int k = 0; k < n; ++k) {
         const float* q = src[gi] + (size_t)(k0 + k) * step;
         x[gi][k][0] = *(const f32x4*)q; x[gi][k][1] = *(const f32x4*)(q + 4);
-        if (EPI == EPI_SWIGLU) { z[gi][k][0] = *(const f32x4*)(q + 16); z[gi][k][1] = *(const f32x4*)(q + 20); }
+        if (EPI == EPI_SWIGLU) { z[k][0] = *(const f32x4*)(q + 16); z[k][1] = *(const f32x4*)(q + 20); }
       }
 #pragma unroll
     for (int gi = 0; gi < GROUPS; ++gi)
 #pragma unroll
       for (int k = 0; k < n; ++k) {
         sum[gi][0] += x[gi][k][0]; sum[gi][1] += x[gi][k][1];
-        if (EPI == EPI_SWIGLU) { sum2[gi][0] += z[gi][k][0]; sum2[gi][1] += z[gi][k][1]; }
+        if (EPI == EPI_SWIGLU) { sum2[0] += z[k][0]; sum2[1] += z[k][1]; }
       }
   };
   int k0 = 0;
@@ -560,9 +560,8 @@ __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part
 #pragma unroll
   for (int gi = 0; gi < GROUPS; ++gi) {
     const int n = c0 + (w * GROUPS + gi) * 32 + c8;
-    if (w * GROUPS + gi >= ALL || n - c8 >= N) continue;                     // N is a multiple of 64 here: whole groups
-    const int g2 = EPI == EPI_SWIGLU ? gi : 0;
-    const f32x4 s0 = sum[gi][0], s1 = sum[gi][1], u0 = sum2[g2][0], u1 = sum2[g2][1];
+    if (n - c8 >= N) continue;                                               // N is a multiple of 64 here: whole groups
+    const f32x4 s0 = sum[gi][0], s1 = sum[gi][1], u0 = sum2[0], u1 = sum2[1];
     f32x4 h0 = res[gi][0], h1 = res[gi][1];
     const u32x4 graw = gain[gi];
     float v[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
@@ -602,7 +601,7 @@ __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part
     }
   }
   if (EPI == EPI_RESID) {
-    // one sum of squares per row and tile
+    // one sum of squares per row and tile of 256 outputs
     hsq = column_sum(hsq);
     if (lane < 16) ss_s[w][lane] = hsq;
     __syncthreads();
