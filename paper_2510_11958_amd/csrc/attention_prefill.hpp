@@ -24,8 +24,8 @@
 // loads are issued one beside each step of the scores, and the exponentials and parts of a contraction step stand six vector
 // instructions beside each product of the step before.  2048 rows behind 0 / 2k / 4k / 6k keys (the passes of a prompt of 8192), us per
 // launch: read and waited for in place 115 / 252 / 392 / 523; in this order 108 / 245 / 378 / 510; the blocks paired long with short
-// (launcher) 97 / 231 / 367 / 500; loads' addresses from two registers a tile 93 / 220 / 347 / 475; rescaling only beyond AP_SLACK
-// 90 / 213 / 339 / 466.  Wave priorities (by block, or raised around the softmax) changed nothing.
+// (launcher) 97 / 231 / 367 / 500; loads' addresses from two registers a tile 93 / 220 / 347 / 475.
+// Wave priorities (by block, or raised around the softmax) changed nothing.
 // Against the decode kernel (attention_mfma.hpp, one pass over K and V per 16 query vectors, the same products) on the same passes,
 // 32/8 heads of 128, us per launch: one prompt of 1003 111 -> 52; 2048 rows against 2k to 8k keys 1044 -> 322 (the prompt of
 // 8192, 2 layers: 14.5 -> 8.8 ms); 32 prompts of 2048 in passes of 64 rows 386 -> 90; one prompt of 400 33 -> 28.
@@ -41,7 +41,6 @@ namespace dmtd {
 // dynamic LDS: per group two buffers of K and V tiles
 constexpr size_t attn_prefill_lds(int hd, int kg) { return (size_t)kg * 4 * 64 * hd * 2; }
 constexpr int AP_QV = 128, AP_KT = 64;       // query vectors of a block, keys of a tile
-constexpr float AP_SLACK = 8.f;              // growth of a row's largest score, in powers of two, that its sums are not rescaled for
 
 template <int HD, int KG>
 __global__ void __launch_bounds__(256 * KG, HD == 64 && KG == 1 ? 3 : 2) attn_prefill_mfma_kernel(
@@ -254,13 +253,12 @@ __global__ void __launch_bounds__(256 * KG, HD == 64 && KG == 1 ? 3 : 2) attn_pr
 #pragma unroll
     for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[1][e]);
     mx = pair_max<32>(mx);
-    // The reference the exponentials are taken against follows the largest score only when that has grown by more than AP_SLACK: a
-    // probability may then be as large as 2^AP_SLACK, with the same relative error, and most tiles leave the accumulators alone.
-    // Each row decides by its own scores, so its bits do not depend on its neighbours.  -inf: the odd tiles so far hold no key this row sees
-    const bool grown = mx > m_run + AP_SLACK;
-    if (__any(grown)) {
-      const float m_new = grown ? mx : m_run;
-      const float f = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.f : m_new));
+    // (A reference that follows only growth beyond 2^8 leaves most tiles' sums alone, 2 % of a launch, but then values beyond 2^120 overflow
+    // them: a probability may be 2^8.)
+    const float m_new = fmaxf(m_run, mx);       // -inf: the odd tiles so far hold no key this row sees
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;
+    if (__any(m_new > m_run)) {
+      const float f = __builtin_amdgcn_exp2f(m_run - m_use);
       l_run *= f;
 #pragma unroll
       for (int t = 0; t < DT; ++t)
@@ -268,7 +266,6 @@ __global__ void __launch_bounds__(256 * KG, HD == 64 && KG == 1 ? 3 : 2) attn_pr
         for (int e = 0; e < 16; ++e) acc[t][e] *= f;
       m_run = m_new;
     }
-    const float m_use = m_run == -INFINITY ? 0.f : m_run;
     // The 8 probabilities of a contraction step q as three bf16 parts (truncated leading 8 bits, the next 8, the rest: exact), pair j of them
     // in three pieces of about six vector instructions
     uint32_t pp[2][3][4];
