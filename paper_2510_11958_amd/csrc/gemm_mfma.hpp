@@ -313,12 +313,9 @@ __global__ void __launch_bounds__(64 * WAVES, WAVES == kLmWaves ? 2 * kLmWaves /
     if (EPI == EPI_SWIGLU) {
       const int n0 = tile[0] * 16 + kg * 4;
       if (mact && tv[0]) {
-        float u[4];
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) u[jj] = swiglu(acc[0][g][jj] * rs, acc[1][g][jj] * rs);
         bf16_t hi[4], lo[4];
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) split_bf16(u[jj], hi[jj], lo[jj]);
+        for (int jj = 0; jj < 4; ++jj) swiglu_split(acc[0][g][jj] * rs, acc[1][g][jj] * rs, hi[jj], lo[jj]);
         *(uint2*)(a.yb + (size_t)m * a.ldyb + n0) = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
         *(uint2*)(a.yb_lo + (size_t)m * a.ldyb + n0) = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
       }
@@ -433,13 +430,13 @@ __global__ void __launch_bounds__(256) gemm_finish_kernel(const float* part_, co
   }
   float hsq = 0.f;
   if (act) {
-    float o[4];
     if (EPI == EPI_STORE) {
       *(float4*)(a.y + (size_t)m * a.ldy + n0) = make_float4(v[0] * rs, v[1] * rs, v[2] * rs, v[3] * rs);
     } else {
+      bf16_t hi[4], lo[4];
       if (EPI == EPI_SWIGLU) {
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) o[jj] = swiglu(v[jj] * rs, v2[jj] * rs);
+        for (int jj = 0; jj < 4; ++jj) swiglu_split(v[jj] * rs, v2[jj] * rs, hi[jj], lo[jj]);
       } else {
         h4.x += v[0]; h4.y += v[1]; h4.z += v[2]; h4.w += v[3];
         *(float4*)(a.y + (size_t)m * a.ldy + n0) = h4;
@@ -447,11 +444,8 @@ __global__ void __launch_bounds__(256) gemm_finish_kernel(const float* part_, co
         const float gn[4] = {__uint_as_float(graw.x << 16), __uint_as_float(graw.x & 0xFFFF0000u),
                              __uint_as_float(graw.y << 16), __uint_as_float(graw.y & 0xFFFF0000u)};
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) { hsq += hn[jj] * hn[jj]; o[jj] = hn[jj] * gn[jj]; }
+        for (int jj = 0; jj < 4; ++jj) { hsq += hn[jj] * hn[jj]; split_bf16(hn[jj] * gn[jj], hi[jj], lo[jj]); }
       }
-      bf16_t hi[4], lo[4];
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) split_bf16(o[jj], hi[jj], lo[jj]);
       const size_t at = (size_t)m * a.ldyb + n0;
       *(uint2*)(a.yb + at) = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
       *(uint2*)(a.yb_lo + at) = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));

@@ -437,13 +437,9 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
 #pragma unroll
         for (int q = 0; q < 2; ++q)
 #pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            float v[2];
-#pragma unroll
-            for (int e = 0; e < 2; ++e) v[e] = swiglu(acc[i][j][4 * q + 2 * h + e] * rs, acc[i][j][8 + 4 * q + 2 * h + e] * rs);
-            hi[q][h] = pack_bf16x2(v[0], v[1]);
-            lo[q][h] = pack_bf16x2(v[0] - __uint_as_float(hi[q][h] << 16), v[1] - __uint_as_float(hi[q][h] & 0xFFFF0000u));
-          }
+          for (int h = 0; h < 2; ++h)
+            swiglu_split2(acc[i][j][4 * q + 2 * h] * rs, acc[i][j][8 + 4 * q + 2 * h] * rs, acc[i][j][4 * q + 2 * h + 1] * rs,
+                          acc[i][j][8 + 4 * q + 2 * h + 1] * rs, hi[q][h], lo[q][h]);
         const LanePair<uint32_t> h0 = halves<32>(hi[0][0], hi[1][0]), h1 = halves<32>(hi[0][1], hi[1][1]);
         const LanePair<uint32_t> l0 = halves<32>(lo[0][0], lo[1][0]), l1 = halves<32>(lo[0][1], lo[1][1]);
         if (m < M && n < N) {
@@ -572,10 +568,11 @@ __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part
       }
       continue;
     }
+    uint32_t hi[4], lo[4];
     if (EPI == EPI_SWIGLU) {
       const float up[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = swiglu(v[e] * rs, up[e] * rs);
+      for (int e = 0; e < 4; ++e) swiglu_split2(v[2 * e] * rs, up[2 * e] * rs, v[2 * e + 1] * rs, up[2 * e + 1] * rs, hi[e], lo[e]);
     } else {
       h0 += s0; h1 += s1;
       if (act) {
@@ -587,12 +584,11 @@ __global__ void __launch_bounds__(256) gemm_wide_finish_kernel(const float* part
       Elem<bf16_t>::unpack(graw, gn);
 #pragma unroll
       for (int e = 0; e < 8; ++e) { hsq += hn[e] * hn[e]; v[e] = hn[e] * gn[e]; }
-    }
-    uint32_t hi[4], lo[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      hi[e] = pack_bf16x2(v[2 * e], v[2 * e + 1]);
-      lo[e] = pack_bf16x2(v[2 * e] - __uint_as_float(hi[e] << 16), v[2 * e + 1] - __uint_as_float(hi[e] & 0xFFFF0000u));
+      for (int e = 0; e < 4; ++e) {
+        hi[e] = pack_bf16x2(v[2 * e], v[2 * e + 1]);
+        lo[e] = pack_bf16x2(v[2 * e] - __uint_as_float(hi[e] << 16), v[2 * e + 1] - __uint_as_float(hi[e] & 0xFFFF0000u));
+      }
     }
     if (act) {
       const size_t at = packed_at(1, m, n, a.ldyb);

@@ -43,9 +43,19 @@ __device__ __forceinline__ void split_bf16(float v, bf16_t& hi, bf16_t& lo) {
   hi = to_bf16_hw(v);
   lo = to_bf16_hw(v - bf16_to_f32(hi));
 }
-// SwiGLU of a gate and an up value: the same bits on every route a row may take (v_rcp_f32, good to one unit in the last place, in some of them
-// would change the low part of one value in 110)
-__device__ __forceinline__ float swiglu(float gate, float up) { return gate / (1.0f + __expf(-gate)) * up; }
+// SwiGLU of a gate and an up value in two bf16 parts: the same bits on every route a row may take.  So the division is one (v_rcp_f32 in its
+// place, good to one unit in the last place, changes the low part of one value in 110), and the low part is what the unrounded product leaves, by a
+// fused multiply-add that is written out: left to the compiler, tiles of 128 rows got it for half of their outputs.
+__device__ __forceinline__ void swiglu_split(float gate, float up, bf16_t& hi, bf16_t& lo) {
+  const float s = gate / (1.0f + __expf(-gate));
+  hi = to_bf16_hw(s * up);
+  lo = to_bf16_hw(__builtin_fmaf(s, up, -bf16_to_f32(hi)));
+}
+__device__ __forceinline__ void swiglu_split2(float gate0, float up0, float gate1, float up1, uint32_t& hi, uint32_t& lo) {
+  const float s0 = gate0 / (1.0f + __expf(-gate0)), s1 = gate1 / (1.0f + __expf(-gate1));
+  hi = pack_bf16x2(s0 * up0, s1 * up1);
+  lo = pack_bf16x2(__builtin_fmaf(s0, up0, -__uint_as_float(hi << 16)), __builtin_fmaf(s1, up1, -__uint_as_float(hi & 0xFFFF0000u)));
+}
 
 constexpr int MFMA_MAX_WAVES = 16;   // waves that split K for one tile
 
@@ -391,7 +401,7 @@ __global__ void __launch_bounds__(64 * NWT) gemv_mfma_kernel(const bf16_t* W_, c
 #pragma unroll
         for (int ww = 0; ww < nw; ++ww) v1 += red[MATS - 1][ww][c][row];
         v1 *= rs;
-        split_bf16(swiglu(v0, v1), a.yb[(size_t)c * a.ldyb + n], a.yb_lo[(size_t)c * a.ldyb + n]);
+        swiglu_split(v0, v1, a.yb[(size_t)c * a.ldyb + n], a.yb_lo[(size_t)c * a.ldyb + n]);
       } else if (EPI == EPI_RESID) {
         const float hn = hpre[q] + v0;
         a.y[(size_t)c * a.ldy + n] = hn;

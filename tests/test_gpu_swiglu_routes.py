@@ -4,7 +4,8 @@
 The models make every sum exact, so that only the activation itself is left to differ.  Embeddings are small whole numbers and one
 entry of 2^20, which alone decides every norm's scale; gate and up weights are small whole numbers times 2^8; attention adds nothing (its
 weights are 0); the down projection and the LM head each pick one element.  A logit is then one SwiGLU output (its two bf16 parts) times
-a power of two.  v_rcp_f32 in place of the division on one route changes 1 in 110 of them."""
+a power of two.  v_rcp_f32 in place of the division on one route changes 1 in 110 of them; a low part taken from the rounded product in half of a
+tile's outputs, as a compiler may choose between routes, 1 in 140."""
 import ctypes as C
 
 import numpy as np
