@@ -198,11 +198,12 @@ __global__ void __launch_bounds__(256 * KG, HD == 64 && KG == 1 ? 3 : 2) attn_pr
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 
-  auto walk = [&](auto drop_c) {
-  constexpr bool DROP = decltype(drop_c)::value;
-  for (int it = 0; KG * it < n_tiles; ++it) {
+  // One tile's work; MORE: with the next one's loads beside it (beyond the last: its last key again, never used).  Waves whose group has one tile in
+  // all do without (us per launch, with / without: 32/8 heads of 128, 40 prompts of 30 22.6 / 20.2, 48 of 50 31.4 / 30.5, 3 of 90 17.7 / 17.0; 14/2 heads
+  // of 64, 48 of 50 11.2 / 10.8).
+  auto tile = [&](int it, auto drop_c, auto more_c) {
+    constexpr bool DROP = decltype(drop_c)::value, MORE = decltype(more_c)::value;
     const int buf = it & 1, base = (KG * it + kg) * AP_KT, ahead = base + KG * AP_KT;
-    if (KG * it + kg < n_tiles) {       // uniform over the wave; every wave meets the barrier below
     // Fragment offsets: chunk 2 t + hi of a K row and slot 2 q + hi of a V^T row, permuted, differ from chunk and slot hi by an exclusive or
     int ko = (lane & 31) * HD + ((hi ^ (lane & (CH - 1))) << 3), vo = (lane & 31) * AP_KT + ((hi ^ ((lane >> 1) & 7)) << 3);
     int ln = lane;
@@ -220,7 +221,7 @@ __global__ void __launch_bounds__(256 * KG, HD == 64 && KG == 1 ? 3 : 2) attn_pr
     bf16x8_t kf[2][2];
     kf[0][0] = read_k(0, 0);
     kf[0][1] = read_k(1, 0);
-    constexpr int LD = KI + 4;          // loads of the next tile (beyond the last: its last key again, never used), shared out over the steps
+    constexpr int LD = MORE ? KI + 4 : 0;          // loads of the next tile, shared out over the steps
 #pragma unroll
     for (int t = 0; t < T; ++t) {
       if (t + 1 < T) {
@@ -312,15 +313,23 @@ __global__ void __launch_bounds__(256 * KG, HD == 64 && KG == 1 ? 3 : 2) attn_pr
         }
       }
     }
-    if (DROP) drop_bad(ahead);
-    store_v(buf ^ 1);
+    if (MORE) {
+      if (DROP) drop_bad(ahead);
+      store_v(buf ^ 1);
     }
-    __builtin_amdgcn_s_waitcnt(7 << 4);
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-  }
   };
-  if (__builtin_amdgcn_readfirstlane(poison_s) == 0x7FFFFFFF) {
+  auto walk = [&](auto drop_c) {
+    for (int it = 0; KG * it < n_tiles; ++it) {
+      if (KG * it + kg < n_tiles) tile(it, drop_c, std::integral_constant<bool, true>());      // uniform over the wave; every wave meets the barrier
+      __builtin_amdgcn_s_waitcnt(7 << 4);
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    }
+  };
+  if (n_tiles <= KG && __builtin_amdgcn_readfirstlane(poison_s) == 0x7FFFFFFF) {
+    if (kg < n_tiles) tile(0, std::integral_constant<bool, false>(), std::integral_constant<bool, false>());
+    if (KG == 2) __syncthreads();
+  } else if (__builtin_amdgcn_readfirstlane(poison_s) == 0x7FFFFFFF) {
     walk(std::integral_constant<bool, false>());
   } else {                            // seldom; the first tile's values once more
     if (kg < n_tiles) { load_v(kg * AP_KT); drop_bad(kg * AP_KT); store_v(0); }

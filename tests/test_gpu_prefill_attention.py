@@ -21,6 +21,10 @@ CASES = {
     "blocks_510_hd64_gq1": (S(1, 128, 17, 17, 64, 64, 300), 6, 600, 0.2),        # 5 slices of 102, three down and two up
     "growing_hd128_gq4": (S(1, 128, 32, 8, 128, 64, 300), 1, 1100, 1.0),
     "growing_hd64_gq2": (S(1, 128, 8, 4, 64, 64, 300), 2, 900, 1.0),             # 120 blocks: even and odd tiles apart
+    # blocks whose groups of waves have one tile of 64 keys, next to blocks with one key more
+    "one_tile_hd128": (S(1, 128, 32, 8, 128, 64, 300), 40, 30, 0.2),             # 320 blocks, one group
+    "one_and_two_tiles_hd64": (S(1, 128, 16, 2, 64, 64, 300), 31, 65, 0.2),      # 310 blocks, one group; the last row sees 65 keys
+    "one_to_three_tiles_hd128": (S(1, 128, 32, 8, 128, 64, 300), 3, 129, 0.2),   # 120 blocks, two groups; the last row sees 129 keys
 }
 
 
