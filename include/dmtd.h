@@ -243,11 +243,15 @@ int dmtd_read_kv(dmtd_ctx* ctx, int32_t layer, int32_t b, int32_t n_pos, float* 
 int dmtd_time_kernel(dmtd_ctx* ctx, int32_t kind, int32_t rows, int32_t reps, float* avg_us);
 
 /* How a projection (one of the five kinds DMTD_K_QKV .. DMTD_K_LMHEAD) of a pass with `rows` activation rows, more than 192, is
- * laid out on a chip of num_cus compute units: plan[0] rows per launch, plan[1] rows of a tile (128 or 256; a tile has 256
- * outputs, gate/up 128), plan[2] tiles a block computes whole, plan[3] tiles that pass through a second launch, plan[4] parts K
+ * laid out on a chip of num_cus compute units: plan[0] rows per launch, plan[1] rows of a tile (128 or 256; its weight rows:
+ * dmtd_wide_tile_width), plan[2] tiles a block computes whole, plan[3] tiles that pass through a second launch, plan[4] parts K
  * of these is split into.  Needs no GPU and changes nothing: with it a test can state which layouts its sizes reach.
  * Errors: DMTD_EINVAL (also an fp32 model, and rows <= 192). */
 int dmtd_wide_plan(const dmtd_config* cfg, int32_t kind, int32_t rows, int32_t num_cus, int32_t plan[5]);
+
+/* Weight rows of a tile of that launch: 256 or 192, which are as many outputs, for gate/up (a gate and an up row each) half as many.  Tiles
+ * of 192 are all computed whole.  Returns the width, or DMTD_EINVAL as dmtd_wide_plan does. */
+int dmtd_wide_tile_width(const dmtd_config* cfg, int32_t kind, int32_t rows, int32_t num_cus);
 
 /* How the sequences that start a cycle in one step of dmtd_decode_per_seq pass the front layers: rows HOST int32 [n], each sequence's
  * pending tokens and its newest one (1 to 16), in any order.  n_passes receives the number of passes; plan HOST int32 [2 n]: for pass i

@@ -83,6 +83,8 @@ def load_library():
     lib.dmtd_time_kernel.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, P(C.c_float)]
     lib.dmtd_wide_plan.restype = C.c_int
     lib.dmtd_wide_plan.argtypes = [P(_Config), C.c_int32, C.c_int32, C.c_int32, P(C.c_int32)]
+    lib.dmtd_wide_tile_width.restype = C.c_int
+    lib.dmtd_wide_tile_width.argtypes = [P(_Config), C.c_int32, C.c_int32, C.c_int32]
     lib.dmtd_front_plan.restype = C.c_int
     lib.dmtd_front_plan.argtypes = [P(_Config), P(C.c_int32), C.c_int32, P(C.c_int32), P(C.c_int32)]
     lib.dmtd_score_plan.restype = C.c_int

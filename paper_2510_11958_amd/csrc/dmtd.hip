@@ -2323,25 +2323,38 @@ int dmtd_time_kernel(dmtd_ctx* c, int32_t kind, int32_t rows, int32_t reps, floa
   return DMTD_OK;
 }
 
-int dmtd_wide_plan(const dmtd_config* cfg, int32_t kind, int32_t rows, int32_t num_cus, int32_t plan[5]) {
+namespace {
+// What a launch of the wide GEMM would be, for the queries below; false: not one it takes
+bool wide_choice(const dmtd_config* cfg, int32_t kind, int32_t rows, int32_t num_cus, WideChoice& w) {
   std::string why;
-  if (!plan || !valid_config(cfg, why) || cfg->dtype != DMTD_DTYPE_BF16 || rows <= kTiledRows || num_cus < 1) return DMTD_EINVAL;
+  if (!valid_config(cfg, why) || cfg->dtype != DMTD_DTYPE_BF16 || rows <= kTiledRows || num_cus < 1) return false;
   const int d = cfg->hidden, qd = cfg->n_q_heads * cfg->head_dim, nqkv = qd + 2 * cfg->n_kv_heads * cfg->head_dim, ff = cfg->intermediate;
-  WideChoice w{};
   switch (kind) {
     case DMTD_K_QKV:    w = choose_wide<EPI_STORE>(*cfg, num_cus, rows, nqkv, d); break;
     case DMTD_K_OPROJ:  w = choose_wide<EPI_RESID>(*cfg, num_cus, rows, d, qd); break;
     case DMTD_K_GATEUP: w = choose_wide<EPI_SWIGLU>(*cfg, num_cus, rows, ff, d); break;
     case DMTD_K_DOWN:   w = choose_wide<EPI_RESID>(*cfg, num_cus, rows, d, ff); break;
     case DMTD_K_LMHEAD: w = choose_wide<EPI_LOGITS>(*cfg, num_cus, rows, cfg->vocab, d); break;
-    default: return DMTD_EINVAL;
+    default: return false;
   }
+  return true;
+}
+}  // namespace
+
+int dmtd_wide_plan(const dmtd_config* cfg, int32_t kind, int32_t rows, int32_t num_cus, int32_t plan[5]) {
+  WideChoice w{};
+  if (!plan || !wide_choice(cfg, kind, rows, num_cus, w)) return DMTD_EINVAL;
   plan[0] = w.pass;
   plan[1] = w.bm;
   plan[2] = w.p.n_full;
   plan[3] = (w.pass + w.bm - 1) / w.bm * w.nt - w.p.n_full;
   plan[4] = w.p.ksplit;
   return DMTD_OK;
+}
+
+int dmtd_wide_tile_width(const dmtd_config* cfg, int32_t kind, int32_t rows, int32_t num_cus) {
+  WideChoice w{};
+  return wide_choice(cfg, kind, rows, num_cus, w) ? w.bn : DMTD_EINVAL;
 }
 
 int dmtd_front_plan(const dmtd_config* cfg, const int32_t* rows, int32_t n, int32_t* plan, int32_t* n_passes) {
