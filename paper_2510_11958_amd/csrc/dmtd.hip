@@ -639,12 +639,14 @@ hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows, const MergeSrc& merge 
   } while (0)
   if (!fits) {
     const int n_tiles = (a.N + 15) / 16;
-    // An LM head with 17 to 32 rows: two blocks share a CU, of 8 waves or of kLmWaves; those that take fewer rounds of the chip for their waves (us, 8 /
-    // 10 waves, 32 rows: 2560 wide, 140000 entries 142 / 132, 151936, 1.16 and 0.93 rounds, 148 / 140, 163840 155 / 148; 1024 wide 68 / 58, 70 / 62, 76 / 66;
-    // up to 131072 entries are one round either way, 163841 to 262144 two).
-    // The wider ones walk K in whole rounds of their pipeline.
+    // An LM head with 17 to 32 rows: two blocks share a CU, of 8 waves or of kLmWaves; those that take fewer rounds of the chip for their waves, where
+    // one round takes them all (us, 8 / 10 waves, 32 rows: 2560 wide, 140000 entries 142 / 132, 151936, 1.16 and 0.93 rounds, 148 / 140, 163840 155 / 148;
+    // 1024 wide 68 / 58, 70 / 62, 76 / 66; 24 rows, 151936 entries: 768 wide 48.4 / 47.5, 640 43.2 / 43.1, 512 37.1 / 35.4, but 384 30.4 / 31.1; up to
+    // 131072 entries are one round either way).  In two rounds against three, or three against four, only at widths of whole 1024s, which blocks of
+    // 8 waves read at a lower rate (24 rows, 300000 / 400000 entries: 768 wide 90.7 / 95.7, 123.7 / 123.4, 1024 126 / 115, 165 / 148, 1536 167 / 174,
+    // 228 / 226, 2048 219 / 220, 293 / 283, 2560 274 / 285, 375 / 369, 4096 433 / 423, 590 / 556).  The wider ones walk K in whole rounds of their pipeline.
     const auto lm_cost = [&](int waves) { return (n_tiles + 4 * waves * c->num_cus - 1) / (4 * waves * c->num_cus) * waves; };
-    const bool lm_wide = KS % gemm_pf(2, EPI_LOGITS) == 0 && lm_cost(kLmWaves) < lm_cost(8);
+    const bool lm_wide = KS % gemm_pf(2, EPI_LOGITS) == 0 && a.K >= 512 && (lm_cost(kLmWaves) == kLmWaves || a.K % 1024 == 0) && lm_cost(kLmWaves) < lm_cost(8);
     for (int m0 = 0; m0 < rows; m0 += kGemmRows) {
       MfmaArgs g = a;
       g.M = rows - m0 < kGemmRows ? rows - m0 : kGemmRows;

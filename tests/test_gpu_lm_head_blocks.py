@@ -1,5 +1,5 @@
-"""GPU parity of the LM head with 17 to 32 rows where it runs in blocks of ten waves (131073 to 163840 entries and a width of whole rounds of
-its pipeline) and next to that, against the CPU oracle.
+"""GPU parity of the LM head with 17 to 32 rows where it runs in blocks of ten waves (131073 to 163840 entries at a width of 512 or more in whole
+rounds of its pipeline, and 262145 to 327680 at widths of whole 1024s) and next to that, against the CPU oracle.
 
 Tolerance: that of the other bf16 parity tests (2e-2 of the largest logit); a wrong row or weight tile is an error of order one.  The token is
 the largest of the reported logits, the first of equal ones.
@@ -15,11 +15,14 @@ from parity_util import engine_config, norm_err, oracle_config
 S = di.ModelShape
 CASES = {
     # name: (width, entries, sequences)
-    "fewest_entries": (128, 131073, 17),          # one entry in the last tile; the first steps are the last
-    "most_entries": (256, 163840, 32),            # 512 full blocks
-    "ragged": (320 + 64, 151936, 25),             # the last block has 16 of 20 tiles
-    "odd_steps": (192, 151936, 25),               # three steps: blocks of eight waves
-    "two_rounds": (128, 163841, 18),              # blocks of eight waves
+    "fewest_entries": (512, 131073, 17),          # one entry in the last tile
+    "most_entries": (512, 163840, 32),            # 512 full blocks
+    "ragged": (640, 151936, 25),                  # the last block has 16 of 20 tiles
+    "odd_steps": (576, 151936, 25),               # nine steps: blocks of eight waves
+    "narrow": (128, 131073, 17),                  # blocks of eight waves, as in the next two
+    "one_round_more": (512, 163841, 18),
+    "two_rounds": (512, 262145, 18),
+    "two_rounds_1024": (1024, 262145, 18),        # blocks of ten
 }
 
 
