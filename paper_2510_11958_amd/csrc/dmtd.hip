@@ -547,8 +547,11 @@ WideChoice choose_wide(const dmtd_config& cf, int num_cus, int rows, int N, int 
   const WidePlan p256 = plan_wide<EPI, 256, GW_BN>(cf, num_cus, w.pass, w.nt, K / 64), p128 = plan_wide<EPI, 128, GW_BN>(cf, num_cus, w.pass, w.nt, K / 64);
   w.bm = p128.us < p256.us ? 128 : 256;
   w.p = w.bm == 128 ? p128 : p256;
-  // 192 weight rows where all tiles of 256 are whole, of the same height, and these fill more than 7/8 of their rounds of the chip: a sum is
-  // then the same chain over all of K either way.  (Where tiles of 256 are split, their sums in parts are nearer to 64 bits: see gemm_wide.hpp.)
+  // 192 weight rows where all tiles of 256 are whole, of the same height: a sum is then the same chain over all of K either way.  (Where tiles of 256
+  // are split, their sums in parts are nearer to 64 bits: see gemm_wide.hpp.)  In one round of the chip they are always the faster ones, of 62
+  // launches by 6 to 18 % (tiles of 256 / 192, us: gate/up 1024 wide, 144 / 192 45.0 / 38.2, 160 / 215 45.1 / 39.7, 192 / 256 44.4 / 39.9; 2048 wide,
+  // 192 / 256 91.8 / 83.0; QKV in tiles of 128 rows 1024 wide, 96 / 128 26.1 / 22.7, 2560 wide, 112 / 154 54.0 / 46.3, 160 / 220 59.7 / 55.3, 192 /
+  // 256 65.8 / 61.0); in more rounds where they fill more than 7/8 of them.
   if constexpr (EPI == EPI_STORE || EPI == EPI_SWIGLU) {
     const WideChoice base = w;
     auto narrow = [&](auto bm_c) {
@@ -556,7 +559,7 @@ WideChoice choose_wide(const dmtd_config& cf, int num_cus, int rows, int N, int 
       if (base.bm != BM || base.p.ksplit > 1) return;
       const int nt = wide_col_tiles<EPI>(N, BN), tiles = (rows + BM - 1) / BM * nt, rounds = (tiles + num_cus - 1) / num_cus;
       const WidePlan p = plan_wide<EPI, BM, BN>(cf, num_cus, rows, nt, K / 64);
-      if (p.ksplit == 1 && tiles * 8L > rounds * (long)num_cus * 7 && p.us < w.p.us) w = WideChoice{nt, rows, BM, BN, p};
+      if (p.ksplit == 1 && (rounds == 1 || tiles * 8L > rounds * (long)num_cus * 7) && p.us < w.p.us) w = WideChoice{nt, rows, BM, BN, p};
     };
     narrow(std::integral_constant<int, 256>());
     if constexpr (EPI == EPI_STORE) narrow(std::integral_constant<int, 128>());

@@ -20,7 +20,7 @@ V, INPUTS = 300, 64
 CASES = {
     # name: (width, SwiGLU width, rows of the long pass), its gate/up launch (rows, rows of a tile, whole tiles, tiles in parts, parts)
     "tiles_of_128": (256, 448, 400, (400, 128, 16, 0, 1)),
-    "tiles_of_256": (256, 4096, 1100, (1100, 256, 160, 0, 1)),
+    "tiles_of_256": (256, 6144, 1100, (1100, 256, 240, 0, 1)),
     "tiles_of_256_by_192": (1024, 3072, 2046, (2046, 256, 256, 0, 1)),       # 256 weight rows a tile would be 192 tiles
     "tiles_in_parts": (1024, 1024, 400, (400, 128, 0, 32, 3)),
 }
