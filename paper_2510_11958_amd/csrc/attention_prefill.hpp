@@ -18,8 +18,8 @@
 // K goes from the cache straight into LDS (global_load ... lds; rows of HD with their 16-byte chunks permuted by the key
 // number), V through registers, transposed on the way (4 keys x HD/16 dims per thread, 8-byte pieces of 4 keys permuted by
 // the dim): fragment reads of both spread over all banks.  Two buffers of each; the next tile's loads fly during a tile.
-// What bounds it: the matrix cores (40 MFMAs of 32 cycles per 32 keys and wave at HD = 128; they work 68 % of the time against 8k keys) at
-// the clock the card's power leaves them (1.83 GHz there), and the softmax and three-way split, about 0.8 times as many vector cycles.
+// What bounds it: the matrix cores (40 MFMAs of 32 cycles per 32 keys and wave at HD = 128; they work 70 % of the time behind 6k keys) at
+// the clock the card's power leaves them (1.75 to 1.83 GHz there), and the softmax and three-way split, about 0.8 times as many vector cycles.
 // So a tile's work is laid out by hand: a K fragment is read a step, a V fragment three products ahead of its use, the next tile's
 // loads are issued one beside each step of the scores, and the exponentials and parts of a contraction step stand six vector
 // instructions beside each product of the step before.  2048 rows behind 0 / 2k / 4k / 6k keys (the passes of a prompt of 8192), us per
@@ -27,8 +27,8 @@
 // (launcher) 97 / 231 / 367 / 500; loads' addresses from two registers a tile 93 / 220 / 347 / 475.
 // Wave priorities (by block, or raised around the softmax) changed nothing.
 // Against the decode kernel (attention_mfma.hpp, one pass over K and V per 16 query vectors, the same products) on the same passes,
-// 32/8 heads of 128, us per launch: one prompt of 1003 111 -> 52; 2048 rows against 2k to 8k keys 1044 -> 322 (the prompt of
-// 8192, 2 layers: 14.5 -> 8.8 ms); 32 prompts of 2048 in passes of 64 rows 386 -> 90; one prompt of 400 33 -> 28.
+// 32/8 heads of 128, us per launch: one prompt of 1003 111 -> 49; 2048 rows against 2k to 8k keys 1044 -> 314 (the prompt of
+// 8192, 2 layers: 14.5 -> 8.7 ms); 32 prompts of 2048 in passes of 64 rows 386 -> 95; one prompt of 400 33 -> 28.
 // The product runs over a whole tile with probability 0 for the keys a row does not see, and 0 * inf is NaN.  So a block looks at the
 // values of its own rows' positions first; if one is not finite, it and its like behind it go into LDS as 0, and the rows at or
 // behind the first of them come out as NaN, which their own products would give; the rows before it are as if it were not there.

@@ -486,9 +486,11 @@ WidePlan plan_wide(const dmtd_config& cf, int num_cus, int rows, int nt, int KS)
   typedef GwTile<BM, BN> T;
   const int tiles = (rows + BM - 1) / BM * nt, slots = num_cus;
   // a k-step of 32 takes 0.8 us with 128 rows; with 256 it takes 1.3, and 1.45 in long runs, where the card lowers its clock (also where
-  // it is summed by itself); a block's start and end take about 4 us.  Fitted to 300 measured launches of five widths from 200 to 2048
-  // rows: with one figure of 1.25 a launch was 0.7 % slower than its better tile on average and up to 14 % (2560 wide, us, tiles of
-  // 256 / 128: down with 896 rows 97 / 89, 1003 rows 98 / 95, O with 1400 rows 74 / 66; 1536 wide, down with 1003 rows 66 / 60), now 0.4 %;
+  // it is summed by itself); a block's start and end take about 4 us.  Fitted to 300 launches of five widths from 200 to 2048 rows of an
+  // earlier form of the loops, in which the chosen tile was 0.4 % slower than the better one on average (with one figure of 1.25 0.7 %).  The loops
+  // have since become 2 to 4 % faster, by different amounts; of 360 launches of these the chosen tile is 0.6 % slower on average and up to 16 % (us,
+  // tiles of 128 / 256: 2560 wide, gate/up with 200 rows 53 / 61, chosen 256; down with 701 rows 75 / 80, chosen 256; QKV with 2048 rows 114 / 98, chosen
+  // 128, whose chains of 4 k-steps are also the nearer sums).  The figures stand, since another choice is another order of the sums;
   // a raw tile's bytes are written and read by blocks all over the chip at about 3.5 TB/s in all; the finishing launch itself 5 us.
   // Against 256 weight rows a step of 192 takes 0.93 times as long (1.31 to 1.4; 0.75 with 128 rows).
   auto step_us = [&](int ks) {
@@ -703,9 +705,11 @@ hipError_t launch_mfma(dmtd_ctx* c, MfmaArgs a, int rows, const MergeSrc& merge 
           }
         }
       } else {
-        // Gate/up whose blocks of 4 waves are a quarter to a half of the CUs: blocks of 2 (us, 8 / 12 / 16 rows, 4 waves / 2: 2048 wide, 384 tiles, 96
-        // blocks 15.2 / 15.9 / 15.6, now 11.8 / 13.1 / 12.5; 1536 wide, 560 tiles, 140 blocks 14.0 / 13.8 / 14.2 against 14.0 / 15.9 / 16.8; 2560 wide, 608
-        // 19.6 / 20.4 / 21.0 against 22.4 / 23.8 / 25.0: each block draws the activations once more; 1024 wide, 16 rows, 48 blocks 6.0 / 6.2)
+        // Gate/up whose blocks of 4 waves are a quarter to a half of the CUs: blocks of 2 (us, 16 rows, blocks of 4 waves / 2, at 65, 96 and 128 blocks of 4:
+        // 1024 wide 9.3 / 8.4, 9.8 / 8.8, 10.2 / 9.4; 1536 12.7 / 10.6, 13.7 / 11.3, 13.7 / 12.2; 2048 15.7 / 13.8, 16.0 / 14.1, 16.9 / 15.4; 2560 19.2 / 17.4,
+        // 20.7 / 17.5, 21.2 / 18.4; 4096 28.3 / 25.4, 29.9 / 25.1, 31.7 / 27.1; with 8 rows of 2048 to 4096 wide 11 to 19 % faster, with 4 to 7 where they come
+        // this way 8 to 30 %).  Outside: 1536 wide, 560 tiles, 140 blocks 14.0 / 13.8 / 14.2 (8 / 12 / 16 rows) against 14.0 / 15.9 / 16.8; 2560 wide, 608
+        // 19.6 / 20.4 / 21.0 against 22.4 / 23.8 / 25.0: each block draws the activations once more; 1024 wide, 16 rows, 48 blocks 6.0 / 6.2.
         const bool gu_narrow = EPI == EPI_SWIGLU && cg == 1 && 4 * (int)ggrid.x > c->num_cus && 2 * (int)ggrid.x <= c->num_cus;
         if (gu_narrow) {
           if constexpr (EPI == EPI_SWIGLU) DMTD_LAUNCH_GEMM_W(1, false, dim3((n_tiles + 1) / 2), 2);

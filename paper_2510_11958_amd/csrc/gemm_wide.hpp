@@ -5,7 +5,8 @@
 // rows x 256 weight rows (SwiGLU: 128 gate and the same 128 up rows, 16 of each in turn) with 8 waves of 64 x 128 (2 x 4 tiles of
 // v_mfma_f32_32x32x16_bf16).  Gate/up and QKV also come with 192 weight rows, where these leave fewer CUs idle
 // (choose_wide).  Tiles of 320 weight rows, all that the registers (240 of 256) and LDS hold, would take gate/up of 1003 rows of 2560 in one round of whole
-// tiles (160 -> 149 us, 2048 rows 305 -> 287); they are not here, since they sum in one chain what 256 sum in five parts (below).  K is walked in steps of 32: weights and both activation planes go from memory straight into
+// tiles (us with the finishing launch 184 -> 159, 2048 rows 337 -> 308); they are not here, since they sum in one chain what 256 sum in five parts
+// (below).  K is walked in steps of 32: weights and both activation planes go from memory straight into
 // LDS (global_load ... lds), 48 pieces of 1 KiB per step, each piece holding 16 rows in the order [16-byte chunk of k][row],
 // which is the order the weights and the blocked activations (packed_at) are stored in; a fragment read then takes 256
 // contiguous bytes per 16 lanes (no bank conflicts).  A ring of three LDS buffers (144 KiB, one block per CU); a step is waited for by the
@@ -15,21 +16,21 @@
 // of a step with all its reads and loads behind it / barrier in the middle: on zeros 263 / 233, on normally distributed data 333 / 314, where
 // the clock falls to 1.9 GHz; one 2560 x 9728 launch in 240 blocks 160 / 154; tiles of 128 rows, 1003 rows of 2560 x 4096 41.3 / 40.2.  With the
 // same tile loaded by every block the launch takes 302, so memory is not it.  But at that clock a loop of nothing but MFMAs on random
-// operands does 1.7 PFLOP/s, and a launch 1.1 to 1.36 with its matrix cores idle for 17 % (gate/up, down) to 35 % (QKV) of a busy CU's time: a step's barrier and reads, a
-// block's start and end, and rounds that are not full (192 blocks of QKV at 2048 rows, a round of split tails behind a full one).  Of a launch's end the stores are the most: 50
+// operands does 1.7 PFLOP/s, and a launch 1.1 to 1.3 with its matrix cores idle for 16 % (down) or 20 % (gate/up) to 37 % (QKV) of a busy CU's time: a step's barrier and reads, a
+// block's start and end, and rounds that are not full (a round of split tails behind a full one).  Of a launch's end the stores are the most: 50
 // MB of QKV sums or 63 MB of raw ones take 10 to 12 us with the matrix cores idle.  Reads two at a time behind their pairs of products, without a branch each (2048 rows of 2560, us
-// before / now): gate/up 301 / 294, down 158 / 154; QKV with its loop laid out likewise 121 / 116 (without any loads 100, the same tile for every
-// block 114, chains of both row tiles in turn 116).  Also measured at the middle barrier, no faster: other orders of
+// before / now): gate/up in tiles of 320 weight rows 301 / 294, down 158 / 154; QKV in tiles of 256 x 192 with its loop laid out likewise 121 / 116
+// (without any loads 100, the same tile for every block 114, chains of both row tiles in turn 116).  Also measured at the middle barrier, no faster: other orders of
 // the products (each weight tile or each row tile held over 4 of them) 312 to 316, raised wave priority 320, 4 waves of 128 x 128 (a quarter
 // less LDS traffic) 5 % slower, tiles of 128 rows in 4 waves of 64 x 128 6 % slower.
 // Blocks go round-robin over the 8 compute dies; a die takes a contiguous run of tiles with the row tiles fastest, so a
 // weight byte enters one die's L2 only and its row tiles share it there.
-// A block costs 10 to 13 us beside its steps; of the SwiGLU epilogue's 6, its divisions are 2 to 4 (us, v_rcp_f32 in their place / divisions: 1003
-// rows of 2560 149 / 152, 2048 rows 287 / 291).  Without loads, reads and barriers in the loop the products alone take
-// 140 of these 152, on zeros 113.
+// A block costs 10 to 13 us beside its steps; of the SwiGLU epilogue's 6, its divisions are 2 to 4 (tiles of 320 weight rows, us, v_rcp_f32 in their
+// place / divisions: 1003 rows of 2560 149 / 152, 2048 rows 287 / 291).  Without loads, reads and barriers in the loop the products alone take 140
+// of these 152, on zeros 113.
 // Tiles of 128 rows (waves of 64 x 64, a ring of four buffers, 0.8 instead of 1.3 us per step) where they pad a launch's rows less.
-// Against passes of 128 rows through gemm_mfma.hpp (4B shapes, 2048 rows, us with the finishing launch, before / now):
-// gate/up 660 / 336, QKV 390 / 128, down + O 763 / 282.
+// Against passes of 128 rows through gemm_mfma.hpp (4B shapes, 2048 rows, us with the finishing launch, before / now; the card of the 2nd figures is
+// one of those that run 5 to 8 % slower than that of the others above): gate/up 660 / 337, QKV 390 / 129, down + O 763 / 283.
 // Sums: a tile that takes its whole K in one block sums it in one fp32 chain, a rounding per 8 products, 4.4e-7 of the result's norm at
 // K = 2560 in two planes; five parts summed apart (gemm_mfma.hpp with 128 rows) leave 2.0e-7.  In the QKV projection, whose K and V are
 // then rounded to bf16, that decides roundings; there a chain has 4 k-steps (tiles of 128 rows) or one (256 rows, 128 additions beside
