@@ -438,9 +438,13 @@ __global__ void __launch_bounds__(64 * GW_WAVES, 2) gemm_wide_mfma_kernel(const 
 #pragma unroll
         for (int q = 0; q < 2; ++q)
 #pragma unroll
-          for (int h = 0; h < 2; ++h)
-            swiglu_split2(acc[i][j][4 * q + 2 * h] * rs, acc[i][j][8 + 4 * q + 2 * h] * rs, acc[i][j][4 * q + 2 * h + 1] * rs,
-                          acc[i][j][8 + 4 * q + 2 * h + 1] * rs, hi[q][h], lo[q][h]);
+          for (int h = 0; h < 2; ++h) {
+            const float g0 = acc[i][j][4 * q + 2 * h] * rs, u0 = acc[i][j][8 + 4 * q + 2 * h] * rs;
+            const float g1 = acc[i][j][4 * q + 2 * h + 1] * rs, u1 = acc[i][j][8 + 4 * q + 2 * h + 1] * rs;
+            if (BM != 128) swiglu_split2(g0, u0, g1, u1, hi[q][h], lo[q][h]);
+            else if (h == 0) swiglu_split2<false, true>(g0, u0, g1, u1, hi[q][h], lo[q][h]);
+            else swiglu_split2<true, false>(g0, u0, g1, u1, hi[q][h], lo[q][h]);
+          }
         const LanePair<uint32_t> h0 = halves<32>(hi[0][0], hi[1][0]), h1 = halves<32>(hi[0][1], hi[1][1]);
         const LanePair<uint32_t> l0 = halves<32>(lo[0][0], lo[1][0]), l1 = halves<32>(lo[0][1], lo[1][1]);
         if (m < M && n < N) {

@@ -43,18 +43,28 @@ __device__ __forceinline__ void split_bf16(float v, bf16_t& hi, bf16_t& lo) {
   hi = to_bf16_hw(v);
   lo = to_bf16_hw(v - bf16_to_f32(hi));
 }
-// SwiGLU of a gate and an up value in two bf16 parts: the same bits on every route a row may take.  So the division is one (v_rcp_f32 in its
+// SwiGLU of a gate and an up value in two bf16 parts, the one function of all routes a row may take.  The division is one (v_rcp_f32 in its
 // place, good to one unit in the last place, changes the low part of one value in 110), and the low part is what the unrounded product leaves, by a
-// fused multiply-add that is written out: left to the compiler, tiles of 128 rows got it for half of their outputs.
-__device__ __forceinline__ void swiglu_split(float gate, float up, bf16_t& hi, bf16_t& lo) {
-  const float s = gate / (1.0f + __expf(-gate));
-  hi = to_bf16_hw(s * up);
-  lo = to_bf16_hw(__builtin_fmaf(s, up, -bf16_to_f32(hi)));
+// fused multiply-add that is written out, so that no route gets another rounding by the compiler's choice.  ROUNDED takes it from the rounded product
+// (another unit in one low part of 70, a value's error of 2.4e-6 is the same): outputs 1 and 2 of four in the wide GEMM's tiles of 128 rows, which keep
+// the bits they have always had.
+template <bool ROUNDED>
+__device__ __forceinline__ float swiglu_rest(float s, float up, float hi) {
+#pragma clang fp contract(off)
+  const float v = s * up;
+  return ROUNDED ? v - hi : __builtin_fmaf(s, up, -hi);
 }
+__device__ __forceinline__ float silu(float x) { return x / (1.0f + __expf(-x)); }
+__device__ __forceinline__ void swiglu_split(float gate, float up, bf16_t& hi, bf16_t& lo) {
+  const float s = silu(gate);
+  hi = to_bf16_hw(s * up);
+  lo = to_bf16_hw(swiglu_rest<false>(s, up, bf16_to_f32(hi)));
+}
+template <bool ROUNDED0 = false, bool ROUNDED1 = false>
 __device__ __forceinline__ void swiglu_split2(float gate0, float up0, float gate1, float up1, uint32_t& hi, uint32_t& lo) {
-  const float s0 = gate0 / (1.0f + __expf(-gate0)), s1 = gate1 / (1.0f + __expf(-gate1));
+  const float s0 = silu(gate0), s1 = silu(gate1);
   hi = pack_bf16x2(s0 * up0, s1 * up1);
-  lo = pack_bf16x2(__builtin_fmaf(s0, up0, -__uint_as_float(hi << 16)), __builtin_fmaf(s1, up1, -__uint_as_float(hi & 0xFFFF0000u)));
+  lo = pack_bf16x2(swiglu_rest<ROUNDED0>(s0, up0, __uint_as_float(hi << 16)), swiglu_rest<ROUNDED1>(s1, up1, __uint_as_float(hi & 0xFFFF0000u)));
 }
 
 constexpr int MFMA_MAX_WAVES = 16;   // waves that split K for one tile
